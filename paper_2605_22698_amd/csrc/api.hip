@@ -211,7 +211,9 @@ struct Workspace {
   std::unique_ptr<DevBuf> P2f;      // first layer's second hidden pre-activation per edge pair (or edge), [., 64]
   std::unique_ptr<DevBuf> q_raw, q, pot, fc, pot_mean;  // electrostatics: charges, potential, forces
   std::vector<std::unique_ptr<DevBuf>> at;             // product block: A~ per layer
-  std::unique_ptr<DevBuf> Ygb, Ygc, ghv, zeroE;        // Hessian-vector products
+  // Hessian-vector products: R, R' and R'' per layer, and a batch of directions' tangents and adjoints
+  std::vector<std::unique_ptr<DevBuf>> R3, vhd, vhtd, vatd, vBpd;
+  std::unique_ptr<DevBuf> vdd, vAd, vA, vx, vh_a, vh_b, vgeo, vg, vmsg, vBp, vat;
   std::vector<int> rp_host;                            // pruned row pointer on the host (receiver chunks)
   bool rp_valid = false;
   std::unique_ptr<DevBuf> Bp, dat;                     // product block: B (or dB), dA~
@@ -878,6 +880,19 @@ bool r_compact_for(const e3mi_model* M, const std::vector<RChunk>& chunks, bool 
   return M->edge_pairs && !keep_A && chunks.size() == 1 && chunks[0].e1 < 0;
 }
 
+// R, R' and R'' of layer t for every edge pair (every edge with flag 8)
+void radial_derivs(e3mi_model* M, e3mi_graph* G, int t, hipStream_t st) {
+  const Config& c = M->cfg;
+  const LayerPlan& L = M->plans[t - 1];
+  LayerWeights& W = *M->lw[t - 1];
+  const EdgePairs prs = graph_pairs(G);
+  ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
+  launch_radial_d2(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
+                   W.rad2.as<float>(), W.rad3.as<float>(), L.p_full * c.channels, L.p_used * c.channels,
+                   M->ws.R3[t]->as<float>(), (float)c.cutoff, c.envelope_p, M->edge_pairs ? prs.own : nullptr,
+                   M->edge_pairs ? prs.n_own : nullptr, st);
+}
+
 void set_chunk(TpArgs& ta, const RChunk& ch) {
   ta.i0 = ch.e1 < 0 ? 0 : ch.i0;
   ta.n_recv = ch.e1 < 0 ? 0 : ch.i1 - ch.i0;
@@ -890,8 +905,11 @@ void set_chunk(TpArgs& ta, const RChunk& ch) {
 // defer_last_gate: a scalar-only last layer (no product block) stops at its
 // pre-gate values (ht, or the partial products in mixp; their count in
 // last_parts) for a readout that applies the gate itself.
+// derivs (with neither of the above): R of every layer with its derivatives
+// in the edge length (R3, one row per edge pair), for Hessian-vector products;
+// the first layer's R3 is left to the caller.
 void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, hipStream_t st, bool bf16,
-                  bool defer_last_gate = false) {
+                  bool defer_last_gate = false, bool derivs = false) {
   const Config& c = M->cfg;
   Allocator* a = &M->alloc;
   const int N = G->N, S = G->S, C = c.channels, T = c.layers;
@@ -927,6 +945,11 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     ensure(w.h[t], a, sizeof(float) * (size_t)N * L.nc_out * C);
     ensure(w.ht[t], a, sizeof(float) * (size_t)N * L.nc_out * C);
     a_max = std::max(a_max, L.a_per_atom);
+    if (derivs) {
+      w.R3.resize(T + 1);
+      ensure(w.R3[t], a, sizeof(float) * 3 * (size_t)(Ecap + 1) * L.p_used * C);
+      continue;
+    }
     if (t == 1 && factorised_first(M) && !keep_A) continue;
     if (fused_last(M, L, keep_A, bf16)) continue;
     // the second-order pass keeps R of every edge (skin-list capacity);
@@ -956,12 +979,14 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     for (int t = 1; t <= T; ++t) ensure(w.Al[t], a, sizeof(float) * (size_t)N * M->plans[t - 1].a_per_atom);
   }
   if (dr_bytes) ensure(w.dR, a, dr_bytes);
-  ensure(w.dY, a, sizeof(float) * 16 * (size_t)(Ecap + 1));
-  ensure(w.g, a, sizeof(float4) * (size_t)(Ecap + 1));
-  ensure(w.dh_a, a, sizeof(float) * (size_t)N * NC * C);
-  ensure(w.dh_b, a, sizeof(float) * (size_t)N * NC * C);
-  ensure(w.dht, a, sizeof(float) * (size_t)N * NC * C);
-  ensure(w.e_atom, a, sizeof(double) * (size_t)N);
+  if (!derivs) {
+    ensure(w.dY, a, sizeof(float) * 16 * (size_t)(Ecap + 1));
+    ensure(w.g, a, sizeof(float4) * (size_t)(Ecap + 1));
+    ensure(w.dh_a, a, sizeof(float) * (size_t)N * NC * C);
+    ensure(w.dh_b, a, sizeof(float) * (size_t)N * NC * C);
+    ensure(w.dht, a, sizeof(float) * (size_t)N * NC * C);
+    ensure(w.e_atom, a, sizeof(double) * (size_t)N);
+  }
   // ---- forward ----
   {
     ProfScope ps(&M->prof, stage_id(kEmbed), st);
@@ -972,7 +997,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
   if (fact) {
     ensure(w.G1, a, sizeof(float) * (size_t)N * M->plans[0].nc_a * S64);
     ensure(w.P2f, a, sizeof(float) * (size_t)c.radial_hidden * (size_t)(Ecap + 1));
-    ensure(w.dG1, a, sizeof(float) * (size_t)N * M->plans[0].nc_a * S64);
+    if (!derivs) ensure(w.dG1, a, sizeof(float) * (size_t)N * M->plans[0].nc_a * S64);
   }
   // product block: the mix writes A~ (no self connection); B follows, then
   // h~ = B W_lin + h_in S
@@ -1044,7 +1069,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
       continue;
     }
     float* A = keep_A ? w.Al[t]->as<float>() : w.A->as<float>();
-    if (fused_last(M, L, keep_A, bf16)) {
+    if (!derivs && fused_last(M, L, keep_A, bf16)) {
       LastArgs la = last_args(M, G, L, W, hin);
       la.A = A;
       {
@@ -1066,9 +1091,9 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
       }
       continue;
     }
-    float* R = w.R[t]->as<float>();  // BF16 values when r_bf16
+    float* R = (derivs ? w.R3[t] : w.R[t])->as<float>();  // BF16 values when r_bf16
     const int PCu = L.p_used * C;
-    const std::vector<RChunk> chunks = keep_A ? std::vector<RChunk>{RChunk{0, N, 0, -1}} : r_chunks(M, G, PCu, st);
+    const std::vector<RChunk> chunks = keep_A || derivs ? std::vector<RChunk>{RChunk{0, N, 0, -1}} : r_chunks(M, G, PCu, st);
     TpArgs ta{};
     const bool lr_bf16 = r_bf16_layer(w, L);
     ta.r_bf16 = lr_bf16 ? 1 : 0;
@@ -1092,7 +1117,11 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     ta.r_row = w.r_compact[t] ? G->pair_of->as<int>() : nullptr;
     for (const RChunk& ch : chunks) {
       void* Rc = chunk_r(w, t, R, ch, PCu, lr_bf16 ? 2 : 4);
-      {
+      if (derivs) {
+        radial_derivs(M, G, t, st);
+        ta.r_stride = 3 * PCu;
+        ta.r_row = first_pair_index(M, G);
+      } else {
         ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
         launch_radial_fwd(c.n_basis, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(),
                           W.rad3.as<float>(), L.p_full * C, PCu, Rc, lr_bf16, rc, p_env, bf16, st, ch.e0, ch.e1,
@@ -1629,13 +1658,12 @@ e3mi_model* new_model(const char* json, const double* wts, size_t n, int precisi
 
 
 // Second-order pass for s = sum_s gE_s E_s - D_v E (v = gF): forward (primal
-// + tangent along v), then the reverse pass over both. out (may be NULL): the
-// gradient of s with respect to every weight, i.e. the vector-Jacobian
-// product of (E, F) -> weights for upstream (gE, gF). hv (may be NULL):
-// -ds/dr, which for gE = 0 is the Hessian-vector product H v (the reverse pass
-// is continued through each layer's edge geometry).
-void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double* gE, const float* gF, double* out,
-                  float* hv, hipStream_t st, bool primal_ready = false) {
+// + tangent along v), then the reverse pass over both. out: the gradient of s
+// with respect to every weight, i.e. the vector-Jacobian product of (E, F) ->
+// weights for upstream (gE, gF).
+void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* gE, const float* gF, double* out,
+                hipStream_t st) {
+  E3MI_REQUIRE(out, E3MI_EINVAL, "null output");
   const Config& c = M->cfg;
   Allocator* a = &M->alloc;
   const int N = G->N, C = c.channels, T = c.layers, H = c.radial_hidden;
@@ -1649,11 +1677,9 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
                "second-order passes (parameter gradients, Hessian-vector products) of the Coulomb term are not implemented");
   const bool prod = c.correlation == 2;
   const WeightOffsets off = weight_offsets(c);
-  if (out) E3MI_HIP(hipMemsetAsync(out, 0, sizeof(double) * off.total, st));
+  E3MI_HIP(hipMemsetAsync(out, 0, sizeof(double) * off.total, st));
   if (N == 0) return;
-  // primal_ready: the previous call on this graph and positions left the
-  // primal values (h, h~, R, A per layer) in the workspace
-  if (!primal_ready) forward_pass(M, G, pos, true, st, false);
+  forward_pass(M, G, pos, true, st, false);
   const int* row_ptr = G->row_ptr_x->as<int>();
   const int* src = G->src_x->as<int>();
   const float4* dvec = G->dvec_x->as<float4>();
@@ -1683,10 +1709,6 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
   for (auto* v : {&w.P1g, &w.P2g}) ensure(*v, a, sizeof(float) * E1 * 2 * H);
   ensure(w.partial, a, sizeof(float) * std::max<size_t>(16u << 20, (size_t)H * pc_max));
   float* partial = w.partial->as<float>();
-  if (hv) {
-    for (auto* v : {&w.Ygb, &w.Ygc}) ensure(*v, a, sizeof(float) * E1 * 16);
-    ensure(w.ghv, a, sizeof(float4) * E1);
-  }
   if (prod) {
     w.atd.resize(T + 1);
     w.Bpd.resize(T + 1);
@@ -1698,7 +1720,7 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
       dw_max = std::max(dw_max, (long)(L.lout + 1 + L.n_prod) * C);
     }
     for (auto* v : {&w.Bpb, &w.Bpc, &w.atb, &w.atc}) ensure(*v, a, sizeof(float) * (size_t)N * NC * C);
-    if (out) ensure(w.dwp, a, sizeof(float) * (size_t)N * dw_max);
+    ensure(w.dwp, a, sizeof(float) * (size_t)N * dw_max);
   }
 
   // ---- tangent forward along v = gF ----
@@ -1756,13 +1778,11 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
   launch_readout_dual(w.h[T]->as<float>(), w.hd[T]->as<float>(), ncT, G->owner->as<int>(), gE, M->read1->as<float>(),
                       M->read2->as<float>(), N, C, w.Prb->as<float>(), w.Prc->as<float>(), w.w2c->as<float>(), hb, hc,
                       w.eb->as<float>(), st);
-  if (out) {
-    launch_gemm_tn(RowMap{w.h[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prb->as<float>(), 16, 0, 1},
-                   RowMap{w.hd[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prc->as<float>(), 16, 0, 1}, N,
-                   nullptr, C, 16, partial, out + off.read1, 16, st);
-    launch_group_sum(w.w2c->as<float>(), 16, nullptr, 1, N, 16, out + off.read2, 16, st);
-    launch_group_sum(w.eb->as<float>(), 1, G->species->as<int>(), c.n_species, N, 1, out + off.e0, 1, st);
-  }
+  launch_gemm_tn(RowMap{w.h[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prb->as<float>(), 16, 0, 1},
+                 RowMap{w.hd[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prc->as<float>(), 16, 0, 1}, N,
+                 nullptr, C, 16, partial, out + off.read1, 16, st);
+  launch_group_sum(w.w2c->as<float>(), 16, nullptr, 1, N, 16, out + off.read2, 16, st);
+  launch_group_sum(w.eb->as<float>(), 1, G->species->as<int>(), c.n_species, N, 1, out + off.e0, 1, st);
 
   // ---- reverse: layers ----
   float* xb = w.xb->as<float>();
@@ -1775,7 +1795,7 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
     const float* hdin = t > 1 ? w.hd[t - 1]->as<float>() : nullptr;
     launch_gate_dual_bwd(w.ht[t]->as<float>(), w.htd[t]->as<float>(), hb, hc, xb, xc, N, L.nc_out, C, st);
     // weight gradients of the self connection (orders present in both h^{t-1} and h~)
-    for (int l = 0; l <= (out ? std::min(L.l1max, prod ? L.lout : L.l3max_used) : -1); ++l) {
+    for (int l = 0; l <= std::min(L.l1max, prod ? L.lout : L.l3max_used); ++l) {
       const int g = 2 * l + 1;
       launch_gemm_tn(RowMap{const_cast<float*>(hin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g},
                      RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
@@ -1796,17 +1816,15 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
       float* Bt = w.Bp->as<float>();
       ProductArgs pa = product_args(M, G, L, W, w.at[t]->as<float>());
       pa.atd = w.atd[t]->as<float>();
-      if (out) {
-        pa.B = Bt;
-        launch_product(true, pa, st);  // B again (the forward pass keeps one layer's)
-        for (int l = 0; l <= L.lout; ++l) {
-          const int g = 2 * l + 1, nb = (L.lout + 1) * (L.lout + 1);
-          launch_gemm_tn(RowMap{Bt + (long)l * l * C, (long)nb * C, (long)C, g},
-                         RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
-                         RowMap{w.Bpd[t]->as<float>() + (long)l * l * C, (long)nb * C, (long)C, g},
-                         RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
-                         partial, out + off.lin[t - 1][l], C, st);
-        }
+      pa.B = Bt;
+      launch_product(true, pa, st);  // B again (the forward pass keeps one layer's)
+      for (int l = 0; l <= L.lout; ++l) {
+        const int g = 2 * l + 1, nb = (L.lout + 1) * (L.lout + 1);
+        launch_gemm_tn(RowMap{Bt + (long)l * l * C, (long)nb * C, (long)C, g},
+                       RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
+                       RowMap{w.Bpd[t]->as<float>() + (long)l * l * C, (long)nb * C, (long)C, g},
+                       RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
+                       partial, out + off.lin[t - 1][l], C, st);
       }
       launch_lin_adjoint(M, L, W, xb, w.Bpb->as<float>(), hb2, N, st, false);
       launch_lin_adjoint(M, L, W, xc, w.Bpc->as<float>(), t > 1 ? hc2 : nullptr, N, st, false);
@@ -1814,22 +1832,20 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
       pa.Bc = w.Bpc->as<float>();
       pa.atb = w.atb->as<float>();
       pa.atc = w.atc->as<float>();
-      pa.dw = out ? w.dwp->as<float>() : nullptr;
+      pa.dw = w.dwp->as<float>();
       launch_product_dual_bwd(pa, st);
-      if (out) {
-        const long ldw = (long)(L.lout + 1 + L.n_prod) * C;
-        launch_group_sum(pa.dw, ldw, G->species->as<int>(), c.n_species, N, (L.lout + 1) * C, out + off.sym1[t - 1],
-                         (long)(L.lout + 1) * C, st);
-        launch_group_sum(pa.dw + (long)(L.lout + 1) * C, ldw, G->species->as<int>(), c.n_species, N, L.n_prod * C,
-                         out + off.sym2[t - 1], (long)L.n_prod * C, st);
-      }
+      const long ldw = (long)(L.lout + 1 + L.n_prod) * C;
+      launch_group_sum(pa.dw, ldw, G->species->as<int>(), c.n_species, N, (L.lout + 1) * C, out + off.sym1[t - 1],
+                       (long)(L.lout + 1) * C, st);
+      launch_group_sum(pa.dw + (long)(L.lout + 1) * C, ldw, G->species->as<int>(), c.n_species, N, L.n_prod * C,
+                       out + off.sym2[t - 1], (long)L.n_prod * C, st);
       mb = w.atb->as<float>();
       mc = w.atc->as<float>();
       m_nc = L.nc_a;
     }
     // weight gradients of the channel mix
     long gbase = 0;
-    for (int l3 = 0; l3 <= (out ? L.l3max_used : -1); ++l3) {
+    for (int l3 = 0; l3 <= L.l3max_used; ++l3) {
       const int P3 = L.p_used_l3[l3], g = 2 * l3 + 1;
       launch_gemm_tn(RowMap{w.Al[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g},
                      RowMap{const_cast<float*>(mb) + (long)l3 * l3 * C, (long)m_nc * C, (long)C, g},
@@ -1873,19 +1889,6 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
     launch_radial_dual_bwd(row_ptr, N, Ecap, W.rad2T.as<float>(), W.rad3T.as<float>(), PCu, w.Rb->as<float>(),
                            w.Rc->as<float>(), w.P1d[t]->as<float>(), w.P2d[t]->as<float>(), w.P1g->as<float>(),
                            w.P2g->as<float>(), st);
-    if (hv) {
-      // continue to the positions through the harmonics and the radial basis
-      ta.Yb = w.Ygb->as<float>();
-      ta.Yc = w.Ygc->as<float>();
-      launch_tp(6, ta, st);
-      launch_hvp_geo(c.lmax, row_ptr, N, Ecap, dvec, dd, w.Ygb->as<float>(), w.Ygc->as<float>(), w.P1g->as<float>(),
-                     W.rad1.as<float>(), rc, p_env, t != T ? 1 : 0, w.ghv->as<float4>(), st);
-    }
-    if (!out) {
-      std::swap(hb, hb2);
-      std::swap(hc, hc2);
-      continue;
-    }
     float* H2d = w.H2d[t]->as<float>();
     float* H1d = w.H1d[t]->as<float>();
     float* Bd = w.Bd->as<float>();
@@ -1903,29 +1906,177 @@ void second_order(e3mi_model* M, e3mi_graph* G, const double* pos, const double*
     std::swap(hc, hc2);
   }
   // embedding: h^0_i = W_emb[z_i]
-  if (out) launch_group_sum(hb, C, G->species->as<int>(), c.n_species, N, C, out + off.emb, C, st);
-  if (hv) launch_forces(row_ptr, G->rev_x->as<int>(), w.ghv->as<float4>(), N, hv, st);
+  launch_group_sum(hb, C, G->species->as<int>(), c.n_species, N, C, out + off.emb, C, st);
 }
 
-void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* gE, const float* gF, double* out,
-                hipStream_t st) {
-  E3MI_REQUIRE(out, E3MI_EINVAL, "null output");
-  second_order(M, G, pos, gE, gF, out, nullptr, st);
+// Directions of one batch of Hessian-vector products. One direction of a small
+// system cannot fill the GPU (a 1,300-atom batch of molecules is 1,300 waves on
+// 1,024 SIMDs, and every launch costs as much as its work), so directions are
+// taken together until a batch has 16,384 atom rows, within 4 GiB of tangents
+// and adjoints; at least one.
+constexpr size_t kHvpBatchRows = 16384, kHvpBatchBytes = size_t(4) << 30;
+int hvp_batch(const e3mi_model* M, const e3mi_graph* G, int n_vec) {
+  const Config& c = M->cfg;
+  const size_t N = G->N, C = c.channels, NC = (size_t)(c.lmax + 1) * (c.lmax + 1), E1 = (size_t)G->E_room + 1;
+  size_t a_max = 0, per = E1 * (16 + 16 + 4 * kHvpGeoRow), msg = 0;
+  for (const LayerPlan& L : M->plans) {
+    per += 4 * N * C * 2 * L.nc_out;
+    if (c.correlation == 2) per += 4 * N * C * (L.nc_a + L.nc_out);
+    a_max = std::max(a_max, (size_t)L.a_per_atom);
+    if (L.kind == 1) msg = 4 * E1 * 2 * L.nc_in * C;
+  }
+  per += msg + 4 * N * (3 * a_max + 6 * NC * C) + (c.correlation == 2 ? 16 * N * NC * C : 0);
+  const size_t by_rows = (kHvpBatchRows + N - 1) / N, by_bytes = std::max<size_t>(1, kHvpBatchBytes / per);
+  return (int)std::min<size_t>((size_t)n_vec, std::max<size_t>(1, std::min(by_rows, by_bytes)));
 }
 
-// H v_k = d(grad E . v_k)/dr for k < n_vec (v, hv: [n_vec, N, 3]): the
-// second-order pass with no energy seed, continued to the positions; the
-// primal forward pass runs once for all directions.
+// H v_b = d(grad E . v_b)/dr = -ds/dr for s = -D_v E, for B directions (v, hv:
+// [B, N, 3]): the tangent pass along v, then the reverse pass over primal and
+// tangent values through every layer's edge geometry to the positions. The
+// primal values (h, h~, R3 and A~ per layer) are in the workspace.
+void hvp_directions(e3mi_model* M, e3mi_graph* G, int B, const float* v, float* hv, hipStream_t st) {
+  const Config& c = M->cfg;
+  Allocator* a = &M->alloc;
+  const int N = G->N, C = c.channels, T = c.layers, BN = B * N;
+  const int NC = (c.lmax + 1) * (c.lmax + 1);
+  const long Ecap = G->E_room;
+  const size_t E1 = (size_t)Ecap + 1;
+  const bool prod = c.correlation == 2;
+  Workspace& w = M->ws;
+  const int* row_ptr = G->row_ptr_x->as<int>();
+  const int* src = G->src_x->as<int>();
+  const float4* dvec = G->dvec_x->as<float4>();
+  auto floats = [&](std::unique_ptr<DevBuf>& b, size_t n) { return ensure(b, a, sizeof(float) * n).as<float>(); };
+  for (auto* q : {&w.vhd, &w.vhtd, &w.vatd, &w.vBpd}) q->resize(T + 1);
+  size_t a_max = 0;
+  for (const LayerPlan& L : M->plans) a_max = std::max(a_max, (size_t)L.a_per_atom);
+  float4* dd = ensure(w.vdd, a, sizeof(float4) * E1 * B).as<float4>();
+  float4* g = ensure(w.vg, a, sizeof(float4) * E1 * B).as<float4>();
+  float* Ad = floats(w.vAd, (size_t)BN * a_max);
+  float* Ab = floats(w.vA, 2 * (size_t)BN * a_max);          // adjoints of A, then of A_dot
+  float* x = floats(w.vx, 2 * (size_t)BN * NC * C);           // adjoints of h~, then of h~_dot
+  float* hcur = floats(w.vh_a, 2 * (size_t)BN * NC * C);      // adjoints of h^t, then of h_dot^t
+  float* hprev = floats(w.vh_b, 2 * (size_t)BN * NC * C);
+  HvpArgs ha{};
+  ha.lmax = c.lmax;
+  ha.N = N;
+  ha.C = C;
+  ha.B = B;
+  ha.row_ptr = row_ptr;
+  ha.src = src;
+  ha.rev = G->rev_x->as<int>();
+  ha.dvec = dvec;
+  ha.dd = dd;
+  ha.e_stride = (long)E1;
+  ha.r_row = first_pair_index(M, G);
+  ha.inv_nu = (float)(1.0 / c.avg_neighbors);
+  ha.Ad = Ad;
+  ha.Ab = Ab;
+  ha.geo = floats(w.vgeo, E1 * B * kHvpGeoRow);
+  auto layer_args = [&](int t) {
+    const LayerPlan& L = M->plans[t - 1];
+    ha.kind = L.kind;
+    ha.R3 = w.R3[t]->as<float>();
+    ha.h = w.h[t - 1]->as<float>();
+    ha.hd = t > 1 ? w.vhd[t - 1]->as<float>() : nullptr;
+    ha.h_nc = L.nc_in;
+  };
+  launch_hvp_edge_tangent(row_ptr, src, dvec, v, N, B, ha.e_stride, dd, st);
+  // ---- tangents ----
+  for (int t = 1; t <= T; ++t) {
+    const LayerPlan& L = M->plans[t - 1];
+    LayerWeights& W = *M->lw[t - 1];
+    layer_args(t);
+    {
+      ProfScope ps(&M->prof, stage_id(kTpFwd, t), st);
+      launch_hvp_tangent_sum(ha, st);
+    }
+    float* htd = floats(w.vhtd[t], (size_t)BN * L.nc_out * C);
+    if (prod) {
+      // A~_dot = A_dot W_mix (no self connection), B_dot, then h~_dot = B_dot W_lin + h_dot S
+      float* atd = floats(w.vatd[t], (size_t)BN * L.nc_a * C);
+      launch_mix(M, L, W, Ad, nullptr, atd, L.nc_a, BN, st);
+      ProductArgs pa = product_args(M, G, L, W, w.at[t]->as<float>());
+      pa.B_dirs = B;
+      pa.atd = atd;
+      pa.Bd = floats(w.vBpd[t], (size_t)BN * L.nc_out * C);
+      launch_product_jvp(pa, st);
+      launch_lin(M, L, W, pa.Bd, ha.hd, htd, BN, st, false);
+    } else {
+      ProfScope ps(&M->prof, stage_id(kMixFwd, t), st);
+      launch_mix(M, L, W, Ad, ha.hd, htd, L.nc_out, BN, st);
+    }
+    if (t < T)
+      launch_gate_dual_fwd(w.ht[t]->as<float>(), htd, floats(w.vhd[t], (size_t)BN * L.nc_out * C), N, L.nc_out, C, st,
+                           B);
+  }
+  // ---- reverse ----
+  for (int t = T; t >= 1; --t) {
+    const LayerPlan& L = M->plans[t - 1];
+    LayerWeights& W = *M->lw[t - 1];
+    layer_args(t);
+    const size_t xs = (size_t)BN * L.nc_out * C, hs = (size_t)BN * L.nc_in * C;
+    if (t == T)  // one component: the readout applies the gate and its reverse
+      launch_hvp_readout(w.ht[t]->as<float>(), w.vhtd[t]->as<float>(), M->read1->as<float>(), M->read2->as<float>(), N,
+                         B, C, x, x + xs, st);
+    else
+      launch_gate_dual_bwd(w.ht[t]->as<float>(), w.vhtd[t]->as<float>(), hcur, hcur + xs, x, x + xs, N, L.nc_out, C,
+                           st, B);
+    // the mix's output adjoints; both halves (of h~ and of h~_dot) go through
+    // the linear maps as one set of 2 B N atoms
+    const float* m = x;
+    int m_nc = L.nc_out;
+    float* dprev = t > 1 ? hprev : nullptr;
+    if (prod) {
+      float* Bb = floats(w.vBp, 2 * (size_t)BN * NC * C);
+      launch_lin_adjoint(M, L, W, x, Bb, dprev, 2 * BN, st, false);
+      const size_t as = (size_t)BN * L.nc_a * C;
+      float* at = floats(w.vat, 2 * (size_t)BN * NC * C);
+      ProductArgs pa = product_args(M, G, L, W, w.at[t]->as<float>());
+      pa.B_dirs = B;
+      pa.atd = w.vatd[t]->as<float>();
+      pa.Bb = Bb;
+      pa.Bc = Bb + xs;
+      pa.atb = at;
+      pa.atc = at + as;
+      launch_product_dual_bwd(pa, st);
+      m = at;
+      m_nc = L.nc_a;
+    }
+    {
+      ProfScope ps(&M->prof, stage_id(kMixBwd, t), st);
+      launch_mix_adjoint(M, L, W, m, m_nc, Ab, prod ? nullptr : dprev, 2 * BN, st);
+    }
+    ha.hb = hprev;
+    ha.hc = hprev + hs;
+    const int l_sc = std::min(prod ? L.lout : L.l3max_used, L.l1max);  // orders the self connection's adjoint wrote
+    ha.dh_acc = (l_sc + 1) * (l_sc + 1);
+    if (L.kind == 1) ha.msg = floats(w.vmsg, E1 * B * 2 * L.nc_in * C);
+    {
+      ProfScope ps(&M->prof, stage_id(kTpBwdEdge, t), st);
+      launch_hvp_adjoint(ha, st);
+    }
+    launch_hvp_geo(ha, Ecap, t != T ? 1 : 0, g, st);
+    std::swap(hcur, hprev);
+  }
+  launch_forces(row_ptr, G->rev_x->as<int>(), g, N, hv, st, nullptr, B, ha.e_stride);
+}
+
+// H v_k for k < n_vec (v, hv: [n_vec, N, 3]); the primal pass runs once for
+// all directions.
 void hessian_vectors(e3mi_model* M, e3mi_graph* G, const double* pos, int n_vec, const float* v, float* hv,
                      hipStream_t st) {
   E3MI_REQUIRE(v && hv, E3MI_EINVAL, "null argument");
   E3MI_REQUIRE(n_vec >= 0, E3MI_EINVAL, "n_vec must be >= 0");
-  Workspace& w = M->ws;
-  ensure(w.zeroE, &M->alloc, sizeof(double) * (size_t)std::max(G->S, 1));
-  E3MI_HIP(hipMemsetAsync(w.zeroE->p, 0, sizeof(double) * (size_t)std::max(G->S, 1), st));
+  if (n_vec == 0 || G->N == 0) return;
+  E3MI_REQUIRE(!M->cfg.coulomb, E3MI_EUNSUPPORTED,
+               "second-order passes (parameter gradients, Hessian-vector products) of the Coulomb term are not implemented");
+  forward_pass(M, G, pos, false, st, false, false, true);
+  if (factorised_first(M)) radial_derivs(M, G, 1, st);
+  const int batch = hvp_batch(M, G, n_vec);
   const size_t stride = 3 * (size_t)G->N;
-  for (int k = 0; k < n_vec; ++k)
-    second_order(M, G, pos, w.zeroE->as<double>(), v + k * stride, nullptr, hv + k * stride, st, k > 0);
+  for (int k = 0; k < n_vec; k += batch)
+    hvp_directions(M, G, std::min(batch, n_vec - k), v + k * stride, hv + k * stride, st);
 }
 
 // Replace the weights of a model (same configuration), e.g. after an optimiser step.

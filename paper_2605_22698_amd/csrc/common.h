@@ -90,34 +90,65 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// Lane exchanges within a wave on the vector ALU (no LDS pipe).
+// dpp<ctrl>: the value of another lane of the 16-lane row (lanes outside the
+// masks keep `old`)
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ float dpp(float old, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, 0xf, BANKS, false));
+}
+__device__ __forceinline__ float lane_xor1(float v) { return dpp<0xB1>(v, v); }   // quad_perm 1,0,3,2
+__device__ __forceinline__ float lane_xor2(float v) { return dpp<0x4E>(v, v); }   // quad_perm 2,3,0,1
+__device__ __forceinline__ float lane_xor8(float v) { return dpp<0x128>(v, v); }  // row_ror:8
+__device__ __forceinline__ float lane_xor4(float v) {
+  // lanes with bit 2 clear read lane + 4 (row_shl:4), the others lane - 4 (row_shr:4)
+  return dpp<0x114, 0xa>(dpp<0x104, 0x5>(v, v), v);
+}
+// lo of this lane and of the lane 32 (16) away where the lane's bit 5 (4) is
+// clear, hi of both where it is set: one swap and one addition
+__device__ __forceinline__ float halve32(float lo, float hi) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float halve16(float lo, float hi) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Sums of NV <= 16 per-lane values over the 64 lanes of a wave, by recursive
 // halving: each exchange over lane bits 5, 4, 3, 2 hands the partner the half
 // of the values this lane does not keep, so lane L ends with a partial of
-// value q = L >> 2, which the exchanges over bits 1 and 0 complete (17 lane
-// exchanges where 16 butterfly reductions take 96). Returns the total of
-// value lane >> 2 (zero for q >= NV).
+// value q = L >> 2, which the exchanges over bits 1 and 0 complete. All
+// exchanges run on the vector ALU. Returns the total of value lane >> 2 (zero
+// for q >= NV).
 template <int NV>
 __device__ __forceinline__ float wave_sum_scatter16(const float* v) {
   static_assert(NV <= 16, "at most 16 values");
   const int lane = threadIdx.x & 63;
   float a[8], b[4], c[2];
-  bool hi = lane & 32;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const float lo_v = q < NV ? v[q] : 0.0f, hi_v = q + 8 < NV ? v[q + 8] : 0.0f;
-    a[q] = (hi ? hi_v : lo_v) + __shfl_xor(hi ? lo_v : hi_v, 32);
-  }
-  hi = lane & 16;
+  for (int q = 0; q < 8; ++q) a[q] = halve32(q < NV ? v[q] : 0.0f, q + 8 < NV ? v[q + 8] : 0.0f);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) b[q] = (hi ? a[q + 4] : a[q]) + __shfl_xor(hi ? a[q] : a[q + 4], 16);
-  hi = lane & 8;
+  for (int q = 0; q < 4; ++q) b[q] = halve16(a[q], a[q + 4]);
+  bool hi = lane & 8;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) c[q] = (hi ? b[q + 2] : b[q]) + __shfl_xor(hi ? b[q] : b[q + 2], 8);
+  for (int q = 0; q < 2; ++q) c[q] = (hi ? b[q + 2] : b[q]) + lane_xor8(hi ? b[q] : b[q + 2]);
   hi = lane & 4;
-  float d = (hi ? c[1] : c[0]) + __shfl_xor(hi ? c[0] : c[1], 4);
-  d += __shfl_xor(d, 2);
-  d += __shfl_xor(d, 1);
+  float d = (hi ? c[1] : c[0]) + lane_xor4(hi ? c[0] : c[1]);
+  d += lane_xor2(d);
+  d += lane_xor1(d);
   return d;
+}
+
+// Sums of two per-lane values: a's total in lanes 0-31, b's in lanes 32-63.
+__device__ __forceinline__ float wave_sum_scatter2(float a, float b) {
+  float s = halve32(a, b);
+  s = halve16(s, s);
+  s += lane_xor8(s);
+  s += lane_xor4(s);
+  s += lane_xor2(s);
+  s += lane_xor1(s);
+  return s;
 }
 
 // Real spherical harmonics of a unit vector, component normalised
@@ -301,6 +332,48 @@ __device__ __forceinline__ void radial_basis(float r, float rc, int p, float* B,
       const float db = pref * ((n + 1) * w * c * inv_r - s * inv_r * inv_r);
       dB[n] = db * u + b * du_dr;
     }
+  }
+}
+
+// Bessel x envelope basis with its first and second radial derivatives.
+// Zero for r >= rc.
+template <int NB>
+__device__ __forceinline__ void radial_basis_d2(float r, float rc, int p, float* B, float* dB, float* d2B) {
+  const float x = r / rc;
+  if (!(x < 1.0f)) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) B[n] = dB[n] = d2B[n] = 0.0f;
+    return;
+  }
+  float xp2 = 1.0f;  // x^(p-2)
+  for (int k = 0; k < p - 2; ++k) xp2 *= x;
+  const float xp1 = xp2 * x, xp = xp1 * x;
+  const float fp = (float)p, c3 = 0.5f * fp * (fp + 1.0f) * (fp + 2.0f);
+  const float u = 1.0f - 0.5f * (fp + 1.0f) * (fp + 2.0f) * xp + fp * (fp + 2.0f) * xp * x -
+                  0.5f * fp * (fp + 1.0f) * xp * x * x;
+  const float om = 1.0f - x;
+  const float du = -c3 * xp1 * om * om / rc;
+  const float d2u = -c3 * ((fp - 1.0f) * xp2 * om * om - 2.0f * xp1 * om) / (rc * rc);
+  const float pref = sqrtf(2.0f / rc);
+  const float ir = 1.0f / r;
+  const float w = 3.14159265358979f / rc;
+  float s1, c1;  // angle addition, as radial_basis
+  sincosf(w * r, &s1, &c1);
+  float s = s1, c = c1;
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    if (n > 0) {
+      const float sn = s * c1 + c * s1;
+      c = c * c1 - s * s1;
+      s = sn;
+    }
+    const float kk = (n + 1) * w;
+    const float b = pref * s * ir;
+    const float b1 = pref * (kk * c * ir - s * ir * ir);
+    const float b2 = pref * (-kk * kk * s * ir - 2.0f * kk * c * ir * ir + 2.0f * s * ir * ir * ir);
+    B[n] = b * u;
+    dB[n] = b1 * u + b * du;
+    d2B[n] = b2 * u + 2.0f * b1 * du + b * d2u;
   }
 }
 

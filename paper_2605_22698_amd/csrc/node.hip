@@ -309,7 +309,9 @@ __global__ void __launch_bounds__(256) k_energy(const double* __restrict__ e_ato
 // reduction tree over the wave (bitwise repeatable).
 __global__ void __launch_bounds__(256) k_forces(const int* __restrict__ row_ptr, const int* __restrict__ rev,
                                                 const float4* __restrict__ g, int N, const float* __restrict__ extra,
-                                                float* __restrict__ F) {
+                                                float* __restrict__ F, long e_stride) {
+  g += blockIdx.y * e_stride;
+  F += 3L * blockIdx.y * N;
   const int i = (int)(((long)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63;
   if (i >= N) return;
@@ -397,9 +399,9 @@ void launch_energy(const double* e_atom, const int64_t* off, int S, double* ener
   k_energy<<<S, 256, 0, st>>>(e_atom, off, energy);
 }
 void launch_forces(const int* row_ptr, const int* rev, const float4* g, int N, float* F, hipStream_t st,
-                   const float* extra) {
+                   const float* extra, int B, long e_stride) {
   if (N == 0) return;
-  k_forces<<<blocks((long)N * 64, 256), 256, 0, st>>>(row_ptr, rev, g, N, extra, F);
+  k_forces<<<dim3(blocks((long)N * 64, 256), B), 256, 0, st>>>(row_ptr, rev, g, N, extra, F, e_stride);
 }
 
 }  // namespace e3mi

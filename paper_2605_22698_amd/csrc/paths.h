@@ -70,6 +70,17 @@ struct PathSet {
   static constexpr int NOUT = T.nout;
 };
 
+// Paths whose coefficients all have one value (those with a scalar factor:
+// (0, l, l), (l, 0, l) and (l, l, 0)): kernels take it out of the sums instead
+// of multiplying every term.
+constexpr bool one_coefficient(int g) {
+  for (int q = kNzBegin[g]; q < kNzBegin[g + 1]; ++q) {
+    const double d = (double)kC[q] - (double)kC[kNzBegin[g]];
+    if (d > 1e-6 || d < -1e-6) return false;
+  }
+  return true;
+}
+
 // Element offset of A[i, p, m3, k] in the grouped layout used between the
 // tensor product and the channel mix: for each output order l3 a block
 // [N, 2 l3 + 1, P_l3, C], blocks consecutive in l3.

@@ -131,19 +131,19 @@ __global__ void __launch_bounds__(256) k_product_bwd(const float* __restrict__ a
 template <int LMAX, int LOUT>
 __global__ void __launch_bounds__(256) k_product_jvp(const float* __restrict__ at, const float* __restrict__ atd,
                                                      const int* __restrict__ species, const float* __restrict__ w1,
-                                                     const float* __restrict__ w2, int N, int lg_c,
+                                                     const float* __restrict__ w2, int N, int B, int lg_c,
                                                      float* __restrict__ Bd) {
   using PS = ProductSet<LMAX, LOUT>;
   const int C = 1 << lg_c;
   const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= ((long)N << lg_c)) return;
-  const int i = (int)(e >> lg_c), k = (int)(e & (C - 1));
+  if (e >= ((long)B * N << lg_c)) return;
+  const int u = (int)(e >> lg_c), i = u % N, k = (int)(e & (C - 1));
   const int z = species[i];
   float a[PS::NA], ad[PS::NA];
 #pragma unroll
   for (int q = 0; q < PS::NA; ++q) {
     a[q] = at[((long)i * PS::NA + q) * C + k];
-    ad[q] = atd[((long)i * PS::NA + q) * C + k];
+    ad[q] = atd[((long)u * PS::NA + q) * C + k];
   }
   const float* w1z = w1 + (long)z * (LOUT + 1) * C + k;
   const float* w2z = w2 + (long)z * PS::NP * C + k;
@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(256) k_product_jvp(const float* __restrict__ a
     for (int m = 0; m < 2 * l3 + 1; ++m) b[l3 * l3 + m] += wp * t[m];
   });
 #pragma unroll
-  for (int q = 0; q < PS::NB; ++q) Bd[((long)i * PS::NB + q) * C + k] = b[q];
+  for (int q = 0; q < PS::NB; ++q) Bd[((long)u * PS::NB + q) * C + k] = b[q];
 }
 
 // Reverse of (B, B_dot) = (f(A~), f'(A~) A~_dot) for adjoints Bb of B and Bc
@@ -188,30 +188,30 @@ __global__ void __launch_bounds__(256) k_product_dual_bwd(const float* __restric
                                                           const int* __restrict__ species,
                                                           const float* __restrict__ w1, const float* __restrict__ w2,
                                                           const float* __restrict__ Bb, const float* __restrict__ Bc,
-                                                          int N, int lg_c, float* __restrict__ atb,
+                                                          int N, int B, int lg_c, float* __restrict__ atb,
                                                           float* __restrict__ atc, float* __restrict__ dw) {
   using PS = ProductSet<LMAX, LOUT>;
   const int C = 1 << lg_c;
   const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= ((long)N << lg_c)) return;
-  const int i = (int)(e >> lg_c), k = (int)(e & (C - 1));
+  if (e >= ((long)B * N << lg_c)) return;
+  const int u = (int)(e >> lg_c), i = u % N, k = (int)(e & (C - 1));
   const int z = species[i];
   float a[PS::NA], ad[PS::NA], ga[PS::NA], gc[PS::NA], bb[PS::NB], bc[PS::NB];
 #pragma unroll
   for (int q = 0; q < PS::NA; ++q) {
     a[q] = at[((long)i * PS::NA + q) * C + k];
-    ad[q] = atd[((long)i * PS::NA + q) * C + k];
+    ad[q] = atd[((long)u * PS::NA + q) * C + k];
     ga[q] = 0.0f;
     gc[q] = 0.0f;
   }
 #pragma unroll
   for (int q = 0; q < PS::NB; ++q) {
-    bb[q] = Bb[((long)i * PS::NB + q) * C + k];
-    bc[q] = Bc[((long)i * PS::NB + q) * C + k];
+    bb[q] = Bb[((long)u * PS::NB + q) * C + k];
+    bc[q] = Bc[((long)u * PS::NB + q) * C + k];
   }
   const float* w1z = w1 + (long)z * (LOUT + 1) * C + k;
   const float* w2z = w2 + (long)z * PS::NP * C + k;
-  float* dwi = DW ? dw + (long)i * (LOUT + 1 + PS::NP) * C + k : nullptr;
+  float* dwi = DW ? dw + (long)u * (LOUT + 1 + PS::NP) * C + k : nullptr;
 #pragma unroll
   for (int L = 0; L <= LOUT; ++L) {
     const float wl = w1z[L * C];
@@ -245,8 +245,8 @@ __global__ void __launch_bounds__(256) k_product_dual_bwd(const float* __restric
   });
 #pragma unroll
   for (int q = 0; q < PS::NA; ++q) {
-    atb[((long)i * PS::NA + q) * C + k] = ga[q];
-    atc[((long)i * PS::NA + q) * C + k] = gc[q];
+    atb[((long)u * PS::NA + q) * C + k] = ga[q];
+    atc[((long)u * PS::NA + q) * C + k] = gc[q];
   }
 }
 
@@ -268,13 +268,13 @@ void product_l(bool fwd, const ProductArgs& p, int lg, int grid, hipStream_t st)
 template <int LMAX, int LOUT>
 void product_dual_l(bool jvp, const ProductArgs& p, int lg, int grid, hipStream_t st) {
   if (jvp)
-    k_product_jvp<LMAX, LOUT><<<grid, 256, 0, st>>>(p.at, p.atd, p.species, p.w1, p.w2, p.N, lg, p.Bd);
+    k_product_jvp<LMAX, LOUT><<<grid, 256, 0, st>>>(p.at, p.atd, p.species, p.w1, p.w2, p.N, p.B_dirs, lg, p.Bd);
   else if (p.dw)
     k_product_dual_bwd<LMAX, LOUT, true><<<grid, 256, 0, st>>>(p.at, p.atd, p.species, p.w1, p.w2, p.Bb, p.Bc, p.N,
-                                                               lg, p.atb, p.atc, p.dw);
+                                                               p.B_dirs, lg, p.atb, p.atc, p.dw);
   else
     k_product_dual_bwd<LMAX, LOUT, false><<<grid, 256, 0, st>>>(p.at, p.atd, p.species, p.w1, p.w2, p.Bb, p.Bc,
-                                                                p.N, lg, p.atb, p.atc, nullptr);
+                                                                p.N, p.B_dirs, lg, p.atb, p.atc, nullptr);
 }
 
 template <class F>
@@ -311,7 +311,7 @@ void launch_product_jvp(const ProductArgs& p, hipStream_t st) {
   if (p.N == 0) return;
   E3MI_REQUIRE(p.at && p.atd && p.Bd, E3MI_EINVAL, "product block tangent: null argument");
   const int lg = log2_channels(p.C);
-  const int grid = (int)(((long)p.N * p.C + 255) / 256);
+  const int grid = (int)(((long)p.B_dirs * p.N * p.C + 255) / 256);
   product_dispatch(p, [&](auto lm, auto lo) { product_dual_l<lm, lo>(true, p, lg, grid, st); });
 }
 
@@ -320,7 +320,7 @@ void launch_product_dual_bwd(const ProductArgs& p, hipStream_t st) {
   E3MI_REQUIRE(p.at && p.atd && p.Bb && p.Bc && p.atb && p.atc, E3MI_EINVAL,
                "product block second-order adjoint: null argument");
   const int lg = log2_channels(p.C);
-  const int grid = (int)(((long)p.N * p.C + 255) / 256);
+  const int grid = (int)(((long)p.B_dirs * p.N * p.C + 255) / 256);
   product_dispatch(p, [&](auto lm, auto lo) { product_dual_l<lm, lo>(false, p, lg, grid, st); });
 }
 

@@ -603,6 +603,99 @@ __global__ void __launch_bounds__(256) k_radial_dual_bwd(const int* __restrict__
   }
 }
 
+// R and its first and second derivative with respect to the edge length, for
+// Hessian-vector products: R, R' and R'' depend on the length alone, so the
+// tangent of R along any direction is R' r_dot, and the adjoint of the MLP is
+// a dot product with R' and R''. One evaluation then serves every direction
+// of a call (the MLP's own tangent and adjoint, 8 products of K = 64 per edge
+// and direction, are never formed). One row [3][PC] (R, R', R'') per pair
+// owner, or per edge without the pair list.
+// With each activation x: s = silu(x), s' = silu'(x) x', s'' = silu''(x) x'^2 + silu'(x) x''.
+template <int NB>
+__global__ void __launch_bounds__(256, 2) k_radial_d2(const float4* __restrict__ dvec, const int* __restrict__ row_ptr_x,
+                                                   int N, const float* __restrict__ W1, const float* __restrict__ W2,
+                                                   const float* __restrict__ W3, int ld3, int PC,
+                                                   float* __restrict__ R3, float rc, int p,
+                                                   const int* __restrict__ own, const int* __restrict__ n_own) {
+  __shared__ float Bs[3][kTile][NB + 1];
+  __shared__ float X[3][kTile][kLd];
+  const int E = own ? *n_own : row_ptr_x[N];
+  const int e0 = blockIdx.x * kTile;
+  if (e0 >= E) return;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (t < kTile) {
+    const int q = e0 + t;
+    const float r = q < E ? dvec[own ? own[q] : q].w : rc;
+    float b[NB], db[NB], d2b[NB];
+    radial_basis_d2<NB>(r, rc, p, b, db, d2b);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      Bs[0][t][n] = b[n];
+      Bs[1][t][n] = db[n];
+      Bs[2][t][n] = d2b[n];
+    }
+  }
+  __syncthreads();
+  {
+    const int row = t >> 2, cb = (t & 3) * 16;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      float x = 0.0f, x1 = 0.0f, x2 = 0.0f;
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const float wv = W1[n * kH + cb + j];
+        x += Bs[0][row][n] * wv;
+        x1 += Bs[1][row][n] * wv;
+        x2 += Bs[2][row][n] * wv;
+      }
+      const float g = silu_grad(x);
+      X[0][row][cb + j] = siluf(x);
+      X[1][row][cb + j] = g * x1;
+      X[2][row][cb + j] = silu_grad2(x) * x1 * x1 + g * x2;
+    }
+  }
+  __syncthreads();
+  {
+    const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
+    f32x16 a[3] = {};
+#pragma unroll 8
+    for (int kk = 0; kk < kH; kk += 2) {
+      const float b = W2[(kk + (lane >> 5)) * kH + cb + (lane & 31)];
+#pragma unroll
+      for (int s = 0; s < 3; ++s) a[s] = mfma32(X[s][rb + (lane & 31)][kk + (lane >> 5)], b, a[s]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = rb + acc_row(r, lane), col = cb + (lane & 31);
+      const float x = a[0][r], x1 = a[1][r], g = silu_grad(x);
+      X[0][row][col] = siluf(x);
+      X[1][row][col] = g * x1;
+      X[2][row][col] = silu_grad2(x) * x1 * x1 + g * a[2][r];
+    }
+  }
+  __syncthreads();
+  // one 32-row block at a time (three accumulators): two would leave one wave per SIMD
+  for (int q = w; q < 2 * (PC / 32); q += 4) {
+    const int cc = (q >> 1) * 32, rb = (q & 1) * 32;
+    f32x16 a[3] = {};
+#pragma unroll 4
+    for (int kk = 0; kk < kH; kk += 2) {
+      const float b = W3[(kk + (lane >> 5)) * ld3 + cc + (lane & 31)];
+#pragma unroll
+      for (int s = 0; s < 3; ++s) a[s] = mfma32(X[s][rb + (lane & 31)][kk + (lane >> 5)], b, a[s]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int e = e0 + rb + acc_row(r, lane);
+      if (e < E) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) R3[((long)e * 3 + s) * PC + cc + (lane & 31)] = a[s][r];
+      }
+    }
+  }
+}
+
 inline int tiles(long n) { return (int)((n + kTile - 1) / kTile); }
 
 
@@ -712,5 +805,13 @@ void launch_radial_dual_bwd(const int* row_ptr_x, int N, long e_cap, const float
                             float* P2g, hipStream_t st) {
   if (e_cap == 0) return;
   k_radial_dual_bwd<<<tiles(e_cap), 256, 0, st>>>(row_ptr_x, N, W2T, W3T, PC, Rb, Rc, P1d, P2d, P1g, P2g);
+}
+void launch_radial_d2(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
+                      const float* W2, const float* W3, int ld3, int PC, float* R3, float rc, int p, const int* own,
+                      const int* n_own, hipStream_t st) {
+  if (e_cap == 0) return;
+  if (n_basis != 8) throw Error(E3MI_EUNSUPPORTED, "n_basis must be 8");
+  if (PC % 32) throw Error(E3MI_EUNSUPPORTED, "paths x channels must be a multiple of 32");
+  k_radial_d2<8><<<tiles(e_cap), 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC, R3, rc, p, own, n_own);
 }
 }  // namespace e3mi

@@ -243,8 +243,6 @@ struct TpArgs {
   float* Rc;         // out: adjoint of the tangent of R
   float* hb;         // in/out (+=): adjoint of h
   float* hc;         // in/out (+=): adjoint of the tangent of h (NULL: not needed)
-  float* Yb;         // out: adjoint of the harmonics per edge [E, 16]
-  float* Yc;         // out: adjoint of the harmonics' tangent per edge [E, 16]
   // receiver chunk (first-order kernels 0-2): receivers i0 .. i0 + n_recv - 1
   // (n_recv 0: all N from i0 = 0), R and dR indexed from edge e_first
   int i0, n_recv, e_first;
@@ -260,7 +258,6 @@ struct TpArgs {
 // which: 0 forward, 1 edge adjoint (dR, dY), 2 node adjoint (dh += ...),
 //        3 tangent forward (Ad), 4 second-order edge adjoint (Rb, Rc),
 //        5 second-order node adjoint (hb, hc += ...),
-//        6 adjoints of the harmonics and their tangent (Yb, Yc) for Hessian-vector products,
 //        7 node adjoint from the messages that pass 1 wrote (msg set), for the
 //          chunk's receivers [i0, i0 + n_recv) as senders' partners
 void launch_tp(int which, const TpArgs& a, hipStream_t st);
@@ -309,18 +306,54 @@ void launch_readout(const float* h, int nc, const int* species, const float* Wr,
 void launch_readout_gated(const float* xt, int n_parts, const int* species, const float* Wr, const float* w2,
                           const float* e0, int N, int C, double* e_atom, float* dht, hipStream_t st);
 void launch_energy(const double* e_atom, const int64_t* off, int S, double* energy, hipStream_t st);
+// (B > 1: g [B, e_stride] -> F [B, N, 3])
 void launch_forces(const int* row_ptr, const int* rev, const float4* g, int N, float* F, hipStream_t st,
-                   const float* extra = nullptr);
+                   const float* extra = nullptr, int B = 1, long e_stride = 0);
 
-// Hessian-vector products (grad.hip): per-edge position adjoint of the
-// second-order scalar through one layer's edge geometry, g (+)= ...
-void launch_hvp_geo(int lmax, const int* row_ptr_x, int N, long e_cap, const float4* dvec, const float4* dd,
-                    const float* Yb, const float* Yc, const float* P1g, const float* W1, float rc, int p,
-                    int accumulate, float4* g, hipStream_t st);
+// ---- Hessian-vector products (hvp.hip) ------------------------------------------------
+// One layer's tangent or adjoint for a batch of B directions: atom rows are
+// (b, i) = b N + i, edge rows b e_stride + e.
+constexpr int kHvpGeoRow = 36;  // floats of an edge's geo row
+struct HvpArgs {
+  int lmax, kind, N, C, B;
+  const int* row_ptr;
+  const int* src;
+  const int* rev;
+  const float4* dvec;
+  const float4* dd;   // per direction and edge: d_dot, r_dot
+  long e_stride;
+  const float* R3;    // [row, 3, P, C]: R, R', R'' (launch_radial_d2)
+  const int* r_row;   // row of edge e (NULL: e)
+  const float* h;     // layer input [N, h_nc, C]
+  const float* hd;    // its tangents [B N, h_nc, C] (not read by the first layer)
+  int h_nc;
+  float inv_nu;
+  float* Ad;          // tangent pass out: A_dot, grouped layout of B N atoms
+  const float* Ab;    // adjoint pass in: adjoints of A (B N atoms), then of A_dot (B N atoms), grouped layout of 2 B N atoms
+  float* geo;         // adjoint pass out, per direction and edge
+  float* msg;         // scratch [B e_stride, 2, h_nc, C] of layers with every path after the first
+  float* hb;          // adjoint pass out [B N, h_nc, C]: adjoint of h and of h_dot; components
+  float* hc;          // below dh_acc are added to, the others written (not written by the first layer)
+  int dh_acc;
+};
+void launch_hvp_tangent_sum(const HvpArgs& a, hipStream_t st);
+void launch_hvp_adjoint(const HvpArgs& a, hipStream_t st);
+void launch_hvp_edge_tangent(const int* row_ptr, const int* src, const float4* dvec, const float* v, int N, int B,
+                             long e_stride, float4* dd, hipStream_t st);
+// g [B, e_stride] (+)= the position adjoint of a layer's geo rows
+void launch_hvp_geo(const HvpArgs& a, long e_cap, int accumulate, float4* g, hipStream_t st);
+// from the last layer's pre-gate values x [N, C] and tangents xd [B N, C]: adjoints xb, xc [B N, C]
+void launch_hvp_readout(const float* x, const float* xd, const float* Wr, const float* w2, int N, int B, int C,
+                        float* xb, float* xc, hipStream_t st);
+// R3 rows of every edge pair (own, n_own) or edge
+void launch_radial_d2(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
+                      const float* W2, const float* W3, int ld3, int PC, float* R3, float rc, int p, const int* own,
+                      const int* n_own, hipStream_t st);
 
 // ---- product block of body order 2 (product.hip) -------------------------------------
 struct ProductArgs {
   int lmax = 0, lout = 0, N = 0, C = 0;
+  int B_dirs = 1;                  // second-order pass: directions; tangents and adjoints have B N atoms, A~ N
   const float* at = nullptr;       // A~ [N, (lmax+1)^2, C]
   const int* species = nullptr;    // [N]
   const float* w1 = nullptr;       // [S, lout+1, C]
@@ -397,9 +430,10 @@ void launch_radial_dual_bwd(const int* row_ptr_x, int N, long e_cap, const float
                             float* P2g, hipStream_t st);
 void launch_edge_tangent(const int* row_ptr, const int* src, const float4* dvec, const float* v, int N, float4* dd,
                          hipStream_t st);
-void launch_gate_dual_fwd(const float* x, const float* xd, float* hd, int N, int nc, int C, hipStream_t st);
+// B directions: x has N atoms, the tangents and adjoints B N
+void launch_gate_dual_fwd(const float* x, const float* xd, float* hd, int N, int nc, int C, hipStream_t st, int B = 1);
 void launch_gate_dual_bwd(const float* x, const float* xd, const float* hb, const float* hc, float* xb, float* xc,
-                          int N, int nc, int C, hipStream_t st);
+                          int N, int nc, int C, hipStream_t st, int B = 1);
 void launch_readout_dual(const float* h, const float* hd, int nc, const int* owner, const double* gE, const float* Wr,
                          const float* w2, int N, int C, float* Pb, float* Pc, float* w2c, float* hb, float* hc,
                          float* eb, hipStream_t st);

@@ -173,3 +173,41 @@ def test_isolated_atom_and_empty_structure(correlation):
     grad = m.param_grad(g, posd, gE, gF)
     torch.cuda.synchronize()
     assert torch.isfinite(grad).all()
+
+
+@pytest.mark.parametrize("lmax,C,layers,correlation,n_vec,per_edge", [
+    (3, 128, 2, 1, 1, False), (3, 128, 2, 1, 5, False), (3, 64, 2, 1, 2, True), (2, 32, 2, 1, 3, False),
+    (2, 32, 1, 1, 3, False), (3, 32, 3, 1, 3, False), (3, 128, 3, 1, 2, False), (2, 64, 2, 2, 4, True)])
+def test_batches_of_directions_against_oracle(lmax, C, layers, correlation, n_vec, per_edge):
+    # several directions per launch (odd counts leave a workgroup with one),
+    # every layer kind and channel count, R per pair and per edge
+    import torch
+    cfg = synth.ModelConfig(lmax=lmax, channels=C, layers=layers, n_species=3, cutoff=5.0,
+                            avg_neighbors=synth.nominal_neighbors(0.1, 5.0), correlation=correlation)
+    rng = np.random.default_rng(160)
+    b = synth.concat([synth.jittered_lattice(25, 0.1, 0.3, 3, rng), synth.open_box(17, 3, rng)])
+    m = model(cfg, 161)
+    m.set_flags(radial_per_edge=per_edge)
+    g, pos = _graph(m, b, 0.5)
+    V = rng.normal(size=(n_vec,) + b.pos.shape)
+    H = m.hessian_vectors(g, pos, torch.tensor(V, dtype=torch.float32, device=device())).cpu().numpy()
+    ref = om.Model(cfg, synth.model_weights(cfg, 161))
+    for k in range(n_vec):
+        _check(H[k].astype(np.float64), om.hessian_vector(ref, b, V[k]), f"direction {k} of {n_vec}")
+
+
+def test_more_directions_than_one_batch_holds():
+    # 270 directions of 90 atoms are more than one batch of atom rows: the
+    # first and last direction of each batch against the oracle
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=2, n_species=3, cutoff=5.0,
+                            avg_neighbors=synth.nominal_neighbors(0.1, 5.0))
+    b = synth.open_box(90, 3, np.random.default_rng(162))
+    m = model(cfg, 163)
+    g, pos = _graph(m, b)
+    H = m.hessian(g, pos)[0].cpu().numpy().astype(np.float64)
+    ref = om.Model(cfg, synth.model_weights(cfg, 163))
+    assert np.abs(H - H.T).max() <= REL * np.abs(H).max()
+    for k in (0, 182, 183, 269):
+        v = np.zeros(270)
+        v[k] = 1.0
+        _check(H[:, k].reshape(-1, 3), om.hessian_vector(ref, b, v.reshape(-1, 3)), f"column {k}")
