@@ -208,7 +208,7 @@ struct Workspace {
   std::unique_ptr<DevBuf> dd, Bd, Prb, Prc, w2c, eb, xb, xc, Ab, Ac, hb_a, hb_b, hc_a, hc_b, Rb, Rc, P1g, P2g,
       partial, vf;
   std::unique_ptr<DevBuf> G1, dG1;  // first layer, [N, (l3+1)^2, S*64]
-  std::unique_ptr<DevBuf> P2f;      // first layer's second hidden pre-activation per edge pair (or edge), [., 64]
+  std::unique_ptr<DevBuf> H2f;      // first layer's second hidden layer and its derivative per edge pair (or edge), [., 128]
   std::unique_ptr<DevBuf> q_raw, q, pot, fc, pot_mean;  // electrostatics: charges, potential, forces
   std::vector<std::unique_ptr<DevBuf>> at;             // product block: A~ per layer
   // Hessian-vector products: R, R' and R'' per layer, and a batch of directions' tangents and adjoints
@@ -756,10 +756,11 @@ void launch_mix_adjoint(e3mi_model* M, const LayerPlan& L, LayerWeights& W, cons
 
 // Whether the energy/force path evaluates layer 1 through the species
 // factorisation (first.hip): always possible for layer 1 (its input is the
-// embedding) when the species x hidden width fits the kernel's LDS budget.
+// embedding), used for up to 8 species (G and dG hold (l+1)^2 x 64 values per
+// atom and species, 64 KB at 8).
 bool factorised_first(const e3mi_model* M) {
   const int S64 = M->cfg.n_species * M->cfg.radial_hidden;
-  return M->first_factorised && S64 <= 512 && first_lds_bytes(M->plans[0].l3max_used, S64) <= 65536;
+  return M->first_factorised && S64 <= 512;
 }
 
 // Whether layer t runs through the fused last-layer kernels (last.hip): the
@@ -870,7 +871,7 @@ EdgePairs graph_pairs(const e3mi_graph* G, bool compact = false) {
 const EdgePairs* pairs_for(const e3mi_model* M, const RChunk& ch, const EdgePairs& p) {
   return M->edge_pairs && ch.e1 < 0 ? &p : nullptr;
 }
-// the first layer's hidden activations: row pair_of[e] per edge pair, or row e
+// rows of the first layer's hidden layers and of R: pair_of[e] per edge pair, or e
 const int* first_pair_index(const e3mi_model* M, const e3mi_graph* G) {
   return M->edge_pairs ? G->pair_of->as<int>() : nullptr;
 }
@@ -996,7 +997,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
   const int S64 = c.n_species * c.radial_hidden;
   if (fact) {
     ensure(w.G1, a, sizeof(float) * (size_t)N * M->plans[0].nc_a * S64);
-    ensure(w.P2f, a, sizeof(float) * (size_t)c.radial_hidden * (size_t)(Ecap + 1));
+    ensure(w.H2f, a, sizeof(float) * 2 * (size_t)c.radial_hidden * (size_t)(Ecap + 1));
     if (!derivs) ensure(w.dG1, a, sizeof(float) * (size_t)N * M->plans[0].nc_a * S64);
   }
   // product block: the mix writes A~ (no self connection); B follows, then
@@ -1031,9 +1032,9 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
         const EdgePairs prs = graph_pairs(G);
         launch_first_hidden(dvec, row_ptr, N, Ecap, M->edge_pairs ? prs.own : nullptr,
                             M->edge_pairs ? prs.n_own : nullptr, W.rad1.as<float>(), W.rad2.as<float>(), rc, p_env,
-                            w.P2f->as<float>(), st);
-        launch_first(true, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, W.rad1.as<float>(), nullptr,
-                     first_pair_index(M, G), w.P2f->as<float>(), G1, nullptr, nullptr, 0, rc, p_env, st);
+                            w.H2f->as<float>(), st);
+        launch_first(true, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, first_pair_index(M, G),
+                     w.H2f->as<float>(), G1, nullptr, nullptr, 0, st);
       }
       float* ht = w.ht[1]->as<float>();
       float* mix_out = prod ? w.at[1]->as<float>() : ht;
@@ -1280,9 +1281,8 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
       }
       {
         ProfScope ps(&M->prof, stage_id(kFirstBwd, 1), st);
-        launch_first(false, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, W.rad1.as<float>(),
-                     W.rad2T.as<float>(), first_pair_index(M, G), w.P2f->as<float>(), nullptr, dG1, g,
-                     T != 1 ? 1 : 0, rc, p_env, st);
+        launch_first(false, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, first_pair_index(M, G),
+                     w.H2f->as<float>(), nullptr, dG1, g, T != 1 ? 1 : 0, st);
       }
       continue;
     }
@@ -1426,7 +1426,7 @@ size_t footprint(const e3mi_model* M, int64_t n_atoms, int64_t n_edges) {
     a_max = std::max(a_max, (size_t)L.a_per_atom);
     if (t == 1 && factorised_first(M)) {
       b += 2 * N * L.nc_out * (size_t)c.n_species * c.radial_hidden * 4;  // G and dG
-      b += E * (size_t)c.radial_hidden * 4;                                // hidden pre-activations
+      b += 2 * E * (size_t)c.radial_hidden * 4;                            // hidden layer and its derivative
       continue;
     }
     if (fused_last(M, L, false, bf16)) continue;  // no per-edge R

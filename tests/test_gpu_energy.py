@@ -207,3 +207,16 @@ def test_fused_last_layer_matches_unfused_path(lmax, channels):
     assert np.abs(Ei1 - Ei2).max() <= 1e-5 * np.abs(Ei2).max()
     assert abs(E1[0] - E2[0]) <= 1e-6 * abs(E2[0])
     assert np.abs(F1 - F2).max() <= 1e-4 * np.abs(F2).max()
+
+
+@pytest.mark.parametrize("n,n_species,lmax", [(2, 1, 3), (17, 1, 3), (18, 2, 2), (65, 1, 2), (66, 4, 3), (130, 1, 3)])
+def test_first_layer_row_lengths(n, n_species, lmax):
+    # every atom inside every other's cutoff: rows of n - 1 edges, at and one
+    # past the blocks of 16 edges and tiles of 64 that the first layer takes
+    cfg = synth.ModelConfig(lmax=lmax, channels=32, layers=2, n_species=n_species, cutoff=5.0, avg_neighbors=float(n))
+    b = synth.uniform_cluster(n, 2.8, 0.3, n_species, np.random.default_rng(170 + n))
+    E, F, Ei, g = gpu_energy_forces(model(cfg, 171), b)
+    assert g.last_edge_count() == n * (n - 1)
+    Er, Fr, Eir = _oracle(cfg, 171, b)
+    check_energy(E, Er, Eir)
+    check_forces(F, Fr)
