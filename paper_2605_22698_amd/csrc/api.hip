@@ -227,11 +227,14 @@ struct Workspace {
   unsigned msg_tag = 0;
   int last_parts = -1;  // last layer left before its gate: partial products in mixp (0: h~ in ht[T])
   bool r_bf16 = false;  // the last forward pass stored R and dR in BF16 where r_bf16_layer says so
-  // per layer: evaluated in receiver chunks with R of every edge kept (the
-  // adjoint reads chunk c's R at its first edge instead of recomputing it)
+  // per layer: R of every edge kept. BF16 mode: evaluated in receiver chunks,
+  // the adjoint reads chunk c's R at its first edge instead of recomputing it.
+  // FP32 (rows of R and R'): evaluated at once
   std::vector<char> r_whole;
   // per layer: R stored once per edge pair (row = the edge's pair index)
   std::vector<char> r_compact;
+  std::vector<size_t> r_rows;                          // per layer (FP32): rows of R in w.R[t], rows of R' follow
+  int n_own_host = 0;                                  // pair owners, read back with rp_host
 };
 
 }  // namespace e3mi
@@ -828,13 +831,14 @@ size_t r_chunk_edges(const e3mi_model* M, long Ecap, int PCu) {
   return std::min<size_t>((size_t)(Ecap + 1), M->r_chunk_bytes / ((size_t)PCu * sizeof(float)));
 }
 
-// The pruned row pointer on the host, read back once per evaluation.
+// The pruned row pointer (and the pair count) on the host, read back once per evaluation.
 const std::vector<int>& pruned_rows(e3mi_model* M, e3mi_graph* G, hipStream_t st) {
   Workspace& w = M->ws;
   if (!w.rp_valid) {
     w.rp_host.resize((size_t)G->N + 1);
     E3MI_HIP(hipMemcpyAsync(w.rp_host.data(), G->row_ptr_x->p, sizeof(int) * ((size_t)G->N + 1),
                             hipMemcpyDeviceToHost, st));
+    E3MI_HIP(hipMemcpyAsync(&w.n_own_host, G->own_ptr->as<int>() + G->N, sizeof(int), hipMemcpyDeviceToHost, st));
     E3MI_HIP(hipStreamSynchronize(st));
     w.rp_valid = true;
   }
@@ -897,7 +901,51 @@ void radial_derivs(e3mi_model* M, e3mi_graph* G, int t, hipStream_t st) {
 void set_chunk(TpArgs& ta, const RChunk& ch) {
   ta.i0 = ch.e1 < 0 ? 0 : ch.i0;
   ta.n_recv = ch.e1 < 0 ? 0 : ch.i1 - ch.i0;
-  ta.e_first = ch.e1 < 0 ? 0 : ch.e0;
+  ta.e_first = ta.r_first = ch.e1 < 0 ? 0 : ch.e0;
+}
+
+// FP32 energies and forces keep rows of R and of R' of every pair (every edge
+// with flag 8) in w.R[t] where they fit, else of one receiver chunk's edges at a
+// time. Fits: the row capacity holds one chunk's worth of R and as much of R'
+// (no host synchronisation), or the rows this call needs stay within
+// r_keep_bytes over the layers (kept: what the layers before took).
+// Returns the rows to allocate.
+size_t r_rows_plan(e3mi_model* M, e3mi_graph* G, int t, int PCu, size_t& kept, hipStream_t st) {
+  Workspace& w = M->ws;
+  const size_t cap = (size_t)G->E_room + 1, chunk = r_chunk_edges(M, G->E_room, PCu);
+  w.r_whole[t] = 1;
+  if (chunk >= cap) return cap;
+  const size_t e_in = (size_t)pruned_rows(M, G, st)[G->N];
+  const size_t n = (M->edge_pairs ? (size_t)w.n_own_host : e_in) + 1;
+  // room for 1/8 more rows than this call has, so that the count's drift
+  // between rebuilds does not reallocate
+  const size_t room = std::min(cap, n + n / 8), bytes = 2 * sizeof(float) * room * PCu;
+  if (kept + bytes <= M->r_keep_bytes) {
+    kept += bytes;
+    return w.R[t] && w.R[t]->bytes >= 2 * sizeof(float) * n * PCu ? n : room;
+  }
+  w.r_whole[t] = 0;
+  return chunk;
+}
+
+// R' rows of layer t, after R's
+float* rp_rows(const e3mi_model* M, int t) {
+  return M->ws.R[t]->as<float>() + M->ws.r_rows[t] * M->plans[t - 1].p_used * M->cfg.channels;
+}
+
+// R and R' of layer t: every row (ch NULL) or a receiver chunk's edges
+void radial_rows(e3mi_model* M, e3mi_graph* G, int t, const RChunk* ch, hipStream_t st) {
+  const Config& c = M->cfg;
+  const LayerPlan& L = M->plans[t - 1];
+  LayerWeights& W = *M->lw[t - 1];
+  const EdgePairs prs = graph_pairs(G);
+  const bool pairs = M->edge_pairs && !ch;
+  ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
+  launch_radial_d1(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
+                   W.rad2.as<float>(), W.rad3.as<float>(), L.p_full * c.channels, L.p_used * c.channels,
+                   M->ws.R[t]->as<float>(), rp_rows(M, t), (float)c.cutoff, c.envelope_p, ch ? ch->e0 : 0,
+                   ch ? ch->e1 : -1,
+                   pairs ? prs.own : nullptr, pairs ? prs.n_own : nullptr, st);
 }
 
 // Primal forward pass: edge selection, embedding and every layer. Leaves
@@ -953,6 +1001,12 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     }
     if (t == 1 && factorised_first(M) && !keep_A) continue;
     if (fused_last(M, L, keep_A, bf16)) continue;
+    if (!keep_A && !bf16) {
+      w.r_rows.resize(T + 1);
+      w.r_rows[t] = r_rows_plan(M, G, t, L.p_used * C, kept, st);
+      ensure(w.R[t], a, 2 * sizeof(float) * w.r_rows[t] * L.p_used * C);
+      continue;
+    }
     // the second-order pass keeps R of every edge (skin-list capacity);
     // otherwise one chunk, or every edge inside the cutoff while the layers'
     // kept R stays within r_keep_bytes
@@ -1034,7 +1088,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
                             M->edge_pairs ? prs.n_own : nullptr, W.rad1.as<float>(), W.rad2.as<float>(), rc, p_env,
                             w.H2f->as<float>(), st);
         launch_first(true, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, first_pair_index(M, G),
-                     w.H2f->as<float>(), G1, nullptr, nullptr, 0, st);
+                     w.H2f->as<float>(), G1, nullptr, nullptr, nullptr, 0, st);
       }
       float* ht = w.ht[1]->as<float>();
       float* mix_out = prod ? w.at[1]->as<float>() : ht;
@@ -1094,10 +1148,12 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     }
     float* R = (derivs ? w.R3[t] : w.R[t])->as<float>();  // BF16 values when r_bf16
     const int PCu = L.p_used * C;
-    const std::vector<RChunk> chunks = keep_A || derivs ? std::vector<RChunk>{RChunk{0, N, 0, -1}} : r_chunks(M, G, PCu, st);
+    const std::vector<RChunk> chunks = keep_A || derivs || (!bf16 && w.r_whole[t])
+                                           ? std::vector<RChunk>{RChunk{0, N, 0, -1}} : r_chunks(M, G, PCu, st);
     TpArgs ta{};
     const bool lr_bf16 = r_bf16_layer(w, L);
     ta.r_bf16 = lr_bf16 ? 1 : 0;
+    ta.fp32 = bf16 ? 0 : 1;
     ta.lmax = c.lmax;
     ta.kind = L.kind;
     ta.cpt = cpt_for(L, C);
@@ -1113,14 +1169,18 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     ta.C = C;
     ta.inv_nu = inv_nu;
     const RadialBf16 bfw = W.bf16_view();
-    w.r_compact[t] = r_compact_for(M, chunks, keep_A) ? 1 : 0;
+    const bool rows = !keep_A && !bf16 && !derivs;  // rows of R and R'
+    if (!rows) w.r_compact[t] = r_compact_for(M, chunks, keep_A) ? 1 : 0;
     const EdgePairs prs = graph_pairs(G, w.r_compact[t]);
     ta.r_row = w.r_compact[t] ? G->pair_of->as<int>() : nullptr;
     for (const RChunk& ch : chunks) {
-      void* Rc = chunk_r(w, t, R, ch, PCu, lr_bf16 ? 2 : 4);
+      void* Rc = rows ? R : chunk_r(w, t, R, ch, PCu, lr_bf16 ? 2 : 4);
       if (derivs) {
         radial_derivs(M, G, t, st);
         ta.r_stride = 3 * PCu;
+        ta.r_row = first_pair_index(M, G);
+      } else if (rows && w.r_whole[t]) {
+        radial_rows(M, G, t, nullptr, st);
         ta.r_row = first_pair_index(M, G);
       } else {
         ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
@@ -1231,6 +1291,8 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
   const int S64 = c.n_species * c.radial_hidden;
   const bool prod = c.correlation == 2;
   const bool bf16 = M->precision == E3MI_BF16_MIX;
+  // what the layers so far left: edge rows [dE/dr, dY] in dY, gradients in g
+  bool rows_live = false, g_live = false;
   for (int t = T; t >= 1; --t) {
     const LayerPlan& L = M->plans[t - 1];
     LayerWeights& W = *M->lw[t - 1];
@@ -1282,8 +1344,10 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
       {
         ProfScope ps(&M->prof, stage_id(kFirstBwd, 1), st);
         launch_first(false, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, first_pair_index(M, G),
-                     w.H2f->as<float>(), nullptr, dG1, g, T != 1 ? 1 : 0, st);
+                     w.H2f->as<float>(), nullptr, dG1, rows_live ? w.dY->as<float>() : nullptr, g, g_live ? 1 : 0,
+                     st);
       }
+      rows_live = false;
       continue;
     }
     {
@@ -1298,8 +1362,9 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
       LastArgs la = last_args(M, G, L, W, hin);
       la.dA = A;
       la.g = g;
-      la.accumulate = t != T ? 1 : 0;
+      la.accumulate = g_live ? 1 : 0;
       la.dh = dother;
+      g_live = true;
       {
         ProfScope ps(&M->prof, stage_id(kLastBwd, t), st);
         launch_last(false, la, st);
@@ -1323,7 +1388,7 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
     ta.h = hin;
     ta.h_nc = L.nc_in;
     ta.dA = A;
-    ta.dR = w.dR->as<float>();
+    ta.dR = bf16 ? w.dR->as<float>() : nullptr;  // FP32 adjoints write none
     ta.dY = w.dY->as<float>();
     ta.N = N;
     ta.C = C;
@@ -1343,13 +1408,44 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
       ta.msg = ensure(w.msg, &M->alloc, sizeof(float) * r_chunk_edges(M, Ecap, PCu) * L.nc_in * C).as<float>();
       ta.touched = ensure(w.touched, &M->alloc, sizeof(int) * ((size_t)N + 1)).as<int>();
     }
-    // with more than one chunk R is recomputed chunk by chunk (the forward
-    // pass kept only the last chunk), unless it was kept whole
+    ta.rev = G->rev_x->as<int>();
+    if (!bf16) {
+      // FP32: R' beside R takes the place of dR and the radial adjoint. With
+      // every row in memory only the messages' buffer makes chunks; else the
+      // chunk's rows are evaluated again
+      const bool whole = w.r_whole[t] != 0, sender = tps_supported(ta);
+      ta.Rp = rp_rows(M, t);
+      ta.row_add = rows_live ? 1 : 0;
+      ta.r_row = whole ? first_pair_index(M, G) : nullptr;
+      if (t == 1) ta.dh = nullptr;
+      const std::vector<RChunk> chunks =
+          whole && !use_msg ? std::vector<RChunk>{RChunk{0, N, 0, -1}} : r_chunks(M, G, PCu, st);
+      for (const RChunk& ch : chunks) {
+        if (!whole) radial_rows(M, G, t, &ch, st);
+        set_chunk(ta, ch);
+        if (whole) ta.r_first = 0;
+        ta.tag = (int)(++w.msg_tag & 0x7fffffffu);
+        {
+          ProfScope ps(&M->prof, stage_id(kTpBwdEdge, t), st);
+          if (sender) launch_tps_sender(ta, st);
+          else launch_tp(1, ta, st);
+        }
+        if (use_msg) {
+          ProfScope ps(&M->prof, stage_id(kTpBwdNode, t), st);
+          launch_tp(7, ta, st);
+        }
+      }
+      rows_live = true;
+      if (t > 1) std::swap(dcur, dother);
+      continue;
+    }
+    // BF16: with more than one chunk R is recomputed chunk by chunk (the
+    // forward pass kept only the last chunk), unless it was kept whole
     const std::vector<RChunk> chunks = r_chunks(M, G, PCu, st);
     const bool recompute = chunks.size() > 1 && !w.r_whole[t];
     const RadialBf16 bfw = W.bf16_view();
     const EdgePairs prs = graph_pairs(G);
-    ta.rev = G->rev_x->as<int>();
+    g_live = true;
     ta.r_row = w.r_compact[t] ? G->pair_of->as<int>() : nullptr;
     // scalar-output layer: the sender-side adjoint gives dR, dY and dh in one
     // pass (chunk by chunk: a chunk's receivers are the senders whose rows it holds)
@@ -1403,6 +1499,7 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
   }
   {
     ProfScope ps(&M->prof, stage_id(kForces), st);
+    if (rows_live) launch_edge_geo(c.lmax, row_ptr, N, Ecap, dvec, w.dY->as<float>(), g_live ? 1 : 0, g, st);
     launch_forces(row_ptr, G->rev_x->as<int>(), g, N, forces, st, coulomb ? w.fc->as<float>() : nullptr);
   }
 }
@@ -1430,11 +1527,24 @@ size_t footprint(const e3mi_model* M, int64_t n_atoms, int64_t n_edges) {
       continue;
     }
     if (fused_last(M, L, false, bf16)) continue;  // no per-edge R
-    // R (FP32 bound) of every edge, or of one receiver chunk unless kept whole
-    // (n_edges stands for the edges inside the cutoff); dR and the
-    // sender-gradient messages of a full layer per chunk
+    // FP32: R and R' of every edge where one chunk holds them, else of every
+    // pair (n_edges stands for the edges inside the cutoff) where that can be
+    // kept, else of one receiver chunk's edges. BF16 mode (its FP32 bound): R of
+    // every edge, or of one receiver chunk unless kept whole; dR per chunk.
+    // The sender-gradient messages of a full layer per chunk
     const size_t PCu = (size_t)L.p_used * C;
     const size_t chunk = std::min(E, M->r_chunk_bytes / (PCu * 4));
+    if (L.kind == 1 && t > 1) msg_max = std::max(msg_max, chunk * L.nc_in * C * 4);
+    if (!bf16) {
+      const size_t rows = M->edge_pairs ? E / 2 + 1 : E;
+      if (chunk < E && kept + 8 * rows * PCu <= M->r_keep_bytes) {
+        b += 8 * rows * PCu;
+        kept += 8 * rows * PCu;
+      } else {
+        b += 8 * chunk * PCu;
+      }
+      continue;
+    }
     bool whole = chunk >= E;
     if (!whole && kept + E * PCu * 4 <= M->r_keep_bytes) {
       whole = true;
@@ -1442,7 +1552,6 @@ size_t footprint(const e3mi_model* M, int64_t n_atoms, int64_t n_edges) {
     }
     b += (whole ? E : chunk) * PCu * 4;
     dr_max = std::max(dr_max, chunk * PCu * 4);
-    if (L.kind == 1 && t > 1) msg_max = std::max(msg_max, chunk * L.nc_in * C * 4);
   }
   b += N * a_max * 4 + dr_max + msg_max + E * (64 + 16) + 3 * N * NC * C * 4 + N * 8;
   if (c.correlation == 2) b += 2 * N * NC * C * 4;  // B / dB and dA~

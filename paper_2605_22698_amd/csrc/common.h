@@ -65,6 +65,15 @@ __device__ __forceinline__ void str_n(__bf16* p, const float* v) {
   *reinterpret_cast<bvec*>(p) = t;
 }
 
+// Element at a byte offset from a uniform address: the address stays in scalar
+// registers and only the 32-bit offset is per lane.
+__device__ __forceinline__ float ld_off(const float* base, unsigned bytes) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + bytes);
+}
+__device__ __forceinline__ float* at_off(float* base, unsigned bytes) {
+  return reinterpret_cast<float*>(reinterpret_cast<char*>(base) + bytes);
+}
+
 // logistic function with the hardware reciprocal (v_rcp_f32, 1 ulp) in place
 // of a correctly rounded division: 1 + exp(-x) >= 1, so no denormal input
 __device__ __forceinline__ float sigmoidf(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }

@@ -263,7 +263,8 @@ __global__ void __launch_bounds__(256) k_first_bwd(const int* __restrict__ row_p
                                                    const float4* __restrict__ dvec, const int* __restrict__ species,
                                                    int N, int S, const int* __restrict__ pair_of,
                                                    const float* __restrict__ H, const float* __restrict__ dG,
-                                                   float4* __restrict__ g, int accumulate) {
+                                                   const float* __restrict__ rows, float4* __restrict__ g,
+                                                   int accumulate) {
   constexpr int NC3 = (L3 + 1) * (L3 + 1);
   __shared__ float CYs[4][kTile][17];
   int i, s;
@@ -312,10 +313,17 @@ __global__ void __launch_bounds__(256) k_first_bwd(const int* __restrict__ row_p
       float dcy[NC3], dy[16];
 #pragma unroll
       for (int q = 0; q < NC3; ++q) dcy[q] = CY[lane][q];
-      const float dr = CY[lane][16];
+      float dr = CY[lane][16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) dy[q] = 0.0f;
       cg_apply_t<L3>(dcy, dy);
+      if (rows) {  // the later layers' share
+        float later[16];
+        ldr_n<16>(rows + (long)x.e * 16, later);
+        dr += later[0];
+#pragma unroll
+        for (int q = 1; q < (LMAX + 1) * (LMAX + 1); ++q) dy[q] += later[q];
+      }
       float Gx, Gy, Gz;
       real_sh_vjp<LMAX>(nx, ny, nz, dy, Gx, Gy, Gz);
       const float dot = Gx * nx + Gy * ny + Gz * nz;
@@ -336,13 +344,13 @@ __global__ void __launch_bounds__(256) k_first_bwd(const int* __restrict__ row_p
 
 template <int LMAX, int L3>
 static void first_launch(bool fwd, const int* row_ptr, const int* src, const float4* dvec, const int* species, int N,
-                         int S, const int* pair_of, const float* H, float* G, const float* dG, float4* g,
-                         int accumulate, hipStream_t st) {
+                         int S, const int* pair_of, const float* H, float* G, const float* dG,
+                         const float* rows, float4* g, int accumulate, hipStream_t st) {
   const int grid = (int)(((long)N * S + 3) / 4);
   if (fwd)
     k_first_fwd<LMAX, L3><<<grid, 256, 0, st>>>(row_ptr, src, dvec, species, N, S, pair_of, H, G);
   else
-    k_first_bwd<LMAX, L3><<<grid, 256, 0, st>>>(row_ptr, src, dvec, species, N, S, pair_of, H, dG, g, accumulate);
+    k_first_bwd<LMAX, L3><<<grid, 256, 0, st>>>(row_ptr, src, dvec, species, N, S, pair_of, H, dG, rows, g, accumulate);
 }
 
 void launch_first_hidden(const float4* dvec, const int* row_ptr_x, int N, long e_cap, const int* own,
@@ -356,18 +364,18 @@ void launch_first_hidden(const float4* dvec, const int* row_ptr_x, int N, long e
 
 void launch_first(bool fwd, int lmax, int l3max, const int* row_ptr, const int* src, const float4* dvec,
                   const int* species, int N, int S64, const int* pair_of, const float* H, float* G, const float* dG,
-                  float4* g, int accumulate, hipStream_t st) {
+                  const float* rows, float4* g, int accumulate, hipStream_t st) {
   if (N == 0) return;
   E3MI_REQUIRE(H, E3MI_EINVAL, "first layer: hidden layers missing");
   const int S = S64 / kH;
   if (lmax == 3 && l3max == 3)
-    first_launch<3, 3>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, g, accumulate, st);
+    first_launch<3, 3>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, rows, g, accumulate, st);
   else if (lmax == 3 && l3max == 0)
-    first_launch<3, 0>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, g, accumulate, st);
+    first_launch<3, 0>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, rows, g, accumulate, st);
   else if (lmax == 2 && l3max == 2)
-    first_launch<2, 2>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, g, accumulate, st);
+    first_launch<2, 2>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, rows, g, accumulate, st);
   else if (lmax == 2 && l3max == 0)
-    first_launch<2, 0>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, g, accumulate, st);
+    first_launch<2, 0>(fwd, row_ptr, src, dvec, species, N, S, pair_of, H, G, dG, rows, g, accumulate, st);
   else
     throw Error(E3MI_EUNSUPPORTED, "first-layer factorisation: unsupported orders");
 }

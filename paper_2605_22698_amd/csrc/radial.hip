@@ -603,6 +603,122 @@ __global__ void __launch_bounds__(256) k_radial_dual_bwd(const int* __restrict__
   }
 }
 
+// R and its derivative R' in the edge length, for energies and forces in FP32:
+// since R depends on the length alone, the adjoint of the whole radial MLP is
+// the dot product dE/dr_e = sum dR_e R'_e, which the tensor product's adjoint
+// takes while it forms dR_e. So dR never goes to memory and no adjoint of the
+// MLP (a product over P C and two of 64 x 64 per pair) is evaluated. One row
+// [PC] of each per pair owner or, without the pair list, per edge of
+// [e_first, e_end) (e_end < 0: every edge inside the cutoff), from row 0.
+// R has the bits of k_radial_fwd. R' is streamed past the caches: the forward
+// pass reads only R, which then stays in the last-level cache.
+//
+// A wave takes 32 columns of W3 for the tile's 64 rows and both outputs at
+// once: each W3 operand feeds four matrix-core steps. Bound: the FP32 matrix
+// cores and the stores. Per launch on the 3,000-atom box (80,132 pairs, P C =
+// 512) 142 us, 83 TFLOP/s, in place of 84 us for R alone and 125 us for the
+// adjoint (185 us with the next operands loaded behind the stores; 353 us when
+// per-lane 64-bit addresses made it spill); on a 20,000-atom box, P C = 2,944
+// and 512, 8.4 ms in place of 9.6 + 9.0 ms edge by edge.
+__global__ void __launch_bounds__(256, 3) k_radial_d1(const float4* __restrict__ dvec, const int* __restrict__ row_ptr_x,
+                                                   int N, const float* __restrict__ W1, const float* __restrict__ W2,
+                                                   const float* __restrict__ W3, int ld3, int PC,
+                                                   float* __restrict__ R, float* __restrict__ Rp, float rc, int p,
+                                                   int e_first, int e_end, const int* __restrict__ own,
+                                                   const int* __restrict__ n_own) {
+  constexpr int NB = 8;
+  __shared__ float Bs[2][kTile][NB + 1];
+  __shared__ float X[2][kTile][kLd];
+  const int E = own ? *n_own : e_end >= 0 ? e_end : row_ptr_x[N];
+  const int e0 = (own ? 0 : e_first) + blockIdx.x * kTile;
+  if (e0 >= E) return;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (t < kTile) {
+    const int q = e0 + t;
+    const float r = q < E ? dvec[own ? own[q] : q].w : rc;
+    float b[NB], db[NB];
+    radial_basis<NB>(r, rc, p, b, db);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      Bs[0][t][n] = b[n];
+      Bs[1][t][n] = db[n];
+    }
+  }
+  __syncthreads();
+  {
+    const int row = t >> 2, cb = (t & 3) * 16;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      float x = 0.0f, x1 = 0.0f;
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const float wv = W1[n * kH + cb + j];
+        x += Bs[0][row][n] * wv;
+        x1 += Bs[1][row][n] * wv;
+      }
+      X[0][row][cb + j] = siluf(x);
+      X[1][row][cb + j] = silu_grad(x) * x1;
+    }
+  }
+  __syncthreads();
+  {
+    const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
+    f32x16 a[2] = {};
+#pragma unroll 8
+    for (int kk = 0; kk < kH; kk += 2) {
+      const float b = W2[(kk + (lane >> 5)) * kH + cb + (lane & 31)];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) a[s] = mfma32(X[s][rb + (lane & 31)][kk + (lane >> 5)], b, a[s]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = rb + acc_row(r, lane), col = cb + (lane & 31);
+      X[0][row][col] = siluf(a[0][r]);
+      X[1][row][col] = silu_grad(a[0][r]) * a[1][r];
+    }
+  }
+  __syncthreads();
+  // lane parts of the addresses, in bytes: a W3 operand (row lane / 32, column
+  // lane % 32) and an output (rows 4 (lane / 32) on)
+  const unsigned wo = 4u * ((lane >> 5) * ld3 + (lane & 31)), oo = 4u * (4 * (lane >> 5) * PC + (lane & 31));
+  float b[kH / 2];
+  auto load_w3 = [&](int cc) {
+#pragma unroll
+    for (int k = 0; k < kH / 2; ++k) b[k] = ld_off(W3 + (long)(2 * k) * ld3 + cc, wo);
+  };
+  const int cw = __builtin_amdgcn_readfirstlane(w) * 32;
+  if (cw < PC) load_w3(cw);
+  for (int cc = cw; cc < PC; cc += 128) {
+    f32x16 a[2][2] = {};
+#pragma unroll
+    for (int k = 0; k < kH / 2; ++k) {
+      if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // few LDS operands in flight: registers
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          a[s][h] = mfma32(X[s][32 * h + (lane & 31)][2 * k + (lane >> 5)], b[k], a[s][h]);
+    }
+    // the next columns' operands before the stores: loads and stores complete
+    // in order, a load behind the stores would wait for them
+    __builtin_amdgcn_sched_barrier(0);
+    if (cc + 128 < PC) load_w3(cc + 128);
+    __builtin_amdgcn_sched_barrier(0);
+    const long o = (long)(e0 - (own ? 0 : e_first)) * PC + cc;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = 32 * h + 8 * (r >> 2) + (r & 3);  // + 4 (lane / 32)
+        if (e0 + row + 4 * (lane >> 5) < E) {
+          *at_off(R + o + (long)row * PC, oo) = a[0][h][r];
+          __builtin_nontemporal_store(a[1][h][r], at_off(Rp + o + (long)row * PC, oo));
+        }
+      }
+  }
+}
+
 // R and its first and second derivative with respect to the edge length, for
 // Hessian-vector products: R, R' and R'' depend on the length alone, so the
 // tangent of R along any direction is R' r_dot, and the adjoint of the MLP is
@@ -729,10 +845,12 @@ void launch_radial_fwd(int n_basis, const float4* dvec, const int* row_ptr_x, in
       k_radial_fwd<8, true, float, MODE><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
                                                                static_cast<float*>(R), rc, p, e_first, e_end,
                                                                wb->W2T, wb->W3T, own, n_own, rev);
-    else
+    else if constexpr (MODE != 2)
       k_radial_fwd<8, false, float, MODE><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
                                                                 static_cast<float*>(R), rc, p, e_first, e_end,
                                                                 nullptr, nullptr, own, n_own, rev);
+    else
+      throw Error(E3MI_EINVAL, "FP32 radial MLP once per pair: k_radial_d1");
   };
   if (mode == 0) go(std::integral_constant<int, 0>{});
   else if (mode == 1) go(std::integral_constant<int, 1>{});
@@ -748,18 +866,15 @@ static void radial_bwd_l(bool bf16, bool r_bf16, long e_cap, const float4* dvec,
   if (grid == 0) return;
   auto go = [&](auto pc) {
     constexpr bool PAIR = decltype(pc)::value;
+    if (!bf16) throw Error(E3MI_EINVAL, "radial adjoint: FP32 forces take R' from the forward pass");
     if (r_bf16)
       k_radial_bwd<8, LMAX, true, __bf16, PAIR><<<grid, 256, 0, st>>>(
           dvec, row_ptr_x, N, W1, W2, W2T, W3T, PC, static_cast<const __bf16*>(dR), dY, g, accumulate, rc, p,
           e_first, e_end, wb->W2T, wb->W2, wb->W3u, own, n_own, rev);
-    else if (bf16)
+    else
       k_radial_bwd<8, LMAX, true, float, PAIR><<<grid, 256, 0, st>>>(
           dvec, row_ptr_x, N, W1, W2, W2T, W3T, PC, static_cast<const float*>(dR), dY, g, accumulate, rc, p,
           e_first, e_end, wb->W2T, wb->W2, wb->W3u, own, n_own, rev);
-    else
-      k_radial_bwd<8, LMAX, false, float, PAIR><<<grid, 256, 0, st>>>(
-          dvec, row_ptr_x, N, W1, W2, W2T, W3T, PC, static_cast<const float*>(dR), dY, g, accumulate, rc, p,
-          e_first, e_end, nullptr, nullptr, nullptr, own, n_own, rev);
   };
   if (own) go(std::true_type{});
   else go(std::false_type{});
@@ -805,6 +920,19 @@ void launch_radial_dual_bwd(const int* row_ptr_x, int N, long e_cap, const float
                             float* P2g, hipStream_t st) {
   if (e_cap == 0) return;
   k_radial_dual_bwd<<<tiles(e_cap), 256, 0, st>>>(row_ptr_x, N, W2T, W3T, PC, Rb, Rc, P1d, P2d, P1g, P2g);
+}
+void launch_radial_d1(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
+                      const float* W2, const float* W3, int ld3, int PC, float* R, float* Rp, float rc, int p,
+                      int e_first, int e_end, const int* own, const int* n_own, hipStream_t st) {
+  if (e_cap == 0) return;
+  if (n_basis != 8) throw Error(E3MI_EUNSUPPORTED, "n_basis must be 8");
+  if (PC % 32) throw Error(E3MI_EUNSUPPORTED, "paths x channels must be a multiple of 32");
+  if (own && (e_first != 0 || e_end >= 0 || !n_own))
+    throw Error(E3MI_EINVAL, "radial MLP per edge pair: needs the whole edge list and the pair owners");
+  const int grid = tiles(e_end >= 0 ? (long)e_end - e_first : e_cap);
+  if (grid == 0) return;
+  k_radial_d1<<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC, R, Rp, rc, p, e_first, e_end, own,
+                                    n_own);
 }
 void launch_radial_d2(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
                       const float* W2, const float* W3, int ld3, int PC, float* R3, float rc, int p, const int* own,

@@ -251,9 +251,16 @@ struct TpArgs {
   int r_bf16;      // R and dR stored as BF16 (passes 0 and 1, and the sender-side adjoint)
   int* touched;    // with msg: per atom, set to `tag` for every sender of the chunk's edges (pass 1), read by pass 7
   int tag;
-  // R rows per edge pair (passes 0-2 and the sender-side adjoint): edge e's
-  // weights in row r_row[e] (NULL: row e - e_first); dR stays per edge
+  // R rows (passes 0-2 and the sender-side adjoint): edge e's weights in row
+  // r_row[e] (its pair index; NULL: row e - r_first); dR stays per edge
   const int* r_row;
+  int r_first;
+  // FP32 energies and forces: R' in rows like R's. The adjoints then write no
+  // dR; dY's first value (the l = 0 harmonic is constant) is dE/dr instead, and
+  // row_add adds to dY's rows
+  const float* Rp;
+  int row_add;
+  int fp32;  // pass 0: FP32 model (layers with every path then need not give the BF16 mode's bits)
 };
 // which: 0 forward, 1 edge adjoint (dR, dY), 2 node adjoint (dh += ...),
 //        3 tangent forward (Ad), 4 second-order edge adjoint (Rb, Rc),
@@ -261,10 +268,13 @@ struct TpArgs {
 //        7 node adjoint from the messages that pass 1 wrote (msg set), for the
 //          chunk's receivers [i0, i0 + n_recv) as senders' partners
 void launch_tp(int which, const TpArgs& a, hipStream_t st);
-// scalar-output layer with R of every edge in memory (tps.hip): the
-// sender-side adjoint, dR and dY of pass 1 and, when a.dh is set, dh of pass 2
+// scalar-output layer (tps.hip): the sender-side adjoint, dY (and in the BF16
+// mode dR) of pass 1 and, when a.dh is set, dh of pass 2
 bool tps_supported(const TpArgs& a);
 void launch_tps_sender(const TpArgs& a, hipStream_t st);
+// g (+)= the position adjoint of the edges' rows [dE/dr, dY 1..] (tps.hip)
+void launch_edge_geo(int lmax, const int* row_ptr_x, int N, long e_cap, const float4* dvec, const float* rows,
+                     int accumulate, float4* g, hipStream_t st);
 
 // ---- per-atom stages (node.hip) -----------------------------------------------------
 // Rows of a matrix whose row r lives at base + (r / g) * s_atom + (r % g) * s_m
@@ -345,6 +355,11 @@ void launch_hvp_geo(const HvpArgs& a, long e_cap, int accumulate, float4* g, hip
 // from the last layer's pre-gate values x [N, C] and tangents xd [B N, C]: adjoints xb, xc [B N, C]
 void launch_hvp_readout(const float* x, const float* xd, const float* Wr, const float* w2, int N, int B, int C,
                         float* xb, float* xc, hipStream_t st);
+// rows of R and of its derivative Rp in the edge length, of every edge pair
+// (own, n_own) or of the edges [e_first, e_end) (e_end < 0: all)
+void launch_radial_d1(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
+                      const float* W2, const float* W3, int ld3, int PC, float* R, float* Rp, float rc, int p,
+                      int e_first, int e_end, const int* own, const int* n_own, hipStream_t st);
 // R3 rows of every edge pair (own, n_own) or edge
 void launch_radial_d2(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
                       const float* W2, const float* W3, int ld3, int PC, float* R3, float rc, int p, const int* own,
@@ -451,10 +466,11 @@ void launch_first_hidden(const float4* dvec, const int* row_ptr_x, int N, long e
                          const int* n_own, const float* W1, const float* W2, float rc, int p, float* H,
                          hipStream_t st);
 // forward (G) or adjoint (g) of the factorised first layer; edge e's row of H
-// is pair_of[e] (or e when pair_of is NULL)
+// is pair_of[e] (or e when pair_of is NULL). The adjoint takes the later
+// layers' edge rows [dE/dr, dY 1..] (rows, or NULL) into its own
 void launch_first(bool fwd, int lmax, int l3max, const int* row_ptr, const int* src, const float4* dvec,
                   const int* species, int N, int S64, const int* pair_of, const float* H, float* G, const float* dG,
-                  float4* g, int accumulate, hipStream_t st);
+                  const float* rows, float4* g, int accumulate, hipStream_t st);
 
 // ---- fused last layer (last.hip) ----------------------------------------------------------
 struct LastArgs {

@@ -220,3 +220,24 @@ def test_first_layer_row_lengths(n, n_species, lmax):
     Er, Fr, Eir = _oracle(cfg, 171, b)
     check_energy(E, Er, Eir)
     check_forces(F, Fr)
+
+
+@pytest.mark.parametrize("lmax,channels,correlation", [(2, 32, 1), (3, 32, 1), (2, 128, 1), (3, 64, 2), (3, 32, 2)])
+@pytest.mark.parametrize("unfactorised", [False, True])
+def test_layers_with_every_path(lmax, channels, correlation, unfactorised):
+    # rows of 0, 1, 2 and many edges through the kernels of layers with every
+    # path and of the scalar-output layer, at every channel count
+    cfg = synth.ModelConfig(lmax=lmax, channels=channels, layers=3, n_species=3, cutoff=5.0, avg_neighbors=10.0,
+                            correlation=correlation)
+    rng = np.random.default_rng(180)
+    parts = [synth.uniform_cluster(n, 4.0, 0.9, 3, rng) for n in (1, 2, 3)] + [synth.jittered_lattice(40, 0.1, 0.3, 3, rng)]
+    b = synth.concat(parts)
+    m = model(cfg, 181)
+    if unfactorised:
+        m.set_flags(unfactorised_first_layer=True)
+    E, F, Ei, _ = gpu_energy_forces(m, b, skin=0.5)
+    Er, Fr, Eir = _oracle(cfg, 181, b)
+    for s in range(b.n_structures):
+        a, z = b.offsets[s], b.offsets[s + 1]
+        check_energy(E[s:s + 1], Er[s:s + 1], Eir[a:z])
+    check_forces(F, Fr)
