@@ -206,7 +206,7 @@ struct Workspace {
   // second-order pass: per layer A, tangents and stored radial activations
   std::vector<std::unique_ptr<DevBuf>> Al, Ad, hd, htd, Rd, P1d, H1d, P2d, H2d;
   std::unique_ptr<DevBuf> dd, Bd, Prb, Prc, w2c, eb, xb, xc, Ab, Ac, hb_a, hb_b, hc_a, hc_b, Rb, Rc, P1g, P2g,
-      partial, vf;
+      partial, gsum, vf;
   std::unique_ptr<DevBuf> G1, dG1;  // first layer, [N, (l3+1)^2, S*64]
   std::unique_ptr<DevBuf> H2f;      // first layer's second hidden layer and its derivative per edge pair (or edge), [., 128]
   std::unique_ptr<DevBuf> q_raw, q, pot, fc, pot_mean;  // electrostatics: charges, potential, forces
@@ -1816,8 +1816,14 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
   for (auto* v : {&w.Ab, &w.Ac}) ensure(*v, a, sizeof(float) * (size_t)N * a_max);
   for (auto* v : {&w.Rb, &w.Rc}) ensure(*v, a, sizeof(float) * E1 * pc_max);
   for (auto* v : {&w.P1g, &w.P2g}) ensure(*v, a, sizeof(float) * E1 * 2 * H);
-  ensure(w.partial, a, sizeof(float) * std::max<size_t>(16u << 20, (size_t)H * pc_max));
-  float* partial = w.partial->as<float>();
+  size_t sum_cols = (size_t)c.n_species * C;  // most (group, column) sums of a group_sum call
+  long mn_max = (long)H * pc_max;
+  for (const LayerPlan& L : M->plans) {
+    sum_cols = std::max(sum_cols, (size_t)c.n_species * std::max(L.n_prod, L.lout + 1) * C);
+    for (int l = 0; l <= L.l3max_used; ++l) mn_max = std::max(mn_max, (long)L.p_used_l3[l] * C * C);
+  }
+  float* partial = ensure(w.partial, a, sizeof(float) * tn_partial_floats(mn_max)).as<float>();
+  double* gsum = ensure(w.gsum, a, sizeof(double) * group_chunks(N) * std::max<size_t>(sum_cols, 16)).as<double>();
   if (prod) {
     w.atd.resize(T + 1);
     w.Bpd.resize(T + 1);
@@ -1887,11 +1893,14 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
   launch_readout_dual(w.h[T]->as<float>(), w.hd[T]->as<float>(), ncT, G->owner->as<int>(), gE, M->read1->as<float>(),
                       M->read2->as<float>(), N, C, w.Prb->as<float>(), w.Prc->as<float>(), w.w2c->as<float>(), hb, hc,
                       w.eb->as<float>(), st);
-  launch_gemm_tn(RowMap{w.h[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prb->as<float>(), 16, 0, 1},
-                 RowMap{w.hd[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prc->as<float>(), 16, 0, 1}, N,
-                 nullptr, C, 16, partial, out + off.read1, 16, st);
-  launch_group_sum(w.w2c->as<float>(), 16, nullptr, 1, N, 16, out + off.read2, 16, st);
-  launch_group_sum(w.eb->as<float>(), 1, G->species->as<int>(), c.n_species, N, 1, out + off.e0, 1, st);
+  {
+    const TnArgs read1{RowMap{w.h[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prb->as<float>(), 16, 0, 1},
+                       RowMap{w.hd[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prc->as<float>(), 16, 0, 1}, N,
+                       nullptr, C, 16, out + off.read1, 16};
+    launch_gemm_tn(&read1, 1, partial, st);
+  }
+  launch_group_sum(w.w2c->as<float>(), 16, nullptr, 1, N, 16, gsum, out + off.read2, 16, st);
+  launch_group_sum(w.eb->as<float>(), 1, G->species->as<int>(), c.n_species, N, 1, gsum, out + off.e0, 1, st);
 
   // ---- reverse: layers ----
   float* xb = w.xb->as<float>();
@@ -1903,15 +1912,18 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
     const float* hin = w.h[t - 1]->as<float>();
     const float* hdin = t > 1 ? w.hd[t - 1]->as<float>() : nullptr;
     launch_gate_dual_bwd(w.ht[t]->as<float>(), w.htd[t]->as<float>(), hb, hc, xb, xc, N, L.nc_out, C, st);
-    // weight gradients of the self connection (orders present in both h^{t-1} and h~)
+    // weight gradients of the self connection (orders present in both h^{t-1}
+    // and h~) and, below, of the channel mix: one group (at most 4 + 4 products)
+    TnArgs tn[kMaxTnGroup];
+    int n_tn = 0;
     for (int l = 0; l <= std::min(L.l1max, prod ? L.lout : L.l3max_used); ++l) {
       const int g = 2 * l + 1;
-      launch_gemm_tn(RowMap{const_cast<float*>(hin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g},
-                     RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
-                     hdin ? RowMap{const_cast<float*>(hdin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g}
-                          : RowMap{nullptr, 0, 0, 1},
-                     RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
-                     partial, out + off.self_[t - 1][l], C, st);
+      tn[n_tn++] = TnArgs{RowMap{const_cast<float*>(hin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g},
+                          RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
+                          hdin ? RowMap{const_cast<float*>(hdin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g}
+                               : RowMap{nullptr, 0, 0, 1},
+                          RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
+                          out + off.self_[t - 1][l], C};
     }
     E3MI_HIP(hipMemsetAsync(hb2, 0, sizeof(float) * (size_t)N * L.nc_in * C, st));
     if (t > 1) E3MI_HIP(hipMemsetAsync(hc2, 0, sizeof(float) * (size_t)N * L.nc_in * C, st));
@@ -1927,14 +1939,16 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
       pa.atd = w.atd[t]->as<float>();
       pa.B = Bt;
       launch_product(true, pa, st);  // B again (the forward pass keeps one layer's)
+      TnArgs lin[4];
       for (int l = 0; l <= L.lout; ++l) {
         const int g = 2 * l + 1, nb = (L.lout + 1) * (L.lout + 1);
-        launch_gemm_tn(RowMap{Bt + (long)l * l * C, (long)nb * C, (long)C, g},
-                       RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
-                       RowMap{w.Bpd[t]->as<float>() + (long)l * l * C, (long)nb * C, (long)C, g},
-                       RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
-                       partial, out + off.lin[t - 1][l], C, st);
+        lin[l] = TnArgs{RowMap{Bt + (long)l * l * C, (long)nb * C, (long)C, g},
+                        RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
+                        RowMap{w.Bpd[t]->as<float>() + (long)l * l * C, (long)nb * C, (long)C, g},
+                        RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
+                        out + off.lin[t - 1][l], C};
       }
+      launch_gemm_tn(lin, L.lout + 1, partial, st);
       launch_lin_adjoint(M, L, W, xb, w.Bpb->as<float>(), hb2, N, st, false);
       launch_lin_adjoint(M, L, W, xc, w.Bpc->as<float>(), t > 1 ? hc2 : nullptr, N, st, false);
       pa.Bb = w.Bpb->as<float>();
@@ -1944,9 +1958,10 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
       pa.dw = w.dwp->as<float>();
       launch_product_dual_bwd(pa, st);
       const long ldw = (long)(L.lout + 1 + L.n_prod) * C;
-      launch_group_sum(pa.dw, ldw, G->species->as<int>(), c.n_species, N, (L.lout + 1) * C, out + off.sym1[t - 1],
+      launch_group_sum(pa.dw, ldw, G->species->as<int>(), c.n_species, N, (L.lout + 1) * C, gsum,
+                       out + off.sym1[t - 1],
                        (long)(L.lout + 1) * C, st);
-      launch_group_sum(pa.dw + (long)(L.lout + 1) * C, ldw, G->species->as<int>(), c.n_species, N, L.n_prod * C,
+      launch_group_sum(pa.dw + (long)(L.lout + 1) * C, ldw, G->species->as<int>(), c.n_species, N, L.n_prod * C, gsum,
                        out + off.sym2[t - 1], (long)L.n_prod * C, st);
       mb = w.atb->as<float>();
       mc = w.atc->as<float>();
@@ -1956,13 +1971,14 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
     long gbase = 0;
     for (int l3 = 0; l3 <= L.l3max_used; ++l3) {
       const int P3 = L.p_used_l3[l3], g = 2 * l3 + 1;
-      launch_gemm_tn(RowMap{w.Al[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g},
-                     RowMap{const_cast<float*>(mb) + (long)l3 * l3 * C, (long)m_nc * C, (long)C, g},
-                     RowMap{w.Ad[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g},
-                     RowMap{const_cast<float*>(mc) + (long)l3 * l3 * C, (long)m_nc * C, (long)C, g}, (long)N * g,
-                     nullptr, P3 * C, C, partial, out + off.mix[t - 1][l3], C, st);
+      tn[n_tn++] = TnArgs{RowMap{w.Al[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g},
+                          RowMap{const_cast<float*>(mb) + (long)l3 * l3 * C, (long)m_nc * C, (long)C, g},
+                          RowMap{w.Ad[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g},
+                          RowMap{const_cast<float*>(mc) + (long)l3 * l3 * C, (long)m_nc * C, (long)C, g}, (long)N * g,
+                          nullptr, P3 * C, C, out + off.mix[t - 1][l3], C};
       gbase += (long)N * g * P3 * C;
     }
+    launch_gemm_tn(tn, n_tn, partial, st);
     // adjoints of A and A_dot; of h^{t-1} and h_dot^{t-1} through the self
     // connection (without the product block, the mix holds it)
     launch_mix_adjoint(M, L, W, mb, m_nc, w.Ab->as<float>(), prod ? nullptr : hb2, N, st);
@@ -2003,19 +2019,20 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
     float* Bd = w.Bd->as<float>();
     float* P1g = w.P1g->as<float>();
     float* P2g = w.P2g->as<float>();
-    launch_gemm_tn(RowMap{H2d, 2L * H, 0, 1}, RowMap{w.Rb->as<float>(), PCu, 0, 1}, RowMap{H2d + H, 2L * H, 0, 1},
-                   RowMap{w.Rc->as<float>(), PCu, 0, 1}, Ecap, rows_dev, H, PCu, partial, out + off.rad3[t - 1],
-                   (long)L.p_full * C, st);
-    launch_gemm_tn(RowMap{H1d, 2L * H, 0, 1}, RowMap{P2g, 2L * H, 0, 1}, RowMap{H1d + H, 2L * H, 0, 1},
-                   RowMap{P2g + H, 2L * H, 0, 1}, Ecap, rows_dev, H, H, partial, out + off.rad2[t - 1], H, st);
-    launch_gemm_tn(RowMap{Bd, 16, 0, 1}, RowMap{P1g, 2L * H, 0, 1}, RowMap{Bd + 8, 16, 0, 1},
-                   RowMap{P1g + H, 2L * H, 0, 1}, Ecap, rows_dev, c.n_basis, H, partial, out + off.rad1[t - 1], H,
-                   st);
+    const TnArgs rad[3] = {
+        TnArgs{RowMap{H2d, 2L * H, 0, 1}, RowMap{w.Rb->as<float>(), PCu, 0, 1}, RowMap{H2d + H, 2L * H, 0, 1},
+               RowMap{w.Rc->as<float>(), PCu, 0, 1}, Ecap, rows_dev, H, PCu, out + off.rad3[t - 1],
+               (long)L.p_full * C},
+        TnArgs{RowMap{H1d, 2L * H, 0, 1}, RowMap{P2g, 2L * H, 0, 1}, RowMap{H1d + H, 2L * H, 0, 1},
+               RowMap{P2g + H, 2L * H, 0, 1}, Ecap, rows_dev, H, H, out + off.rad2[t - 1], H},
+        TnArgs{RowMap{Bd, 16, 0, 1}, RowMap{P1g, 2L * H, 0, 1}, RowMap{Bd + 8, 16, 0, 1},
+               RowMap{P1g + H, 2L * H, 0, 1}, Ecap, rows_dev, c.n_basis, H, out + off.rad1[t - 1], H}};
+    launch_gemm_tn(rad, 3, partial, st);
     std::swap(hb, hb2);
     std::swap(hc, hc2);
   }
   // embedding: h^0_i = W_emb[z_i]
-  launch_group_sum(hb, C, G->species->as<int>(), c.n_species, N, C, out + off.emb, C, st);
+  launch_group_sum(hb, C, G->species->as<int>(), c.n_species, N, C, gsum, out + off.emb, C, st);
 }
 
 // Directions of one batch of Hessian-vector products. One direction of a small

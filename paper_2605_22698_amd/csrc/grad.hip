@@ -137,80 +137,145 @@ __global__ void __launch_bounds__(256) k_readout_dual(const float* __restrict__ 
   }
 }
 
-// out[g, c] = sum over atoms i with species[i] == g (all atoms when species is
-// NULL) of X[i * ld + c], in atom order, accumulated in FP64.
-__global__ void k_group_sum(const float* __restrict__ X, long ld, const int* __restrict__ species, int n_groups, int N,
-                            int ncols, double* __restrict__ out, long ld_out) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+// Sums over atoms by group, in two passes of fixed order, in FP64: partials
+// over chunks of kSumAtoms atoms, then over the chunks. part[chunk, g, c] =
+// sum over the chunk's atoms i with species[i] == g (all when species is NULL)
+// of X[i * ld + c]. One pass over all atoms per output leaves as many threads
+// as outputs (16 to a few hundred), each with a chain of N loads: 1.0-1.3 ms on
+// 7,000 atoms, against 20 us for both passes.
+constexpr int kSumAtoms = 64;
+__global__ void __launch_bounds__(256) k_group_partial(const float* __restrict__ X, long ld,
+                                                       const int* __restrict__ species, int n_groups, int N,
+                                                       int ncols, double* __restrict__ part) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= n_groups * ncols) return;
   const int g = t / ncols, c = t % ncols;
+  const int i0 = blockIdx.y * kSumAtoms, n = min(kSumAtoms, N - i0);
   double acc = 0.0;
-  for (int i = 0; i < N; ++i)
-    if (!species || species[i] == g) acc += (double)X[(long)i * ld + c];
-  out[(long)g * ld_out + c] = acc;
+#pragma unroll 8
+  for (int i = 0; i < n; ++i) {
+    const float v = X[(long)(i0 + i) * ld + c];
+    if (!species || species[i0 + i] == g) acc += (double)v;
+  }
+  part[(long)blockIdx.y * n_groups * ncols + t] = acc;
+}
+__global__ void __launch_bounds__(256) k_group_total(const double* __restrict__ part, int chunks, int n_groups,
+                                                     int ncols, double* __restrict__ out, long ld_out) {
+  // 32 outputs x 8 shares of the chunks
+  __shared__ double red[8][32];
+  const int total = n_groups * ncols;
+  const int t = blockIdx.x * 32 + (threadIdx.x & 31), w = threadIdx.x >> 5;
+  double acc = 0.0;
+  if (t < total) {
+#pragma unroll 4
+    for (int q = w; q < chunks; q += 8) acc += part[(long)q * total + t];
+  }
+  red[w][threadIdx.x & 31] = acc;
+  __syncthreads();
+  if (w == 0 && t < total) {
+    for (int q = 1; q < 8; ++q) acc += red[q][threadIdx.x];
+    out[(long)(t / ncols) * ld_out + t % ncols] = acc;
+  }
 }
 
-// Partial sums over a chunk of rows of X1^T Y1 + X2^T Y2 (X: [rows, mo],
-// Y: [rows, no], rows addressed through RowMaps), 64x64 output tiles on the
-// FP32 matrix cores; grid.z enumerates the row chunks.
-__global__ void __launch_bounds__(256) k_gemm_tn(RowMap x1, RowMap y1, RowMap x2, RowMap y2, int rows,
-                                                 const int* __restrict__ rows_dev, int mo, int no, int chunk_rows,
-                                                 float* __restrict__ partial) {
-  __shared__ float Xs[16][65];
-  __shared__ float Ys[16][65];
-  int R = rows;
-  if (rows_dev) R = min(R, *rows_dev);
-  const int bm = blockIdx.x * 64, bn = blockIdx.y * 64;
-  const int r0 = blockIdx.z * chunk_rows, r1 = min(R, r0 + chunk_rows);
+// Weight gradients: products X1^T Y1 + X2^T Y2 over rows (X: [rows, mo], Y:
+// [rows, no], rows addressed through RowMaps), several in one launch. A
+// workgroup takes a 64 x 64 output tile and a chunk of the rows (kTnRows at a
+// time through LDS, the next ones in flight) on the FP32 matrix cores; its
+// partial sum goes to memory and k_tn_reduce adds the chunks in order in FP64.
+struct TnGroup {
+  TnArgs g[kMaxTnGroup];
+  int block0[kMaxTnGroup + 1];  // first workgroup
+  int tiles[kMaxTnGroup], ncol[kMaxTnGroup], chunks[kMaxTnGroup];
+  long part0[kMaxTnGroup];      // first float of the partials
+  int red0[kMaxTnGroup + 1];    // first workgroup of the reduction
+  int n;
+};
+constexpr int kTnRows = 32;
+
+__device__ __forceinline__ const float* tn_row(const RowMap& m, int r) {
+  const int a = m.g == 1 ? r : r / m.g;
+  return m.base + a * m.s_atom + (r - a * m.g) * m.s_m;
+}
+
+__global__ void __launch_bounds__(256) k_gemm_tn(TnGroup gg, float* __restrict__ partial) {
+  __shared__ __align__(16) float Xs[kTnRows][64];
+  __shared__ __align__(16) float Ys[kTnRows][64];
+  int gi = 0;
+  while (gi + 1 < gg.n && (int)blockIdx.x >= gg.block0[gi + 1]) ++gi;
+  const TnArgs& a = gg.g[gi];
+  const int local = blockIdx.x - gg.block0[gi];
+  const int chunk = local / gg.tiles[gi], tile = local % gg.tiles[gi];
+  const int bm = tile / gg.ncol[gi] * 64, bn = tile % gg.ncol[gi] * 64;
+  const int R = a.rows_dev ? min((int)a.rows, *a.rows_dev) : (int)a.rows;
+  const int per = ((R + gg.chunks[gi] - 1) / gg.chunks[gi] + kTnRows - 1) / kTnRows * kTnRows;
+  const int r0 = min(R, chunk * per), r1 = min(R, r0 + per);
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
-  f32x16 acc = {};
-  for (int term = 0; term < 2; ++term) {
-    const RowMap X = term ? x2 : x1, Y = term ? y2 : y1;
-    if (!X.base) continue;
-    for (int r = r0; r < r1; r += 16) {
-      {
-        const int kr = t >> 4, c4 = (t & 15) * 4;
-        const int gr = r + kr;
+  // this thread stages columns c4 .. c4 + 3 of rows kr and kr + 16
+  const int kr = t >> 4, c4 = (t & 15) * 4;
+  const bool in_m = bm + c4 < a.mo, in_n = bn + c4 < a.no;
+  const int terms = a.x2.base ? 2 : 1;
+  const int steps = (r1 - r0 + kTnRows - 1) / kTnRows * terms;
+  float4 xv[2], yv[2];
+  auto load = [&](int s) {
+    const RowMap& X = s % terms ? a.x2 : a.x1;
+    const RowMap& Y = s % terms ? a.y2 : a.y1;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int cm = bm + c4 + q, cn = bn + c4 + q;
-          float xv = 0.0f, yv = 0.0f;
-          if (gr < r1) {
-            const long ro_x = (long)(gr / X.g) * X.s_atom + (long)(gr % X.g) * X.s_m;
-            const long ro_y = (long)(gr / Y.g) * Y.s_atom + (long)(gr % Y.g) * Y.s_m;
-            if (cm < mo) xv = X.base[ro_x + cm];
-            if (cn < no) yv = Y.base[ro_y + cn];
-          }
-          Xs[kr][c4 + q] = xv;
-          Ys[kr][c4 + q] = yv;
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int kk = 0; kk < 16; kk += 2)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Xs[kk + (lane >> 5)][rb + (lane & 31)],
-                                                    Ys[kk + (lane >> 5)][cb + (lane & 31)], acc, 0, 0, 0);
-      __syncthreads();
+    for (int q = 0; q < 2; ++q) {
+      const int r = r0 + s / terms * kTnRows + kr + 16 * q;
+      xv[q] = yv[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (r < r1 && in_m) xv[q] = *reinterpret_cast<const float4*>(tn_row(X, r) + bm + c4);
+      if (r < r1 && in_n) yv[q] = *reinterpret_cast<const float4*>(tn_row(Y, r) + bn + c4);
     }
+  };
+  f32x16 acc = {};
+  if (steps > 0) load(0);
+  for (int s = 0; s < steps; ++s) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      *reinterpret_cast<float4*>(&Xs[kr + 16 * q][c4]) = xv[q];
+      *reinterpret_cast<float4*>(&Ys[kr + 16 * q][c4]) = yv[q];
+    }
+    __syncthreads();
+    if (s + 1 < steps) load(s + 1);
+#pragma unroll
+    for (int kk = 0; kk < kTnRows; kk += 2)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Xs[kk + (lane >> 5)][rb + (lane & 31)],
+                                                  Ys[kk + (lane >> 5)][cb + (lane & 31)], acc, 0, 0, 0);
+    __syncthreads();
   }
-  float* P = partial + (long)blockIdx.z * mo * no;
+  float* P = partial + gg.part0[gi] + (long)chunk * a.mo * a.no;
   const int col = bn + cb + (lane & 31);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int row = bm + rb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    if (row < mo && col < no) P[(long)row * no + col] = acc[r];
+    if (row < a.mo && col < a.no) P[(long)row * a.no + col] = acc[r];
   }
 }
 
-// out[i * ld_out + j] = sum over chunks of partial[c][i][j], chunks in order, FP64.
-__global__ void k_reduce_partials(const float* __restrict__ partial, int chunks, int mo, int no,
-                                  double* __restrict__ out, long ld_out) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long)mo * no) return;
+// out[i * ld_out + j] = sum over chunks of partial[c][i][j] in FP64: 32 outputs
+// x 8 shares of the chunks per workgroup, each in order.
+__global__ void __launch_bounds__(256) k_tn_reduce(TnGroup gg, const float* __restrict__ partial) {
+  __shared__ double red[8][32];
+  int gi = 0;
+  while (gi + 1 < gg.n && (int)blockIdx.x >= gg.red0[gi + 1]) ++gi;
+  const TnArgs& a = gg.g[gi];
+  const int total = a.mo * a.no, chunks = gg.chunks[gi];
+  const int idx = (blockIdx.x - gg.red0[gi]) * 32 + (threadIdx.x & 31), w = threadIdx.x >> 5;
+  const float* P = partial + gg.part0[gi];
+  const int per = (chunks + 7) / 8, c1 = min(chunks, (w + 1) * per);
   double s = 0.0;
-  for (int c = 0; c < chunks; ++c) s += (double)partial[(long)c * mo * no + idx];
-  out[(idx / no) * ld_out + idx % no] = s;
+  if (idx < total) {
+#pragma unroll 8
+    for (int c = w * per; c < c1; ++c) s += (double)P[(long)c * total + idx];
+  }
+  red[w][threadIdx.x & 31] = s;
+  __syncthreads();
+  if (w == 0 && idx < total) {
+    for (int q = 1; q < 8; ++q) s += red[q][threadIdx.x];
+    a.out[(long)(idx / a.no) * a.ld_out + idx % a.no] = s;
+  }
 }
 
 }  // namespace
@@ -236,31 +301,50 @@ void launch_readout_dual(const float* h, const float* hd, int nc, const int* own
   k_readout_dual<<<blocks((long)N * 64, 256), 256, 0, st>>>(h, hd, nc, owner, gE, Wr, w2, N, C, Pb, Pc, w2c, hb, hc,
                                                              eb);
 }
-void launch_group_sum(const float* X, long ld, const int* species, int n_groups, int N, int ncols, double* out,
-                      long ld_out, hipStream_t st) {
-  k_group_sum<<<blocks((long)n_groups * ncols, 64), 64, 0, st>>>(X, ld, species, n_groups, N, ncols, out, ld_out);
+void launch_group_sum(const float* X, long ld, const int* species, int n_groups, int N, int ncols, double* part,
+                      double* out, long ld_out, hipStream_t st) {
+  const int total = n_groups * ncols, chunks = group_chunks(N);
+  if (total == 0) return;
+  if (N > 0)
+    k_group_partial<<<dim3(blocks(total, 256), chunks), 256, 0, st>>>(X, ld, species, n_groups, N, ncols, part);
+  k_group_total<<<blocks(total, 32), 256, 0, st>>>(part, N > 0 ? chunks : 0, n_groups, ncols, out, ld_out);
 }
-// out (FP64, row stride ld_out) = X1^T Y1 + X2^T Y2 over `rows` rows (capped
-// at *rows_dev when given); `partial` must hold chunks(rows) * mo * no floats.
-int tn_chunks(long rows) {
-  const long c = (rows + 1023) / 1024;
-  return (int)std::max<long>(1, std::min<long>(c, 256));
-}
-static int tn_chunks_for(long rows, int mo, int no) {
-  // cap the partial buffer at 16 M floats
-  const long cap = std::max<long>(1, (16L << 20) / ((long)mo * no));
-  return (int)std::min<long>(tn_chunks(rows), cap);
-}
-void launch_gemm_tn(RowMap x1, RowMap y1, RowMap x2, RowMap y2, long rows, const int* rows_dev, int mo, int no,
-                    float* partial, double* out, long ld_out, hipStream_t st) {
-  if (mo == 0 || no == 0) return;
-  const int chunks = tn_chunks_for(rows, mo, no);
-  const int chunk_rows = (int)((rows + chunks - 1) / chunks);
-  dim3 grid(blocks(mo, 64), blocks(no, 64), chunks);
-  if (rows > 0) {
-    k_gemm_tn<<<grid, 256, 0, st>>>(x1, y1, x2, y2, (int)rows, rows_dev, mo, no, chunk_rows, partial);
-    k_reduce_partials<<<blocks((long)mo * no, 256), 256, 0, st>>>(partial, chunks, mo, no, out, ld_out);
+int group_chunks(int N) { return std::max(1, blocks(N, kSumAtoms)); }
+
+// Chunks of a product's rows: enough workgroups for the GPU (about four per
+// CU over the group's share) without chunks of fewer than 128 rows, the
+// partials within kTnPartial floats per group.
+void launch_gemm_tn(const TnArgs* args, int n, float* partial, hipStream_t st) {
+  E3MI_REQUIRE(n >= 0 && n <= kMaxTnGroup, E3MI_EINVAL, "weight-gradient group size out of range");
+  TnGroup gg{};
+  int m = 0, nblocks = 0, nred = 0;
+  long part = 0;
+  for (int k = 0; k < n; ++k) {
+    const TnArgs& a = args[k];
+    if (a.mo == 0 || a.no == 0 || a.rows <= 0) continue;
+    E3MI_REQUIRE(a.mo % 4 == 0 && a.no % 4 == 0 && a.rows < (1L << 31), E3MI_EUNSUPPORTED,
+                 "weight gradients: dimensions must be multiples of 4");
+    gg.g[m] = a;
+    gg.ncol[m] = blocks(a.no, 64);
+    gg.tiles[m] = blocks(a.mo, 64) * gg.ncol[m];
+    const long by_rows = (a.rows + 127) / 128, by_part = std::max<long>(1, kTnPartial / kMaxTnGroup / ((long)a.mo * a.no));
+    gg.chunks[m] = (int)std::max<long>(1, std::min({by_rows, by_part, (long)std::max(1, 1024 / gg.tiles[m])}));
+    gg.block0[m] = nblocks;
+    gg.part0[m] = part;
+    gg.red0[m] = nred;
+    nblocks += gg.tiles[m] * gg.chunks[m];
+    part += (long)gg.chunks[m] * a.mo * a.no;
+    nred += blocks((long)a.mo * a.no, 32);
+    ++m;
   }
+  if (m == 0) return;
+  gg.block0[m] = nblocks;
+  gg.red0[m] = nred;
+  gg.n = m;
+  k_gemm_tn<<<nblocks, 256, 0, st>>>(gg, partial);
+  k_tn_reduce<<<nred, 256, 0, st>>>(gg, partial);
 }
+
+size_t tn_partial_floats(long mo_no_max) { return std::max<size_t>((size_t)kTnPartial, (size_t)kMaxTnGroup * mo_no_max); }
 
 }  // namespace e3mi

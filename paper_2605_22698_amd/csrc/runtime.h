@@ -452,11 +452,26 @@ void launch_gate_dual_bwd(const float* x, const float* xd, const float* hb, cons
 void launch_readout_dual(const float* h, const float* hd, int nc, const int* owner, const double* gE, const float* Wr,
                          const float* w2, int N, int C, float* Pb, float* Pc, float* w2c, float* hb, float* hc,
                          float* eb, hipStream_t st);
-void launch_group_sum(const float* X, long ld, const int* species, int n_groups, int N, int ncols, double* out,
-                      long ld_out, hipStream_t st);
-int tn_chunks(long rows);
-void launch_gemm_tn(RowMap x1, RowMap y1, RowMap x2, RowMap y2, long rows, const int* rows_dev, int mo, int no,
-                    float* partial, double* out, long ld_out, hipStream_t st);
+// out[g, c] = sum over atoms of X[i * ld + c] by species (all atoms in group 0
+// when species is NULL), FP64; part: group_chunks(N) * n_groups * ncols doubles
+int group_chunks(int N);
+void launch_group_sum(const float* X, long ld, const int* species, int n_groups, int N, int ncols, double* part,
+                      double* out, long ld_out, hipStream_t st);
+// out (FP64 [mo, no], row stride ld_out) = X1^T Y1 + X2^T Y2 over `rows` rows
+// (capped at *rows_dev when given; x2.base NULL: one term); rows 16-byte aligned
+struct TnArgs {
+  RowMap x1, y1, x2, y2;
+  long rows;
+  const int* rows_dev;
+  int mo, no;
+  double* out;
+  long ld_out;
+};
+constexpr int kMaxTnGroup = 8;
+constexpr long kTnPartial = 16L << 20;  // floats of partial sums per group
+// floats of `partial` for products of up to mo_no_max outputs
+size_t tn_partial_floats(long mo_no_max);
+void launch_gemm_tn(const TnArgs* args, int n, float* partial, hipStream_t st);
 
 // ---- species-factorised first layer (first.hip) ---------------------------------------
 // H = [H2 | H2'] [rows, 128] of the first layer, the second hidden layer and
