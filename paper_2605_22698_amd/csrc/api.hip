@@ -203,24 +203,21 @@ struct LayerWeights {
 struct Workspace {
   std::vector<std::unique_ptr<DevBuf>> h, ht, R;
   std::unique_ptr<DevBuf> A, dR, dY, g, dh_a, dh_b, dht, e_atom;
-  // second-order pass: per layer A, tangents and stored radial activations
-  std::vector<std::unique_ptr<DevBuf>> Al, Ad, hd, htd, Rd, P1d, H1d, P2d, H2d;
-  std::unique_ptr<DevBuf> dd, Bd, Prb, Prc, w2c, eb, xb, xc, Ab, Ac, hb_a, hb_b, hc_a, hc_b, Rb, Rc, P1g, P2g,
-      partial, gsum, vf;
+  // weight gradients: A and A_dot per layer, the readout's rows, the adjoints
+  // of R and R', operands of the radial weights' products, partial sums
+  std::vector<std::unique_ptr<DevBuf>> Al, Ad;
+  std::unique_ptr<DevBuf> Prb, Prc, w2c, eb, Rb, Rc, Bd, H1d, H2d, P1g, P2g, partial, gsum, dwp;
   std::unique_ptr<DevBuf> G1, dG1;  // first layer, [N, (l3+1)^2, S*64]
   std::unique_ptr<DevBuf> H2f;      // first layer's second hidden layer and its derivative per edge pair (or edge), [., 128]
   std::unique_ptr<DevBuf> q_raw, q, pot, fc, pot_mean;  // electrostatics: charges, potential, forces
   std::vector<std::unique_ptr<DevBuf>> at;             // product block: A~ per layer
-  // Hessian-vector products: R, R' and R'' per layer, and a batch of directions' tangents and adjoints
+  // Hessian-vector products: R, R' and R'' per layer; a batch of directions'
+  // tangents and adjoints (the v buffers, one direction in weight gradients)
   std::vector<std::unique_ptr<DevBuf>> R3, vhd, vhtd, vatd, vBpd;
   std::unique_ptr<DevBuf> vdd, vAd, vA, vx, vh_a, vh_b, vgeo, vg, vmsg, vBp, vat;
   std::vector<int> rp_host;                            // pruned row pointer on the host (receiver chunks)
   bool rp_valid = false;
   std::unique_ptr<DevBuf> Bp, dat;                     // product block: B (or dB), dA~
-  // product block, second-order pass: A~_dot and B_dot per layer; adjoints of
-  // B, B_dot, A~, A~_dot; per-atom weight-gradient rows
-  std::vector<std::unique_ptr<DevBuf>> atd, Bpd;
-  std::unique_ptr<DevBuf> Bpb, Bpc, atb, atc, dwp;
   std::unique_ptr<DevBuf> mixp;                        // partial products of a K-split channel mix
   std::unique_ptr<DevBuf> msg;                         // per-edge sender-gradient messages of a full layer
   std::unique_ptr<DevBuf> touched;                     // per atom: tag of the last chunk that sent it a message
@@ -869,8 +866,8 @@ void* chunk_r(const Workspace& w, int t, void* R, const RChunk& ch, int PCu, siz
 
 // The pair owners of the pruned list, used by a layer's radial passes when
 // the model runs them per edge pair and the chunk is the whole edge list.
-EdgePairs graph_pairs(const e3mi_graph* G, bool compact = false) {
-  return EdgePairs{G->own->as<int>(), G->own_ptr->as<int>() + G->N, G->rev_x->as<int>(), compact ? 1 : 0};
+EdgePairs graph_pairs(const e3mi_graph* G) {
+  return EdgePairs{G->own->as<int>(), G->own_ptr->as<int>() + G->N, G->rev_x->as<int>()};
 }
 const EdgePairs* pairs_for(const e3mi_model* M, const RChunk& ch, const EdgePairs& p) {
   return M->edge_pairs && ch.e1 < 0 ? &p : nullptr;
@@ -879,10 +876,9 @@ const EdgePairs* pairs_for(const e3mi_model* M, const RChunk& ch, const EdgePair
 const int* first_pair_index(const e3mi_model* M, const e3mi_graph* G) {
   return M->edge_pairs ? G->pair_of->as<int>() : nullptr;
 }
-// R of a layer once per edge pair: the pair mode on a single chunk, in a
-// first-order evaluation (the second-order passes read R per edge)
-bool r_compact_for(const e3mi_model* M, const std::vector<RChunk>& chunks, bool keep_A) {
-  return M->edge_pairs && !keep_A && chunks.size() == 1 && chunks[0].e1 < 0;
+// BF16 mode: R of a layer once per edge pair, in the pair mode on a single chunk
+bool r_compact_for(const e3mi_model* M, const std::vector<RChunk>& chunks) {
+  return M->edge_pairs && chunks.size() == 1 && chunks[0].e1 < 0;
 }
 
 // R, R' and R'' of layer t for every edge pair (every edge with flag 8)
@@ -1001,19 +997,20 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     }
     if (t == 1 && factorised_first(M) && !keep_A) continue;
     if (fused_last(M, L, keep_A, bf16)) continue;
-    if (!keep_A && !bf16) {
+    if (!bf16) {
+      // weight gradients keep the rows of every edge (skin-list capacity)
       w.r_rows.resize(T + 1);
-      w.r_rows[t] = r_rows_plan(M, G, t, L.p_used * C, kept, st);
+      if (keep_A) w.r_whole[t] = 1;
+      w.r_rows[t] = keep_A ? (size_t)(Ecap + 1) : r_rows_plan(M, G, t, L.p_used * C, kept, st);
       ensure(w.R[t], a, 2 * sizeof(float) * w.r_rows[t] * L.p_used * C);
       continue;
     }
-    // the second-order pass keeps R of every edge (skin-list capacity);
-    // otherwise one chunk, or every edge inside the cutoff while the layers'
+    // BF16 mode: one chunk, or every edge inside the cutoff while the layers'
     // kept R stays within r_keep_bytes
     const size_t chunk_edges = r_chunk_edges(M, Ecap, L.p_used * C);
     const size_t r_elem = r_bf16_layer(w, L) ? 2 : 4;
-    size_t r_edges = keep_A ? (size_t)(Ecap + 1) : chunk_edges;
-    if (!keep_A && chunk_edges < (size_t)(Ecap + 1)) {
+    size_t r_edges = chunk_edges;
+    if (chunk_edges < (size_t)(Ecap + 1)) {
       // room for 1/8 more edges than this call has inside the cutoff, so
       // that the count's drift between rebuilds does not reallocate
       const size_t e_in = (size_t)pruned_rows(M, G, st)[N] + 1;
@@ -1034,7 +1031,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     for (int t = 1; t <= T; ++t) ensure(w.Al[t], a, sizeof(float) * (size_t)N * M->plans[t - 1].a_per_atom);
   }
   if (dr_bytes) ensure(w.dR, a, dr_bytes);
-  if (!derivs) {
+  if (!derivs && !keep_A) {
     ensure(w.dY, a, sizeof(float) * 16 * (size_t)(Ecap + 1));
     ensure(w.g, a, sizeof(float4) * (size_t)(Ecap + 1));
     ensure(w.dh_a, a, sizeof(float) * (size_t)N * NC * C);
@@ -1148,7 +1145,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     }
     float* R = (derivs ? w.R3[t] : w.R[t])->as<float>();  // BF16 values when r_bf16
     const int PCu = L.p_used * C;
-    const std::vector<RChunk> chunks = keep_A || derivs || (!bf16 && w.r_whole[t])
+    const std::vector<RChunk> chunks = derivs || (!bf16 && w.r_whole[t])
                                            ? std::vector<RChunk>{RChunk{0, N, 0, -1}} : r_chunks(M, G, PCu, st);
     TpArgs ta{};
     const bool lr_bf16 = r_bf16_layer(w, L);
@@ -1169,9 +1166,9 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     ta.C = C;
     ta.inv_nu = inv_nu;
     const RadialBf16 bfw = W.bf16_view();
-    const bool rows = !keep_A && !bf16 && !derivs;  // rows of R and R'
-    if (!rows) w.r_compact[t] = r_compact_for(M, chunks, keep_A) ? 1 : 0;
-    const EdgePairs prs = graph_pairs(G, w.r_compact[t]);
+    const bool rows = !bf16 && !derivs;  // rows of R and R'
+    if (bf16) w.r_compact[t] = r_compact_for(M, chunks) ? 1 : 0;
+    const EdgePairs prs = graph_pairs(G);
     ta.r_row = w.r_compact[t] ? G->pair_of->as<int>() : nullptr;
     for (const RChunk& ch : chunks) {
       void* Rc = rows ? R : chunk_r(w, t, R, ch, PCu, lr_bf16 ? 2 : 4);
@@ -1769,7 +1766,8 @@ e3mi_model* new_model(const char* json, const double* wts, size_t n, int precisi
 // Second-order pass for s = sum_s gE_s E_s - D_v E (v = gF): forward (primal
 // + tangent along v), then the reverse pass over both. out: the gradient of s
 // with respect to every weight, i.e. the vector-Jacobian product of (E, F) ->
-// weights for upstream (gE, gF).
+// weights for upstream (gE, gF). The adjoints of a value and of its tangent
+// are halves of one buffer, so that the linear maps take both at once.
 void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* gE, const float* gF, double* out,
                 hipStream_t st) {
   E3MI_REQUIRE(out, E3MI_EINVAL, "null output");
@@ -1778,261 +1776,226 @@ void param_grad(e3mi_model* M, e3mi_graph* G, const double* pos, const double* g
   const int N = G->N, C = c.channels, T = c.layers, H = c.radial_hidden;
   const long Ecap = G->E_room;  // edge capacity (>= the skin-list count)
   const int NC = (c.lmax + 1) * (c.lmax + 1);
-  const float inv_nu = (float)(1.0 / c.avg_neighbors);
   const float rc = (float)c.cutoff;
-  const int p_env = c.envelope_p;
   Workspace& w = M->ws;
   E3MI_REQUIRE(!c.coulomb, E3MI_EUNSUPPORTED,
                "second-order passes (parameter gradients, Hessian-vector products) of the Coulomb term are not implemented");
   const bool prod = c.correlation == 2;
   const WeightOffsets off = weight_offsets(c);
-  E3MI_HIP(hipMemsetAsync(out, 0, sizeof(double) * off.total, st));
+  launch_zero(out, sizeof(double) * off.total, st);
   if (N == 0) return;
   forward_pass(M, G, pos, true, st, false);
   const int* row_ptr = G->row_ptr_x->as<int>();
   const int* src = G->src_x->as<int>();
   const float4* dvec = G->dvec_x->as<float4>();
-  const int* rows_dev = row_ptr + N;  // number of edges inside the cutoff
+  const EdgePairs prs = graph_pairs(G);
+  const int* own = M->edge_pairs ? prs.own : nullptr;
+  const int* n_own = M->edge_pairs ? prs.n_own : nullptr;
+  const int* rows_dev = own ? n_own : row_ptr + N;  // rows of the radial MLP
   const size_t E1 = (size_t)Ecap + 1;
+  auto floats = [&](std::unique_ptr<DevBuf>& b, size_t n) { return ensure(b, a, sizeof(float) * n).as<float>(); };
 
   // ---- workspace ----
-  for (auto* v : {&w.Ad, &w.hd, &w.htd, &w.Rd, &w.P1d, &w.H1d, &w.P2d, &w.H2d}) v->resize(T + 1);
-  long a_max = 0, pc_max = 0;
+  for (auto* v : {&w.Ad, &w.vhd, &w.vhtd, &w.vatd, &w.vBpd}) v->resize(T + 1);
+  size_t a_max = 0, pc_max = 0, dw_max = 0, msg_max = 0;
+  size_t sum_cols = (size_t)c.n_species * C;  // most (group, column) sums of a group_sum call
+  long mn_max = 0;
   for (int t = 1; t <= T; ++t) {
     const LayerPlan& L = M->plans[t - 1];
     ensure(w.Ad[t], a, sizeof(float) * (size_t)N * L.a_per_atom);
-    ensure(w.hd[t], a, sizeof(float) * (size_t)N * L.nc_out * C);
-    ensure(w.htd[t], a, sizeof(float) * (size_t)N * L.nc_out * C);
-    ensure(w.Rd[t], a, sizeof(float) * E1 * L.p_used * C);
-    for (auto* v : {&w.P1d, &w.H1d, &w.P2d, &w.H2d}) ensure((*v)[t], a, sizeof(float) * E1 * 2 * H);
-    a_max = std::max(a_max, L.a_per_atom);
-    pc_max = std::max(pc_max, (long)L.p_used * C);
-  }
-  ensure(w.dd, a, sizeof(float4) * E1);
-  ensure(w.Bd, a, sizeof(float) * E1 * 16);
-  for (auto* v : {&w.Prb, &w.Prc, &w.w2c}) ensure(*v, a, sizeof(float) * (size_t)N * 16);
-  ensure(w.eb, a, sizeof(float) * (size_t)N);
-  for (auto* v : {&w.xb, &w.xc, &w.hb_a, &w.hb_b, &w.hc_a, &w.hc_b}) ensure(*v, a, sizeof(float) * (size_t)N * NC * C);
-  for (auto* v : {&w.Ab, &w.Ac}) ensure(*v, a, sizeof(float) * (size_t)N * a_max);
-  for (auto* v : {&w.Rb, &w.Rc}) ensure(*v, a, sizeof(float) * E1 * pc_max);
-  for (auto* v : {&w.P1g, &w.P2g}) ensure(*v, a, sizeof(float) * E1 * 2 * H);
-  size_t sum_cols = (size_t)c.n_species * C;  // most (group, column) sums of a group_sum call
-  long mn_max = (long)H * pc_max;
-  for (const LayerPlan& L : M->plans) {
-    sum_cols = std::max(sum_cols, (size_t)c.n_species * std::max(L.n_prod, L.lout + 1) * C);
+    ensure(w.vhd[t], a, sizeof(float) * (size_t)N * L.nc_out * C);
+    ensure(w.vhtd[t], a, sizeof(float) * (size_t)N * L.nc_out * C);
+    a_max = std::max(a_max, (size_t)L.a_per_atom);
+    pc_max = std::max(pc_max, (size_t)L.p_used * C);
+    if (L.kind == 1) msg_max = std::max(msg_max, 2 * (size_t)L.nc_in * C);
+    else if (t == 1) msg_max = std::max(msg_max, (size_t)C);
+    if (prod) {
+      ensure(w.vatd[t], a, sizeof(float) * (size_t)N * L.nc_a * C);
+      ensure(w.vBpd[t], a, sizeof(float) * (size_t)N * L.nc_out * C);
+      dw_max = std::max(dw_max, (size_t)(L.lout + 1 + L.n_prod) * C);
+      sum_cols = std::max(sum_cols, (size_t)c.n_species * std::max(L.n_prod, L.lout + 1) * C);
+    }
+    mn_max = std::max(mn_max, (long)H * L.p_used * C);
     for (int l = 0; l <= L.l3max_used; ++l) mn_max = std::max(mn_max, (long)L.p_used_l3[l] * C * C);
   }
-  float* partial = ensure(w.partial, a, sizeof(float) * tn_partial_floats(mn_max)).as<float>();
+  float4* dd = ensure(w.vdd, a, sizeof(float4) * E1).as<float4>();
+  float* Prb = floats(w.Prb, (size_t)N * 16);
+  float* Prc = floats(w.Prc, (size_t)N * 16);
+  float* w2c = floats(w.w2c, (size_t)N * 16);
+  float* eb = floats(w.eb, (size_t)N);
+  float* x = floats(w.vx, 2 * (size_t)N * NC * C);       // adjoints of h~, then of h~_dot
+  float* hcur = floats(w.vh_a, 2 * (size_t)N * NC * C);  // adjoints of h^t, then of h_dot^t
+  float* hprev = floats(w.vh_b, 2 * (size_t)N * NC * C);
+  float* Ab = floats(w.vA, 2 * (size_t)N * a_max);       // adjoints of A, then of A_dot
+  float* Rb = floats(w.Rb, E1 * pc_max);                 // adjoints of R and of R'
+  float* Rc = floats(w.Rc, E1 * pc_max);
+  float* Bd = floats(w.Bd, E1 * 16);
+  float* H1d = floats(w.H1d, E1 * 2 * H);
+  float* H2d = floats(w.H2d, E1 * 2 * H);
+  float* P1g = floats(w.P1g, E1 * 2 * H);
+  float* P2g = floats(w.P2g, E1 * 2 * H);
+  float* partial = floats(w.partial, tn_partial_floats(mn_max));
   double* gsum = ensure(w.gsum, a, sizeof(double) * group_chunks(N) * std::max<size_t>(sum_cols, 16)).as<double>();
-  if (prod) {
-    w.atd.resize(T + 1);
-    w.Bpd.resize(T + 1);
-    long dw_max = 0;
-    for (int t = 1; t <= T; ++t) {
-      const LayerPlan& L = M->plans[t - 1];
-      ensure(w.atd[t], a, sizeof(float) * (size_t)N * L.nc_a * C);
-      ensure(w.Bpd[t], a, sizeof(float) * (size_t)N * (L.lout + 1) * (L.lout + 1) * C);
-      dw_max = std::max(dw_max, (long)(L.lout + 1 + L.n_prod) * C);
-    }
-    for (auto* v : {&w.Bpb, &w.Bpc, &w.atb, &w.atc}) ensure(*v, a, sizeof(float) * (size_t)N * NC * C);
-    ensure(w.dwp, a, sizeof(float) * (size_t)N * dw_max);
-  }
+  HvpArgs ha{};
+  ha.lmax = c.lmax;
+  ha.N = N;
+  ha.C = C;
+  ha.B = 1;
+  ha.row_ptr = row_ptr;
+  ha.src = src;
+  ha.rev = G->rev_x->as<int>();
+  ha.dvec = dvec;
+  ha.dd = dd;
+  ha.e_stride = (long)E1;
+  ha.r_row = first_pair_index(M, G);
+  ha.inv_nu = (float)(1.0 / c.avg_neighbors);
+  ha.Ab = Ab;
+  ha.msg = floats(w.vmsg, E1 * msg_max);
+  auto layer_args = [&](int t) {
+    const LayerPlan& L = M->plans[t - 1];
+    ha.kind = L.kind;
+    ha.R = w.R[t]->as<float>();
+    ha.Rp = rp_rows(M, t);
+    ha.r_stride = (long)L.p_used * C;
+    ha.h = w.h[t - 1]->as<float>();
+    ha.hd = t > 1 ? w.vhd[t - 1]->as<float>() : nullptr;
+    ha.h_nc = L.nc_in;
+    ha.Ad = w.Ad[t]->as<float>();
+  };
 
   // ---- tangent forward along v = gF ----
-  launch_edge_tangent(row_ptr, src, dvec, gF, N, w.dd->as<float4>(), st);
-  const float4* dd = w.dd->as<float4>();
+  launch_hvp_edge_tangent(row_ptr, src, dvec, gF, N, 1, ha.e_stride, dd, st);
   for (int t = 1; t <= T; ++t) {
     const LayerPlan& L = M->plans[t - 1];
     LayerWeights& W = *M->lw[t - 1];
-    const int PCu = L.p_used * C;
-    launch_radial_dual_fwd(c.n_basis, dvec, dd, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(),
-                           W.rad3.as<float>(), L.p_full * C, PCu, w.Rd[t]->as<float>(), w.Bd->as<float>(),
-                           w.P1d[t]->as<float>(), w.H1d[t]->as<float>(), w.P2d[t]->as<float>(), w.H2d[t]->as<float>(),
-                           rc, p_env, st);
-    TpArgs ta{};
-    ta.lmax = c.lmax;
-    ta.kind = L.kind;
-    ta.cpt = cpt_for(L, C);
-    ta.row_ptr = row_ptr;
-    ta.src = src;
-    ta.dvec = dvec;
-    ta.dd = dd;
-    ta.R = w.R[t]->as<float>();
-    ta.Rd = w.Rd[t]->as<float>();
-    ta.r_stride = PCu;
-    ta.h = w.h[t - 1]->as<float>();
-    ta.hd = t > 1 ? w.hd[t - 1]->as<float>() : nullptr;
-    ta.h_nc = L.nc_in;
-    ta.Ad = w.Ad[t]->as<float>();
-    ta.N = N;
-    ta.C = C;
-    ta.inv_nu = inv_nu;
-    launch_tp(3, ta, st);
+    layer_args(t);
+    launch_hvp_tangent_sum(ha, st);
+    float* htd = w.vhtd[t]->as<float>();
     if (prod) {
       // A~_dot = A_dot W_mix (no self connection), B_dot, then h~_dot = B_dot W_lin + h_dot S
-      launch_mix(M, L, W, w.Ad[t]->as<float>(), nullptr, w.atd[t]->as<float>(), L.nc_a, N, st);
+      launch_mix(M, L, W, ha.Ad, nullptr, w.vatd[t]->as<float>(), L.nc_a, N, st);
       ProductArgs pa = product_args(M, G, L, W, w.at[t]->as<float>());
-      pa.atd = w.atd[t]->as<float>();
-      pa.Bd = w.Bpd[t]->as<float>();
+      pa.atd = w.vatd[t]->as<float>();
+      pa.Bd = w.vBpd[t]->as<float>();
       launch_product_jvp(pa, st);
-      launch_lin(M, L, W, w.Bpd[t]->as<float>(), t > 1 ? w.hd[t - 1]->as<float>() : nullptr, w.htd[t]->as<float>(),
-                 N, st, false);
+      launch_lin(M, L, W, pa.Bd, ha.hd, htd, N, st, false);
     } else {
-      launch_mix(M, L, W, w.Ad[t]->as<float>(), t > 1 ? w.hd[t - 1]->as<float>() : nullptr,
-                 w.htd[t]->as<float>(), L.nc_out, N, st);
+      launch_mix(M, L, W, ha.Ad, ha.hd, htd, L.nc_out, N, st);
     }
-    launch_gate_dual_fwd(w.ht[t]->as<float>(), w.htd[t]->as<float>(), w.hd[t]->as<float>(), N, L.nc_out, C, st);
+    launch_gate_dual_fwd(w.ht[t]->as<float>(), htd, w.vhd[t]->as<float>(), N, L.nc_out, C, st);
   }
 
   // ---- reverse: readout ----
   const int ncT = M->plans[T - 1].nc_out;
-  float* hb = w.hb_a->as<float>();
-  float* hc = w.hc_a->as<float>();
-  float* hb2 = w.hb_b->as<float>();
-  float* hc2 = w.hc_b->as<float>();
-  launch_readout_dual(w.h[T]->as<float>(), w.hd[T]->as<float>(), ncT, G->owner->as<int>(), gE, M->read1->as<float>(),
-                      M->read2->as<float>(), N, C, w.Prb->as<float>(), w.Prc->as<float>(), w.w2c->as<float>(), hb, hc,
-                      w.eb->as<float>(), st);
+  float* hdT = w.vhd[T]->as<float>();
+  launch_readout_dual(w.h[T]->as<float>(), hdT, ncT, G->owner->as<int>(), gE, M->read1->as<float>(),
+                      M->read2->as<float>(), N, C, Prb, Prc, w2c, hcur, hcur + (size_t)N * ncT * C, eb, st);
   {
-    const TnArgs read1{RowMap{w.h[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prb->as<float>(), 16, 0, 1},
-                       RowMap{w.hd[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{w.Prc->as<float>(), 16, 0, 1}, N,
-                       nullptr, C, 16, out + off.read1, 16};
+    const TnArgs read1{RowMap{w.h[T]->as<float>(), (long)ncT * C, 0, 1}, RowMap{Prb, 16, 0, 1},
+                       RowMap{hdT, (long)ncT * C, 0, 1}, RowMap{Prc, 16, 0, 1}, N, nullptr, C, 16, nullptr,
+                       out + off.read1, 16};
     launch_gemm_tn(&read1, 1, partial, st);
   }
-  launch_group_sum(w.w2c->as<float>(), 16, nullptr, 1, N, 16, gsum, out + off.read2, 16, st);
-  launch_group_sum(w.eb->as<float>(), 1, G->species->as<int>(), c.n_species, N, 1, gsum, out + off.e0, 1, st);
+  launch_group_sum(w2c, 16, nullptr, 1, N, 16, gsum, out + off.read2, 16, st);
+  launch_group_sum(eb, 1, G->species->as<int>(), c.n_species, N, 1, gsum, out + off.e0, 1, st);
 
   // ---- reverse: layers ----
-  float* xb = w.xb->as<float>();
-  float* xc = w.xc->as<float>();
   for (int t = T; t >= 1; --t) {
     const LayerPlan& L = M->plans[t - 1];
     LayerWeights& W = *M->lw[t - 1];
     const int PCu = L.p_used * C;
-    const float* hin = w.h[t - 1]->as<float>();
-    const float* hdin = t > 1 ? w.hd[t - 1]->as<float>() : nullptr;
-    launch_gate_dual_bwd(w.ht[t]->as<float>(), w.htd[t]->as<float>(), hb, hc, xb, xc, N, L.nc_out, C, st);
+    layer_args(t);
+    float* hin = w.h[t - 1]->as<float>();
+    float* hdin = t > 1 ? w.vhd[t - 1]->as<float>() : nullptr;
+    const size_t xs = (size_t)N * L.nc_out * C, hs = (size_t)N * L.nc_in * C;
+    launch_gate_dual_bwd(w.ht[t]->as<float>(), w.vhtd[t]->as<float>(), hcur, hcur + xs, x, x + xs, N, L.nc_out, C, st);
+    // rows (atom, m) of order l: of a feature buffer, and of X1^T Y1 + X2^T Y2 over them
+    auto rows_of = [&](float* base, int l, int nc) {
+      return RowMap{base ? base + (long)l * l * C : nullptr, (long)nc * C, (long)C, 2 * l + 1};
+    };
     // weight gradients of the self connection (orders present in both h^{t-1}
     // and h~) and, below, of the channel mix: one group (at most 4 + 4 products)
     TnArgs tn[kMaxTnGroup];
     int n_tn = 0;
-    for (int l = 0; l <= std::min(L.l1max, prod ? L.lout : L.l3max_used); ++l) {
-      const int g = 2 * l + 1;
-      tn[n_tn++] = TnArgs{RowMap{const_cast<float*>(hin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g},
-                          RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
-                          hdin ? RowMap{const_cast<float*>(hdin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g}
-                               : RowMap{nullptr, 0, 0, 1},
-                          RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
+    for (int l = 0; l <= std::min(L.l1max, prod ? L.lout : L.l3max_used); ++l)
+      tn[n_tn++] = TnArgs{rows_of(hin, l, L.nc_in), rows_of(x, l, L.nc_out), rows_of(hdin, l, L.nc_in),
+                          rows_of(x + xs, l, L.nc_out), (long)N * (2 * l + 1), nullptr, C, C, nullptr,
                           out + off.self_[t - 1][l], C};
-    }
-    E3MI_HIP(hipMemsetAsync(hb2, 0, sizeof(float) * (size_t)N * L.nc_in * C, st));
-    if (t > 1) E3MI_HIP(hipMemsetAsync(hc2, 0, sizeof(float) * (size_t)N * L.nc_in * C, st));
-    // the mix's output adjoints (of A~ or h~, and of their tangents)
-    const float* mb = xb;
-    const float* mc = xc;
+    // the mix's output adjoints (of A~ or h~, then of their tangents)
+    float* m = x;
     int m_nc = L.nc_out;
     if (prod) {
       // h~ = B W_lin + h^{t-1} S: adjoints of B and B_dot (and of h^{t-1},
       // h_dot^{t-1} through S), W_lin's gradient from B and B_dot
       float* Bt = w.Bp->as<float>();
       ProductArgs pa = product_args(M, G, L, W, w.at[t]->as<float>());
-      pa.atd = w.atd[t]->as<float>();
+      pa.atd = w.vatd[t]->as<float>();
       pa.B = Bt;
       launch_product(true, pa, st);  // B again (the forward pass keeps one layer's)
       TnArgs lin[4];
-      for (int l = 0; l <= L.lout; ++l) {
-        const int g = 2 * l + 1, nb = (L.lout + 1) * (L.lout + 1);
-        lin[l] = TnArgs{RowMap{Bt + (long)l * l * C, (long)nb * C, (long)C, g},
-                        RowMap{xb + (long)l * l * C, (long)L.nc_out * C, (long)C, g},
-                        RowMap{w.Bpd[t]->as<float>() + (long)l * l * C, (long)nb * C, (long)C, g},
-                        RowMap{xc + (long)l * l * C, (long)L.nc_out * C, (long)C, g}, (long)N * g, nullptr, C, C,
+      for (int l = 0; l <= L.lout; ++l)
+        lin[l] = TnArgs{rows_of(Bt, l, L.nc_out), rows_of(x, l, L.nc_out), rows_of(w.vBpd[t]->as<float>(), l, L.nc_out),
+                        rows_of(x + xs, l, L.nc_out), (long)N * (2 * l + 1), nullptr, C, C, nullptr,
                         out + off.lin[t - 1][l], C};
-      }
       launch_gemm_tn(lin, L.lout + 1, partial, st);
-      launch_lin_adjoint(M, L, W, xb, w.Bpb->as<float>(), hb2, N, st, false);
-      launch_lin_adjoint(M, L, W, xc, w.Bpc->as<float>(), t > 1 ? hc2 : nullptr, N, st, false);
-      pa.Bb = w.Bpb->as<float>();
-      pa.Bc = w.Bpc->as<float>();
-      pa.atb = w.atb->as<float>();
-      pa.atc = w.atc->as<float>();
-      pa.dw = w.dwp->as<float>();
+      float* Bb = floats(w.vBp, 2 * (size_t)N * NC * C);
+      launch_lin_adjoint(M, L, W, x, Bb, hprev, 2 * N, st, false);
+      float* at = floats(w.vat, 2 * (size_t)N * NC * C);
+      pa.Bb = Bb;
+      pa.Bc = Bb + xs;
+      pa.atb = at;
+      pa.atc = at + (size_t)N * L.nc_a * C;
+      pa.dw = floats(w.dwp, (size_t)N * dw_max);
       launch_product_dual_bwd(pa, st);
       const long ldw = (long)(L.lout + 1 + L.n_prod) * C;
       launch_group_sum(pa.dw, ldw, G->species->as<int>(), c.n_species, N, (L.lout + 1) * C, gsum,
-                       out + off.sym1[t - 1],
-                       (long)(L.lout + 1) * C, st);
+                       out + off.sym1[t - 1], (long)(L.lout + 1) * C, st);
       launch_group_sum(pa.dw + (long)(L.lout + 1) * C, ldw, G->species->as<int>(), c.n_species, N, L.n_prod * C, gsum,
                        out + off.sym2[t - 1], (long)L.n_prod * C, st);
-      mb = w.atb->as<float>();
-      mc = w.atc->as<float>();
+      m = at;
       m_nc = L.nc_a;
     }
-    // weight gradients of the channel mix
+    float* mc = m + (size_t)N * m_nc * C;
     long gbase = 0;
-    for (int l3 = 0; l3 <= L.l3max_used; ++l3) {
-      const int P3 = L.p_used_l3[l3], g = 2 * l3 + 1;
-      tn[n_tn++] = TnArgs{RowMap{w.Al[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g},
-                          RowMap{const_cast<float*>(mb) + (long)l3 * l3 * C, (long)m_nc * C, (long)C, g},
-                          RowMap{w.Ad[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g},
-                          RowMap{const_cast<float*>(mc) + (long)l3 * l3 * C, (long)m_nc * C, (long)C, g}, (long)N * g,
-                          nullptr, P3 * C, C, out + off.mix[t - 1][l3], C};
+    for (int l = 0; l <= L.l3max_used; ++l) {
+      const int P3 = L.p_used_l3[l], g = 2 * l + 1;
+      const RowMap A{w.Al[t]->as<float>() + gbase, (long)g * P3 * C, (long)P3 * C, g};
+      const RowMap Ad{ha.Ad + gbase, (long)g * P3 * C, (long)P3 * C, g};
+      tn[n_tn++] = TnArgs{A, rows_of(m, l, m_nc), Ad, rows_of(mc, l, m_nc), (long)N * g, nullptr, P3 * C, C, nullptr,
+                          out + off.mix[t - 1][l], C};
       gbase += (long)N * g * P3 * C;
     }
     launch_gemm_tn(tn, n_tn, partial, st);
     // adjoints of A and A_dot; of h^{t-1} and h_dot^{t-1} through the self
     // connection (without the product block, the mix holds it)
-    launch_mix_adjoint(M, L, W, mb, m_nc, w.Ab->as<float>(), prod ? nullptr : hb2, N, st);
-    launch_mix_adjoint(M, L, W, mc, m_nc, w.Ac->as<float>(), (!prod && t > 1) ? hc2 : nullptr, N, st);
-    // tensor product: adjoints of R and R_dot, then of h and h_dot
-    TpArgs ta{};
-    ta.lmax = c.lmax;
-    ta.kind = L.kind;
-    ta.cpt = cpt_for(L, C);
-    ta.row_ptr = row_ptr;
-    ta.src = src;
-    ta.dvec = dvec;
-    ta.dd = dd;
-    ta.R = w.R[t]->as<float>();
-    ta.Rd = w.Rd[t]->as<float>();
-    ta.r_stride = PCu;
-    ta.h = hin;
-    ta.hd = hdin;
-    ta.h_nc = L.nc_in;
-    ta.Ab = w.Ab->as<float>();
-    ta.Ac = w.Ac->as<float>();
-    ta.Rb = w.Rb->as<float>();
-    ta.Rc = w.Rc->as<float>();
-    ta.hb = hb2;
-    ta.hc = t > 1 ? hc2 : nullptr;
-    ta.dh_nc = L.nc_in;
-    ta.N = N;
-    ta.C = C;
-    ta.inv_nu = inv_nu;
-    launch_tp(4, ta, st);
-    launch_tp(5, ta, st);
+    launch_mix_adjoint(M, L, W, m, m_nc, Ab, prod ? nullptr : hprev, 2 * N, st);
+    // tensor product: adjoints of R and R' per edge, and of h and h_dot
+    ha.hb = hprev;
+    ha.hc = hprev + hs;
+    const int l_sc = std::min(prod ? L.lout : L.l3max_used, L.l1max);  // orders the self connection's adjoint wrote
+    ha.dh_acc = (l_sc + 1) * (l_sc + 1);
+    ha.Rb = Rb;
+    ha.Rc = Rc;
+    launch_hvp_adjoint(ha, st);
     // radial MLP: adjoints of the pre-activations, then the weight gradients
-    launch_radial_dual_bwd(row_ptr, N, Ecap, W.rad2T.as<float>(), W.rad3T.as<float>(), PCu, w.Rb->as<float>(),
-                           w.Rc->as<float>(), w.P1d[t]->as<float>(), w.P2d[t]->as<float>(), w.P1g->as<float>(),
-                           w.P2g->as<float>(), st);
-    float* H2d = w.H2d[t]->as<float>();
-    float* H1d = w.H1d[t]->as<float>();
-    float* Bd = w.Bd->as<float>();
-    float* P1g = w.P1g->as<float>();
-    float* P2g = w.P2g->as<float>();
+    launch_radial_wgrad(dvec, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(), W.rad2T.as<float>(),
+                        W.rad3T.as<float>(), PCu, Rb, Rc, rc, c.envelope_p, own, n_own, prs.rev, Bd, H1d, H2d, P1g,
+                        P2g, st);
+    auto halves = [&](float* base, int width, bool second) {
+      return RowMap{base + (second ? width : 0), 2L * width, 0, 1};
+    };
     const TnArgs rad[3] = {
-        TnArgs{RowMap{H2d, 2L * H, 0, 1}, RowMap{w.Rb->as<float>(), PCu, 0, 1}, RowMap{H2d + H, 2L * H, 0, 1},
-               RowMap{w.Rc->as<float>(), PCu, 0, 1}, Ecap, rows_dev, H, PCu, out + off.rad3[t - 1],
-               (long)L.p_full * C},
-        TnArgs{RowMap{H1d, 2L * H, 0, 1}, RowMap{P2g, 2L * H, 0, 1}, RowMap{H1d + H, 2L * H, 0, 1},
-               RowMap{P2g + H, 2L * H, 0, 1}, Ecap, rows_dev, H, H, out + off.rad2[t - 1], H},
-        TnArgs{RowMap{Bd, 16, 0, 1}, RowMap{P1g, 2L * H, 0, 1}, RowMap{Bd + 8, 16, 0, 1},
-               RowMap{P1g + H, 2L * H, 0, 1}, Ecap, rows_dev, c.n_basis, H, out + off.rad1[t - 1], H}};
+        TnArgs{halves(H2d, H, false), RowMap{Rb, PCu, 0, 1}, halves(H2d, H, true), RowMap{Rc, PCu, 0, 1}, Ecap,
+               rows_dev, H, PCu, own, out + off.rad3[t - 1], (long)L.p_full * C},
+        TnArgs{halves(H1d, H, false), halves(P2g, H, false), halves(H1d, H, true), halves(P2g, H, true), Ecap, rows_dev,
+               H, H, nullptr, out + off.rad2[t - 1], H},
+        TnArgs{halves(Bd, c.n_basis, false), halves(P1g, H, false), halves(Bd, c.n_basis, true), halves(P1g, H, true),
+               Ecap, rows_dev, c.n_basis, H, nullptr, out + off.rad1[t - 1], H}};
     launch_gemm_tn(rad, 3, partial, st);
-    std::swap(hb, hb2);
-    std::swap(hc, hc2);
+    std::swap(hcur, hprev);
   }
   // embedding: h^0_i = W_emb[z_i]
-  launch_group_sum(hb, C, G->species->as<int>(), c.n_species, N, C, gsum, out + off.emb, C, st);
+  launch_group_sum(hcur, C, G->species->as<int>(), c.n_species, N, C, gsum, out + off.emb, C, st);
 }
 
 // Directions of one batch of Hessian-vector products. One direction of a small
@@ -2102,7 +2065,11 @@ void hvp_directions(e3mi_model* M, e3mi_graph* G, int B, const float* v, float* 
   auto layer_args = [&](int t) {
     const LayerPlan& L = M->plans[t - 1];
     ha.kind = L.kind;
-    ha.R3 = w.R3[t]->as<float>();
+    const long PCu = (long)L.p_used * C;
+    ha.R = w.R3[t]->as<float>();
+    ha.Rp = ha.R + PCu;
+    ha.Rpp = ha.R + 2 * PCu;
+    ha.r_stride = 3 * PCu;
     ha.h = w.h[t - 1]->as<float>();
     ha.hd = t > 1 ? w.vhd[t - 1]->as<float>() : nullptr;
     ha.h_nc = L.nc_in;

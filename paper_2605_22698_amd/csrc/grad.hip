@@ -21,23 +21,6 @@ namespace {
 
 inline int blocks(long n, int t) { return (int)((n + t - 1) / t); }
 
-// d_dot = v_j - v_i for edge e = (i <- j); r_dot = n . d_dot. One wave per row.
-__global__ void __launch_bounds__(256) k_edge_tangent(const int* __restrict__ row_ptr, const int* __restrict__ src,
-                                                      const float4* __restrict__ dvec, const float* __restrict__ v,
-                                                      int N, float4* __restrict__ dd) {
-  const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (i >= N) return;
-  const float vx = v[3 * i], vy = v[3 * i + 1], vz = v[3 * i + 2];
-  const int b = row_ptr[i + 1];
-  for (int e = row_ptr[i] + lane; e < b; e += 64) {
-    const int j = src[e];
-    const float4 d = dvec[e];
-    const float x = v[3 * j] - vx, y = v[3 * j + 1] - vy, z = v[3 * j + 2] - vz;
-    dd[e] = make_float4(x, y, z, (d.x * x + d.y * y + d.z * z) / d.w);
-  }
-}
-
 // h_dot = gate'(h~) h~_dot
 __global__ void k_gate_dual_fwd(const float* __restrict__ x, const float* __restrict__ xd, float* __restrict__ hd,
                                 int N, int nc, int C, int B) {
@@ -226,7 +209,7 @@ __global__ void __launch_bounds__(256) k_gemm_tn(TnGroup gg, float* __restrict__
       const int r = r0 + s / terms * kTnRows + kr + 16 * q;
       xv[q] = yv[q] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (r < r1 && in_m) xv[q] = *reinterpret_cast<const float4*>(tn_row(X, r) + bm + c4);
-      if (r < r1 && in_n) yv[q] = *reinterpret_cast<const float4*>(tn_row(Y, r) + bn + c4);
+      if (r < r1 && in_n) yv[q] = *reinterpret_cast<const float4*>(tn_row(Y, a.y_row ? a.y_row[r] : r) + bn + c4);
     }
   };
   f32x16 acc = {};
@@ -280,11 +263,6 @@ __global__ void __launch_bounds__(256) k_tn_reduce(TnGroup gg, const float* __re
 
 }  // namespace
 
-void launch_edge_tangent(const int* row_ptr, const int* src, const float4* dvec, const float* v, int N, float4* dd,
-                         hipStream_t st) {
-  if (N == 0) return;
-  k_edge_tangent<<<blocks((long)N * 64, 256), 256, 0, st>>>(row_ptr, src, dvec, v, N, dd);
-}
 void launch_gate_dual_fwd(const float* x, const float* xd, float* hd, int N, int nc, int C, hipStream_t st, int B) {
   if (N == 0) return;
   k_gate_dual_fwd<<<blocks((long)B * N * C, 256), 256, 0, st>>>(x, xd, hd, N, nc, C, B);

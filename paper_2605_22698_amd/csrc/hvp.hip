@@ -19,6 +19,10 @@
 // per edge ("geo row"), which k_hvp_geo turns into the edge's position
 // adjoint; neither R_dot nor the adjoints of R go to memory.
 //
+// The weight gradient of a loss on energies and forces runs the same kernels
+// along one direction (W variants); it stops at the adjoints of R and R' = dR/dr,
+// sb and rho sc, which radial.hip takes back through the radial MLP.
+//
 // Bound: the feature and adjoint gathers from L2 (16 x C values each) and, in
 // the adjoints, the vector ALU. Measured (l_max 3, 128 channels, 2 layers): the
 // full Hessians of 64 molecules of 10-31 atoms (93 products, 13 directions at
@@ -101,7 +105,7 @@ __global__ void __launch_bounds__(KIND == kFull ? 128 : 64) k_hvp_fwd(HvpArgs a)
       t[n] = dd[n][e];
       real_sh_dual<LMAX>(d, t[n], Y, Yd[n]);
     }
-    const float* R0 = a.R3 + (long)(a.r_row ? a.r_row[e] : e) * 3 * NP * C;
+    const long ro = (long)(a.r_row ? a.r_row[e] : e) * a.r_stride;
     float hv[NIN][CH], hdv[ND][H ? NIN : 1][CH];
 #pragma unroll
     for (int q = 0; q < NIN; ++q) {
@@ -114,8 +118,8 @@ __global__ void __launch_bounds__(KIND == kFull ? 128 : 64) k_hvp_fwd(HvpArgs a)
     float r0[NP][CH], r1[NP][CH];
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
-      ldr_n<CH>(R0 + q * C + ln.k0, r0[q]);
-      ldr_n<CH>(R0 + (NP + q) * C + ln.k0, r1[q]);
+      ldr_n<CH>(a.R + ro + q * C + ln.k0, r0[q]);
+      ldr_n<CH>(a.Rp + ro + q * C + ln.k0, r1[q]);
     }
     static_for<NP>([&](auto pi) {
       constexpr int g = PS::T.id[pi];
@@ -216,14 +220,15 @@ __device__ __forceinline__ void load_adjoints(const HvpArgs& a, long u, Lane ln,
 }
 
 // One path's share of an edge: the sums above for CH channels (ab and ac from
-// output O0 on). H: h_dot is not zero, and the adjoints of h and h_dot are
-// wanted.
-template <class PS, int PI, int O0, bool H, int CH, int NY>
+// output O0 on). HD: h_dot is not zero, and its adjoint is wanted; HB: the
+// adjoint of h is wanted. W (weight gradients): instead of the geo sums, rb and
+// rc get the adjoints of R and of R' (rho times that of R_dot).
+template <class PS, int PI, int O0, bool HD, bool HB, bool W, int CH, int NY>
 __device__ __forceinline__ void path_adjoint(const float (*hv)[CH], const float (*hdv)[CH], const float* Y,
                                              const float* Yd, float rho, const float* r0, const float* r1,
                                              const float* r2, const float (*ab)[CH], const float (*ac)[CH],
                                              float& sr, float& sd, float* yb, float* yc, float (*hb)[CH],
-                                             float (*hc)[CH]) {
+                                             float (*hc)[CH], float* rb = nullptr, float* rc = nullptr) {
   constexpr int g = PS::T.id[PI];
   constexpr int l1 = kL1[g], l2 = kL2[g], l3 = kL3[g];
   constexpr int z0 = kNzBegin[g], nz = kNzBegin[g + 1] - kNzBegin[g];
@@ -234,7 +239,7 @@ __device__ __forceinline__ void path_adjoint(const float (*hv)[CH], const float 
     float tm[2 * l3 + 1], td[2 * l3 + 1], eb[2 * l3 + 1], ec[2 * l3 + 1];
     // the path's one coefficient, if it has one, goes into R and its derivatives
     const float c0 = ONE ? kC[z0] : 1.0f;
-    const float s0 = c0 * r0[c], s1 = c0 * r1[c], s2 = c0 * r2[c], rd = s1 * rho;
+    const float s0 = c0 * r0[c], s1 = c0 * r1[c], rd = s1 * rho;
 #pragma unroll
     for (int m = 0; m < 2 * l3 + 1; ++m) {
       tm[m] = td[m] = 0.0f;
@@ -248,15 +253,17 @@ __device__ __forceinline__ void path_adjoint(const float (*hv)[CH], const float 
       const float x = hv[q1][c], cx = ONE ? x : kC[q] * x;
       tm[m] += x * cy;
       td[m] += x * cyd;
-      yb[q2] += eb[m] * cx;
-      yc[q2] += ec[m] * cx;
-      if constexpr (H) {
+      if constexpr (!W) {
+        yb[q2] += eb[m] * cx;
+        yc[q2] += ec[m] * cx;
+      }
+      if constexpr (HD) {
         const float xd = hdv[q1][c];
         td[m] += xd * cy;
-        yb[q2] += ec[m] * (ONE ? xd : kC[q] * xd);
-        hb[q1][c] += eb[m] * cy + ec[m] * cyd;
+        if constexpr (!W) yb[q2] += ec[m] * (ONE ? xd : kC[q] * xd);
         hc[q1][c] += ec[m] * cy;
       }
+      if constexpr (HB) hb[q1][c] += eb[m] * cy + ec[m] * cyd;
     });
     float sb = 0.0f, sc = 0.0f;
 #pragma unroll
@@ -264,8 +271,13 @@ __device__ __forceinline__ void path_adjoint(const float (*hv)[CH], const float 
       sb += ab[off + m][c] * tm[m] + ac[off + m][c] * td[m];
       sc += ac[off + m][c] * tm[m];
     }
-    sr += sb * s1 + sc * (rho * s2);
-    sd += sc * s1;
+    if constexpr (W) {
+      rb[c] = c0 * sb;
+      rc[c] = c0 * sc * rho;
+    } else {
+      sr += sb * s1 + sc * (rho * (c0 * r2[c]));
+      sd += sc * s1;
+    }
   }
 }
 
@@ -285,8 +297,10 @@ __device__ __forceinline__ void reduce_geo(const float* yb, const float* yc, flo
 
 // ---- receiver-side edge adjoint --------------------------------------------------
 // Scalar-input layers: one wave per (direction, receiver), ab_i and ac_i in
-// registers, one geo row per edge (h_dot is zero and nothing depends on h).
-template <int LMAX, int KIND, int CH>
+// registers (h_dot is zero). W false: one geo row per edge (nothing depends on
+// h). W true (weight gradients, one direction): the edges' adjoints of R and
+// R', and the edge's share of its sender's embedding gradient, msg [E, C].
+template <int LMAX, int KIND, int CH, bool W>
 __global__ void __launch_bounds__(64) k_hvp_edge(HvpArgs a) {
   using PS = PathSet<LMAX, KIND>;
   constexpr int NP = PS::NP, NOUT = PS::NOUT, NIN = PS::NIN, NY = PS::NY;
@@ -295,7 +309,7 @@ __global__ void __launch_bounds__(64) k_hvp_edge(HvpArgs a) {
   const int b = (int)(u / a.N), i = (int)(u % a.N), C = a.C;
   const Lane ln = lane_channels<CH>(C);
   const float4* dd = a.dd + (long)b * a.e_stride;
-  float* geo = a.geo + (long)b * a.e_stride * kGeo;
+  float* geo = W ? nullptr : a.geo + (long)b * a.e_stride * kGeo;
   float ab[NOUT][CH], ac[NOUT][CH];
   load_adjoints<PS, 0, 3, CH>(a, u, ln, ab, ac);
   const int e1 = a.row_ptr[i + 1];
@@ -305,18 +319,31 @@ __global__ void __launch_bounds__(64) k_hvp_edge(HvpArgs a) {
     real_sh_dual<LMAX>(a.dvec[e], t, Y, Yd);
 #pragma unroll
     for (int q = 0; q < NY; ++q) yb[q] = yc[q] = 0.0f;
-    const float* R0 = a.R3 + (long)(a.r_row ? a.r_row[e] : e) * 3 * NP * C;
-    float hv[1][CH], none[1][CH];
+    const long ro = (long)(a.r_row ? a.r_row[e] : e) * a.r_stride;
+    float hv[1][CH], hb[1][CH], none[1][CH];
     ldr_n<CH>(a.h + (long)a.src[e] * a.h_nc * C + ln.k0, hv[0]);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) hb[0][c] = 0.0f;
     float sr = 0.0f, sd = 0.0f;
     static_for<NP>([&](auto pi) {
-      float r0[CH], r1[CH], r2[CH];
-      ldr_n<CH>(R0 + pi * C + ln.k0, r0);
-      ldr_n<CH>(R0 + (NP + pi) * C + ln.k0, r1);
-      ldr_n<CH>(R0 + (2 * NP + pi) * C + ln.k0, r2);
-      path_adjoint<PS, pi, 0, false, CH, NY>(hv, none, Y, Yd, t.w, r0, r1, r2, ab, ac, sr, sd, yb, yc, none, none);
+      float r0[CH], r1[CH], r2[CH], rb[CH], rc[CH];
+      ldr_n<CH>(a.R + ro + pi * C + ln.k0, r0);
+      ldr_n<CH>(a.Rp + ro + pi * C + ln.k0, r1);
+      if constexpr (!W) ldr_n<CH>(a.Rpp + ro + pi * C + ln.k0, r2);
+      path_adjoint<PS, pi, 0, false, W, W, CH, NY>(hv, none, Y, Yd, t.w, r0, r1, r2, ab, ac, sr, sd, yb, yc, hb, none,
+                                                   rb, rc);
+      if constexpr (W) {
+        if (ln.on) {
+          str_n<CH>(a.Rb + ((long)e * NP + pi) * C + ln.k0, rb);
+          str_n<CH>(a.Rc + ((long)e * NP + pi) * C + ln.k0, rc);
+        }
+      }
     });
-    reduce_geo<NY>(yb, yc, sr, sd, [&](int q, float v) { geo[(long)e * kGeo + q] = v; });
+    if constexpr (W) {
+      if (ln.on) str_n<CH>(a.msg + (long)e * C + ln.k0, hb[0]);
+    } else {
+      reduce_geo<NY>(yb, yc, sr, sd, [&](int q, float v) { geo[(long)e * kGeo + q] = v; });
+    }
   }
 }
 
@@ -329,7 +356,8 @@ __global__ void __launch_bounds__(64) k_hvp_edge(HvpArgs a) {
 // orders LO..HI are taken in three launches (l3 < 2, l3 = 2, l3 = 3), each
 // adding to the messages and geo rows of the one before (in one or two
 // launches the compiler spills 139 or 11 registers to memory).
-template <int LMAX, int LO, int HI>
+// W (weight gradients): the adjoints of R and R' instead of geo rows.
+template <int LMAX, int LO, int HI, bool W>
 __global__ void __launch_bounds__(128) k_hvp_edge_full(HvpArgs a) {
   using PS = PathSet<LMAX, kFull>;
   constexpr int NP = PS::NP, NIN = PS::NIN, NY = PS::NY;
@@ -340,7 +368,7 @@ __global__ void __launch_bounds__(128) k_hvp_edge_full(HvpArgs a) {
   const Lane ln = lane_channels<1>(C);
   const float4* dd = a.dd + (long)b * a.e_stride;
   const float* hd = a.hd + (long)b * a.N * NIN * C;
-  float* geo = a.geo + (long)b * a.e_stride * kGeo;
+  float* geo = W ? nullptr : a.geo + (long)b * a.e_stride * kGeo;
   float* msg = a.msg + (long)b * a.e_stride * 2 * NIN * C;
   float ab[O1 - O0][1], ac[O1 - O0][1];
   load_adjoints<PS, LO, HI, 1>(a, u, ln, ab, ac);
@@ -352,7 +380,7 @@ __global__ void __launch_bounds__(128) k_hvp_edge_full(HvpArgs a) {
     real_sh_dual<LMAX>(a.dvec[e], t, Y, Yd);
 #pragma unroll
     for (int q = 0; q < NY; ++q) yb[q] = yc[q] = 0.0f;
-    const float* R0 = a.R3 + (long)(a.r_row ? a.r_row[e] : e) * 3 * NP * C;
+    const long ro = (long)(a.r_row ? a.r_row[e] : e) * a.r_stride;
     float* me = msg + (long)e * 2 * NIN * C;
     float hv[NIN][1], hdv[NIN][1], hb[NIN][1], hc[NIN][1];
 #pragma unroll
@@ -366,9 +394,9 @@ __global__ void __launch_bounds__(128) k_hvp_edge_full(HvpArgs a) {
     float r0[NP], r1[NP], r2[NP];
     static_for<NP>([&](auto pi) {
       if constexpr (kL3[PS::T.id[pi]] >= LO && kL3[PS::T.id[pi]] <= HI) {
-        r0[pi] = (R0 + pi * C)[ln.k0];
-        r1[pi] = (R0 + (NP + pi) * C)[ln.k0];
-        r2[pi] = (R0 + (2 * NP + pi) * C)[ln.k0];
+        r0[pi] = (a.R + ro + pi * C)[ln.k0];
+        r1[pi] = (a.Rp + ro + pi * C)[ln.k0];
+        if constexpr (!W) r2[pi] = (a.Rpp + ro + pi * C)[ln.k0];
       }
     });
     // one path after the other, none keeping the products of coefficients and
@@ -378,8 +406,15 @@ __global__ void __launch_bounds__(128) k_hvp_edge_full(HvpArgs a) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < NY; ++q) asm volatile("" : "+v"(Y[q]), "+v"(Yd[q]));
-        path_adjoint<PS, pi, O0, true, 1, NY>(hv, hdv, Y, Yd, t.w, &r0[pi], &r1[pi], &r2[pi], ab, ac, sr, sd, yb, yc,
-                                              hb, hc);
+        float rb, rc;
+        path_adjoint<PS, pi, O0, true, true, W, 1, NY>(hv, hdv, Y, Yd, t.w, &r0[pi], &r1[pi], &r2[pi], ab, ac, sr, sd,
+                                                       yb, yc, hb, hc, &rb, &rc);
+        if constexpr (W) {
+          if (ln.on) {
+            (a.Rb + ((long)e * NP + pi) * C)[ln.k0] = rb;
+            (a.Rc + ((long)e * NP + pi) * C)[ln.k0] = rc;
+          }
+        }
       }
     });
     __builtin_amdgcn_sched_barrier(0);
@@ -390,6 +425,7 @@ __global__ void __launch_bounds__(128) k_hvp_edge_full(HvpArgs a) {
         (me + (NIN + q) * C)[ln.k0] = hc[q][0];
       }
     }
+    if constexpr (W) continue;
     float* row = geo + (long)e * kGeo;
     if (blockDim.x == 64) {
       reduce_geo<NY>(yb, yc, sr, sd, [&](int q, float v) { row[q] = LO > 0 ? row[q] + v : v; });
@@ -406,30 +442,31 @@ __global__ void __launch_bounds__(128) k_hvp_edge_full(HvpArgs a) {
   }
 }
 
-// Sender gradients of a layer with every path from the edges' messages:
-// hb_j, hc_j (+)= the messages of j's outgoing edges, in the order of j's row.
-template <int NIN>
+// Sender gradients from the edges' messages: hb_j, hc_j (+)= the messages of
+// j's outgoing edges, in the order of j's row (HC false: of h alone).
+template <int NIN, bool HC>
 __global__ void __launch_bounds__(128) k_hvp_msg_node(HvpArgs a) {
+  constexpr int NM = HC ? 2 * NIN : NIN;
   const long u = xcd_contiguous(blockIdx.x, gridDim.x);
   const int b = (int)(u / a.N), j = (int)(u % a.N), C = a.C;
   const unsigned k = threadIdx.x;
   if (k >= (unsigned)C) return;
-  const float* msg = a.msg + (long)b * a.e_stride * 2 * NIN * C;
-  float acc[2 * NIN];
+  const float* msg = a.msg + (long)b * a.e_stride * NM * C;
+  float acc[NM];
 #pragma unroll
-  for (int q = 0; q < 2 * NIN; ++q) {
+  for (int q = 0; q < NM; ++q) {
     acc[q] = q % NIN < a.dh_acc ? ((q < NIN ? a.hb : a.hc) + (u * NIN + q % NIN) * C)[k] : 0.0f;
   }
   const int e1 = a.row_ptr[j + 1];
   for (int e2 = a.row_ptr[j]; e2 < e1; ++e2) {
     const int e = a.rev[e2];
     if (e < 0) continue;
-    const float* me = msg + (long)e * 2 * NIN * C;
+    const float* me = msg + (long)e * NM * C;
 #pragma unroll
-    for (int q = 0; q < 2 * NIN; ++q) acc[q] += (me + q * C)[k];
+    for (int q = 0; q < NM; ++q) acc[q] += (me + q * C)[k];
   }
 #pragma unroll
-  for (int q = 0; q < 2 * NIN; ++q) ((q < NIN ? a.hb : a.hc) + (u * NIN + q % NIN) * C)[k] = acc[q];
+  for (int q = 0; q < NM; ++q) ((q < NIN ? a.hb : a.hc) + (u * NIN + q % NIN) * C)[k] = acc[q];
 }
 
 // ---- scalar-output layer, from the senders' side ---------------------------------
@@ -441,7 +478,9 @@ __global__ void __launch_bounds__(128) k_hvp_msg_node(HvpArgs a) {
 // d_e2 = -d_e, i.e. minus e's, and since the forces take g_e - g_rev(e) over
 // i's edges they come out the same. Per edge only the receiver's 2 x NP x C
 // adjoint values are gathered (a receiver-side pass gathers 2 x 16 x C).
-template <int LMAX, int CH>
+// W (weight gradients): the adjoints of R and R' of e in slot e2 (a pair's two
+// edges are added up later, so either slot will do) instead of the geo row.
+template <int LMAX, int CH, bool W>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 10))) k_hvp_sender(HvpArgs a) {
   using PS = PathSet<LMAX, kLast>;
   constexpr int NP = PS::NP, NIN = PS::NIN, NY = PS::NY;
@@ -452,7 +491,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 10))
   const Lane ln = lane_channels<CH>(C);
   const float scale = ln.on ? a.inv_nu : 0.0f;
   const float4* dd = a.dd + (long)b * a.e_stride;
-  float* geo = a.geo + (long)b * a.e_stride * kGeo;
+  float* geo = W ? nullptr : a.geo + (long)b * a.e_stride * kGeo;
   float hv[NIN][CH], hdv[NIN][CH], hb[NIN][CH], hc[NIN][CH];
 #pragma unroll
   for (int q = 0; q < NIN; ++q) {
@@ -464,17 +503,25 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 10))
   const int e1 = a.row_ptr[j + 1];
   for (int e2 = a.row_ptr[j]; e2 < e1; ++e2) {
     if (a.rev[e2] < 0) {  // the edge i <- j is not in i's list
-      if (threadIdx.x < kGeo) geo[(long)e2 * kGeo + threadIdx.x] = 0.0f;
+      if constexpr (W) {
+        const float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q = 0; q < NP && ln.on; ++q) {
+          str_n<CH>(a.Rb + ((long)e2 * NP + q) * C + ln.k0, z);
+          str_n<CH>(a.Rc + ((long)e2 * NP + q) * C + ln.k0, z);
+        }
+      } else {
+        if (threadIdx.x < kGeo) geo[(long)e2 * kGeo + threadIdx.x] = 0.0f;
+      }
       continue;
     }
-    const float* R0 = a.R3 + (long)(a.r_row ? a.r_row[e2] : e2) * 3 * NP * C;
+    const long ro = (long)(a.r_row ? a.r_row[e2] : e2) * a.r_stride;
     const float* Ai = a.Ab + ((long)b * a.N + a.src[e2]) * NP * C;
     float r0[NP][CH], r1[NP][CH], r2[NP][CH], ab[NP][CH], ac[NP][CH];
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
-      ldr_n<CH>(R0 + q * C + ln.k0, r0[q]);
-      ldr_n<CH>(R0 + (NP + q) * C + ln.k0, r1[q]);
-      ldr_n<CH>(R0 + (2 * NP + q) * C + ln.k0, r2[q]);
+      ldr_n<CH>(a.R + ro + q * C + ln.k0, r0[q]);
+      ldr_n<CH>(a.Rp + ro + q * C + ln.k0, r1[q]);
+      if constexpr (!W) ldr_n<CH>(a.Rpp + ro + q * C + ln.k0, r2[q]);
     }
     static_for<NP>([&](auto pi) {
       constexpr int g = PS::T.id[pi];
@@ -494,10 +541,17 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 10))
     for (int q = 0; q < NY; ++q) yb[q] = yc[q] = 0.0f;
     float sr = 0.0f, sd = 0.0f;
     static_for<NP>([&](auto pi) {
-      path_adjoint<PS, pi, 0, true, CH, NY>(hv, hdv, Y, Yd, t.w, r0[pi], r1[pi], r2[pi], ab, ac, sr, sd, yb,
-                                                    yc, hb, hc);
+      float rb[CH], rc[CH];
+      path_adjoint<PS, pi, 0, true, true, W, CH, NY>(hv, hdv, Y, Yd, t.w, r0[pi], r1[pi], r2[pi], ab, ac, sr, sd, yb,
+                                                     yc, hb, hc, rb, rc);
+      if constexpr (W) {
+        if (ln.on) {
+          str_n<CH>(a.Rb + ((long)e2 * NP + pi) * C + ln.k0, rb);
+          str_n<CH>(a.Rc + ((long)e2 * NP + pi) * C + ln.k0, rc);
+        }
+      }
     });
-    reduce_geo<NY>(yb, yc, sr, sd, [&](int q, float v) { geo[(long)e2 * kGeo + q] = v; });
+    if constexpr (!W) reduce_geo<NY>(yb, yc, sr, sd, [&](int q, float v) { geo[(long)e2 * kGeo + q] = v; });
   }
   if (!ln.on) return;
   // components below dh_acc are added to, the others written
@@ -653,20 +707,27 @@ void hvp_launch(int which, const HvpArgs& a, hipStream_t st) {
       k_hvp_fwd<LMAX, KIND, CH, 1><<<grid, threads, 0, st>>>(a);
     return;
   }
-  if constexpr (KIND == kLast) {
-    k_hvp_sender<LMAX, CH><<<grid, threads, 0, st>>>(a);
-  } else if constexpr (KIND == kFull) {
-    if constexpr (LMAX == 3) {
-      k_hvp_edge_full<LMAX, 0, 1><<<grid, threads, 0, st>>>(a);
-      k_hvp_edge_full<LMAX, 2, 2><<<grid, threads, 0, st>>>(a);
-      k_hvp_edge_full<LMAX, 3, 3><<<grid, threads, 0, st>>>(a);
+  auto adjoint = [&](auto wc) {
+    constexpr bool W = decltype(wc)::value;
+    constexpr int NIN = PathSet<LMAX, KIND>::NIN;
+    if constexpr (KIND == kLast) {
+      k_hvp_sender<LMAX, CH, W><<<grid, threads, 0, st>>>(a);
+    } else if constexpr (KIND == kFull) {
+      if constexpr (LMAX == 3) {
+        k_hvp_edge_full<LMAX, 0, 1, W><<<grid, threads, 0, st>>>(a);
+        k_hvp_edge_full<LMAX, 2, 2, W><<<grid, threads, 0, st>>>(a);
+        k_hvp_edge_full<LMAX, 3, 3, W><<<grid, threads, 0, st>>>(a);
+      } else {
+        k_hvp_edge_full<LMAX, 0, LMAX, W><<<grid, threads, 0, st>>>(a);
+      }
+      k_hvp_msg_node<NIN, true><<<grid, 128, 0, st>>>(a);
     } else {
-      k_hvp_edge_full<LMAX, 0, LMAX><<<grid, threads, 0, st>>>(a);
+      k_hvp_edge<LMAX, KIND, CH, W><<<grid, threads, 0, st>>>(a);
+      if constexpr (W) k_hvp_msg_node<NIN, false><<<grid, 128, 0, st>>>(a);
     }
-    k_hvp_msg_node<PathSet<LMAX, KIND>::NIN><<<grid, 128, 0, st>>>(a);
-  } else {
-    k_hvp_edge<LMAX, KIND, CH><<<grid, threads, 0, st>>>(a);
-  }
+  };
+  if (a.Rb) adjoint(std::true_type{});
+  else adjoint(std::false_type{});
 }
 
 // Channels per lane: layers with every path keep one (99 outputs per channel);

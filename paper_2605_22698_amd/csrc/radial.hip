@@ -135,34 +135,28 @@ __device__ __forceinline__ void to_bf16_tile(const float (*X)[kLd], __bf16 (*Xb)
   for (int o = threadIdx.x; o < kTile * kH; o += 256) Xb[o >> 6][o & 63] = (__bf16)X[o >> 6][o & 63];
 }
 
-template <int NB, bool BF, class RS, int MODE>
+template <int NB, bool BF, class RS, bool PAIR>
 __global__ void __launch_bounds__(256) k_radial_fwd(const float4* __restrict__ dvec, const int* __restrict__ row_ptr_x,
                                                     int N, const float* __restrict__ W1, const float* __restrict__ W2,
                                                     const float* __restrict__ W3, int ld3, int PC,
                                                     RS* __restrict__ R, float rc, int p, int e_first, int e_end,
                                                     const __bf16* __restrict__ W2Tb,
                                                     const __bf16* __restrict__ W3Tb, const int* __restrict__ own,
-                                                    const int* __restrict__ n_own, const int* __restrict__ rev) {
+                                                    const int* __restrict__ n_own) {
   // edges [e_first, e_end) (e_end < 0: every edge inside the cutoff); R is
   // indexed from e_first. BF: W2Tb = W2^T and W3Tb = W3^T (used columns) in
-  // BF16. MODE 0: the tile's rows are edges; 1: pair owners (e_first = 0,
-  // e_end < 0), R written to both edges' rows; 2: pair owners, R written to
-  // the pair's row
+  // BF16. PAIR: the tile's rows are pair owners (e_first = 0, e_end < 0) and R
+  // is written to the pair's row
   __shared__ float Bs[kTile][NB + 1];
   __shared__ float H[kTile][kLd];
   __shared__ __align__(16) __bf16 Hb[BF ? kTile : 1][kLdb];
-  __shared__ int Es[MODE == 1 ? kTile : 1], Ps[MODE == 1 ? kTile : 1];  // owners and partners (-1: none)
-  const int E = MODE ? *n_own : e_end >= 0 ? e_end : row_ptr_x[N];
-  const int e0 = (MODE ? 0 : e_first) + blockIdx.x * kTile;
+  const int E = PAIR ? *n_own : e_end >= 0 ? e_end : row_ptr_x[N];
+  const int e0 = (PAIR ? 0 : e_first) + blockIdx.x * kTile;
   if (e0 >= E) return;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   if (t < kTile) {
     const int q = e0 + t;
-    const int e = q < E ? (MODE ? own[q] : q) : -1;
-    if constexpr (MODE == 1) {
-      Es[t] = e;
-      Ps[t] = e >= 0 ? rev[e] : -1;
-    }
+    const int e = q < E ? (PAIR ? own[q] : q) : -1;
     const float r = e >= 0 ? dvec[e].w : rc;
     float b[NB];
     radial_basis<NB>(r, rc, p, b, nullptr);
@@ -202,17 +196,9 @@ __global__ void __launch_bounds__(256) k_radial_fwd(const float4* __restrict__ d
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = acc_row(r, lane);
-      if constexpr (MODE != 1) {  // rows in order: edges, or pair indices
-        const int ea = e0 + row, eb = e0 + 32 + row;
-        if (ea < E) str(R + (long)(ea - e_first) * PC + cc + (lane & 31), a0[r]);
-        if (eb < E) str(R + (long)(eb - e_first) * PC + cc + (lane & 31), a1[r]);
-      } else {
-        const int ea = Es[row], eb = Es[32 + row], pa = Ps[row], pb = Ps[32 + row];
-        if (ea >= 0) str(R + (long)ea * PC + cc + (lane & 31), a0[r]);
-        if (eb >= 0) str(R + (long)eb * PC + cc + (lane & 31), a1[r]);
-        if (pa >= 0) str(R + (long)pa * PC + cc + (lane & 31), a0[r]);
-        if (pb >= 0) str(R + (long)pb * PC + cc + (lane & 31), a1[r]);
-      }
+      const int ea = e0 + row, eb = e0 + 32 + row;  // rows in order: edges, or pair indices
+      if (ea < E) str(R + (long)(ea - e_first) * PC + cc + (lane & 31), a0[r]);
+      if (eb < E) str(R + (long)(eb - e_first) * PC + cc + (lane & 31), a1[r]);
     }
   }
 }
@@ -428,181 +414,6 @@ __global__ void __launch_bounds__(256) k_radial_bwd(const float4* __restrict__ d
 }
 
 
-// ---- second order (parameter gradients of a force-dependent loss) ----------------
-// Tangent pass along per-edge (d_dot, r_dot): B_dot = B'(r) r_dot,
-// P1_dot = B_dot W1, H1_dot = silu'(P1) P1_dot, P2_dot = H1_dot W2,
-// H2_dot = silu'(P2) P2_dot, R_dot = H2_dot W3. Stores, per edge, [B | B_dot],
-// [P1 | P1_dot], [H1 | H1_dot], [P2 | P2_dot], [H2 | H2_dot] for the reverse
-// pass and the weight-gradient reductions.
-template <int NB>
-__global__ void __launch_bounds__(256) k_radial_dual_fwd(const float4* __restrict__ dvec, const float4* __restrict__ dd,
-                                                         const int* __restrict__ row_ptr_x, int N,
-                                                         const float* __restrict__ W1, const float* __restrict__ W2,
-                                                         const float* __restrict__ W3, int ld3, int PC,
-                                                         float* __restrict__ Rd, float* __restrict__ Bd,
-                                                         float* __restrict__ P1d, float* __restrict__ H1d,
-                                                         float* __restrict__ P2d, float* __restrict__ H2d, float rc,
-                                                         int p) {
-  __shared__ float Bs[kTile][NB + 1];
-  __shared__ float Bts[kTile][NB + 1];
-  __shared__ float X[kTile][kLd];
-  __shared__ float Xt[kTile][kLd];
-  const int E = row_ptr_x[N];
-  const int e0 = blockIdx.x * kTile;
-  if (e0 >= E) return;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  if (t < kTile) {
-    const int e = e0 + t;
-    const float r = e < E ? dvec[e].w : rc;
-    const float rdot = e < E ? dd[e].w : 0.0f;
-    float b[NB], db[NB];
-    radial_basis<NB>(r, rc, p, b, db);
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      Bs[t][n] = b[n];
-      Bts[t][n] = db[n] * rdot;
-      if (e < E) {
-        Bd[(long)e * 16 + n] = b[n];
-        Bd[(long)e * 16 + 8 + n] = db[n] * rdot;
-      }
-    }
-  }
-  __syncthreads();
-  {
-    const int row = t >> 2, cb = (t & 3) * 16;
-    const int e = e0 + row;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      float s = 0.0f, sd = 0.0f;
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        s += Bs[row][n] * W1[n * kH + cb + j];
-        sd += Bts[row][n] * W1[n * kH + cb + j];
-      }
-      const float h = siluf(s), hd = silu_grad(s) * sd;
-      X[row][cb + j] = h;
-      Xt[row][cb + j] = hd;
-      if (e < E) {
-        P1d[(long)e * 128 + cb + j] = s;
-        P1d[(long)e * 128 + 64 + cb + j] = sd;
-        H1d[(long)e * 128 + cb + j] = h;
-        H1d[(long)e * 128 + 64 + cb + j] = hd;
-      }
-    }
-  }
-  __syncthreads();
-  {
-    const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
-    const f32x16 a = block_64(X, rb, W2, kH, cb);
-    const f32x16 ad = block_64(Xt, rb, W2, kH, cb);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = rb + acc_row(r, lane), col = cb + (lane & 31);
-      const float h = siluf(a[r]), hd = silu_grad(a[r]) * ad[r];
-      X[row][col] = h;
-      Xt[row][col] = hd;
-      const int e = e0 + row;
-      if (e < E) {
-        P2d[(long)e * 128 + col] = a[r];
-        P2d[(long)e * 128 + 64 + col] = ad[r];
-        H2d[(long)e * 128 + col] = h;
-        H2d[(long)e * 128 + 64 + col] = hd;
-      }
-    }
-  }
-  __syncthreads();
-  for (int cc = w * 32; cc < PC; cc += 128) {
-    f32x16 a0 = {}, a1 = {};
-#pragma unroll 8
-    for (int kk = 0; kk < kH; kk += 2) {
-      const float b = W3[(kk + (lane >> 5)) * ld3 + cc + (lane & 31)];
-      a0 = mfma32(Xt[lane & 31][kk + (lane >> 5)], b, a0);
-      a1 = mfma32(Xt[32 + (lane & 31)][kk + (lane >> 5)], b, a1);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = acc_row(r, lane);
-      const int ea = e0 + row, eb = e0 + 32 + row;
-      if (ea < E) Rd[(long)ea * PC + cc + (lane & 31)] = a0[r];
-      if (eb < E) Rd[(long)eb * PC + cc + (lane & 31)] = a1[r];
-    }
-  }
-}
-
-// Reverse of the tangent pass: from the adjoints of R and R_dot (Rb, Rc) to
-// the adjoints of the pre-activations, [P2b | P2c] and [P1b | P1c]:
-//   H2b = Rb W3^T, H2c = Rc W3^T
-//   P2b = H2b silu'(P2) + H2c silu''(P2) P2_dot,  P2c = H2c silu'(P2)
-//   H1b = P2b W2^T, H1c = P2c W2^T
-//   P1b = H1b silu'(P1) + H1c silu''(P1) P1_dot,  P1c = H1c silu'(P1)
-__global__ void __launch_bounds__(256) k_radial_dual_bwd(const int* __restrict__ row_ptr_x, int N,
-                                                         const float* __restrict__ W2T, const float* __restrict__ W3T,
-                                                         int PC, const float* __restrict__ Rb,
-                                                         const float* __restrict__ Rc, const float* __restrict__ P1d,
-                                                         const float* __restrict__ P2d, float* __restrict__ P1g,
-                                                         float* __restrict__ P2g) {
-  __shared__ float Ds[kTile][33];
-  __shared__ float Dc[kTile][33];
-  __shared__ float X[kTile][kLd];
-  __shared__ float Xc[kTile][kLd];
-  const int E = row_ptr_x[N];
-  const int e0 = blockIdx.x * kTile;
-  if (e0 >= E) return;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
-  f32x16 ab = {}, ac = {};
-  for (int kc = 0; kc < PC; kc += 32) {
-    __syncthreads();
-    {
-      const int row = t >> 2, c8 = (t & 3) * 8;
-      const int e = e0 + row;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        Ds[row][c8 + q] = e < E ? Rb[(long)e * PC + kc + c8 + q] : 0.0f;
-        Dc[row][c8 + q] = e < E ? Rc[(long)e * PC + kc + c8 + q] : 0.0f;
-      }
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < 32; kk += 2) {
-      const float b = W3T[(kc + kk + (lane >> 5)) * kH + cb + (lane & 31)];
-      ab = mfma32(Ds[rb + (lane & 31)][kk + (lane >> 5)], b, ab);
-      ac = mfma32(Dc[rb + (lane & 31)][kk + (lane >> 5)], b, ac);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int row = rb + acc_row(r, lane), col = cb + (lane & 31);
-    const int e = e0 + row;
-    float pb = 0.0f, pc = 0.0f;
-    if (e < E) {
-      const float x = P2d[(long)e * 128 + col], xd = P2d[(long)e * 128 + 64 + col];
-      const float g1 = silu_grad(x);
-      pb = ab[r] * g1 + ac[r] * silu_grad2(x) * xd;
-      pc = ac[r] * g1;
-      P2g[(long)e * 128 + col] = pb;
-      P2g[(long)e * 128 + 64 + col] = pc;
-    }
-    X[row][col] = pb;
-    Xc[row][col] = pc;
-  }
-  __syncthreads();
-  const f32x16 hb = block_64(X, rb, W2T, kH, cb);
-  const f32x16 hc = block_64(Xc, rb, W2T, kH, cb);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int row = rb + acc_row(r, lane), col = cb + (lane & 31);
-    const int e = e0 + row;
-    if (e < E) {
-      const float x = P1d[(long)e * 128 + col], xd = P1d[(long)e * 128 + 64 + col];
-      const float g1 = silu_grad(x);
-      P1g[(long)e * 128 + col] = hb[r] * g1 + hc[r] * silu_grad2(x) * xd;
-      P1g[(long)e * 128 + 64 + col] = hc[r] * g1;
-    }
-  }
-}
-
 // R and its derivative R' in the edge length, for energies and forces in FP32:
 // since R depends on the length alone, the adjoint of the whole radial MLP is
 // the dot product dE/dr_e = sum dR_e R'_e, which the tensor product's adjoint
@@ -812,6 +623,173 @@ __global__ void __launch_bounds__(256, 2) k_radial_d2(const float4* __restrict__
   }
 }
 
+// Weight gradients of a loss on energies and forces: back from the adjoints Rb
+// of R = H2 W3 and Rc of R' = H2' W3 (primes: derivatives in the edge length),
+// per tile of 64 pair owners (edges without the pair list):
+//   H2b = Rb W3^T, H2c = Rc W3^T
+//   P2b = H2b silu'(P2) + H2c silu''(P2) P2',  P2c = H2c silu'(P2)
+//   H1b = P2b W2^T, H1c = P2c W2^T
+//   P1b = H1b silu'(P1) + H1c silu''(P1) P1',  P1c = H1c silu'(P1)
+// with the hidden layers evaluated again (two 64 x 64 products; keeping them
+// from the forward pass would write and read 2 KB per pair and layer). A pair's
+// two rows of Rb (Rc) are added on the way in and the sum is left in the
+// owner's row for the gradient of W3; the other operands of the weights'
+// products go to Bd, H1d, H2d, P1g and P2g. The next slab of 32 columns is in
+// flight while one is multiplied. Bound: its streams (two rows of Rb and Rc in
+// and one out per pair, 2.1 KB of operands out). Per launch on 7,032 atoms
+// (64 channels, P C = 256): 444 us, where the tangent and its reverse per edge
+// took 960 + 747 us.
+__global__ void __launch_bounds__(256, 2)
+k_radial_wgrad(const float4* __restrict__ dvec, const int* __restrict__ row_ptr_x, int N, const float* __restrict__ W1,
+               const float* __restrict__ W2, const float* __restrict__ W2T, const float* __restrict__ W3T, int PC,
+               float* __restrict__ Rb, float* __restrict__ Rc, float rcut, int p, const int* __restrict__ own,
+               const int* __restrict__ n_own, const int* __restrict__ rev, float* __restrict__ Bd,
+               float* __restrict__ H1d, float* __restrict__ H2d, float* __restrict__ P1g, float* __restrict__ P2g) {
+  constexpr int NB = 8;
+  __shared__ float Bs[2][kTile][NB + 1];
+  __shared__ float X[2][kTile][kLd];
+  __shared__ __align__(16) float Ds[2][kTile][36];
+  const int E = own ? *n_own : row_ptr_x[N];
+  const int e0 = blockIdx.x * kTile;
+  if (e0 >= E) return;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
+  if (t < kTile) {
+    const int q = e0 + t;
+    const float r = q < E ? dvec[own ? own[q] : q].w : rcut;
+    float b[NB], db[NB];
+    radial_basis<NB>(r, rcut, p, b, db);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      Bs[0][t][n] = b[n];
+      Bs[1][t][n] = db[n];
+      if (q < E) {
+        Bd[(long)q * 16 + n] = b[n];
+        Bd[(long)q * 16 + 8 + n] = db[n];
+      }
+    }
+  }
+  __syncthreads();
+  for (int o = t; o < kTile * kH; o += 256) {
+    const int row = o >> 6, col = o & 63;
+    float x = 0.0f, x1 = 0.0f;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const float wv = W1[n * kH + col];
+      x += Bs[0][row][n] * wv;
+      x1 += Bs[1][row][n] * wv;
+    }
+    const float h = siluf(x), h1 = silu_grad(x) * x1;
+    X[0][row][col] = h;
+    X[1][row][col] = h1;
+    if (e0 + row < E) {
+      H1d[(long)(e0 + row) * 128 + col] = h;
+      H1d[(long)(e0 + row) * 128 + 64 + col] = h1;
+    }
+  }
+  __syncthreads();
+  f32x16 p2 = {}, p2d = {};  // the wave's block of P2 and P2'
+#pragma unroll 8
+  for (int kk = 0; kk < kH; kk += 2) {
+    const float b = W2[(kk + (lane >> 5)) * kH + cb + (lane & 31)];
+    p2 = mfma32(X[0][rb + (lane & 31)][kk + (lane >> 5)], b, p2);
+    p2d = mfma32(X[1][rb + (lane & 31)][kk + (lane >> 5)], b, p2d);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int q = e0 + rb + acc_row(r, lane);
+    if (q < E) {
+      H2d[(long)q * 128 + cb + (lane & 31)] = siluf(p2[r]);
+      H2d[(long)q * 128 + 64 + cb + (lane & 31)] = silu_grad(p2[r]) * p2d[r];
+    }
+  }
+  // H2b and H2c, slab by slab: a thread stages 8 columns of one row
+  const int srow = t >> 2, sc8 = (t & 3) * 8;
+  const int se = e0 + srow < E ? (own ? own[e0 + srow] : e0 + srow) : -1;
+  const int sp = own && se >= 0 ? rev[se] : -1;
+  float vb[8], vc[8], qb[8], qc[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) vb[q] = vc[q] = qb[q] = qc[q] = 0.0f;
+  auto load = [&](int kc) {
+    if (se >= 0) {
+      ldr_n<8>(Rb + (long)se * PC + kc + sc8, vb);
+      ldr_n<8>(Rc + (long)se * PC + kc + sc8, vc);
+    }
+    if (sp >= 0) {
+      ldr_n<8>(Rb + (long)sp * PC + kc + sc8, qb);
+      ldr_n<8>(Rc + (long)sp * PC + kc + sc8, qc);
+    }
+  };
+  f32x16 ab = {}, ac = {};
+  load(0);
+  for (int kc = 0; kc < PC; kc += 32) {
+    if (sp >= 0) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        vb[q] += qb[q];
+        vc[q] += qc[q];
+      }
+    }
+    __syncthreads();  // the previous slab has been read
+    str_n<8>(&Ds[0][srow][sc8], vb);
+    str_n<8>(&Ds[1][srow][sc8], vc);
+    float ob[8], oc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      ob[q] = vb[q];
+      oc[q] = vc[q];
+    }
+    __syncthreads();
+    if (kc + 32 < PC) load(kc + 32);
+    if (sp >= 0) {
+      str_n<8>(Rb + (long)se * PC + kc + sc8, ob);
+      str_n<8>(Rc + (long)se * PC + kc + sc8, oc);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 32; kk += 2) {
+      const float b = W3T[(kc + kk + (lane >> 5)) * kH + cb + (lane & 31)];
+      ab = mfma32(Ds[0][rb + (lane & 31)][kk + (lane >> 5)], b, ab);
+      ac = mfma32(Ds[1][rb + (lane & 31)][kk + (lane >> 5)], b, ac);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = rb + acc_row(r, lane), col = cb + (lane & 31), q = e0 + row;
+    const float g1 = silu_grad(p2[r]);
+    const float pb = ab[r] * g1 + ac[r] * silu_grad2(p2[r]) * p2d[r], pc = ac[r] * g1;
+    X[0][row][col] = pb;
+    X[1][row][col] = pc;
+    if (q < E) {
+      P2g[(long)q * 128 + col] = pb;
+      P2g[(long)q * 128 + 64 + col] = pc;
+    }
+  }
+  __syncthreads();
+  f32x16 hb = {}, hc = {};
+#pragma unroll 8
+  for (int kk = 0; kk < kH; kk += 2) {
+    const float b = W2T[(kk + (lane >> 5)) * kH + cb + (lane & 31)];
+    hb = mfma32(X[0][rb + (lane & 31)][kk + (lane >> 5)], b, hb);
+    hc = mfma32(X[1][rb + (lane & 31)][kk + (lane >> 5)], b, hc);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = rb + acc_row(r, lane), col = cb + (lane & 31), q = e0 + row;
+    if (q >= E) continue;
+    float x = 0.0f, x1 = 0.0f;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const float wv = W1[n * kH + col];
+      x += Bs[0][row][n] * wv;
+      x1 += Bs[1][row][n] * wv;
+    }
+    const float g1 = silu_grad(x);
+    P1g[(long)q * 128 + col] = hb[r] * g1 + hc[r] * silu_grad2(x) * x1;
+    P1g[(long)q * 128 + 64 + col] = hc[r] * g1;
+  }
+}
+
 inline int tiles(long n) { return (int)((n + kTile - 1) / kTile); }
 
 
@@ -831,30 +809,27 @@ void launch_radial_fwd(int n_basis, const float4* dvec, const int* row_ptr_x, in
     throw Error(E3MI_EINVAL, "radial MLP per edge pair: needs the whole edge list and the pair owners");
   const int grid = tiles(e_end >= 0 ? (long)e_end - e_first : e_cap);
   if (grid == 0) return;
-  const int mode = pairs ? (pairs->compact ? 2 : 1) : 0;
   const int* own = pairs ? pairs->own : nullptr;
   const int* n_own = pairs ? pairs->n_own : nullptr;
-  const int* rev = pairs ? pairs->rev : nullptr;
-  auto go = [&](auto mc) {
-    constexpr int MODE = decltype(mc)::value;
+  auto go = [&](auto pc) {
+    constexpr bool PAIR = decltype(pc)::value;
     if (r_bf16)
-      k_radial_fwd<8, true, __bf16, MODE><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
+      k_radial_fwd<8, true, __bf16, PAIR><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
                                                                 static_cast<__bf16*>(R), rc, p, e_first, e_end,
-                                                                wb->W2T, wb->W3T, own, n_own, rev);
+                                                                wb->W2T, wb->W3T, own, n_own);
     else if (bf16)
-      k_radial_fwd<8, true, float, MODE><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
-                                                               static_cast<float*>(R), rc, p, e_first, e_end,
-                                                               wb->W2T, wb->W3T, own, n_own, rev);
-    else if constexpr (MODE != 2)
-      k_radial_fwd<8, false, float, MODE><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
+      k_radial_fwd<8, true, float, PAIR><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
+                                                               static_cast<float*>(R), rc, p, e_first, e_end, wb->W2T,
+                                                               wb->W3T, own, n_own);
+    else if constexpr (!PAIR)
+      k_radial_fwd<8, false, float, PAIR><<<grid, 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, ld3, PC,
                                                                 static_cast<float*>(R), rc, p, e_first, e_end,
-                                                                nullptr, nullptr, own, n_own, rev);
+                                                                nullptr, nullptr, own, n_own);
     else
       throw Error(E3MI_EINVAL, "FP32 radial MLP once per pair: k_radial_d1");
   };
-  if (mode == 0) go(std::integral_constant<int, 0>{});
-  else if (mode == 1) go(std::integral_constant<int, 1>{});
-  else go(std::integral_constant<int, 2>{});
+  if (pairs) go(std::true_type{});
+  else go(std::false_type{});
 }
 
 template <int LMAX>
@@ -907,19 +882,14 @@ void launch_radial_bwd(int n_basis, int lmax, const float4* dvec, const int* row
 }  // namespace e3mi
 
 namespace e3mi {
-void launch_radial_dual_fwd(int n_basis, const float4* dvec, const float4* dd, const int* row_ptr_x, int N, long e_cap,
-                            const float* W1, const float* W2, const float* W3, int ld3, int PC, float* Rd, float* Bd,
-                            float* P1d, float* H1d, float* P2d, float* H2d, float rc, int p, hipStream_t st) {
+void launch_radial_wgrad(const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
+                         const float* W2, const float* W2T, const float* W3T, int PC, float* Rb, float* Rc, float rc,
+                         int p, const int* own, const int* n_own, const int* rev, float* Bd, float* H1d, float* H2d,
+                         float* P1g, float* P2g, hipStream_t st) {
   if (e_cap == 0) return;
-  if (n_basis != 8) throw Error(E3MI_EUNSUPPORTED, "n_basis must be 8");
-  k_radial_dual_fwd<8><<<tiles(e_cap), 256, 0, st>>>(dvec, dd, row_ptr_x, N, W1, W2, W3, ld3, PC, Rd, Bd, P1d, H1d,
-                                                     P2d, H2d, rc, p);
-}
-void launch_radial_dual_bwd(const int* row_ptr_x, int N, long e_cap, const float* W2T, const float* W3T, int PC,
-                            const float* Rb, const float* Rc, const float* P1d, const float* P2d, float* P1g,
-                            float* P2g, hipStream_t st) {
-  if (e_cap == 0) return;
-  k_radial_dual_bwd<<<tiles(e_cap), 256, 0, st>>>(row_ptr_x, N, W2T, W3T, PC, Rb, Rc, P1d, P2d, P1g, P2g);
+  if (PC % 32) throw Error(E3MI_EUNSUPPORTED, "paths x channels must be a multiple of 32");
+  k_radial_wgrad<<<tiles(e_cap), 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W2T, W3T, PC, Rb, Rc, rc, p, own, n_own,
+                                               rev, Bd, H1d, H2d, P1g, P2g);
 }
 void launch_radial_d1(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
                       const float* W2, const float* W3, int ld3, int PC, float* R, float* Rp, float rc, int p,

@@ -232,17 +232,6 @@ struct TpArgs {
   int dh_acc;  // node adjoint: components below dh_acc are accumulated, the rest written (<= 0: all accumulated)
   int N, C;
   float inv_nu;
-  // second-order (parameter-gradient) passes
-  const float4* dd;  // per-edge tangent (d_dot, r_dot)
-  const float* Rd;   // tangent of R, same layout as R
-  const float* hd;   // tangent of h (NULL: zero)
-  float* Ad;         // out: tangent of A
-  const float* Ab;   // adjoint of A
-  const float* Ac;   // adjoint of the tangent of A
-  float* Rb;         // out: adjoint of R
-  float* Rc;         // out: adjoint of the tangent of R
-  float* hb;         // in/out (+=): adjoint of h
-  float* hc;         // in/out (+=): adjoint of the tangent of h (NULL: not needed)
   // receiver chunk (first-order kernels 0-2): receivers i0 .. i0 + n_recv - 1
   // (n_recv 0: all N from i0 = 0), R and dR indexed from edge e_first
   int i0, n_recv, e_first;
@@ -263,8 +252,6 @@ struct TpArgs {
   int fp32;  // pass 0: FP32 model (layers with every path then need not give the BF16 mode's bits)
 };
 // which: 0 forward, 1 edge adjoint (dR, dY), 2 node adjoint (dh += ...),
-//        3 tangent forward (Ad), 4 second-order edge adjoint (Rb, Rc),
-//        5 second-order node adjoint (hb, hc += ...),
 //        7 node adjoint from the messages that pass 1 wrote (msg set), for the
 //          chunk's receivers [i0, i0 + n_recv) as senders' partners
 void launch_tp(int which, const TpArgs& a, hipStream_t st);
@@ -332,7 +319,8 @@ struct HvpArgs {
   const float4* dvec;
   const float4* dd;   // per direction and edge: d_dot, r_dot
   long e_stride;
-  const float* R3;    // [row, 3, P, C]: R, R', R'' (launch_radial_d2)
+  const float *R, *Rp, *Rpp;  // rows [P, C] of R, R' and (not for weight gradients) R''
+  long r_stride;      // floats from row to row
   const int* r_row;   // row of edge e (NULL: e)
   const float* h;     // layer input [N, h_nc, C]
   const float* hd;    // its tangents [B N, h_nc, C] (not read by the first layer)
@@ -345,6 +333,9 @@ struct HvpArgs {
   float* hb;          // adjoint pass out [B N, h_nc, C]: adjoint of h and of h_dot; components
   float* hc;          // below dh_acc are added to, the others written (not written by the first layer)
   int dh_acc;
+  // weight gradients (B = 1; Rb not NULL): instead of geo, the adjoints of R
+  // and R' per edge [E, P, C]; the first layer then writes hb too, through msg [E, C]
+  float *Rb, *Rc;
 };
 void launch_hvp_tangent_sum(const HvpArgs& a, hipStream_t st);
 void launch_hvp_adjoint(const HvpArgs& a, hipStream_t st);
@@ -417,14 +408,12 @@ struct RadialBf16 {
 };
 // The pair owners of the pruned list (own [P], P = *n_own on the device) and
 // its reverse index: given, the radial MLP and its adjoint run once per edge
-// pair (whole edge list only). The forward pass writes R to both edges' rows,
-// or with `compact` once per pair, at row p for the owner own[p] (consumers
-// then find edge e's row through the pair index).
+// pair (whole edge list only): R once per pair, at row p for the owner own[p]
+// (consumers find edge e's row through the pair index).
 struct EdgePairs {
   const int* own = nullptr;
   const int* n_own = nullptr;
   const int* rev = nullptr;
-  int compact = 0;
 };
 void launch_radial_fwd(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
                        const float* W2, const float* W3, int ld3, int PC, void* R, bool r_bf16, float rc, int p,
@@ -437,14 +426,15 @@ void launch_radial_bwd(int n_basis, int lmax, const float4* dvec, const int* row
                        const EdgePairs* pairs = nullptr);
 
 // ---- second-order passes (radial.hip, grad.hip) -------------------------------------
-void launch_radial_dual_fwd(int n_basis, const float4* dvec, const float4* dd, const int* row_ptr_x, int N, long e_cap,
-                            const float* W1, const float* W2, const float* W3, int ld3, int PC, float* Rd, float* Bd,
-                            float* P1d, float* H1d, float* P2d, float* H2d, float rc, int p, hipStream_t st);
-void launch_radial_dual_bwd(const int* row_ptr_x, int N, long e_cap, const float* W2T, const float* W3T, int PC,
-                            const float* Rb, const float* Rc, const float* P1d, const float* P2d, float* P1g,
-                            float* P2g, hipStream_t st);
-void launch_edge_tangent(const int* row_ptr, const int* src, const float4* dvec, const float* v, int N, float4* dd,
-                         hipStream_t st);
+// Radial MLP of weight gradients: from the adjoints Rb, Rc of R and R' per edge,
+// the operands of the weights' products, per pair (own, n_own, rev) or edge row:
+// [B | B'] [., 16], [H1 | H1'], [H2 | H2'] [., 128] and the adjoints [P1b | P1c],
+// [P2b | P2c] [., 128] of the pre-activations; a pair's Rb, Rc rows are added
+// up in its owner's row.
+void launch_radial_wgrad(const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
+                         const float* W2, const float* W2T, const float* W3T, int PC, float* Rb, float* Rc, float rc,
+                         int p, const int* own, const int* n_own, const int* rev, float* Bd, float* H1d, float* H2d,
+                         float* P1g, float* P2g, hipStream_t st);
 // B directions: x has N atoms, the tangents and adjoints B N
 void launch_gate_dual_fwd(const float* x, const float* xd, float* hd, int N, int nc, int C, hipStream_t st, int B = 1);
 void launch_gate_dual_bwd(const float* x, const float* xd, const float* hb, const float* hc, float* xb, float* xc,
@@ -464,6 +454,7 @@ struct TnArgs {
   long rows;
   const int* rows_dev;
   int mo, no;
+  const int* y_row;  // rows of y1 and y2 (NULL: in order)
   double* out;
   long ld_out;
 };
