@@ -281,9 +281,11 @@ int e3mi_model_set_r_chunk_bytes(e3mi_model* model, size_t bytes);
  * messages stay chunk-sized). Results are bitwise the same either way. */
 int e3mi_model_set_r_keep_bytes(e3mi_model* model, size_t bytes);
 
-/* Replace the weights (host FP64, same configuration and layout as at
- * creation), e.g. after an optimiser step. Synchronises the device first. */
-int e3mi_model_set_weights(e3mi_model* model, const double* weights_host, size_t n_weights);
+/* Replace the weights (FP64 in host or device memory, same configuration and
+ * layout as at creation), e.g. after an optimiser step. Synchronises the device
+ * first, and returns when the new weights are in place. ENAN, the old weights
+ * kept, when one is not finite. */
+int e3mi_model_set_weights(e3mi_model* model, const double* weights, size_t n_weights);
 
 /* Number of edges inside the model cutoff at the last energy_forces call on
  * this graph. Synchronises `stream`. */

@@ -93,9 +93,14 @@ class Model:
 
     def set_weights(self, weights) -> None:
         """Replace the weights (FP64 vector in the documented layout; any device)."""
-        w = weights.detach().to("cpu", dtype=__import__("torch").float64).contiguous().numpy() \
-            if hasattr(weights, "detach") else np.ascontiguousarray(weights, dtype=np.float64)
-        check(lib().e3mi_model_set_weights(self.handle, w.ctypes.data, w.size))
+        import torch
+        if isinstance(weights, torch.Tensor) and weights.device == self.device:
+            w = weights.detach().to(torch.float64).contiguous()
+            check(lib().e3mi_model_set_weights(self.handle, w.data_ptr(), w.numel()))
+        else:
+            w = weights.detach().to("cpu", dtype=torch.float64).contiguous().numpy() \
+                if hasattr(weights, "detach") else np.ascontiguousarray(weights, dtype=np.float64)
+            check(lib().e3mi_model_set_weights(self.handle, w.ctypes.data, w.size))
         self._uploaded = None
 
     def _use_weights(self, weights):

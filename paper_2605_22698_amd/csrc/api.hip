@@ -252,6 +252,10 @@ struct e3mi_model {
   // receiver chunks: such a layer's adjoint then reads R instead of recomputing it
   size_t r_keep_bytes = size_t(160) << 30;
   std::unique_ptr<e3mi::DevBuf> U[4], UT[4];
+  // how the flat FP64 vector becomes the tensors above
+  e3mi::FirstWeights first_w{};
+  int n_copies = 0;
+  std::unique_ptr<e3mi::DevBuf> w_copies, w_flat, w_bad;
   e3mi::Workspace ws;
   e3mi::Profiler prof;
 };
@@ -324,26 +328,6 @@ std::unique_ptr<DevBuf> upload(Allocator* a, const void* host, size_t bytes) {
   b->ensure(bytes);
   if (bytes) E3MI_HIP(hipMemcpy(b->p, host, bytes, hipMemcpyHostToDevice));
   return b;
-}
-
-std::unique_ptr<DevBuf> upload_f32(Allocator* a, const std::vector<float>& v) {
-  return upload(a, v.data(), v.size() * sizeof(float));
-}
-
-// FP32 -> BF16 bits, rounded to nearest even (finite inputs; weights are
-// checked finite on upload)
-uint16_t bf16_rne(float x) {
-  uint32_t u;
-  std::memcpy(&u, &x, sizeof(u));
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-std::vector<float> transpose(const std::vector<float>& m, int rows, int cols) {
-  std::vector<float> t((size_t)rows * cols);
-  for (int r = 0; r < rows; ++r)
-    for (int c = 0; c < cols; ++c) t[(size_t)c * rows + r] = m[(size_t)r * cols + c];
-  return t;
 }
 
 DevBuf& ensure(std::unique_ptr<DevBuf>& b, Allocator* a, size_t bytes) {
@@ -1619,128 +1603,107 @@ WeightOffsets weight_offsets(const Config& c) {
   return o;
 }
 
-// Convert the FP64 weights to FP32 device tensors (and the transposed copies
-// the adjoint GEMMs read). Buffers are reused when they exist.
-void upload_weights(e3mi_model* M, const double* wts) {
+// The device tensors of every weight and where they come from in the flat
+// vector (offsets in file order). Called once, at creation.
+std::vector<WeightCopy> plan_weights(e3mi_model* M) {
   const Config& c = M->cfg;
   Allocator* a = &M->alloc;
   const int C = c.channels, H = c.radial_hidden;
-  size_t cur = 0;
-  auto take = [&](size_t cnt) {
-    std::vector<float> v(cnt);
-    for (size_t i = 0; i < cnt; ++i) v[i] = (float)wts[cur + i];
-    cur += cnt;
-    return v;
+  const WeightOffsets off = weight_offsets(c);
+  std::vector<WeightCopy> out;
+  auto add = [&](DevBuf& b, int kind, size_t src, int rows, int cols, int ld) {
+    b.a = a;
+    b.ensure((size_t)rows * cols * (kind >= kCopyBf16 ? 2 : 4));
+    out.push_back(WeightCopy{kind, rows, cols, ld, (long)src, b.p});
   };
-  M->emb = upload_f32(a, take((size_t)c.n_species * C));
+  auto add_new = [&](std::unique_ptr<DevBuf>& b, size_t src, int n) {
+    b = std::make_unique<DevBuf>(a);
+    add(*b, kCopyF32, src, 1, n, n);
+  };
+  add_new(M->emb, off.emb, c.n_species * C);
   for (int t = 1; t <= c.layers; ++t) {
     const LayerPlan L = plan_layer(c, t);
-    if ((int)M->lw.size() < t) {
-      M->plans.push_back(L);
-      auto Wn = std::make_unique<LayerWeights>();
-      for (DevBuf* b : {&Wn->rad1, &Wn->rad2, &Wn->rad2T, &Wn->rad3, &Wn->rad3T, &Wn->rad3u, &Wn->rad2b, &Wn->rad2Tb,
-                        &Wn->rad3Tb, &Wn->rad3ub, &Wn->sym1, &Wn->sym2})
-        b->a = a;
-      for (int l = 0; l < 4; ++l)
-        Wn->mix[l].a = Wn->mixT[l].a = Wn->self_[l].a = Wn->selfT[l].a = Wn->lin[l].a = Wn->linT[l].a = a;
-      M->lw.push_back(std::move(Wn));
-    }
-    LayerWeights* W = M->lw[t - 1].get();
-    auto up = [&](DevBuf& b, const std::vector<float>& v) {
-      b.ensure(v.size() * sizeof(float));
-      E3MI_HIP(hipMemcpy(b.p, v.data(), v.size() * sizeof(float), hipMemcpyHostToDevice));
-    };
-    auto up16 = [&](DevBuf& b, const std::vector<float>& v) {
-      std::vector<uint16_t> h(v.size());
-      for (size_t k = 0; k < v.size(); ++k) h[k] = bf16_rne(v[k]);
-      b.ensure(h.size() * sizeof(uint16_t));
-      E3MI_HIP(hipMemcpy(b.p, h.data(), h.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
-    };
-    const auto r1 = take((size_t)c.n_basis * H);
-    const auto r2 = take((size_t)H * H);
-    const auto r3 = take((size_t)H * L.p_full * C);
-    up(W->rad1, r1);
-    up(W->rad2, r2);
-    up(W->rad2T, transpose(r2, H, H));
-    up(W->rad3, r3);
-    // transpose of the used columns only: [p_used C, H]
-    std::vector<float> r3t((size_t)L.p_used * C * H);
-    for (int k = 0; k < H; ++k)
-      for (int col = 0; col < L.p_used * C; ++col) r3t[(size_t)col * H + k] = r3[(size_t)k * L.p_full * C + col];
-    up(W->rad3T, r3t);
-    // the used columns alone, row-major [H, p_used C]
-    std::vector<float> r3u((size_t)H * L.p_used * C);
-    for (int k = 0; k < H; ++k)
-      for (int col = 0; col < L.p_used * C; ++col)
-        r3u[(size_t)k * L.p_used * C + col] = r3[(size_t)k * L.p_full * C + col];
-    up(W->rad3u, r3u);
-    // BF16 copies (round to nearest even, as the device's conversion does)
-    up16(W->rad2b, r2);
-    up16(W->rad2Tb, transpose(r2, H, H));
-    up16(W->rad3Tb, r3t);
-    {
-      // W3 (used columns) in slabs of 32 columns: [PC / 32][64][32]
-      const int PCu = L.p_used * C;
-      std::vector<float> r3s((size_t)H * PCu);
-      for (int q = 0; q < H; ++q)
-        for (int col = 0; col < PCu; ++col)
-          r3s[((size_t)(col / 32) * H + q) * 32 + col % 32] = r3u[(size_t)q * PCu + col];
-      up16(W->rad3ub, r3s);
-    }
-    for (int l3 = 0; l3 <= c.lmax; ++l3) {
-      const int P3 = L.p_full_l3[l3];
-      const auto m = take((size_t)P3 * C * C);
-      if (l3 <= L.l3max_used) {
-        up(W->mix[l3], m);
-        up(W->mixT[l3], transpose(m, P3 * C, C));
-      }
+    M->plans.push_back(L);
+    M->lw.push_back(std::make_unique<LayerWeights>());
+    LayerWeights& W = *M->lw.back();
+    const size_t r1 = off.rad1[t - 1], r2 = off.rad2[t - 1], r3 = off.rad3[t - 1];
+    const int PF = L.p_full * C, PU = L.p_used * C;
+    add(W.rad1, kCopyF32, r1, c.n_basis, H, H);
+    add(W.rad2, kCopyF32, r2, H, H, H);
+    add(W.rad2T, kTransposeF32, r2, H, H, H);
+    add(W.rad3, kCopyF32, r3, H, PF, PF);
+    add(W.rad3T, kTransposeF32, r3, H, PU, PF);  // used columns only
+    add(W.rad3u, kCopyF32, r3, H, PU, PF);
+    add(W.rad2b, kCopyBf16, r2, H, H, H);
+    add(W.rad2Tb, kTransposeBf16, r2, H, H, H);
+    add(W.rad3Tb, kTransposeBf16, r3, H, PU, PF);
+    add(W.rad3ub, kSlabsBf16, r3, H, PU, PF);
+    for (int l = 0; l <= L.l3max_used; ++l) {
+      add(W.mix[l], kCopyF32, off.mix[t - 1][l], L.p_full_l3[l] * C, C, C);
+      add(W.mixT[l], kTransposeF32, off.mix[t - 1][l], L.p_full_l3[l] * C, C, C);
     }
     for (int l = 0; l <= L.l1max; ++l) {
-      const auto s = take((size_t)C * C);
-      up(W->self_[l], s);
-      up(W->selfT[l], transpose(s, C, C));
+      add(W.self_[l], kCopyF32, off.self_[t - 1][l], C, C, C);
+      add(W.selfT[l], kTransposeF32, off.self_[t - 1][l], C, C, C);
     }
     if (L.n_prod) {
-      up(W->sym1, take((size_t)c.n_species * (L.lout + 1) * C));
-      up(W->sym2, take((size_t)c.n_species * L.n_prod * C));
+      add(W.sym1, kCopyF32, off.sym1[t - 1], 1, c.n_species * (L.lout + 1) * C, 0);
+      add(W.sym2, kCopyF32, off.sym2[t - 1], 1, c.n_species * L.n_prod * C, 0);
       for (int l = 0; l <= L.lout; ++l) {
-        const auto m = take((size_t)C * C);
-        up(W->lin[l], m);
-        up(W->linT[l], transpose(m, C, C));
+        add(W.lin[l], kCopyF32, off.lin[t - 1][l], C, C, C);
+        add(W.linT[l], kTransposeF32, off.lin[t - 1][l], C, C, C);
       }
     }
   }
-  M->read1 = upload_f32(a, take((size_t)C * c.readout_hidden));
-  M->read2 = upload_f32(a, take((size_t)c.readout_hidden));
-  M->e0 = upload_f32(a, take((size_t)c.n_species));
+  add_new(M->read1, off.read1, C * c.readout_hidden);
+  add_new(M->read2, off.read2, c.readout_hidden);
+  add_new(M->e0, off.e0, c.n_species);
   if (c.coulomb) {
-    M->qhead = upload_f32(a, take((size_t)C));
-    M->qbias = upload_f32(a, take((size_t)c.n_species));
+    add_new(M->qhead, off.qhead, C);
+    add_new(M->qbias, off.qbias, c.n_species);
   }
-  E3MI_REQUIRE(cur == weight_count(c), E3MI_EINVAL, "internal: weight cursor mismatch");
-  // U_l = nu^-1 (W3[:, l C + k] W_emb[s, k]) W_mix_l, rows (s, q), in FP64.
-  const WeightOffsets off = weight_offsets(c);
-  const LayerPlan L1p = plan_layer(c, 1);
-  const int S64 = c.n_species * H;
-  for (int l = 0; l <= L1p.l3max_used; ++l) {
-    std::vector<double> U((size_t)S64 * C, 0.0);
-    const double* W3 = wts + off.rad3[0];
-    const double* Wm = wts + off.mix[0][l];   // [C, C]: one path (0,l,l) per order
-    const double* We = wts + off.emb;
-    std::vector<double> V(C);
-    for (int sp = 0; sp < c.n_species; ++sp)
-      for (int q = 0; q < H; ++q) {
-        for (int k = 0; k < C; ++k) V[k] = W3[(size_t)q * L1p.p_full * C + (size_t)l * C + k] * We[(size_t)sp * C + k];
-        double* Ur = &U[((size_t)sp * H + q) * C];
-        for (int k = 0; k < C; ++k) {
-          const double v = V[k] / c.avg_neighbors;
-          for (int kp = 0; kp < C; ++kp) Ur[kp] += v * Wm[(size_t)k * C + kp];
-        }
-      }
-    std::vector<float> Uf(U.begin(), U.end());
-    M->U[l] = upload_f32(a, Uf);
-    M->UT[l] = upload_f32(a, transpose(Uf, S64, C));
+  E3MI_REQUIRE(off.total == weight_count(c), E3MI_EINVAL, "internal: weight offsets mismatch");
+  FirstWeights& f = M->first_w;
+  const LayerPlan& L1 = M->plans[0];
+  f = FirstWeights{};
+  f.C = C;
+  f.H = H;
+  f.n_species = c.n_species;
+  f.n_orders = L1.l3max_used + 1;
+  f.ld3 = L1.p_full * C;
+  f.nu = c.avg_neighbors;
+  f.emb = (long)off.emb;
+  f.rad3 = (long)off.rad3[0];
+  for (int l = 0; l < f.n_orders; ++l) {
+    const size_t bytes = sizeof(float) * c.n_species * H * C;
+    f.mix[l] = (long)off.mix[0][l];  // [C, C]: one path (0, l, l) per order
+    f.U[l] = ensure(M->U[l], a, bytes).as<float>();
+    f.UT[l] = ensure(M->UT[l], a, bytes).as<float>();
   }
+  return out;
+}
+
+// Lay the weights out on the device. wts: host or device FP64; values of a
+// device vector are checked there. Synchronous.
+void upload_weights(e3mi_model* M, const double* wts, bool on_device) {
+  Allocator* a = &M->alloc;
+  const size_t n = weight_count(M->cfg);
+  if (!M->w_copies) {
+    const std::vector<WeightCopy> copies = plan_weights(M);
+    M->n_copies = (int)copies.size();
+    M->w_copies = upload(a, copies.data(), sizeof(WeightCopy) * copies.size());
+  }
+  const double* src = wts;
+  if (!on_device) {
+    ensure(M->w_flat, a, sizeof(double) * n);
+    E3MI_HIP(hipMemcpy(M->w_flat->p, wts, sizeof(double) * n, hipMemcpyHostToDevice));
+    src = M->w_flat->as<double>();
+  }
+  int* bad = ensure(M->w_bad, a, sizeof(int)).as<int>();
+  launch_weights(src, (long)n, M->w_copies->as<WeightCopy>(), M->n_copies, M->first_w, on_device, bad, nullptr);
+  int bad_h = 0;
+  E3MI_HIP(hipMemcpy(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost));
+  E3MI_REQUIRE(!bad_h, E3MI_ENAN, "weights are not finite");
 }
 
 e3mi_model* new_model(const char* json, const double* wts, size_t n, int precision, e3mi_alloc_fn al,
@@ -1758,7 +1721,7 @@ e3mi_model* new_model(const char* json, const double* wts, size_t n, int precisi
   M->alloc.alloc = al;
   M->alloc.free_fn = fr;
   M->alloc.ctx = ctx;
-  upload_weights(M.get(), wts);
+  upload_weights(M.get(), wts, false);
   return M.release();
 }
 
@@ -2177,9 +2140,13 @@ void set_weights(e3mi_model* M, const double* wts, size_t n) {
   const Config& c = M->cfg;
   E3MI_REQUIRE(wts, E3MI_EINVAL, "weights are NULL");
   E3MI_REQUIRE(n == weight_count(c), E3MI_EINVAL, "weight count does not match the configuration");
-  for (size_t i = 0; i < n; ++i) E3MI_REQUIRE(std::isfinite(wts[i]), E3MI_ENAN, "weights are not finite");
+  hipPointerAttribute_t at{};
+  const bool on_device = hipPointerGetAttributes(&at, wts) == hipSuccess && at.type == hipMemoryTypeDevice;
+  (void)hipGetLastError();  // an ordinary host pointer is not an error
+  if (!on_device)
+    for (size_t i = 0; i < n; ++i) E3MI_REQUIRE(std::isfinite(wts[i]), E3MI_ENAN, "weights are not finite");
   E3MI_HIP(hipDeviceSynchronize());  // no kernel may still read the old weights
-  upload_weights(M, wts);
+  upload_weights(M, wts, on_device);
 }
 
 // ---- MD -----------------------------------------------------------------------------------

@@ -464,6 +464,28 @@ constexpr long kTnPartial = 16L << 20;  // floats of partial sums per group
 size_t tn_partial_floats(long mo_no_max);
 void launch_gemm_tn(const TnArgs* args, int n, float* partial, hipStream_t st);
 
+// ---- weights (weights.hip) ------------------------------------------------------------
+// A device tensor taken from a [rows, cols] block (row stride ld) at `src` of
+// the flat FP64 vector
+enum WeightLayout : int { kCopyF32, kTransposeF32, kCopyBf16, kTransposeBf16, kSlabsBf16 };
+struct WeightCopy {
+  int kind, rows, cols, ld;
+  long src;
+  void* dst;
+};
+// What U_l is formed from: offsets of W_emb, the first layer's W3 (row stride
+// ld3) and mixes, and the outputs per order
+struct FirstWeights {
+  int C, H, n_species, n_orders, ld3;
+  double nu;
+  long emb, rad3, mix[4];
+  float *U[4], *UT[4];
+};
+// *bad (device) = 1, and no weight written, when `check` finds a value of the
+// n that is not finite
+void launch_weights(const double* w, long n, const WeightCopy* copies, int n_copies, const FirstWeights& f,
+                    bool check, int* bad, hipStream_t st);
+
 // ---- species-factorised first layer (first.hip) ---------------------------------------
 // H = [H2 | H2'] [rows, 128] of the first layer, the second hidden layer and
 // its derivative in the edge length: per pair owner (own, P = *n_own on the

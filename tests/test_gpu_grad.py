@@ -207,3 +207,33 @@ def test_gradient_of_every_layer_kind(lmax, C, layers, correlation, per_edge):
     flat_o = synth.flatten_weights(cfg, grads_o)
     assert np.linalg.norm(grad - flat_o) <= 1e-4 * np.linalg.norm(flat_o)
     _per_tensor(cfg, grad, flat_o)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_weights_replaced_from_the_device(precision):
+    # a device tensor gives the bits of the host vector; a value that is not
+    # finite is refused and leaves the weights alone
+    import torch
+    import paper_2605_22698_amd as e3
+    cfg, b, _, _ = synth.differentiation_config(2, 20, 30)
+    d = device()
+    w0, w1 = (synth.flatten_weights(cfg, synth.model_weights(cfg, k)) for k in (200, 201))
+    fresh = e3.Model(cfg.to_json(), w1, precision=precision, device=d)
+    m = e3.Model(cfg.to_json(), w0, precision=precision, device=d)
+    pos = torch.tensor(b.pos, dtype=torch.float64, device=d)
+    sp = torch.tensor(b.species, dtype=torch.int32, device=d)
+
+    def evaluate(x):
+        E, F, _ = x.energy_forces(x.build_graph(b.offsets, pos, sp, b.cell, b.pbc, cfg.cutoff), pos)
+        return E.cpu().numpy(), F.cpu().numpy()
+    ref = evaluate(fresh)
+    for w in (torch.tensor(w1, device=d), torch.tensor(w1), w1):
+        m.set_weights(w0)
+        m.set_weights(w)
+        assert all(np.array_equal(a, r) for a, r in zip(evaluate(m), ref))
+    for at in (0, w0.size - 1):
+        bad = torch.tensor(w0, device=d)
+        bad[at] = float("nan")
+        with pytest.raises(e3.E3miError, match="not finite"):
+            m.set_weights(bad)
+        assert all(np.array_equal(a, r) for a, r in zip(evaluate(m), ref))
