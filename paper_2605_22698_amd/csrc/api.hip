@@ -585,13 +585,11 @@ void launch_mix(e3mi_model* M, const LayerPlan& L, LayerWeights& W, const float*
     const int P3 = L.p_used_l3[l3], g = 2 * l3 + 1;
     GemmArgs& ga = grp[n++] = GemmArgs{};
     ga.a0 = RowMap{const_cast<float*>(A) + gbase, (long)g * P3 * C, (long)P3 * C, g};
-    ga.b0 = W.mix[l3].as<float>();
-    ga.ldb0 = C;
+    ga.b0 = W.mix[l3].as<__bf16>();
     ga.k0 = P3 * C;
     if (hin && l3 <= L.l1max) {
       ga.a1 = RowMap{const_cast<float*>(hin) + (long)l3 * l3 * C, (long)L.nc_in * C, (long)C, g};
-      ga.b1 = W.self_[l3].as<float>();
-      ga.ldb1 = C;
+      ga.b1 = W.self_[l3].as<__bf16>();
       ga.k1 = C;
     }
     ga.c = RowMap{ht + (long)l3 * l3 * C, (long)out_nc * C, (long)C, g};
@@ -622,14 +620,12 @@ int launch_mix_scalar_split(e3mi_model* M, const LayerPlan& L, LayerWeights& W, 
     GemmArgs& ga = grp[n] = GemmArgs{};
     const int a_hi = std::min(ke, KA);
     ga.a0 = RowMap{const_cast<float*>(A) + std::min(kb, KA), (long)KA, (long)KA, 1};
-    ga.b0 = W.mix[0].as<float>() + (long)std::min(kb, KA) * C;
-    ga.ldb0 = C;
+    ga.b0 = W.mix[0].as<__bf16>() + fragment_at(std::min(kb, KA), 0, C);
     ga.k0 = std::max(0, a_hi - kb);
     const int s_lo = std::max(kb, KA) - KA, s_hi = ke - KA;
     if (s_hi > s_lo) {
       ga.a1 = RowMap{const_cast<float*>(hin) + s_lo, (long)L.nc_in * C, (long)C, 1};
-      ga.b1 = W.self_[0].as<float>() + (long)s_lo * C;
-      ga.ldb1 = C;
+      ga.b1 = W.self_[0].as<__bf16>() + fragment_at(s_lo, 0, C);
       ga.k1 = s_hi - s_lo;
     }
     ga.c = RowMap{part + (long)n * N * C, (long)C, (long)C, 1};
@@ -651,13 +647,11 @@ void launch_lin(e3mi_model* M, const LayerPlan& L, LayerWeights& W, const float*
     const int g = 2 * l + 1;
     GemmArgs& ga = grp[n++] = GemmArgs{};
     ga.a0 = RowMap{const_cast<float*>(B) + (long)l * l * C, (long)L.nc_out * C, (long)C, g};
-    ga.b0 = W.lin[l].as<float>();
-    ga.ldb0 = C;
+    ga.b0 = W.lin[l].as<__bf16>();
     ga.k0 = C;
     if (hin && l <= L.l1max) {
       ga.a1 = RowMap{const_cast<float*>(hin) + (long)l * l * C, (long)L.nc_in * C, (long)C, g};
-      ga.b1 = W.self_[l].as<float>();
-      ga.ldb1 = C;
+      ga.b1 = W.self_[l].as<__bf16>();
       ga.k1 = C;
     }
     ga.c = RowMap{ht + (long)l * l * C, (long)L.nc_out * C, (long)C, g};
@@ -679,8 +673,7 @@ void launch_lin_adjoint(e3mi_model* M, const LayerPlan& L, LayerWeights& W, cons
       if (which == 1 && (!dprev || l > L.l1max)) continue;
       GemmArgs& ga = grp[n++] = GemmArgs{};
       ga.a0 = RowMap{const_cast<float*>(dht) + (long)l * l * C, (long)L.nc_out * C, (long)C, g};
-      ga.b0 = which == 0 ? W.linT[l].as<float>() : W.selfT[l].as<float>();
-      ga.ldb0 = C;
+      ga.b0 = which == 0 ? W.linT[l].as<__bf16>() : W.selfT[l].as<__bf16>();
       ga.k0 = C;
       ga.c = which == 0 ? RowMap{dB + (long)l * l * C, (long)L.nc_out * C, (long)C, g}
                         : RowMap{dprev + (long)l * l * C, (long)L.nc_in * C, (long)C, g};
@@ -716,8 +709,7 @@ void launch_mix_adjoint(e3mi_model* M, const LayerPlan& L, LayerWeights& W, cons
     const int P3 = L.p_used_l3[l3], gg = 2 * l3 + 1;
     GemmArgs& ga = grp[n++] = GemmArgs{};
     ga.a0 = RowMap{const_cast<float*>(dht) + (long)l3 * l3 * C, (long)dht_nc * C, (long)C, gg};
-    ga.b0 = W.mixT[l3].as<float>();
-    ga.ldb0 = P3 * C;
+    ga.b0 = W.mixT[l3].as<__bf16>();
     ga.k0 = C;
     ga.c = RowMap{dA + gbase, (long)gg * P3 * C, (long)P3 * C, gg};
     ga.M = N * gg;
@@ -728,8 +720,7 @@ void launch_mix_adjoint(e3mi_model* M, const LayerPlan& L, LayerWeights& W, cons
     const int gg = 2 * l3 + 1;
     GemmArgs& ga = grp[n++] = GemmArgs{};
     ga.a0 = RowMap{const_cast<float*>(dht) + (long)l3 * l3 * C, (long)dht_nc * C, (long)C, gg};
-    ga.b0 = W.selfT[l3].as<float>();
-    ga.ldb0 = C;
+    ga.b0 = W.selfT[l3].as<__bf16>();
     ga.k0 = C;
     ga.c = RowMap{dprev + (long)l3 * l3 * C, (long)L.nc_in * C, (long)C, gg};
     ga.M = N * gg;
@@ -1082,13 +1073,11 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
           const int g = 2 * l3 + 1;
           GemmArgs& ga = grp[n++] = GemmArgs{};
           ga.a0 = RowMap{G1 + (long)l3 * l3 * S64, (long)L.nc_a * S64, (long)S64, g};
-          ga.b0 = M->U[l3]->as<float>();
-          ga.ldb0 = C;
+          ga.b0 = M->U[l3]->as<__bf16>();
           ga.k0 = S64;
           if (l3 == 0 && !prod) {
             ga.a1 = RowMap{const_cast<float*>(hin), (long)C, (long)C, 1};
-            ga.b1 = W.self_[0].as<float>();
-            ga.ldb1 = C;
+            ga.b1 = W.self_[0].as<__bf16>();
             ga.k1 = C;
           }
           ga.c = RowMap{mix_out + (long)l3 * l3 * C, (long)mix_nc * C, (long)C, g};
@@ -1313,8 +1302,7 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
           const int gg = 2 * l3 + 1;
           GemmArgs& ga = grp[n++] = GemmArgs{};
           ga.a0 = RowMap{const_cast<float*>(dmix) + (long)l3 * l3 * C, (long)dmix_nc * C, (long)C, gg};
-          ga.b0 = M->UT[l3]->as<float>();
-          ga.ldb0 = S64;
+          ga.b0 = M->UT[l3]->as<__bf16>();
           ga.k0 = C;
           ga.c = RowMap{dG1 + (long)l3 * l3 * S64, (long)L.nc_a * S64, (long)S64, gg};
           ga.M = N * gg;
@@ -1613,7 +1601,7 @@ std::vector<WeightCopy> plan_weights(e3mi_model* M) {
   std::vector<WeightCopy> out;
   auto add = [&](DevBuf& b, int kind, size_t src, int rows, int cols, int ld) {
     b.a = a;
-    b.ensure((size_t)rows * cols * (kind >= kCopyBf16 ? 2 : 4));
+    b.ensure((size_t)rows * cols * (kind >= kFragments ? 6 : kind >= kCopyBf16 ? 2 : 4));
     out.push_back(WeightCopy{kind, rows, cols, ld, (long)src, b.p});
   };
   auto add_new = [&](std::unique_ptr<DevBuf>& b, size_t src, int n) {
@@ -1639,19 +1627,19 @@ std::vector<WeightCopy> plan_weights(e3mi_model* M) {
     add(W.rad3Tb, kTransposeBf16, r3, H, PU, PF);
     add(W.rad3ub, kSlabsBf16, r3, H, PU, PF);
     for (int l = 0; l <= L.l3max_used; ++l) {
-      add(W.mix[l], kCopyF32, off.mix[t - 1][l], L.p_full_l3[l] * C, C, C);
-      add(W.mixT[l], kTransposeF32, off.mix[t - 1][l], L.p_full_l3[l] * C, C, C);
+      add(W.mix[l], kFragments, off.mix[t - 1][l], L.p_full_l3[l] * C, C, C);
+      add(W.mixT[l], kFragmentsT, off.mix[t - 1][l], L.p_full_l3[l] * C, C, C);
     }
     for (int l = 0; l <= L.l1max; ++l) {
-      add(W.self_[l], kCopyF32, off.self_[t - 1][l], C, C, C);
-      add(W.selfT[l], kTransposeF32, off.self_[t - 1][l], C, C, C);
+      add(W.self_[l], kFragments, off.self_[t - 1][l], C, C, C);
+      add(W.selfT[l], kFragmentsT, off.self_[t - 1][l], C, C, C);
     }
     if (L.n_prod) {
       add(W.sym1, kCopyF32, off.sym1[t - 1], 1, c.n_species * (L.lout + 1) * C, 0);
       add(W.sym2, kCopyF32, off.sym2[t - 1], 1, c.n_species * L.n_prod * C, 0);
       for (int l = 0; l <= L.lout; ++l) {
-        add(W.lin[l], kCopyF32, off.lin[t - 1][l], C, C, C);
-        add(W.linT[l], kTransposeF32, off.lin[t - 1][l], C, C, C);
+        add(W.lin[l], kFragments, off.lin[t - 1][l], C, C, C);
+        add(W.linT[l], kFragmentsT, off.lin[t - 1][l], C, C, C);
       }
     }
   }
@@ -1675,10 +1663,10 @@ std::vector<WeightCopy> plan_weights(e3mi_model* M) {
   f.emb = (long)off.emb;
   f.rad3 = (long)off.rad3[0];
   for (int l = 0; l < f.n_orders; ++l) {
-    const size_t bytes = sizeof(float) * c.n_species * H * C;
+    const size_t bytes = 3 * sizeof(__bf16) * c.n_species * H * C;
     f.mix[l] = (long)off.mix[0][l];  // [C, C]: one path (0, l, l) per order
-    f.U[l] = ensure(M->U[l], a, bytes).as<float>();
-    f.UT[l] = ensure(M->UT[l], a, bytes).as<float>();
+    f.U[l] = ensure(M->U[l], a, bytes).as<__bf16>();
+    f.UT[l] = ensure(M->UT[l], a, bytes).as<__bf16>();
   }
   return out;
 }

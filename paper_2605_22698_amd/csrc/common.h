@@ -9,6 +9,33 @@ namespace e3mi {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// v = a + b + c + O(2^-27 |v|)
+__device__ __forceinline__ void split_bf16(float v, __bf16& a, __bf16& b, __bf16& c) {
+  a = (__bf16)v;
+  v -= (float)a;
+  b = (__bf16)v;
+  c = (__bf16)(v - (float)b);
+}
+__device__ __forceinline__ void split_bf16(const float* v, bf16x8& a, bf16x8& b, bf16x8& c) {
+#pragma unroll
+  for (int q = 0; q < 8; q += 2) {
+    f32x2 r = {v[q], v[q + 1]};
+    const bf16x2 x = __builtin_convertvector(r, bf16x2);
+    r -= __builtin_convertvector(x, f32x2);
+    const bf16x2 y = __builtin_convertvector(r, bf16x2);
+    r -= __builtin_convertvector(y, f32x2);
+    const bf16x2 z = __builtin_convertvector(r, bf16x2);
+    a[q] = x[0];
+    a[q + 1] = x[1];
+    b[q] = y[0];
+    b[q + 1] = y[1];
+    c[q] = z[0];
+    c[q + 1] = z[1];
+  }
+}
 
 constexpr int kWave = 64;
 

@@ -1,6 +1,4 @@
-// Per-atom stages of the interaction:
-//   channel mix + self connection (dense contractions on the FP32 matrix cores)
-//     h~[l3] = A[l3] W[l3] + h[l3] S[l3]        rows (atom, m), columns channels
+// Per-atom stages of the interaction besides its dense contractions (gemm.hip):
 //   gate (MACE table of Appendix F: gate_nodes):
 //     h[0] = silu(h~[0]),  h[l>0] = h~[l] sigmoid(h~[0])
 //   embedding h0 = W_emb[z];  readout E_i = w2 . silu(W_r^T h[0]) + E0[z_i]
@@ -13,139 +11,6 @@
 namespace e3mi {
 
 namespace {
-
-__device__ __forceinline__ long row_off(const RowMap& m, int r) {
-  return (long)(r / m.g) * m.s_atom + (long)(r % m.g) * m.s_m;
-}
-__device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
-
-// 64x64 output tile per workgroup, each wave a 32x32 block on
-// v_mfma_f32_32x32x2f32 (FP32), or with both operands rounded to BF16 on
-// v_mfma_f32_32x32x16_bf16 (BF), FP32 accumulation. K runs over the two
-// operand pairs in slabs of 32 staged through LDS; the next slab is fetched
-// into registers while the current one is multiplied.
-constexpr int kSlab = 32;
-constexpr int kPer = kSlab / 16;  // float4 of each operand per thread and slab
-constexpr int kRowQ = kSlab / 4;  // float4 per row of an A slab
-
-struct Slab {
-  float4 a[kPer], b[kPer];
-};
-
-// Slab s of the K loop (products 0 then 1) into registers: A through the row
-// pointers of the rows this thread stages (null past M), B row-major.
-__device__ __forceinline__ void gemm_load_slab(const GemmArgs& a, const float* const* ap0, const float* const* ap1,
-                                               int s, int s0, int bn, Slab& r) {
-  const int t = threadIdx.x;
-  const int op = s >= s0;
-  const float* __restrict__ B = op ? a.b1 : a.b0;
-  const int ldb = op ? a.ldb1 : a.ldb0;
-  const int K = op ? a.k1 : a.k0;
-  const int k0 = (op ? s - s0 : s) * kSlab;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int idx = t + 256 * i;
-    const int kq = (idx % kRowQ) * 4;
-    const float* p = op ? ap1[i] : ap0[i];
-    r.a[i] = (p && k0 + kq < K) ? *reinterpret_cast<const float4*>(p + k0 + kq) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const int kr = idx >> 4, c4 = (idx & 15) * 4, gk = k0 + kr, gc = bn + c4;
-    r.b[i] = (gk < K && gc < a.Nc) ? *reinterpret_cast<const float4*>(B + (long)gk * ldb + gc)
-                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-}
-
-// Independent products of one group share a launch: workgroup b (after the
-// XCD-contiguous remapping, so that the column blocks of a row tile and
-// neighbouring row tiles meet in one L2) takes tile b - tile0[k] of product k,
-// column blocks fastest.
-struct GemmGroup {
-  GemmArgs g[kMaxGemmGroup];
-  int tile0[kMaxGemmGroup + 1];
-  int ncb[kMaxGemmGroup];
-  int n;
-};
-
-template <bool BF>
-__global__ void __launch_bounds__(256) k_gemm(GemmGroup gg) {
-  __shared__ float As[64][kSlab + 1];
-  __shared__ float Bs[kSlab][65];
-  __shared__ long coff[64];  // offsets of the tile's output rows (-1 past M)
-  const int b = xcd_contiguous(blockIdx.x, gridDim.x);
-  int gi = 0;
-  while (gi + 1 < gg.n && b >= gg.tile0[gi + 1]) ++gi;
-  const GemmArgs& a = gg.g[gi];
-  const int local = b - gg.tile0[gi];
-  const int bm = (local / gg.ncb[gi]) * 64, bn = (local % gg.ncb[gi]) * 64;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
-  const int s0 = (a.k0 + kSlab - 1) / kSlab, ns = s0 + (a.k1 + kSlab - 1) / kSlab;
-  // row offsets (a division by the rows per atom each) once per tile, not per slab
-  if (t < 64) {
-    const int r = bm + t;
-    coff[t] = r < a.M ? row_off(a.c, r) : -1;
-  }
-  const float* ap0[kPer];
-  const float* ap1[kPer];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int gr = bm + (t + 256 * i) / kRowQ;
-    const bool in = gr < a.M;
-    ap0[i] = in ? a.a0.base + row_off(a.a0, gr) : nullptr;
-    ap1[i] = (in && a.k1 > 0) ? a.a1.base + row_off(a.a1, gr) : nullptr;
-  }
-  f32x16 acc = {};
-  Slab cur;
-  if (ns > 0) gemm_load_slab(a, ap0, ap1, 0, s0, bn, cur);
-  else __syncthreads();
-  for (int s = 0; s < ns; ++s) {
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int idx = t + 256 * i;
-      const int row = idx / kRowQ, kq = (idx % kRowQ) * 4;
-      As[row][kq] = cur.a[i].x;
-      As[row][kq + 1] = cur.a[i].y;
-      As[row][kq + 2] = cur.a[i].z;
-      As[row][kq + 3] = cur.a[i].w;
-      const int kr = idx >> 4, c4 = (idx & 15) * 4;
-      Bs[kr][c4] = cur.b[i].x;
-      Bs[kr][c4 + 1] = cur.b[i].y;
-      Bs[kr][c4 + 2] = cur.b[i].z;
-      Bs[kr][c4 + 3] = cur.b[i].w;
-    }
-    __syncthreads();
-    if (s + 1 < ns) gemm_load_slab(a, ap0, ap1, s + 1, s0, bn, cur);
-    if constexpr (BF) {
-#pragma unroll
-      for (int kb = 0; kb < kSlab; kb += 16) {
-        const int k0 = kb + 8 * (lane >> 5);
-        bf16x8 x, y;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          x[q] = (__bf16)As[rb + (lane & 31)][k0 + q];
-          y[q] = (__bf16)Bs[k0 + q][cb + (lane & 31)];
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < kSlab; kk += 2)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[rb + (lane & 31)][kk + (lane >> 5)],
-                                                    Bs[kk + (lane >> 5)][cb + (lane & 31)], acc, 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  const int col = bn + cb + (lane & 31);
-  if (col < a.Nc) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const long o = coff[rb + acc_row(r, lane)];
-      if (o >= 0) {
-        float* p = a.c.base + o + col;
-        *p = a.accumulate ? *p + acc[r] : acc[r];
-      }
-    }
-  }
-}
 
 __global__ void k_gate_fwd(const float* __restrict__ ht, float* __restrict__ h, int N, int nc, int C) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -344,30 +209,6 @@ inline int blocks(long n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
 
-void launch_gemm(const GemmArgs& a, hipStream_t st, bool bf16) { launch_gemm_group(&a, 1, st, bf16); }
-
-void launch_gemm_group(const GemmArgs* a, int n, hipStream_t st, bool bf16) {
-  if (n < 1 || n > kMaxGemmGroup) throw Error(E3MI_EINVAL, "GEMM group size out of range");
-  GemmGroup gg{};
-  int tiles = 0, m = 0;
-  for (int k = 0; k < n; ++k) {
-    if (a[k].M == 0 || a[k].Nc == 0) continue;
-    if ((a[k].k0 % 4) || (a[k].k1 % 4) || (a[k].Nc % 4) || (a[k].ldb0 % 4) || (a[k].k1 && (a[k].ldb1 % 4)))
-      throw Error(E3MI_EUNSUPPORTED, "GEMM dimensions must be multiples of 4");
-    gg.g[m] = a[k];
-    gg.tile0[m] = tiles;
-    gg.ncb[m] = (int)blocks(a[k].Nc, 64);
-    tiles += (int)blocks(a[k].M, 64) * gg.ncb[m];
-    ++m;
-  }
-  if (m == 0) return;
-  gg.tile0[m] = tiles;
-  gg.n = m;
-  if (bf16)
-    k_gemm<true><<<tiles, 256, 0, st>>>(gg);
-  else
-    k_gemm<false><<<tiles, 256, 0, st>>>(gg);
-}
 void launch_gate_fwd(const float* ht, float* h, int N, int nc, int C, hipStream_t st) {
   if (N == 0) return;
   k_gate_fwd<<<blocks((long)N * C, 256), 256, 0, st>>>(ht, h, N, nc, C);

@@ -272,18 +272,18 @@ struct RowMap {
   long s_m;
   int g;
 };
-// C[M x Nc] (+)= A0[M x k0] B0[k0 x Nc] + A1[M x k1] B1[k1 x Nc]; B row-major.
+// C[M x Nc] = A0[M x k0] B0[k0 x Nc] + A1[M x k1] B1[k1 x Nc]; k0, k1 and Nc
+// multiples of 32, the weights B laid out by kFragments
 struct GemmArgs {
   RowMap a0;
-  const float* b0;
-  int ldb0, k0;
+  const __bf16* b0;
+  int k0;
   RowMap a1;  // optional second product (k1 = 0: none)
-  const float* b1;
-  int ldb1, k1;
+  const __bf16* b1;
+  int k1;
   RowMap c;
-  int M, Nc, accumulate;
+  int M, Nc;
 };
-void launch_gemm(const GemmArgs& a, hipStream_t st, bool bf16 = false);
 // Up to kMaxGemmGroup independent products (no output read or written by
 // another of the group) in one launch. With l_max <= 3 a layer's groups hold
 // at most 4 + 4 products (one per output order, plus the self connection's).
@@ -467,7 +467,13 @@ void launch_gemm_tn(const TnArgs* args, int n, float* partial, hipStream_t st);
 // ---- weights (weights.hip) ------------------------------------------------------------
 // A device tensor taken from a [rows, cols] block (row stride ld) at `src` of
 // the flat FP64 vector
-enum WeightLayout : int { kCopyF32, kTransposeF32, kCopyBf16, kTransposeBf16, kSlabsBf16 };
+enum WeightLayout : int { kCopyF32, kTransposeF32, kCopyBf16, kTransposeBf16, kSlabsBf16, kFragments, kFragmentsT };
+// kFragments(T): the matrix B (its transpose) as operands of the BF16 matrix
+// cores, split into three BF16 parts that add up to the FP32 value (gemm.hip):
+// element (k, c) at fragment_at(k, c, columns), its parts 512 apart
+__host__ __device__ constexpr long fragment_at(int k, int c, int cols) {
+  return ((long)(k / 16) * (cols / 32) + c / 32) * 1536 + ((k % 16) / 8 * 32 + c % 32) * 8 + k % 8;
+}
 struct WeightCopy {
   int kind, rows, cols, ld;
   long src;
@@ -479,7 +485,7 @@ struct FirstWeights {
   int C, H, n_species, n_orders, ld3;
   double nu;
   long emb, rad3, mix[4];
-  float *U[4], *UT[4];
+  __bf16 *U[4], *UT[4];  // kFragments
 };
 // *bad (device) = 1, and no weight written, when `check` finds a value of the
 // n that is not finite

@@ -1,6 +1,7 @@
 // Device copies of a model's weights, laid out from the flat FP64 vector on the
 // device: the kernels' FP32 tensors, their transposes, the BF16 copies (rounded
-// to nearest even from the FP32 values) and the first layer's U_l. A training
+// to nearest even from the FP32 values), the three-part BF16 operands of the
+// per-atom contractions and the first layer's U_l. A training
 // step replaces the weights every time: laid out on the host and sent tensor by
 // tensor (41 copies, 10 M multiply-adds for U at 64 channels and 5 species) that
 // took 1.4 ms of a 6.5 ms step.
@@ -9,6 +10,13 @@
 
 namespace e3mi {
 namespace {
+
+__device__ __forceinline__ void put_fragment(__bf16* __restrict__ f, float v) {
+  __bf16 x[3];
+  split_bf16(v, x[0], x[1], x[2]);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) f[512 * p] = x[p];
+}
 
 // *bad = 1 when a value is not finite. Everything below leaves the weights
 // alone when *bad is set.
@@ -32,6 +40,8 @@ __global__ void __launch_bounds__(256) k_weights_layout(const double* __restrict
       case kTransposeF32: static_cast<float*>(c.dst)[t] = v; break;
       case kCopyBf16: static_cast<__bf16*>(c.dst)[i] = (__bf16)v; break;
       case kTransposeBf16: static_cast<__bf16*>(c.dst)[t] = (__bf16)v; break;
+      case kFragments: put_fragment(static_cast<__bf16*>(c.dst) + fragment_at(r, k, c.cols), v); break;
+      case kFragmentsT: put_fragment(static_cast<__bf16*>(c.dst) + fragment_at(k, r, c.rows), v); break;
       default:  // slabs of 32 columns
         static_cast<__bf16*>(c.dst)[((long)(k / 32) * c.rows + r) * 32 + k % 32] = (__bf16)v;
     }
@@ -53,8 +63,8 @@ __global__ void __launch_bounds__(128) k_weights_u(const double* __restrict__ w,
   double u = 0.0;
 #pragma unroll 8
   for (int j = 0; j < C; ++j) u += V[j] * Wm[(long)j * C];
-  f.U[l][(long)row * C + k] = (float)u;
-  f.UT[l][(long)k * gridDim.x + row] = (float)u;
+  put_fragment(f.U[l] + fragment_at(row, k, C), (float)u);
+  put_fragment(f.UT[l] + fragment_at(k, row, gridDim.x), (float)u);
 }
 
 }  // namespace

@@ -241,3 +241,25 @@ def test_layers_with_every_path(lmax, channels, correlation, unfactorised):
         a, z = b.offsets[s], b.offsets[s + 1]
         check_energy(E[s:s + 1], Er[s:s + 1], Eir[a:z])
     check_forces(F, Fr)
+
+
+@pytest.mark.parametrize("channels,copies,correlation", [(32, 64, 1), (64, 40, 2), (128, 20, 1)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_contractions_of_few_and_many_rows(channels, copies, correlation, bf16):
+    # the per-atom contractions take another kernel from 1,024 blocks of 32 x 32
+    # outputs on: a structure alone is below it in every one, `copies` of it are
+    # above it in the mixes (33 atoms: a last row tile of one row), with the same bits
+    cfg = synth.ModelConfig(lmax=3, channels=channels, layers=2, n_species=3, cutoff=4.0, avg_neighbors=10.0,
+                            correlation=correlation)
+    one = synth.jittered_lattice(33, 0.1, 0.3, 3, np.random.default_rng(190))
+    b = synth.concat([one] * copies)
+    m = model(cfg, 191, precision=int(bf16))
+    E1, F1, Ei1, _ = gpu_energy_forces(m, one)
+    E, F, Ei, _ = gpu_energy_forces(m, b)
+    assert np.array_equal(E, np.repeat(E1, copies))
+    assert np.array_equal(F, np.tile(F1, (copies, 1)))
+    assert np.array_equal(Ei, np.tile(Ei1, copies))
+    if not bf16:
+        Er, Fr, Eir = _oracle(cfg, 191, one)
+        check_energy(E1, Er, Eir)
+        check_forces(F1, Fr)
