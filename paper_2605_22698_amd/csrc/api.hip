@@ -191,7 +191,8 @@ inline int stage_id(Stage s, int layer = 0) { return (int)s * 8 + layer; }
 
 // ---- model -----------------------------------------------------------------------
 struct LayerWeights {
-  DevBuf rad1, rad2, rad2T, rad3, rad3T, rad3u;
+  DevBuf rad1, rad2, rad2T, rad3T, rad3u;
+  DevBuf rad2f, rad3f;                  // kFragments: the FP32 radial rows
   DevBuf rad2b, rad2Tb, rad3Tb, rad3ub;  // BF16 copies for the BF16 mode (see RadialBf16)
   RadialBf16 bf16_view() const {
     return RadialBf16{rad2Tb.as<__bf16>(), rad2b.as<__bf16>(), rad3Tb.as<__bf16>(), rad3ub.as<__bf16>()};
@@ -863,10 +864,11 @@ void radial_derivs(e3mi_model* M, e3mi_graph* G, int t, hipStream_t st) {
   LayerWeights& W = *M->lw[t - 1];
   const EdgePairs prs = graph_pairs(G);
   ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
-  launch_radial_d2(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
-                   W.rad2.as<float>(), W.rad3.as<float>(), L.p_full * c.channels, L.p_used * c.channels,
-                   M->ws.R3[t]->as<float>(), (float)c.cutoff, c.envelope_p, M->edge_pairs ? prs.own : nullptr,
-                   M->edge_pairs ? prs.n_own : nullptr, st);
+  const int PC = L.p_used * c.channels;
+  launch_radial_rows(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
+                     W.rad2f.as<__bf16>(), W.rad3f.as<__bf16>(), PC, 3, M->ws.R3[t]->as<float>(), PC, 3 * PC,
+                     (float)c.cutoff, c.envelope_p, 0, -1, M->edge_pairs ? prs.own : nullptr,
+                     M->edge_pairs ? prs.n_own : nullptr, st);
 }
 
 void set_chunk(TpArgs& ta, const RChunk& ch) {
@@ -904,19 +906,19 @@ float* rp_rows(const e3mi_model* M, int t) {
   return M->ws.R[t]->as<float>() + M->ws.r_rows[t] * M->plans[t - 1].p_used * M->cfg.channels;
 }
 
-// R and R' of layer t: every row (ch NULL) or a receiver chunk's edges
-void radial_rows(e3mi_model* M, e3mi_graph* G, int t, const RChunk* ch, hipStream_t st) {
+// R (and with `derivs` R') of layer t: every row (ch NULL) or a receiver chunk's edges
+void radial_rows(e3mi_model* M, e3mi_graph* G, int t, const RChunk* ch, bool derivs, hipStream_t st) {
   const Config& c = M->cfg;
   const LayerPlan& L = M->plans[t - 1];
   LayerWeights& W = *M->lw[t - 1];
   const EdgePairs prs = graph_pairs(G);
   const bool pairs = M->edge_pairs && !ch;
+  const int PC = L.p_used * c.channels;
   ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
-  launch_radial_d1(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
-                   W.rad2.as<float>(), W.rad3.as<float>(), L.p_full * c.channels, L.p_used * c.channels,
-                   M->ws.R[t]->as<float>(), rp_rows(M, t), (float)c.cutoff, c.envelope_p, ch ? ch->e0 : 0,
-                   ch ? ch->e1 : -1,
-                   pairs ? prs.own : nullptr, pairs ? prs.n_own : nullptr, st);
+  launch_radial_rows(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
+                     W.rad2f.as<__bf16>(), W.rad3f.as<__bf16>(), PC, derivs ? 2 : 1, M->ws.R[t]->as<float>(),
+                     rp_rows(M, t) - M->ws.R[t]->as<float>(), PC, (float)c.cutoff, c.envelope_p, ch ? ch->e0 : 0,
+                     ch ? ch->e1 : -1, pairs ? prs.own : nullptr, pairs ? prs.n_own : nullptr, st);
 }
 
 // Primal forward pass: edge selection, embedding and every layer. Leaves
@@ -1150,13 +1152,14 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
         ta.r_stride = 3 * PCu;
         ta.r_row = first_pair_index(M, G);
       } else if (rows && w.r_whole[t]) {
-        radial_rows(M, G, t, nullptr, st);
+        radial_rows(M, G, t, nullptr, true, st);
         ta.r_row = first_pair_index(M, G);
+      } else if (rows) {
+        radial_rows(M, G, t, &ch, false, st);
       } else {
         ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
-        launch_radial_fwd(c.n_basis, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(),
-                          W.rad3.as<float>(), L.p_full * C, PCu, Rc, lr_bf16, rc, p_env, bf16, st, ch.e0, ch.e1,
-                          &bfw, pairs_for(M, ch, prs));
+        launch_radial_fwd(c.n_basis, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), PCu, Rc, lr_bf16, rc, p_env, st,
+                          ch.e0, ch.e1, &bfw, pairs_for(M, ch, prs));
       }
       set_chunk(ta, ch);
       ta.R = static_cast<const float*>(Rc);
@@ -1390,7 +1393,7 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
       const std::vector<RChunk> chunks =
           whole && !use_msg ? std::vector<RChunk>{RChunk{0, N, 0, -1}} : r_chunks(M, G, PCu, st);
       for (const RChunk& ch : chunks) {
-        if (!whole) radial_rows(M, G, t, &ch, st);
+        if (!whole) radial_rows(M, G, t, &ch, true, st);
         set_chunk(ta, ch);
         if (whole) ta.r_first = 0;
         ta.tag = (int)(++w.msg_tag & 0x7fffffffu);
@@ -1424,9 +1427,8 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
       if (sender_side) {
         if (recompute) {
           ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
-          launch_radial_fwd(c.n_basis, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(),
-                            W.rad3.as<float>(), L.p_full * C, PCu, w.R[t]->p, r_bf16, rc, p_env, bf16, st, ch.e0,
-                            ch.e1, &bfw);
+          launch_radial_fwd(c.n_basis, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), PCu, w.R[t]->p, r_bf16, rc, p_env,
+                            st, ch.e0, ch.e1, &bfw);
         }
         set_chunk(ta, ch);
         TpArgs ts = ta;
@@ -1436,16 +1438,15 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
           launch_tps_sender(ts, st);
         }
         ProfScope ps(&M->prof, stage_id(kRadialBwd, t), st);
-        launch_radial_bwd(c.n_basis, c.lmax, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(),
-                          W.rad2T.as<float>(), W.rad3T.as<float>(), PCu, w.dR->p, r_bf16, w.dY->as<float>(), g,
-                          t != T ? 1 : 0, rc, p_env, bf16, st, ch.e0, ch.e1, &bfw, pairs_for(M, ch, prs));
+        launch_radial_bwd(c.n_basis, c.lmax, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), PCu, w.dR->p, r_bf16,
+                          w.dY->as<float>(), g, t != T ? 1 : 0, rc, p_env, st, ch.e0, ch.e1, &bfw,
+                          pairs_for(M, ch, prs));
         continue;
       }
       if (recompute) {
         ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
-        launch_radial_fwd(c.n_basis, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(),
-                          W.rad3.as<float>(), L.p_full * C, PCu, w.R[t]->p, r_bf16, rc, p_env, bf16, st, ch.e0,
-                          ch.e1, &bfw);
+        launch_radial_fwd(c.n_basis, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), PCu, w.R[t]->p, r_bf16, rc, p_env, st,
+                          ch.e0, ch.e1, &bfw);
       }
       set_chunk(ta, ch);
       ta.tag = (int)(++w.msg_tag & 0x7fffffffu);
@@ -1455,9 +1456,9 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
       }
       {
         ProfScope ps(&M->prof, stage_id(kRadialBwd, t), st);
-        launch_radial_bwd(c.n_basis, c.lmax, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), W.rad2.as<float>(),
-                          W.rad2T.as<float>(), W.rad3T.as<float>(), PCu, w.dR->p, r_bf16, w.dY->as<float>(), g,
-                          t != T ? 1 : 0, rc, p_env, bf16, st, ch.e0, ch.e1, &bfw, pairs_for(M, ch, prs));
+        launch_radial_bwd(c.n_basis, c.lmax, dvec, row_ptr, N, Ecap, W.rad1.as<float>(), PCu, w.dR->p, r_bf16,
+                          w.dY->as<float>(), g, t != T ? 1 : 0, rc, p_env, st, ch.e0, ch.e1, &bfw,
+                          pairs_for(M, ch, prs));
       }
       if (t > 1) {
         ProfScope ps(&M->prof, stage_id(kTpBwdNode, t), st);
@@ -1619,7 +1620,8 @@ std::vector<WeightCopy> plan_weights(e3mi_model* M) {
     add(W.rad1, kCopyF32, r1, c.n_basis, H, H);
     add(W.rad2, kCopyF32, r2, H, H, H);
     add(W.rad2T, kTransposeF32, r2, H, H, H);
-    add(W.rad3, kCopyF32, r3, H, PF, PF);
+    add(W.rad2f, kFragments, r2, H, H, H);
+    add(W.rad3f, kFragments, r3, H, PU, PF);
     add(W.rad3T, kTransposeF32, r3, H, PU, PF);  // used columns only
     add(W.rad3u, kCopyF32, r3, H, PU, PF);
     add(W.rad2b, kCopyBf16, r2, H, H, H);

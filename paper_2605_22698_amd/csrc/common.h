@@ -9,6 +9,7 @@ namespace e3mi {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -19,9 +20,10 @@ __device__ __forceinline__ void split_bf16(float v, __bf16& a, __bf16& b, __bf16
   b = (__bf16)v;
   c = (__bf16)(v - (float)b);
 }
-__device__ __forceinline__ void split_bf16(const float* v, bf16x8& a, bf16x8& b, bf16x8& c) {
+template <class V>
+__device__ __forceinline__ void split_bf16(const float* v, V& a, V& b, V& c) {
 #pragma unroll
-  for (int q = 0; q < 8; q += 2) {
+  for (int q = 0; q < (int)(sizeof(V) / sizeof(__bf16)); q += 2) {
     f32x2 r = {v[q], v[q + 1]};
     const bf16x2 x = __builtin_convertvector(r, bf16x2);
     r -= __builtin_convertvector(x, f32x2);
@@ -36,6 +38,12 @@ __device__ __forceinline__ void split_bf16(const float* v, bf16x8& a, bf16x8& b,
     c[q + 1] = z[1];
   }
 }
+__device__ __forceinline__ f32x16 mfma_bf(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+// The six products of two split operands that count: parts kSplitA[i] of A and
+// kSplitB[i] of B, the largest last
+constexpr int kSplitA[6] = {2, 0, 1, 1, 0, 0}, kSplitB[6] = {0, 2, 1, 0, 1, 0};
 
 constexpr int kWave = 64;
 

@@ -83,19 +83,15 @@ struct ARow {
     }
   }
 };
-__device__ __forceinline__ f32x16 mfma_bf(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
 // per column block hi += x1 y1; lo += the five small products (PARTS 1: hi alone)
 template <int PARTS, int NB>
 __device__ __forceinline__ void mul_split(const bf16x8* x, const bf16x8* y, f32x16* hi, f32x16* lo) {
-  constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
   for (int i = PARTS == 3 ? 0 : 5; i < 6; ++i)
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
       f32x16& acc = i < 5 ? lo[n] : hi[n];
-      acc = mfma_bf(x[kA[i]], y[n * PARTS + kB[i]], acc);
+      acc = mfma_bf(x[kSplitA[i]], y[n * PARTS + kSplitB[i]], acc);
     }
 }
 

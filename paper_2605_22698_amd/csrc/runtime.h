@@ -346,15 +346,12 @@ void launch_hvp_geo(const HvpArgs& a, long e_cap, int accumulate, float4* g, hip
 // from the last layer's pre-gate values x [N, C] and tangents xd [B N, C]: adjoints xb, xc [B N, C]
 void launch_hvp_readout(const float* x, const float* xd, const float* Wr, const float* w2, int N, int B, int C,
                         float* xb, float* xc, hipStream_t st);
-// rows of R and of its derivative Rp in the edge length, of every edge pair
-// (own, n_own) or of the edges [e_first, e_end) (e_end < 0: all)
-void launch_radial_d1(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
-                      const float* W2, const float* W3, int ld3, int PC, float* R, float* Rp, float rc, int p,
-                      int e_first, int e_end, const int* own, const int* n_own, hipStream_t st);
-// R3 rows of every edge pair (own, n_own) or edge
-void launch_radial_d2(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
-                      const float* W2, const float* W3, int ld3, int PC, float* R3, float rc, int p, const int* own,
-                      const int* n_own, hipStream_t st);
+// FP32 rows of R and its first n_out - 1 derivatives in the edge length (output
+// s from out + s out_gap, rows out_ld apart), of every edge pair (own, n_own) or
+// of the edges [e_first, e_end) (e_end < 0: all); W2 and W3 by kFragments
+void launch_radial_rows(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
+                        const __bf16* W2, const __bf16* W3, int PC, int n_out, float* out, long out_gap, int out_ld,
+                        float rc, int p, int e_first, int e_end, const int* own, const int* n_own, hipStream_t st);
 
 // ---- product block of body order 2 (product.hip) -------------------------------------
 struct ProductArgs {
@@ -416,14 +413,12 @@ struct EdgePairs {
   const int* rev = nullptr;
 };
 void launch_radial_fwd(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
-                       const float* W2, const float* W3, int ld3, int PC, void* R, bool r_bf16, float rc, int p,
-                       bool bf16, hipStream_t st, int e_first = 0, int e_end = -1, const RadialBf16* wb = nullptr,
-                       const EdgePairs* pairs = nullptr);
+                       int PC, void* R, bool r_bf16, float rc, int p, hipStream_t st, int e_first, int e_end,
+                       const RadialBf16* wb, const EdgePairs* pairs = nullptr);
 void launch_radial_bwd(int n_basis, int lmax, const float4* dvec, const int* row_ptr_x, int N, long e_cap,
-                       const float* W1, const float* W2, const float* W2T, const float* W3T, int PC, const void* dR,
-                       bool r_bf16, const float* dY, float4* g, int accumulate, float rc, int p, bool bf16,
-                       hipStream_t st, int e_first = 0, int e_end = -1, const RadialBf16* wb = nullptr,
-                       const EdgePairs* pairs = nullptr);
+                       const float* W1, int PC, const void* dR, bool r_bf16, const float* dY, float4* g, int accumulate,
+                       float rc, int p, hipStream_t st, int e_first, int e_end, const RadialBf16* wb,
+                       const EdgePairs* pairs);
 
 // ---- second-order passes (radial.hip, grad.hip) -------------------------------------
 // Radial MLP of weight gradients: from the adjoints Rb, Rc of R and R' per edge,
