@@ -467,11 +467,12 @@ __global__ void __launch_bounds__(256, 2) k_radial_rows(const float4* __restrict
       for (int r = 0; r < 16; ++r) {
         const int row = 32 * h + 8 * (r >> 2) + (r & 3);  // + 4 (lane / 32)
         if (e0 + row + 4 * (lane >> 5) < E) {
-#pragma unroll
-          for (int s = 0; s < ND; ++s) {
-            float* d = at_off(o + s * out_gap + (long)row * out_ld, oo);
-            if (ND == 2 && s == 1) __builtin_nontemporal_store(v[s][r], d);
-            else *d = v[s][r];
+          float* d = o + (long)row * out_ld;
+          *at_off(d, oo) = v[0][r];
+          if constexpr (ND == 2) __builtin_nontemporal_store(v[1][r], at_off(d + out_gap, oo));
+          if constexpr (ND == 3) {
+            *at_off(d + out_gap, oo) = v[1][r];
+            *at_off(d + 2 * out_gap, oo) = v[2][r];
           }
         }
       }
