@@ -1164,7 +1164,8 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
       set_chunk(ta, ch);
       ta.R = static_cast<const float*>(Rc);
       ProfScope ps(&M->prof, stage_id(kTpFwd, t), st);
-      launch_tp(0, ta, st);
+      if (!bf16 && (L.kind == 2 || L.kind == 3)) launch_tps_fwd(ta, st);
+      else launch_tp(0, ta, st);
     }
     float* ht = w.ht[t]->as<float>();
     const int split = (!prod && L.nc_out == 1) ? mix_split_parts(L.p_used_l3[0] * C + (hin ? C : 0)) : 1;

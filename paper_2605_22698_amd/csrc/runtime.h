@@ -259,6 +259,8 @@ void launch_tp(int which, const TpArgs& a, hipStream_t st);
 // mode dR) of pass 1 and, when a.dh is set, dh of pass 2
 bool tps_supported(const TpArgs& a);
 void launch_tps_sender(const TpArgs& a, hipStream_t st);
+// pass 0 in FP32
+void launch_tps_fwd(const TpArgs& a, hipStream_t st);
 // g (+)= the position adjoint of the edges' rows [dE/dr, dY 1..] (tps.hip)
 void launch_edge_geo(int lmax, const int* row_ptr_x, int N, long e_cap, const float4* dvec, const float* rows,
                      int accumulate, float4* g, hipStream_t st);

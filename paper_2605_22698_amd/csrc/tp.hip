@@ -30,11 +30,12 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
-// The scalar-output layer's forward is compiled for at most three waves per
-// SIMD: the compiler then schedules its edge loop with 88 registers instead
-// of 72 (the hardware still holds five waves) and it runs faster (0.134 ms
-// against 0.141 on the 3,000-atom step). Holding residency at three or two
-// waves for real, by reserving LDS, is slower (0.167, 0.196 ms).
+// The scalar-output layer's forward (here in the BF16 mode; in FP32 k_tps_fwd)
+// is compiled for at most three waves per SIMD: the compiler then schedules its
+// edge loop with 88 registers instead of 72 (the hardware still holds five
+// waves) and it runs faster (0.134 ms against 0.141 on the 3,000-atom step).
+// Holding residency at three or two waves for real, by reserving LDS, is slower
+// (0.167, 0.196 ms).
 template <int LMAX, int KIND, int CPT, class RS, bool IDX>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, KIND == kLast ? 3 : 10))) k_tp_fwd(const int* __restrict__ row_ptr, const int* __restrict__ src,
                                                 const float4* __restrict__ dvec, const RS* __restrict__ R,
@@ -626,8 +627,11 @@ static void first_order_launch(int which, const TpArgs& a, int nr, int tpr, hipS
         return;
       }
     }
-    k_tp_fwd<LMAX, KIND, CPT, float, IDX><<<nr, tpr, 0, st>>>(a.row_ptr, a.src, a.dvec, a.R, a.r_stride, a.h, a.h_nc,
-                                                               a.A, a.N, a.C, a.inv_nu, a.i0, rf, a.r_row);
+    if constexpr (KIND == kLast || KIND == kFirstLast)
+      throw Error(E3MI_EINVAL, "tensor product: scalar-output layers in FP32 take launch_tps_fwd");
+    else
+      k_tp_fwd<LMAX, KIND, CPT, float, IDX><<<nr, tpr, 0, st>>>(a.row_ptr, a.src, a.dvec, a.R, a.r_stride, a.h, a.h_nc,
+                                                                 a.A, a.N, a.C, a.inv_nu, a.i0, rf, a.r_row);
     return;
   }
   constexpr bool MSG = KIND == kFull;

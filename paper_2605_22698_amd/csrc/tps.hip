@@ -30,6 +30,8 @@
 // each edge with both signs, so the forces are the same. An edge inside the
 // cutoff whose reverse is not (its FP64 length within rounding of r_c, where
 // the envelope and its derivatives vanish) gets zeros.
+#include <type_traits>
+
 #include "common.h"
 #include "paths.h"
 #include "runtime.h"
@@ -46,6 +48,69 @@ __device__ __forceinline__ void str_nt(__bf16* p, const float* v) {
 #pragma unroll
   for (int q = 0; q < n; ++q) t[q] = (__bf16)v[q];
   __builtin_nontemporal_store(t, reinterpret_cast<bvec*>(p));
+}
+
+// Forward of the layer in FP32: a workgroup of C x S threads per receiver, a
+// thread per channel and stream; stream s takes the edges s, s + S, ... of the
+// row and the streams' sums meet in LDS, added in their order.
+// Bound: the senders' rows (8 KB an edge in models of 128) out of the L2s; on
+// small systems the chain of a row's edges. us with one, two and four streams:
+// 24 atoms 10.5, 6.5, 5.0; 138 atoms 24, 14, 9; 1,205 atoms 34, 36, 31; 3,000
+// atoms 99, 102, 95; 64 charged clusters 158, 154, 144; 20,000 atoms 1,275,
+// 1,290, 1,310. Two adjacent channels a lane with the next edge's rows loaded
+// ahead: 14 on 138 atoms, 134 on 3,000 (four streams).
+template <int LMAX, int KIND, int S, bool WAVES>
+__global__ void __launch_bounds__(128 * S) __attribute__((amdgpu_waves_per_eu(1, 3))) k_tps_fwd(
+    const int* __restrict__ row_ptr, const int* __restrict__ src, const float4* __restrict__ dvec,
+    const float* __restrict__ R, int r_stride, const float* __restrict__ h, int h_nc, float* __restrict__ A, int C,
+    float inv_nu, int i0, int r_first, const int* __restrict__ r_row) {
+  using PS = PathSet<LMAX, KIND>;
+  constexpr int NP = PS::NP, NIN = PS::NIN, NY = PS::NY;
+  static_assert(PS::NOUT == NP, "scalar outputs only");
+  __shared__ float part[S][NP][128];
+  const int i = i0 + xcd_contiguous(blockIdx.x, gridDim.x);
+  const int k = threadIdx.x;
+  // WAVES: whole waves per stream (C a multiple of 64)
+  const int s = WAVES ? __builtin_amdgcn_readfirstlane(threadIdx.y) : threadIdx.y;
+  float acc[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) acc[p] = 0.0f;
+  const int e1 = row_ptr[i + 1];
+  for (int e = row_ptr[i] + s; e < e1; e += S) {
+    const float4 d = dvec[e];
+    const float ir = 1.0f / d.w;
+    float Y[NY], hv[NIN], rv[NP];
+    real_sh<LMAX>(d.x * ir, d.y * ir, d.z * ir, Y);
+    const float* Re = R + (long)(r_row ? r_row[e] : e - r_first) * r_stride;
+    const float* hj = h + (long)src[e] * h_nc * C;
+#pragma unroll
+    for (int q = 0; q < NIN; ++q) hv[q] = hj[q * C + k];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) rv[p] = Re[p * C + k];
+    static_for<NP>([&](auto pi) {
+      constexpr int g = PS::T.id[pi];
+      constexpr int l1 = kL1[g], l2 = kL2[g];
+      constexpr int z0 = kNzBegin[g], nz = kNzBegin[g + 1] - kNzBegin[g];
+      static_assert(one_coefficient(g), "paths (l, l, 0)");
+      float t = 0.0f;
+      static_for<nz>([&](auto z) {
+        constexpr int q = z0 + z;
+        t += hv[l1 * l1 + kM1[q]] * Y[l2 * l2 + kM2[q]];
+      });
+      acc[pi] += rv[pi] * t;
+    });
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) part[s][p][k] = acc[p];
+  __syncthreads();
+  static_for<NP>([&](auto pi) {
+    if (pi % S != s) return;
+    constexpr int g = PS::T.id[pi];
+    float sum = 0.0f;
+#pragma unroll
+    for (int x = 0; x < S; ++x) sum += part[x][pi][k];
+    A[((long)i * NP + PS::T.rank[pi]) * C + k] = sum * (kC[kNzBegin[g]] * inv_nu);
+  });
 }
 
 // FP32: W waves per sender, wave w taking the edges w, w + W, ... of the row,
@@ -368,7 +433,7 @@ void sender_launch_bf16(const TpArgs& a, int nr, hipStream_t st) {
                                                                a.i0, a.e_first, a.r_row, a.r_first);
 }
 
-constexpr int kSenderWaves = 4;
+constexpr int kSenderWaves = 4, kFwdStreams = 4;
 
 template <int LMAX, int KIND, int CH>
 void sender_launch(const TpArgs& a, int nr, hipStream_t st) {
@@ -381,6 +446,18 @@ void sender_launch(const TpArgs& a, int nr, hipStream_t st) {
     k_tps_sender<LMAX, KIND, CH, false, W><<<nr, 64 * W, 0, st>>>(a.row_ptr, a.src, a.rev, a.dvec, a.R, a.Rp, a.h, a.h_nc,
                                                                   a.dA, a.dY, nullptr, 0, 0, a.C, a.inv_nu, a.i0,
                                                                   a.r_first, a.r_row);
+}
+
+template <int LMAX, int KIND>
+void fwd_kind(const TpArgs& a, int nr, hipStream_t st) {
+  constexpr int S = kFwdStreams;
+  auto go = [&](auto waves) {
+    k_tps_fwd<LMAX, KIND, S, decltype(waves)::value><<<nr, dim3(a.C, S), 0, st>>>(
+        a.row_ptr, a.src, a.dvec, a.R, a.r_stride, a.h, a.h_nc, a.A, a.C, a.inv_nu, a.i0, a.r_first, a.r_row);
+  };
+  if (a.C == 128 || a.C == 64) go(std::true_type{});
+  else if (a.C == 32) go(std::false_type{});
+  else throw Error(E3MI_EUNSUPPORTED, "scalar-output tensor product: unsupported channels");
 }
 
 template <int LMAX, int KIND>
@@ -444,6 +521,20 @@ void launch_tps_sender(const TpArgs& a, hipStream_t st) {
   }
   if (a.kind == kLast) return tps_kind<3, kLast>(a, nr, st);
   return tps_kind<3, kFirstLast>(a, nr, st);
+}
+
+void launch_tps_fwd(const TpArgs& a, hipStream_t st) {
+  if (a.N == 0) return;
+  E3MI_REQUIRE(tps_supported(a) && !a.r_bf16, E3MI_EUNSUPPORTED, "scalar-output tensor product: unsupported layer");
+  const int nr = a.n_recv > 0 ? a.n_recv : a.N;
+  if (a.n_recv == 0 && (a.i0 != 0 || a.r_first != 0))
+    throw Error(E3MI_EINVAL, "tensor product: receiver offset without a receiver count");
+  if (a.lmax == 2) {
+    if (a.kind == kLast) return fwd_kind<2, kLast>(a, nr, st);
+    return fwd_kind<2, kFirstLast>(a, nr, st);
+  }
+  if (a.kind == kLast) return fwd_kind<3, kLast>(a, nr, st);
+  return fwd_kind<3, kFirstLast>(a, nr, st);
 }
 
 void launch_edge_geo(int lmax, const int* row_ptr_x, int N, long e_cap, const float4* dvec, const float* rows,
