@@ -11,6 +11,14 @@
 namespace e3mi {
 namespace {
 
+// Rounded to FP32, and whatever is rounded to BF16 next from that value: the
+// compiler otherwise rounds the FP64 one to BF16 directly, which differs at ties
+__device__ __forceinline__ float to_f32(double x) {
+  float v = (float)x;
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 __device__ __forceinline__ void put_fragment(__bf16* __restrict__ f, float v) {
   __bf16 x[3];
   split_bf16(v, x[0], x[1], x[2]);
@@ -33,7 +41,7 @@ __global__ void __launch_bounds__(256) k_weights_layout(const double* __restrict
   const long n = (long)c.rows * c.cols;
   for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
     const int r = (int)(i / c.cols), k = (int)(i % c.cols);
-    const float v = (float)w[c.src + (long)r * c.ld + k];
+    const float v = to_f32(w[c.src + (long)r * c.ld + k]);
     const long t = (long)k * c.rows + r;  // transposed
     switch (c.kind) {
       case kCopyF32: static_cast<float*>(c.dst)[i] = v; break;
@@ -63,8 +71,9 @@ __global__ void __launch_bounds__(128) k_weights_u(const double* __restrict__ w,
   double u = 0.0;
 #pragma unroll 8
   for (int j = 0; j < C; ++j) u += V[j] * Wm[(long)j * C];
-  put_fragment(f.U[l] + fragment_at(row, k, C), (float)u);
-  put_fragment(f.UT[l] + fragment_at(k, row, gridDim.x), (float)u);
+  const float v = to_f32(u);
+  put_fragment(f.U[l] + fragment_at(row, k, C), v);
+  put_fragment(f.UT[l] + fragment_at(k, row, gridDim.x), v);
 }
 
 }  // namespace

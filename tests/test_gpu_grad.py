@@ -9,7 +9,7 @@ import pytest
 
 import synth
 from oracle import model as om
-from tests.gpu_util import check_energy, check_forces, device, record, say
+from tests.gpu_util import check_energy, check_forces, device, gpu_energy_forces, record, say
 
 pytestmark = pytest.mark.gpu
 
@@ -237,3 +237,23 @@ def test_weights_replaced_from_the_device(precision):
         with pytest.raises(e3.E3miError, match="not finite"):
             m.set_weights(bad)
         assert all(np.array_equal(a, r) for a, r in zip(evaluate(m), ref))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_weights_rounded_to_fp32_first(precision):
+    # weights that FP32 cannot hold, next to halfway between BF16 neighbours:
+    # rounded to FP32 first (to the tie) they give what FP32 weights give, bit for bit
+    import paper_2605_22698_amd as e3
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=2, n_species=2, cutoff=4.0, avg_neighbors=8.0)
+    b = synth.uniform_cluster(20, 3.0, 0.9, 2, np.random.default_rng(140))
+    w = synth.flatten_weights(cfg, synth.model_weights(cfg, 141)).astype(np.float32)
+    tie = ((w.view(np.uint32) & 0xffff0000) | 0x8000).view(np.float32).astype(np.float64)
+    near = tie * (1.0 + 2.0 ** -40)
+    assert np.array_equal(near.astype(np.float32).astype(np.float64), tie) and not np.array_equal(near, tie)
+    out = []
+    for v in (tie, near):
+        m = e3.Model(cfg.to_json(), v, precision=precision, device=device())
+        m.set_flags(unfactorised_first_layer=True)  # the factorisation forms products in FP64
+        out.append(gpu_energy_forces(m, b)[:3])
+    for x, y in zip(*out):
+        assert np.array_equal(x, y)
