@@ -5,8 +5,6 @@
 //   (Section 5.3 readout with one head), fused with its adjoint dE/dh[0]
 //   energy reduction per structure in FP64, fixed summation order
 //   force assembly F_i = sum_{e in in(i)} (g_e - g_rev(e))
-#include <type_traits>
-
 #include "common.h"
 #include "runtime.h"
 
@@ -218,16 +216,6 @@ __global__ void __launch_bounds__(256) k_forces(const int* __restrict__ row_ptr,
 inline int blocks(long n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
-
-// go(components) for the (l + 1)^2 that features have
-template <class F>
-static void with_components(int nc, F go) {
-  if (nc == 1) go(std::integral_constant<int, 1>{});
-  else if (nc == 4) go(std::integral_constant<int, 4>{});
-  else if (nc == 9) go(std::integral_constant<int, 9>{});
-  else if (nc == 16) go(std::integral_constant<int, 16>{});
-  else throw Error(E3MI_EINVAL, "internal: components of the gate");
-}
 
 void launch_gate_fwd(const float* ht, float* h, int N, int nc, int C, hipStream_t st) {
   if (N == 0) return;

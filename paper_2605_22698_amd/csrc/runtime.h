@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <stdexcept>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/e3mi.h"
@@ -291,6 +292,15 @@ struct GemmArgs {
 // at most 4 + 4 products (one per output order, plus the self connection's).
 constexpr int kMaxGemmGroup = 8;
 void launch_gemm_group(const GemmArgs* a, int n, hipStream_t st, bool bf16 = false);
+// go(components) for the (l + 1)^2 that features have
+template <class F>
+inline void with_components(int nc, F go) {
+  if (nc == 1) go(std::integral_constant<int, 1>{});
+  else if (nc == 4) go(std::integral_constant<int, 4>{});
+  else if (nc == 9) go(std::integral_constant<int, 9>{});
+  else if (nc == 16) go(std::integral_constant<int, 16>{});
+  else throw Error(E3MI_EINVAL, "internal: components of the gate");
+}
 void launch_gate_fwd(const float* ht, float* h, int N, int nc, int C, hipStream_t st);
 void launch_gate_bwd(const float* ht, const float* dh, float* dht, int N, int nc, int C, hipStream_t st);
 // h~ [N, C] = sum of n_parts partial products [n_parts, N, C] in order; h = silu(h~)
