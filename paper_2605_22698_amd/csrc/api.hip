@@ -281,6 +281,9 @@ struct e3mi_graph {
   // plans last uploaded (re-sent only when they change)
   std::unique_ptr<e3mi::DevBuf> bb, plan_d, cell_count, cell_start, cell_fill, cell_atoms, atom_cell, wrap, err;
   std::vector<e3mi::GridPlan> plan_h;
+  // what the buffers above are pieces of: sizes fixed by the batch, by the edges
+  // there is room for and by the cells
+  std::unique_ptr<e3mi::DevBuf> batch_block, edge_block, cell_block;
 };
 
 struct e3mi_md {
@@ -337,6 +340,30 @@ DevBuf& ensure(std::unique_ptr<DevBuf>& b, Allocator* a, size_t bytes) {
   return *b;
 }
 
+// Buffers that are pieces of one allocation. A graph has some thirty small ones:
+// allocated one by one through a caller's allocator they took longer than the
+// kernels that fill them.
+struct Pieces {
+  struct Piece {
+    std::unique_ptr<DevBuf>* buf;
+    size_t at, bytes;
+  };
+  std::vector<Piece> all;
+  size_t total = 0;
+  void add(std::unique_ptr<DevBuf>& b, size_t bytes) {
+    all.push_back({&b, total, bytes});
+    total += (std::max<size_t>(bytes, 1) + 255) & ~(size_t)255;
+  }
+  void place(std::unique_ptr<DevBuf>& block, Allocator* a) {
+    char* base = ensure(block, a, total).as<char>();
+    for (const Piece& q : all) {
+      *q.buf = std::make_unique<DevBuf>();  // no allocator: the block owns the memory
+      (*q.buf)->p = base + q.at;
+      (*q.buf)->bytes = q.bytes;
+    }
+  }
+};
+
 void fill_plan(const Config& c, int S, const std::vector<int64_t>& off, const double* cell, const uint8_t* pbc,
                const std::vector<double>& bbox, double rc_eff, std::vector<GridPlan>& plans, int& n_cells) {
   plans.resize(S);
@@ -379,7 +406,8 @@ void fill_plan(const Config& c, int S, const std::vector<int64_t>& off, const do
   }
 }
 
-void build_lists(e3mi_graph* G, const double* pos, hipStream_t st) {
+// check: read the flag of new_graph's checks of the inputs too
+void build_lists(e3mi_graph* G, const double* pos, hipStream_t st, bool check = false) {
   e3mi_model* M = G->model;
   Allocator* a = &M->alloc;
   const int S = G->S, N = G->N;
@@ -389,11 +417,19 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st) {
   bool any_open = false;
   for (int s = 0; s < S; ++s)
     for (int k = 0; k < 3; ++k) any_open |= !G->pbc_h[3 * s + k];
-  if (any_open && N) {
-    double* bb = ensure(G->bb, a, sizeof(double) * 6 * S).as<double>();
-    launch_bbox(pos, G->off_d->as<int64_t>(), S, bb, st);
-    E3MI_HIP(hipMemcpyAsync(bbox.data(), bb, sizeof(double) * 6 * S, hipMemcpyDeviceToHost, st));
+  if (any_open && N) launch_bbox(pos, G->off_d->as<int64_t>(), S, G->bb->as<double>(), st);
+  if ((any_open || check) && N) {
+    // the check's flag lies behind the boxes: one copy, one wait
+    std::vector<double> back((size_t)6 * S + 1);
+    E3MI_HIP(hipMemcpyAsync(back.data(), G->bb->p, sizeof(double) * back.size(), hipMemcpyDeviceToHost, st));
     E3MI_HIP(hipStreamSynchronize(st));
+    if (check) {
+      int fh;
+      std::memcpy(&fh, &back[(size_t)6 * S], sizeof(int));
+      E3MI_REQUIRE(!(fh & 8), E3MI_EINVAL, "species outside [0, n_species)");
+      E3MI_REQUIRE(!fh, E3MI_ENAN, "positions are not finite");
+    }
+    if (any_open) bbox.assign(back.begin(), back.end() - 1);
   }
   std::vector<double> cell9((size_t)9 * S, 0.0);
   for (int s = 0; s < S; ++s)
@@ -402,31 +438,29 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st) {
   int n_cells = 0;
   fill_plan(M->cfg, S, G->off_h, cell9.data(), G->pbc_h.data(), bbox, rc_eff, plans, n_cells);
   const size_t plan_bytes = sizeof(GridPlan) * plans.size();
-  if (!G->plan_d || G->plan_h.size() != plans.size() ||
+  if (G->plan_h.size() != plans.size() ||
       std::memcmp(G->plan_h.data(), plans.data(), plan_bytes) != 0) {
-    ensure(G->plan_d, a, plan_bytes);
-    if (plan_bytes) E3MI_HIP(hipMemcpy(G->plan_d->p, plans.data(), plan_bytes, hipMemcpyHostToDevice));
-    G->plan_h = plans;
+    G->plan_h = plans;  // outlives the copy: the call waits for the stream below
+    if (plan_bytes)
+      E3MI_HIP(hipMemcpyAsync(G->plan_d->p, G->plan_h.data(), plan_bytes, hipMemcpyHostToDevice, st));
   }
-  DevBuf& plan_d = *G->plan_d;
-  DevBuf& cell_count = ensure(G->cell_count, a, sizeof(int) * (n_cells + 1));
-  DevBuf& cell_start = ensure(G->cell_start, a, sizeof(int) * (n_cells + 1));
-  DevBuf& cell_fill = ensure(G->cell_fill, a, sizeof(int) * (n_cells + 1));
-  DevBuf& cell_atoms = ensure(G->cell_atoms, a, sizeof(int) * (N + 1));
-  DevBuf& atom_cell = ensure(G->atom_cell, a, sizeof(int) * (N + 1));
-  DevBuf& wrap = ensure(G->wrap, a, sizeof(int) * 3 * (N + 1));
-  DevBuf& err = ensure(G->err, a, sizeof(int));
-  E3MI_HIP(hipMemsetAsync(cell_count.p, 0, sizeof(int) * (n_cells + 1), st));
-  E3MI_HIP(hipMemsetAsync(cell_fill.p, 0, sizeof(int) * (n_cells + 1), st));
-  E3MI_HIP(hipMemsetAsync(err.p, 0, sizeof(int), st));
+  DevBuf &plan_d = *G->plan_d, &cell_atoms = *G->cell_atoms, &atom_cell = *G->atom_cell, &wrap = *G->wrap;
+  const size_t cell_bytes = sizeof(int) * (n_cells + 1);
+  Pieces cells;
+  cells.add(G->err, sizeof(int));
+  cells.add(G->cell_count, cell_bytes);
+  cells.add(G->cell_fill, cell_bytes);
+  const size_t zeroed = cells.total;
+  cells.add(G->cell_start, cell_bytes);
+  cells.place(G->cell_block, a);
+  DevBuf &cell_count = *G->cell_count, &cell_start = *G->cell_start, &cell_fill = *G->cell_fill, &err = *G->err;
+  E3MI_HIP(hipMemsetAsync(G->cell_block->p, 0, zeroed, st));
   launch_bin(pos, G->owner->as<int>(), plan_d.as<GridPlan>(), N, atom_cell.as<int>(), wrap.as<int>(),
              cell_count.as<int>(), st);
   launch_exclusive_scan(cell_count.as<int>(), cell_start.as<int>(), n_cells, st);
   launch_bin_fill(atom_cell.as<int>(), cell_start.as<int>(), N, cell_fill.as<int>(), cell_atoms.as<int>(), st);
 
   const double rc2 = rc_eff * rc_eff;
-  ensure(G->cnt, a, sizeof(int) * (N + 1));
-  ensure(G->row_ptr, a, sizeof(int) * (N + 1));
   launch_edges(false, pos, G->owner->as<int>(), plan_d.as<GridPlan>(), atom_cell.as<int>(), wrap.as<int>(),
                cell_start.as<int>(), cell_atoms.as<int>(), nullptr, N, rc2, G->cnt->as<int>(), nullptr,
                err.as<int>(), st);
@@ -439,11 +473,15 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st) {
   // a list that outgrows its buffers on a rebuild gets 1/8 more room, so that
   // the count's drift over a trajectory does not reallocate at every rebuild
   if (E > G->E_room) G->E_room = G->E_room == 0 ? E : E + E / 8 + 64;
-  const long Er = G->E_room;
-  ensure(G->keys, a, sizeof(uint64_t) * (Er + 1));
-  ensure(G->src, a, sizeof(int) * (Er + 1));
-  ensure(G->shift, a, sizeof(int) * (Er + 1));
-  ensure(G->rev, a, sizeof(int) * (Er + 1));
+  const size_t Er = (size_t)G->E_room + 1;
+  if (!G->keys || G->keys->bytes < sizeof(uint64_t) * Er) {
+    Pieces e;
+    e.add(G->keys, sizeof(uint64_t) * Er);
+    e.add(G->dvec_x, sizeof(float4) * Er);
+    for (auto* q : {&G->src, &G->shift, &G->rev, &G->src_x, &G->old_idx, &G->new_idx, &G->rev_x, &G->own, &G->pair_of})
+      e.add(*q, sizeof(int) * Er);
+    e.place(G->edge_block, a);
+  }
   launch_edges(true, pos, G->owner->as<int>(), plan_d.as<GridPlan>(), atom_cell.as<int>(), wrap.as<int>(),
                cell_start.as<int>(), cell_atoms.as<int>(), G->row_ptr->as<int>(), N, rc2, nullptr,
                G->keys->as<uint64_t>(), err.as<int>(), st);
@@ -455,18 +493,7 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st) {
   E3MI_HIP(hipStreamSynchronize(st));
   E3MI_REQUIRE(!(errh & 1), E3MI_EOVERFLOW, "image index beyond +-127 cells: wrap positions into the cell");
   E3MI_REQUIRE(!(errh & 2), E3MI_EDEVICE, "neighbour list is not symmetric");
-  // pruned-list capacity and the reference positions for the skin check
-  ensure(G->row_ptr_x, a, sizeof(int) * (N + 1));
-  ensure(G->src_x, a, sizeof(int) * (Er + 1));
-  ensure(G->dvec_x, a, sizeof(float4) * (Er + 1));
-  ensure(G->old_idx, a, sizeof(int) * (Er + 1));
-  ensure(G->new_idx, a, sizeof(int) * (Er + 1));
-  ensure(G->rev_x, a, sizeof(int) * (Er + 1));
-  ensure(G->own_cnt, a, sizeof(int) * (N + 1));
-  ensure(G->own_ptr, a, sizeof(int) * (N + 1));
-  ensure(G->own, a, sizeof(int) * (Er + 1));
-  ensure(G->pair_of, a, sizeof(int) * (Er + 1));
-  ensure(G->x_ref, a, sizeof(double) * 3 * (N + 1));
+  // the reference positions for the skin check
   if (N) E3MI_HIP(hipMemcpyAsync(G->x_ref->p, pos, sizeof(double) * 3 * N, hipMemcpyDeviceToDevice, st));
 }
 
@@ -508,17 +535,10 @@ e3mi_graph* new_graph(e3mi_model* M, int S, const int64_t* off, const double* po
       }
   }
   Allocator* a = &M->alloc;
-  G->off_d = upload(a, G->off_h.data(), sizeof(int64_t) * (S + 1));
-  G->box_d = upload(a, G->box_h.data(), sizeof(double) * 3 * S);
-  G->pbc_d = upload(a, G->pbc_h.data(), 3 * S);
-  {
-    const std::vector<double> zero((size_t)S, 0.0);
-    G->charge = upload(a, zero.data(), sizeof(double) * S);
-  }
+  std::vector<int2> tiles;
   if (M->cfg.coulomb) {
     for (int s = 0; s < S * 3; ++s)
       E3MI_REQUIRE(!pbc[s], E3MI_EUNSUPPORTED, "the Coulomb term is defined for open structures only (pbc all 0)");
-    std::vector<int2> tiles;
     int64_t n_max = 0;
     for (int s = 0; s < S; ++s) {
       n_max = std::max<int64_t>(n_max, off[s + 1] - off[s]);
@@ -527,27 +547,42 @@ e3mi_graph* new_graph(e3mi_model* M, int S, const int64_t* off, const double* po
     G->n_ctiles = (int)tiles.size();
     // enough waves per tile to cover the largest structure's senders in one round, at most 16
     while (G->c_waves < 16 && 64 * G->c_waves < n_max) G->c_waves *= 2;
-    G->ctiles = upload(a, tiles.data(), sizeof(int2) * tiles.size());
   }
-  G->owner = std::make_unique<DevBuf>(a);
-  G->owner->ensure(sizeof(int) * (G->N + 1));
-  G->species = std::make_unique<DevBuf>(a);
-  G->species->ensure(sizeof(int) * (G->N + 1));
+  // the first pieces come from the host in one copy, zeros behind them: the
+  // structures' charges, the boxes of open axes and the checks' flag
+  Pieces b;
+  const size_t N1 = (size_t)G->N + 1;
+  b.add(G->off_d, sizeof(int64_t) * (S + 1));
+  b.add(G->box_d, sizeof(double) * 3 * S);
+  b.add(G->pbc_d, 3 * S);
+  if (M->cfg.coulomb) b.add(G->ctiles, sizeof(int2) * tiles.size());
+  b.add(G->charge, sizeof(double) * S);
+  b.add(G->bb, sizeof(double) * (6 * S + 1));
+  const size_t sent = b.total;
+  b.add(G->plan_d, sizeof(GridPlan) * S);
+  b.add(G->x_ref, sizeof(double) * 3 * N1);
+  b.add(G->wrap, sizeof(int) * 3 * N1);
+  for (auto* q : {&G->owner, &G->species, &G->cnt, &G->row_ptr, &G->row_ptr_x, &G->own_cnt, &G->own_ptr, &G->cell_atoms,
+                  &G->atom_cell})
+    b.add(*q, sizeof(int) * N1);
+  b.place(G->batch_block, a);
+  std::vector<char> host(sent, 0);  // outlives the copy: build_lists waits for the stream
+  auto put = [&](const std::unique_ptr<DevBuf>& d, const void* from) {
+    if (d && d->bytes) std::memcpy(&host[d->as<char>() - G->batch_block->as<char>()], from, d->bytes);
+  };
+  put(G->off_d, G->off_h.data());
+  put(G->box_d, G->box_h.data());
+  put(G->pbc_d, G->pbc_h.data());
+  put(G->ctiles, tiles.data());
+  E3MI_HIP(hipMemcpyAsync(G->batch_block->p, host.data(), sent, hipMemcpyHostToDevice, st));
   if (G->N) E3MI_HIP(hipMemcpyAsync(G->species->p, species, sizeof(int) * G->N, hipMemcpyDeviceToDevice, st));
   launch_owner(G->off_d->as<int64_t>(), S, G->owner->as<int>(), st);
   if (G->N) {
-    DevBuf flag(a);
-    flag.ensure(sizeof(int));
-    E3MI_HIP(hipMemsetAsync(flag.p, 0, sizeof(int), st));
-    launch_nonfinite(pos, 3 * G->N, flag.as<int>(), st);
-    launch_species_range(G->species->as<int>(), G->N, M->cfg.n_species, flag.as<int>(), st);
-    int fh = 0;
-    E3MI_HIP(hipMemcpyAsync(&fh, flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
-    E3MI_HIP(hipStreamSynchronize(st));
-    E3MI_REQUIRE(!(fh & 8), E3MI_EINVAL, "species outside [0, n_species)");
-    E3MI_REQUIRE(!fh, E3MI_ENAN, "positions are not finite");
+    int* flag = reinterpret_cast<int*>(G->bb->as<double>() + 6 * S);
+    launch_nonfinite(pos, 3 * G->N, flag, st);
+    launch_species_range(G->species->as<int>(), G->N, M->cfg.n_species, flag, st);
   }
-  build_lists(G.get(), pos, st);
+  build_lists(G.get(), pos, st, true);
   return G.release();
 }
 
