@@ -892,18 +892,26 @@ bool r_compact_for(const e3mi_model* M, const std::vector<RChunk>& chunks) {
   return M->edge_pairs && chunks.size() == 1 && chunks[0].e1 < 0;
 }
 
-// R, R' and R'' of layer t for every edge pair (every edge with flag 8)
-void radial_derivs(e3mi_model* M, e3mi_graph* G, int t, hipStream_t st) {
+// FP32 rows of the radial MLPs, in one launch: per edge pair (per edge with flag
+// 8), or a receiver chunk's edges
+void launch_rows(e3mi_model* M, e3mi_graph* G, const RadialJob* jobs, int n_jobs, int n_out, const RChunk* ch,
+                 hipStream_t st) {
   const Config& c = M->cfg;
-  const LayerPlan& L = M->plans[t - 1];
-  LayerWeights& W = *M->lw[t - 1];
   const EdgePairs prs = graph_pairs(G);
+  const bool pairs = M->edge_pairs && !ch;
+  launch_radial_rows(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, jobs, n_jobs, n_out,
+                     (float)c.cutoff, c.envelope_p, ch ? ch->e0 : 0, ch ? ch->e1 : -1, pairs ? prs.own : nullptr,
+                     pairs ? prs.n_own : nullptr, st);
+}
+
+// R, R' and R'' of layer t
+void radial_derivs(e3mi_model* M, e3mi_graph* G, int t, hipStream_t st) {
+  const LayerWeights& W = *M->lw[t - 1];
+  const int PC = M->plans[t - 1].p_used * M->cfg.channels;
+  const RadialJob job{W.rad1.as<float>(), W.rad2f.as<__bf16>(), W.rad3f.as<__bf16>(), PC, M->ws.R3[t]->as<float>(), PC,
+                      3 * PC};
   ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
-  const int PC = L.p_used * c.channels;
-  launch_radial_rows(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
-                     W.rad2f.as<__bf16>(), W.rad3f.as<__bf16>(), PC, 3, M->ws.R3[t]->as<float>(), PC, 3 * PC,
-                     (float)c.cutoff, c.envelope_p, 0, -1, M->edge_pairs ? prs.own : nullptr,
-                     M->edge_pairs ? prs.n_own : nullptr, st);
+  launch_rows(M, G, &job, 1, 3, nullptr, st);
 }
 
 void set_chunk(TpArgs& ta, const RChunk& ch) {
@@ -941,19 +949,58 @@ float* rp_rows(const e3mi_model* M, int t) {
   return M->ws.R[t]->as<float>() + M->ws.r_rows[t] * M->plans[t - 1].p_used * M->cfg.channels;
 }
 
+// R and R' of layer t
+RadialJob rows_job(const e3mi_model* M, int t) {
+  const LayerWeights& W = *M->lw[t - 1];
+  const int PC = M->plans[t - 1].p_used * M->cfg.channels;
+  float* R = M->ws.R[t]->as<float>();
+  return RadialJob{W.rad1.as<float>(), W.rad2f.as<__bf16>(), W.rad3f.as<__bf16>(), PC, R, rp_rows(M, t) - R, PC};
+}
+
 // R (and with `derivs` R') of layer t: every row (ch NULL) or a receiver chunk's edges
 void radial_rows(e3mi_model* M, e3mi_graph* G, int t, const RChunk* ch, bool derivs, hipStream_t st) {
-  const Config& c = M->cfg;
-  const LayerPlan& L = M->plans[t - 1];
-  LayerWeights& W = *M->lw[t - 1];
-  const EdgePairs prs = graph_pairs(G);
-  const bool pairs = M->edge_pairs && !ch;
-  const int PC = L.p_used * c.channels;
+  const RadialJob job = rows_job(M, t);
   ProfScope ps(&M->prof, stage_id(kRadialFwd, t), st);
-  launch_radial_rows(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, W.rad1.as<float>(),
-                     W.rad2f.as<__bf16>(), W.rad3f.as<__bf16>(), PC, derivs ? 2 : 1, M->ws.R[t]->as<float>(),
-                     rp_rows(M, t) - M->ws.R[t]->as<float>(), PC, (float)c.cutoff, c.envelope_p, ch ? ch->e0 : 0,
-                     ch ? ch->e1 : -1, pairs ? prs.own : nullptr, pairs ? prs.n_own : nullptr, st);
+  launch_rows(M, G, &job, 1, derivs ? 2 : 1, ch, st);
+}
+
+// The first layer's hidden rows (factorised) and R and R' of the layers that
+// keep them whole need the edges' lengths alone: up to this much room for R
+// (about half is used) they share one launch, at the front, and small systems
+// wait for one chain of hidden layers. Past it the first layer's own streams
+// would push R out of the last-level cache (256 MB) before it is read. Both
+// measured, us a call, together and apart: 24 atoms 80 and 87, 138 atoms (9 MB)
+// 121 and 126, 64 molecules 361 and 378, an MD step of 1,205 atoms (176 MB) 263
+// and 273, of 3,000 (600 MB) 568 and 552, 64 charged clusters (620 MB) 852 and 840.
+constexpr size_t kRowsTogether = 256UL << 20;
+
+// Launches them (together: R too); returns whether R was among them.
+bool first_rows(e3mi_model* M, e3mi_graph* G, bool fact, bool whole_rows, hipStream_t st) {
+  Workspace& w = M->ws;
+  const int T = M->cfg.layers, H = M->cfg.radial_hidden;
+  size_t r_bytes = 0;
+  std::vector<RadialJob> jobs;
+  int stage = stage_id(kFirstFwd, 1);
+  if (fact) {
+    const LayerWeights& W = *M->lw[0];
+    jobs.push_back(RadialJob{W.rad1.as<float>(), W.rad2f.as<__bf16>(), nullptr, 0, w.H2f->as<float>(), H, 2 * H});
+  }
+  for (int t = fact ? 2 : 1; whole_rows && t <= T; ++t)
+    if (w.r_whole[t]) {
+      const RadialJob job = rows_job(M, t);
+      r_bytes += sizeof(float) * w.r_rows[t] * job.PC;
+      jobs.push_back(job);
+      stage = stage_id(kRadialFwd, t);
+    }
+  const bool together = whole_rows && r_bytes <= kRowsTogether;
+  if (!together) {
+    jobs.resize(fact ? 1 : 0);
+    stage = stage_id(kFirstFwd, 1);
+  }
+  ProfScope ps(&M->prof, stage, st);
+  for (size_t k = 0; k < jobs.size(); k += kMaxRadialJobs)
+    launch_rows(M, G, &jobs[k], (int)std::min<size_t>(kMaxRadialJobs, jobs.size() - k), 2, nullptr, st);
+  return together;
 }
 
 // Primal forward pass: edge selection, embedding and every layer. Leaves
@@ -1082,6 +1129,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     ProfScope ps(&M->prof, stage_id(kMixFwd, t), st);
     launch_lin(M, L, W, w.Bp->as<float>(), hin, ht, N, st, bf16);
   };
+  const bool rows_done = !bf16 && first_rows(M, G, fact, !derivs, st);
   for (int t = 1; t <= T; ++t) {
     const LayerPlan& L = M->plans[t - 1];
     LayerWeights& W = *M->lw[t - 1];
@@ -1093,9 +1141,10 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
         // the per-species neighbour sums read them through the pair index
         ProfScope ps(&M->prof, stage_id(kFirstFwd, 1), st);
         const EdgePairs prs = graph_pairs(G);
-        launch_first_hidden(dvec, row_ptr, N, Ecap, M->edge_pairs ? prs.own : nullptr,
-                            M->edge_pairs ? prs.n_own : nullptr, W.rad1.as<float>(), W.rad2.as<float>(), rc, p_env,
-                            w.H2f->as<float>(), st);
+        if (bf16)
+          launch_first_hidden(dvec, row_ptr, N, Ecap, M->edge_pairs ? prs.own : nullptr,
+                              M->edge_pairs ? prs.n_own : nullptr, W.rad1.as<float>(), W.rad2.as<float>(), rc, p_env,
+                              w.H2f->as<float>(), st);
         launch_first(true, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, first_pair_index(M, G),
                      w.H2f->as<float>(), G1, nullptr, nullptr, nullptr, 0, st);
       }
@@ -1187,7 +1236,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
         ta.r_stride = 3 * PCu;
         ta.r_row = first_pair_index(M, G);
       } else if (rows && w.r_whole[t]) {
-        radial_rows(M, G, t, nullptr, true, st);
+        if (!rows_done) radial_rows(M, G, t, nullptr, true, st);
         ta.r_row = first_pair_index(M, G);
       } else if (rows) {
         radial_rows(M, G, t, &ch, false, st);

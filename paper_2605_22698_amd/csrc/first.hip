@@ -14,10 +14,11 @@
 // computed once per model.
 //
 // The hidden layers depend on the edge length only, so an edge and its
-// reverse share them: k_first_hidden computes the second hidden layer H2 =
-// silu(silu(B W1) W2) and its derivative H2' in the length once per edge pair
-// (tiles of 64 pair owners, or of 64 edges without the pair list), and both
-// kernels below read them through the edge's pair index.
+// reverse share them: the second hidden layer H2 = silu(silu(B W1) W2) and its
+// derivative H2' in the length are computed once per edge pair (tiles of 64 pair
+// owners, or of 64 edges without the pair list; in FP32 by k_radial_rows, in the
+// BF16 mode by k_first_hidden), and both kernels below read them through the
+// edge's pair index.
 //
 // With dG = dh~_l U_l^T the adjoint is one contraction over q, of H2 and of
 // H2' with the receiver's rows of the sender's species:
@@ -27,7 +28,7 @@
 // edge) is formed.
 //
 // Kernels:
-//   k_first_hidden  [H2 | H2'] [pairs, 128]
+//   k_first_hidden  [H2 | H2'] [pairs, 128] (BF16 mode)
 //   k_first_fwd  G_i [N, (L3+1)^2, S*64]
 //   k_first_bwd  g_e = dE/dd_e (added to the other layers')
 // The last two give a wave to each (receiver, sender species): it picks the

@@ -353,18 +353,24 @@ __global__ void __launch_bounds__(256) k_radial_bwd(const float4* __restrict__ d
 // v_mfma_f32_32x32x2_f32: ND 2, 3,000 atoms (80,132 pairs, P C = 512) 92 and
 // 142; 64 charged clusters 138 and 182; 138 atoms 17 and 31; 20,000 atoms, P C =
 // 2,944 and 512 together 6,000 and 8,120. ND 3, 3,000 atoms 160 and 268.
+struct RadialJobs {
+  RadialJob j[kMaxRadialJobs];
+};
 template <int ND>
 __global__ void __launch_bounds__(256, 2) k_radial_rows(const float4* __restrict__ dvec, const int* __restrict__ row_ptr_x,
-                                                     int N, const float* __restrict__ W1,
-                                                     const __bf16* __restrict__ W2, const __bf16* __restrict__ W3,
-                                                     int PC, float* __restrict__ out, long out_gap, int out_ld,
-                                                     float rc, int p, int e_first, int e_end,
-                                                     const int* __restrict__ own, const int* __restrict__ n_own) {
+                                                        int N, RadialJobs jobs, float rc, int p, int e_first, int e_end,
+                                                        const int* __restrict__ own, const int* __restrict__ n_own) {
   constexpr int NB = 8;
   __shared__ bf16x8 X[ND][2][kH / 16][3][64];  // [output][32 rows][16 K][part][lane]
+  const RadialJob& job = jobs.j[blockIdx.z];
+  const float* __restrict__ W1 = job.W1;
+  const __bf16 *__restrict__ W2 = job.W2, *__restrict__ W3 = job.W3;
+  const int PC = job.PC, out_ld = job.out_ld;
+  const long out_gap = job.out_gap;
+  float* __restrict__ out = job.out;
   const int E = own ? *n_own : e_end >= 0 ? e_end : row_ptr_x[N];
   const int e0 = (own ? 0 : e_first) + blockIdx.x * kTile;
-  if (e0 >= E) return;
+  if (e0 >= E || (PC == 0 ? blockIdx.y > 0 : blockIdx.y * 128 >= (unsigned)PC)) return;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   // the weights' operands of one product, on their way while the rows before are formed
   bf16x8 y[kH / 16][3];
@@ -449,6 +455,15 @@ __global__ void __launch_bounds__(256, 2) k_radial_rows(const float4* __restrict
           v[1][k] = d * x1;
           if constexpr (ND > 2) v[2][k] = silu_grad2(x) * x1 * x1 + d * (hi[2][4 * g + k] + lo[2][4 * g + k]);
         }
+      }
+      if (PC == 0) {
+        const int row = 32 * rb + (lane & 31);
+        if (e0 + row < E)
+#pragma unroll
+          for (int s = 0; s < ND; ++s)
+            str_n<4>(out + (long)(e0 - (own ? 0 : e_first) + row) * out_ld + s * out_gap + 32 * cb + 8 * g + 4 * (lane >> 5),
+                     v[s]);
+        continue;
       }
 #pragma unroll
       for (int s = 0; s < ND; ++s) {
@@ -749,12 +764,19 @@ void launch_radial_wgrad(const float4* dvec, const int* row_ptr_x, int N, long e
   k_radial_wgrad<<<tiles(e_cap), 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W2T, W3T, PC, Rb, Rc, rc, p, own, n_own,
                                                rev, Bd, H1d, H2d, P1g, P2g);
 }
-void launch_radial_rows(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
-                        const __bf16* W2, const __bf16* W3, int PC, int n_out, float* out, long out_gap, int out_ld,
-                        float rc, int p, int e_first, int e_end, const int* own, const int* n_own, hipStream_t st) {
+void launch_radial_rows(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap,
+                        const RadialJob* jobs, int n_jobs, int n_out, float rc, int p, int e_first, int e_end,
+                        const int* own, const int* n_own, hipStream_t st) {
   if (e_cap == 0) return;
   if (n_basis != 8) throw Error(E3MI_EUNSUPPORTED, "n_basis must be 8");
-  if (PC % 32) throw Error(E3MI_EUNSUPPORTED, "paths x channels must be a multiple of 32");
+  if (n_jobs < 1 || n_jobs > kMaxRadialJobs) throw Error(E3MI_EINVAL, "internal: radial rows of too many layers");
+  RadialJobs jj{};
+  int PC = 0;
+  for (int k = 0; k < n_jobs; ++k) {
+    if (jobs[k].PC % 32) throw Error(E3MI_EUNSUPPORTED, "paths x channels must be a multiple of 32");
+    jj.j[k] = jobs[k];
+    PC = std::max(PC, jobs[k].PC);
+  }
   if (own && (e_first != 0 || e_end >= 0 || !n_own))
     throw Error(E3MI_EINVAL, "radial MLP per edge pair: needs the whole edge list and the pair owners");
   const int grid = tiles(e_end >= 0 ? (long)e_end - e_first : e_cap);
@@ -764,10 +786,10 @@ void launch_radial_rows(int n_basis, const float4* dvec, const int* row_ptr_x, i
   // over (the grid is sized for the list's capacity, about twice the pairs).
   // Both measured (us, split and not): 138 atoms 17 and 28, 64 molecules of 10
   // to 31 atoms 25 and 30, 1,205 atoms (no split left) 40 and 40.
-  const int split = std::max(1, std::min((PC + 127) / 128, 1024 / grid));
+  const int split = std::max(1, std::min((PC + 127) / 128, 1024 / (grid * n_jobs)));
   auto go = [&](auto nd) {
-    k_radial_rows<decltype(nd)::value><<<dim3(grid, split), 256, 0, st>>>(dvec, row_ptr_x, N, W1, W2, W3, PC, out, out_gap, out_ld,
-                                                             rc, p, e_first, e_end, own, n_own);
+    k_radial_rows<decltype(nd)::value><<<dim3(grid, split, n_jobs), 256, 0, st>>>(dvec, row_ptr_x, N, jj, rc, p, e_first,
+                                                                             e_end, own, n_own);
   };
   if (n_out == 1) go(std::integral_constant<int, 1>{});
   else if (n_out == 2) go(std::integral_constant<int, 2>{});

@@ -359,11 +359,22 @@ void launch_hvp_geo(const HvpArgs& a, long e_cap, int accumulate, float4* g, hip
 void launch_hvp_readout(const float* x, const float* xd, const float* Wr, const float* w2, int N, int B, int C,
                         float* xb, float* xc, hipStream_t st);
 // FP32 rows of R and its first n_out - 1 derivatives in the edge length (output
-// s from out + s out_gap, rows out_ld apart), of every edge pair (own, n_own) or
-// of the edges [e_first, e_end) (e_end < 0: all); W2 and W3 by kFragments
-void launch_radial_rows(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap, const float* W1,
-                        const __bf16* W2, const __bf16* W3, int PC, int n_out, float* out, long out_gap, int out_ld,
-                        float rc, int p, int e_first, int e_end, const int* own, const int* n_own, hipStream_t st);
+// s from out + s out_gap, rows out_ld apart; W2 and W3 by kFragments), or with PC
+// 0 of the second hidden layer [., 64] and its derivatives instead
+struct RadialJob {
+  const float* W1;
+  const __bf16 *W2, *W3;
+  int PC;
+  float* out;
+  long out_gap;
+  int out_ld;
+};
+constexpr int kMaxRadialJobs = 4;
+// up to kMaxRadialJobs of them in one launch, for every edge pair (own, n_own) or
+// the edges [e_first, e_end) (e_end < 0: all)
+void launch_radial_rows(int n_basis, const float4* dvec, const int* row_ptr_x, int N, long e_cap,
+                        const RadialJob* jobs, int n_jobs, int n_out, float rc, int p, int e_first, int e_end,
+                        const int* own, const int* n_own, hipStream_t st);
 
 // ---- product block of body order 2 (product.hip) -------------------------------------
 struct ProductArgs {
