@@ -591,15 +591,29 @@ e3mi_graph* new_graph(e3mi_model* M, int S, const int64_t* off, const double* po
 void prune(e3mi_graph* G, const double* pos, hipStream_t st) {
   const int N = G->N;
   const double rc2 = G->model->cfg.cutoff * G->model->cfg.cutoff;
-  launch_prune_count(pos, G->owner->as<int>(), G->box_d->as<double>(), G->row_ptr->as<int>(), G->src->as<int>(),
-                     G->shift->as<int>(), N, rc2, G->cnt->as<int>(), st);
-  launch_exclusive_scan(G->cnt->as<int>(), G->row_ptr_x->as<int>(), N, st);
-  launch_prune_compact(pos, G->owner->as<int>(), G->box_d->as<double>(), G->row_ptr->as<int>(), G->src->as<int>(),
-                       G->shift->as<int>(), G->row_ptr_x->as<int>(), N, rc2, G->src_x->as<int>(),
-                       G->dvec_x->as<float4>(), G->old_idx->as<int>(), G->new_idx->as<int>(), st);
-  launch_prune_rev(G->row_ptr_x->as<int>(), N, G->old_idx->as<int>(), G->new_idx->as<int>(), G->rev->as<int>(),
-                   G->rev_x->as<int>(), G->own_cnt->as<int>(), G->own_ptr->as<int>(), G->own->as<int>(),
-                   G->pair_of->as<int>(), st);
+  auto p = [](const std::unique_ptr<DevBuf>& b) { return b->as<int>(); };
+  PruneArgs a;
+  a.pos = pos;
+  a.box = G->box_d->as<double>();
+  a.owner = p(G->owner);
+  a.row_ptr = p(G->row_ptr);
+  a.src = p(G->src);
+  a.shift = p(G->shift);
+  a.rev = p(G->rev);
+  a.N = N;
+  a.rc2 = rc2;
+  a.cnt = p(G->cnt);
+  a.own_cnt = p(G->own_cnt);
+  a.row_ptr_x = p(G->row_ptr_x);
+  a.own_ptr = p(G->own_ptr);
+  a.src_x = p(G->src_x);
+  a.dvec_x = G->dvec_x->as<float4>();
+  a.old_idx = p(G->old_idx);
+  a.new_idx = p(G->new_idx);
+  a.rev_x = p(G->rev_x);
+  a.own = p(G->own);
+  a.pair_of = p(G->pair_of);
+  launch_prune(a, st);
 }
 
 // Channels per thread of the tensor-product kernels (threads per receiver = C / cpt).

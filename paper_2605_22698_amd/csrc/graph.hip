@@ -12,6 +12,8 @@
 // Edge key: (uint64)j << 24 | (nx+128) << 16 | (ny+128) << 8 | (nz+128),
 // so sorting keys sorts by (j, nx, ny, nz); the low 24 bits are the packed
 // image vector stored per edge.
+#include <type_traits>
+
 #include "common.h"
 #include "runtime.h"
 
@@ -300,44 +302,103 @@ __device__ __forceinline__ void edge_vec(const double* __restrict__ pos, const d
   dz = (pos[3 * j + 2] - pos[3 * i + 2]) + (double)unpack_n(s, 2) * L[2];
 }
 
+// Selection of the edges inside the cutoff, one wave per receiver: count them
+// and the pairs' owners, then write both lists from every row's first places,
+// then the reverse index. A pair's two edges have exactly opposite vectors and
+// equal lengths (edge_vec), so both are selected or neither; the one that comes
+// first in the list owns the pair, and a function of the length is computed
+// once per owner. Selection keeps the order, so the order in the skin list
+// decides. Bound: the launches (three; with the owners counted after the
+// reverse index and two scans there were six: 3,000 atoms 29 us, now 18).
 __global__ void __launch_bounds__(256) k_prune_count(const double* __restrict__ pos, const int* __restrict__ owner,
                                                      const double* __restrict__ box, const int* __restrict__ row_ptr,
-                                                     const int* __restrict__ src, const int* __restrict__ shift, int N,
-                                                     double rc2, int* __restrict__ cnt) {
+                                                     const int* __restrict__ src, const int* __restrict__ shift,
+                                                     const int* __restrict__ rev, int N, double rc2,
+                                                     int* __restrict__ cnt, int* __restrict__ own_cnt) {
   const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (i >= N) return;
   const double* L = box + 3 * owner[i];
   const int a = row_ptr[i], b = row_ptr[i + 1];
-  int total = 0;
+  int total = 0, owners = 0;
   for (int base = a; base < b; base += 64) {
     const int e = base + lane;
-    bool keep = false;
+    bool keep = false, first = false;
     if (e < b) {
       double dx, dy, dz;
       edge_vec(pos, L, i, src[e], shift[e], dx, dy, dz);
       keep = dx * dx + dy * dy + dz * dz < rc2;
+      first = e < rev[e];
     }
     total += __popcll(__ballot(keep));
+    owners += __popcll(__ballot(keep && first));
   }
-  if (lane == 0) cnt[i] = total;
+  if (lane == 0) {
+    cnt[i] = total;
+    own_cnt[i] = owners;
+  }
 }
 
+// Sums of a[0 .. n) and b[0 .. n) over the workgroup (256 threads)
+__device__ __forceinline__ int2 block_sums(const int* __restrict__ a, const int* __restrict__ b, int n) {
+  __shared__ int2 red[4];
+  int2 s = make_int2(0, 0);
+  for (int k = threadIdx.x; k < n; k += 256) {
+    s.x += a[k];
+    s.y += b[k];
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    s.x += __shfl_xor(s.x, off);
+    s.y += __shfl_xor(s.y, off);
+  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  return make_int2(red[0].x + red[1].x + red[2].x + red[3].x, red[0].y + red[1].y + red[2].y + red[3].y);
+}
+
+// SUM: row_ptr_x and own_ptr are formed here, every workgroup adding up the rows
+// before its own; else they are given.
+template <bool SUM>
 __global__ void __launch_bounds__(256) k_prune_compact(const double* __restrict__ pos, const int* __restrict__ owner,
                                                        const double* __restrict__ box, const int* __restrict__ row_ptr,
                                                        const int* __restrict__ src, const int* __restrict__ shift,
-                                                       const int* __restrict__ row_ptr_x, int N, double rc2,
+                                                       const int* __restrict__ rev, const int* __restrict__ cnt,
+                                                       const int* __restrict__ own_cnt, int* __restrict__ row_ptr_x,
+                                                       int* __restrict__ own_ptr, int N, double rc2,
                                                        int* __restrict__ src_x, float4* __restrict__ dvec_x,
-                                                       int* __restrict__ old_idx, int* __restrict__ new_idx) {
-  const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+                                                       int* __restrict__ old_idx, int* __restrict__ new_idx,
+                                                       int* __restrict__ own, int* __restrict__ pair_of) {
+  const int i0 = blockIdx.x * 4, i = i0 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
+  int2 before = make_int2(0, 0);
+  if constexpr (SUM) before = block_sums(cnt, own_cnt, i0);
   if (i >= N) return;
+  int out, pair;
+  if constexpr (SUM) {
+    out = before.x;
+    pair = before.y;
+    for (int k = i0; k < i; ++k) {
+      out += cnt[k];
+      pair += own_cnt[k];
+    }
+    if (lane == 0) {
+      row_ptr_x[i] = out;
+      own_ptr[i] = pair;
+      if (i == N - 1) {
+        row_ptr_x[N] = out + cnt[i];
+        own_ptr[N] = pair + own_cnt[i];
+      }
+    }
+  } else {
+    out = row_ptr_x[i];
+    pair = own_ptr[i];
+  }
   const double* L = box + 3 * owner[i];
   const int a = row_ptr[i], b = row_ptr[i + 1];
-  int out = row_ptr_x[i];
   for (int base = a; base < b; base += 64) {
     const int e = base + lane;
-    bool keep = false;
+    bool keep = false, first = false;
     double dx = 0, dy = 0, dz = 0, r2 = 0;
     int j = 0;
     if (e < b) {
@@ -345,76 +406,53 @@ __global__ void __launch_bounds__(256) k_prune_compact(const double* __restrict_
       edge_vec(pos, L, i, j, shift[e], dx, dy, dz);
       r2 = dx * dx + dy * dy + dz * dz;
       keep = r2 < rc2;
+      first = e < rev[e];
     }
-    const uint64_t m = __ballot(keep);
-    const int before = __popcll(m & ((1ull << lane) - 1ull));
+    const uint64_t m = __ballot(keep), mo = __ballot(keep && first), below = (1ull << lane) - 1ull;
     if (e < b) {
       if (keep) {
-        const int o = out + before;
+        const int o = out + __popcll(m & below);
         src_x[o] = j;
         dvec_x[o] = make_float4((float)dx, (float)dy, (float)dz, (float)sqrt(r2));
         old_idx[o] = e;
         new_idx[e] = o;
+        if (first) {
+          const int p = pair + __popcll(mo & below);
+          own[p] = o;
+          pair_of[o] = p;
+        }
       } else {
         new_idx[e] = -1;
       }
     }
     out += __popcll(m);
+    pair += __popcll(mo);
   }
 }
 
-// The pruned reverse index, and per receiver the number of edges that own
-// their pair: e owns {e, rev(e)} when e < rev(e), or alone when its reverse
-// is not listed. The two edges of a pair have exactly opposite vectors and
-// equal lengths, so a function of the length is computed once per owner.
-__device__ __forceinline__ bool owns_pair(int e, int re) { return re < 0 || e < re; }
-
+// The pruned reverse index, and the pair index of the edges that are not their
+// pair's owner.
 __global__ void __launch_bounds__(256) k_prune_rev(const int* __restrict__ row_ptr_x, int N,
                                                    const int* __restrict__ old_idx, const int* __restrict__ new_idx,
                                                    const int* __restrict__ rev_skin, int* __restrict__ rev_x,
-                                                   int* __restrict__ own_cnt) {
+                                                   int* __restrict__ pair_of) {
   const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (i >= N) return;
-  const int a = row_ptr_x[i], b = row_ptr_x[i + 1];
-  int total = 0;
-  for (int base = a; base < b; base += 64) {
-    const int e = base + lane;
-    bool own = false;
-    if (e < b) {
-      const int re = new_idx[rev_skin[old_idx[e]]];
-      rev_x[e] = re;
-      own = owns_pair(e, re);
-    }
-    total += __popcll(__ballot(own));
+  const int b = row_ptr_x[i + 1];
+  for (int e = row_ptr_x[i] + lane; e < b; e += 64) {
+    const int re = new_idx[rev_skin[old_idx[e]]];
+    rev_x[e] = re;
+    if (re >= 0 && re < e) pair_of[e] = pair_of[re];
   }
-  if (lane == 0) own_cnt[i] = total;
 }
 
-// the owners in edge order, own[own_ptr[i] + k] = the k-th owner of row i,
-// and each edge's pair index (its owner's position in own)
-__global__ void __launch_bounds__(256) k_pair_owners(const int* __restrict__ row_ptr_x, int N,
-                                                     const int* __restrict__ rev_x, const int* __restrict__ own_ptr,
-                                                     int* __restrict__ own, int* __restrict__ pair_of) {
-  const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (i >= N) return;
-  const int a = row_ptr_x[i], b = row_ptr_x[i + 1];
-  int out = own_ptr[i];
-  for (int base = a; base < b; base += 64) {
-    const int e = base + lane;
-    const int re = e < b ? rev_x[e] : -1;
-    const bool o = e < b && owns_pair(e, re);
-    const uint64_t m = __ballot(o);
-    if (o) {
-      const int p = out + __popcll(m & ((1ull << lane) - 1ull));
-      own[p] = e;
-      pair_of[e] = p;
-      if (re >= 0) pair_of[re] = p;
-    }
-    out += __popcll(m);
-  }
-}
+// Rows up to which every workgroup of k_prune_compact adds up the counts before
+// its own (N^2 / 2 of them in all) instead of two scans in launches of their own.
+// Both measured, us of the selection (sums, scans): 24 atoms 10 and 14, 3,000
+// atoms 18 and 25, 7,032 atoms 24 and 30, 20,000 atoms 98 and 105; the sums grow
+// with the square.
+constexpr int kSumRows = 16384;
 
 inline int blocks(long n, int t) { return (int)((n + t - 1) / t); }
 
@@ -467,27 +505,24 @@ void launch_unpack_shift(const int* shift_packed, int E, int* shift3, hipStream_
   if (E == 0) return;
   k_unpack_shift<<<blocks(E, 256), 256, 0, st>>>(shift_packed, E, shift3);
 }
-void launch_prune_count(const double* pos, const int* owner, const double* box, const int* row_ptr, const int* src,
-                        const int* shift, int N, double rc2, int* cnt, hipStream_t st) {
-  if (N == 0) return;
-  k_prune_count<<<blocks((long)N * 64, 256), 256, 0, st>>>(pos, owner, box, row_ptr, src, shift, N, rc2, cnt);
-}
-void launch_prune_compact(const double* pos, const int* owner, const double* box, const int* row_ptr, const int* src,
-                          const int* shift, const int* row_ptr_x, int N, double rc2, int* src_x, float4* dvec_x,
-                          int* old_idx, int* new_idx, hipStream_t st) {
-  if (N == 0) return;
-  k_prune_compact<<<blocks((long)N * 64, 256), 256, 0, st>>>(pos, owner, box, row_ptr, src, shift, row_ptr_x, N, rc2,
-                                                              src_x, dvec_x, old_idx, new_idx);
-}
-void launch_prune_rev(const int* row_ptr_x, int N, const int* old_idx, const int* new_idx, const int* rev_skin,
-                      int* rev_x, int* own_cnt, int* own_ptr, int* own, int* pair_of, hipStream_t st) {
-  if (N == 0) {
-    launch_exclusive_scan(own_cnt, own_ptr, 0, st);  // own_ptr[0] = 0
-    return;
+void launch_prune(const PruneArgs& a, hipStream_t st) {
+  const int N = a.N, grid = blocks((long)N * 64, 256);
+  if (N > 0)
+    k_prune_count<<<grid, 256, 0, st>>>(a.pos, a.owner, a.box, a.row_ptr, a.src, a.shift, a.rev, N, a.rc2, a.cnt,
+                                        a.own_cnt);
+  if (N == 0 || N > kSumRows) {
+    launch_exclusive_scan(a.cnt, a.row_ptr_x, N, st);
+    launch_exclusive_scan(a.own_cnt, a.own_ptr, N, st);
   }
-  k_prune_rev<<<blocks((long)N * 64, 256), 256, 0, st>>>(row_ptr_x, N, old_idx, new_idx, rev_skin, rev_x, own_cnt);
-  launch_exclusive_scan(own_cnt, own_ptr, N, st);
-  k_pair_owners<<<blocks((long)N * 64, 256), 256, 0, st>>>(row_ptr_x, N, rev_x, own_ptr, own, pair_of);
+  if (N == 0) return;
+  auto compact = [&](auto sum) {
+    k_prune_compact<decltype(sum)::value><<<grid, 256, 0, st>>>(
+        a.pos, a.owner, a.box, a.row_ptr, a.src, a.shift, a.rev, a.cnt, a.own_cnt, a.row_ptr_x, a.own_ptr, N, a.rc2,
+        a.src_x, a.dvec_x, a.old_idx, a.new_idx, a.own, a.pair_of);
+  };
+  if (N > kSumRows) compact(std::false_type{});
+  else compact(std::true_type{});
+  k_prune_rev<<<grid, 256, 0, st>>>(a.row_ptr_x, N, a.old_idx, a.new_idx, a.rev, a.rev_x, a.pair_of);
 }
 
 }  // namespace e3mi

@@ -203,16 +203,21 @@ void launch_edges(bool fill, const double* pos, const int* owner, const GridPlan
 void launch_sort_rows(const int* row_ptr, int N, uint64_t* keys, int* src, int* shift, hipStream_t st);
 void launch_reverse(const int* row_ptr, const uint64_t* keys, int N, int* rev, int* err, hipStream_t st);
 void launch_unpack_shift(const int* shift_packed, int E, int* shift3, hipStream_t st);
-void launch_prune_count(const double* pos, const int* owner, const double* box, const int* row_ptr,
-                        const int* src, const int* shift, int N, double rc2, int* cnt, hipStream_t st);
-void launch_prune_compact(const double* pos, const int* owner, const double* box, const int* row_ptr,
-                          const int* src, const int* shift, const int* row_ptr_x, int N, double rc2,
-                          int* src_x, float4* dvec_x, int* old_idx, int* new_idx, hipStream_t st);
-// rev_x, the pair owners (own_cnt [N], own_ptr [N + 1], own [E]; own_ptr[N]
-// is their count on the device) and each edge's pair index (pair_of [E])
-void launch_prune_rev(const int* row_ptr_x, int N, const int* old_idx, const int* new_idx,
-                      const int* rev_skin, int* rev_x, int* own_cnt, int* own_ptr, int* own, int* pair_of,
-                      hipStream_t st);
+// The edges inside the cutoff (rc2: its square) out of the skin list (row_ptr,
+// src, shift, rev): row_ptr_x [N + 1], src_x, dvec_x and rev_x, the skin edge of
+// each (old_idx) and back (new_idx, -1: not selected), the pair owners in edge
+// order (own_ptr [N + 1], own; own_ptr[N] is their count on the device) and each
+// edge's pair index (pair_of); cnt and own_cnt are scratch [N]
+struct PruneArgs {
+  const double *pos, *box;
+  const int *owner, *row_ptr, *src, *shift, *rev;
+  int N;
+  double rc2;
+  int *cnt, *own_cnt, *row_ptr_x, *own_ptr, *src_x;
+  float4* dvec_x;
+  int *old_idx, *new_idx, *rev_x, *own, *pair_of;
+};
+void launch_prune(const PruneArgs& a, hipStream_t st);
 
 // ---- tensor product (tp.hip) ---------------------------------------------------
 struct TpArgs {

@@ -77,3 +77,28 @@ def test_pairs_larger_box(precision, correlation):
     record("pairs_vs_per_edge", precision=precision, correlation=correlation, max_abs=d, rel_to_max_abs_F=d / fmax)
     assert np.array_equal(E0, E1) and np.array_equal(Ei0, Ei1)
     assert d <= (1e-5 if precision == 0 else 1e-2) * fmax
+
+
+@pytest.mark.parametrize("n,species_seed", [(1, 5), (4, 6), (5, 7), (16384, 8), (16385, 9)])
+def test_selected_edges_and_pairs_at_block_edges(n, species_seed):
+    # rows per workgroup (4) and the row count from which the first places of the
+    # rows come from scans: the number of selected edges is the oracle's, and every
+    # pair has one owner whose radial weights both edges read (energies and forces
+    # are those of the edge-by-edge evaluation)
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=2, n_species=2, cutoff=2.5, avg_neighbors=6.5)
+    b = synth.jittered_lattice(n, 0.1, 0.3, 2, np.random.default_rng(species_seed))
+    m = model(cfg, 196)
+    E, F, Ei, g = gpu_energy_forces(m, b, skin=0.3)
+    x = b.pos
+    L = np.diagonal(np.asarray(b.cell).reshape(-1, 3, 3)[0])
+    pbc = np.asarray(b.pbc).reshape(-1, 3)[0]
+    if n > 5:
+        from scipy.spatial import cKDTree
+        tree = cKDTree(np.mod(x, L) if pbc.any() else x, boxsize=L if pbc.any() else None)
+        assert g.last_edge_count() == 2 * len(tree.query_pairs(2.5))
+    m.set_flags(radial_per_edge=True)
+    E1, F1, _, g1 = gpu_energy_forces(m, b, skin=0.3)
+    assert g1.last_edge_count() == g.last_edge_count()
+    assert abs(E[0] - E1[0]) <= 1e-6 * np.abs(Ei).sum()
+    # (a lone atom among its images: forces of rounding alone)
+    assert np.abs(F - F1).max() <= 1e-5 * max(np.abs(F1).max(), 1e-2)
