@@ -177,7 +177,8 @@ int e3mi_energy_forces(e3mi_model* model, e3mi_graph* graph, const double* pos, 
  * The graph must have been built beforehand (e3mi_build_graph allocates).
  * Errors: ENOMEM when the evaluation needs more than the array (outputs are
  * then unspecified; roughly N x 16 x C x 4 bytes per feature buffer plus
- * 4 x P x C bytes per edge for each layer's radial weights and their adjoint),
+ * 4 x P x C bytes per edge for each layer's radial weights and their
+ * derivative, stored once per pair of edges),
  * EINVAL when a layer's per-edge radial weights would have to be split into
  * receiver chunks. The array keeps the last call's contents; every buffer the
  * evaluation reads is written first. All calls on one GPU share the array:
@@ -246,39 +247,42 @@ int e3mi_hessian_vectors(e3mi_model* model, e3mi_graph* graph, const double* pos
 /*   An edge and its reverse have exactly opposite vectors (the same FP64
  *     difference of the two positions plus the image shift, negated), so
  *     equal lengths and equal radial weights R. By default a layer whose
- *     edges are all in memory at once (one receiver chunk) runs its radial
- *     MLP once per edge pair. In an energy+forces call it stores R once per
- *     pair (the same values as edge by edge; the second-order passes write
- *     them to both edges' rows). Its adjoint runs once per pair on the sum of
- *     the two edges' dR (forces agree with the edge-by-edge adjoint to
- *     rounding). The species-factorised first layer's radial hidden layers
- *     run once per pair likewise.
+ *     rows of radial weights are all in memory at once runs its radial MLP
+ *     once per edge pair and stores R (in FP32 with its derivative in the
+ *     length, R', which takes the place of the MLP's adjoint) once per pair.
+ *     The BF16 mode's adjoint runs once per pair on the sum of the two edges'
+ *     dR (forces agree with the edge-by-edge adjoint to rounding). The
+ *     species-factorised first layer's radial hidden layers run once per pair
+ *     likewise.
  *   E3MI_FLAG_RADIAL_PER_EDGE (8) runs all of them per edge instead, as
  *     layers in receiver chunks always do; results are then bitwise those of
  *     any chunking. */
 #define E3MI_FLAG_RADIAL_PER_EDGE 8
 int e3mi_model_set_flags(e3mi_model* model, int flags);
 
-/* Most bytes of per-edge radial weights R (and of their adjoint) that an
- * energy_forces call holds at once for the layers evaluated with R in memory
- * (middle layers, and every layer of a model with the product block); default
- * 8 GiB, at least 1 MiB. Larger edge sets are processed in chunks of whole
- * receivers (the adjoint then recomputes R per chunk), so a 100,000-atom,
- * 9-million-edge, 3-layer model (about 106 GB of R per layer in FP32, Section
- * 4's tensor product at scale) runs in bounded memory. The chunking reads the
- * pruned row pointer back to the host once per call. Chunked layers run the
- * radial MLP edge by edge; results are bitwise those of the unchunked
- * evaluation with E3MI_FLAG_RADIAL_PER_EDGE (each receiver's and each
- * sender's sums run in the same order whatever the chunks), and agree with
- * the default per-pair radial adjoint of an unchunked layer to rounding. */
+/* Most bytes of per-edge radial weights R (in FP32 as many again of R', in the
+ * BF16 mode of their adjoint) that an energy_forces call holds at once for the
+ * layers evaluated with R in memory (middle layers, and every layer of a model
+ * with the product block); default 8 GiB, at least 1 MiB. Larger edge sets are
+ * processed in chunks of whole receivers unless their rows are kept whole
+ * (below), so a 100,000-atom, 9-million-edge, 3-layer model (about 106 GB of R
+ * per layer in FP32 edge by edge, Section 4's tensor product at scale) runs in
+ * bounded memory. The chunking reads the pruned row pointer back to the host
+ * once per call. Chunked layers run the radial MLP edge by edge (the adjoint
+ * again per chunk); results are bitwise those of the unchunked evaluation with
+ * E3MI_FLAG_RADIAL_PER_EDGE (each receiver's and each sender's sums run in the
+ * same order whatever the chunks), and in the BF16 mode agree with the default
+ * per-pair radial adjoint of an unchunked layer to rounding. */
 int e3mi_model_set_r_chunk_bytes(e3mi_model* model, size_t bytes);
 
-/* Most bytes of per-edge R kept for every edge inside the cutoff, summed
- * over the layers evaluated in receiver chunks (default 160 GiB of the 288 GB
- * of HBM; 0: never). Layers are taken in order while the sum fits; such a layer's
- * forward pass writes every chunk's R into one buffer and its adjoint reads
- * it there instead of recomputing R chunk by chunk (dR and the sender
- * messages stay chunk-sized). Results are bitwise the same either way. */
+/* Most bytes of radial weights kept for every edge inside the cutoff, summed
+ * over the layers too large for one receiver chunk (default 160 GiB of the 288
+ * GB of HBM; 0: never). Layers are taken in order while the sum fits. In FP32
+ * such a layer's rows of R and R' are evaluated at once, per edge pair; in the
+ * BF16 mode its forward pass writes every chunk's R into one buffer and its
+ * adjoint reads it there instead of recomputing R chunk by chunk. dR and the
+ * sender messages stay chunk-sized. Results are the same either way (bitwise
+ * with E3MI_FLAG_RADIAL_PER_EDGE). */
 int e3mi_model_set_r_keep_bytes(e3mi_model* model, size_t bytes);
 
 /* Replace the weights (FP64 in host or device memory, same configuration and

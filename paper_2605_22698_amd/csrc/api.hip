@@ -980,13 +980,13 @@ void radial_rows(e3mi_model* M, e3mi_graph* G, int t, const RChunk* ch, bool der
 
 // The first layer's hidden rows (factorised) and R and R' of the layers that
 // keep them whole need the edges' lengths alone: up to this much room for R
-// (about half is used) they share one launch, at the front, and small systems
-// wait for one chain of hidden layers. Past it the first layer's own streams
-// would push R out of the last-level cache (256 MB) before it is read. Both
-// measured, us a call, together and apart: 24 atoms 80 and 87, 138 atoms (9 MB)
-// 121 and 126, 64 molecules 361 and 378, an MD step of 1,205 atoms (176 MB) 263
-// and 273, of 3,000 (600 MB) 568 and 552, 64 charged clusters (620 MB) 852 and 840.
-constexpr size_t kRowsTogether = 256UL << 20;
+// they share one launch, at the front, and small systems wait for one chain of
+// hidden layers. Past it the first layer's own streams would push R out of the
+// last-level cache (256 MB) before it is read. Both measured, us a call, together
+// and apart: 24 atoms 80 and 87, 138 atoms (5 MB) 121 and 126, 64 molecules 361
+// and 378, an MD step of 1,205 atoms (88 MB) 263 and 273, of 3,000 (300 MB) 568
+// and 552, 64 charged clusters (310 MB) 852 and 840.
+constexpr size_t kRowsTogether = 128UL << 20;
 
 // Launches them (together: R too); returns whether R was among them.
 bool first_rows(e3mi_model* M, e3mi_graph* G, bool fact, bool whole_rows, hipStream_t st) {
@@ -1056,6 +1056,8 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
   ensure(w.h[0], a, sizeof(float) * (size_t)N * C);
   long a_max = 0;
   size_t dr_bytes = 0, kept = 0;
+  // rows of radial weights: one of every two edges of the list owns a pair
+  const size_t rows_cap = (M->edge_pairs ? (size_t)Ecap / 2 : (size_t)Ecap) + 1;
   w.r_whole.assign(T + 1, 0);
   w.r_compact.assign(T + 1, 0);
   for (int t = 1; t <= T; ++t) {
@@ -1065,16 +1067,16 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     a_max = std::max(a_max, L.a_per_atom);
     if (derivs) {
       w.R3.resize(T + 1);
-      ensure(w.R3[t], a, sizeof(float) * 3 * (size_t)(Ecap + 1) * L.p_used * C);
+      ensure(w.R3[t], a, sizeof(float) * 3 * rows_cap * L.p_used * C);
       continue;
     }
     if (t == 1 && factorised_first(M) && !keep_A) continue;
     if (fused_last(M, L, keep_A, bf16)) continue;
     if (!bf16) {
-      // weight gradients keep the rows of every edge (skin-list capacity)
       w.r_rows.resize(T + 1);
       if (keep_A) w.r_whole[t] = 1;
-      w.r_rows[t] = keep_A ? (size_t)(Ecap + 1) : r_rows_plan(M, G, t, L.p_used * C, kept, st);
+      w.r_rows[t] = keep_A ? rows_cap : r_rows_plan(M, G, t, L.p_used * C, kept, st);
+      if (w.r_whole[t]) w.r_rows[t] = std::min(w.r_rows[t], rows_cap);
       ensure(w.R[t], a, 2 * sizeof(float) * w.r_rows[t] * L.p_used * C);
       continue;
     }
@@ -1121,7 +1123,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
   const int S64 = c.n_species * c.radial_hidden;
   if (fact) {
     ensure(w.G1, a, sizeof(float) * (size_t)N * M->plans[0].nc_a * S64);
-    ensure(w.H2f, a, sizeof(float) * 2 * (size_t)c.radial_hidden * (size_t)(Ecap + 1));
+    ensure(w.H2f, a, sizeof(float) * 2 * (size_t)c.radial_hidden * rows_cap);
     if (!derivs) ensure(w.dG1, a, sizeof(float) * (size_t)N * M->plans[0].nc_a * S64);
   }
   // product block: the mix writes A~ (no self connection); B follows, then

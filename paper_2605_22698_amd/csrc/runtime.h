@@ -420,11 +420,10 @@ void launch_coulomb_dq(const int64_t* off, const int* owner, int S, int N, const
                        const float* wq, int C, float* dh, hipStream_t st);
 
 // ---- radial MLP (radial.hip) ---------------------------------------------------------
-// R (dR) is FP32, or BF16 when r_bf16 is set
-// BF16 copies of a layer's radial weights (rounded to nearest even), laid out
-// for the BF16 matrix-core steps: W2^T and W2 [64][64], W3^T [PC][64] and W3
-// (used columns) in slabs of 32 columns, [PC / 32][64][32]. Needed when bf16
-// is set.
+// The BF16 mode's R and the adjoint of its MLP; R and dR are FP32, or BF16 when
+// r_bf16 is set. BF16 copies of a layer's radial weights (rounded to nearest
+// even), laid out for the BF16 matrix-core steps: W2^T and W2 [64][64], W3^T
+// [PC][64] and W3 (used columns) in slabs of 32 columns, [PC / 32][64][32].
 struct RadialBf16 {
   const __bf16* W2T = nullptr;
   const __bf16* W2 = nullptr;

@@ -1,7 +1,7 @@
-// Adjoint of the tensor product + neighbour sum of a scalar-output layer
-// (only the paths (l, l, 0): the last layer, whose outputs only the readout
-// reads), from the senders' side, for 64 x CH channels (CH adjacent channels
-// per lane, loaded as one vector).
+// Tensor product + neighbour sum of a scalar-output layer (only the paths
+// (l, l, 0): the last layer, whose outputs only the readout reads): the FP32
+// forward, and the adjoint from the senders' side, for 64 x CH channels (CH
+// adjacent channels per lane, loaded as one vector).
 //
 // For an edge e = (i <- j) with direction d_e the forward gives
 //   A[i,p,k] = nu^-1 sum_e R[e,p,k] T[e,p,k],  T[e,p,k] = sum_m C^p[m,m,0] h[j,k,l m] Y_e[l m],
