@@ -28,10 +28,30 @@ sys.path.insert(0, ROOT)
 
 PEAK_HBM = 8.0e12        # bytes/s
 PEAK_FP32_MFMA = 157.3e12
+PEAK_FP32_SPLIT = 2.5e15 / 6   # FP32 products as six BF16 ones on the dense BF16 matrix cores
 PEAK_FP32_VALU = 157.3e12           # datasheet, counts packed FP32
 PEAK_FP32_VALU_NONPACKED = 78.65e12  # 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz
-# kernels that run a stage in place of the general one: (stage, last layer) -> kernel
-KERNEL_OF_STAGE = {("tp_bwd_edge", True): "k_tps_bwd_sender", ("tp_bwd_node", False): "k_tp_msg_node"}
+
+
+def kernel_of_stage(stage, layer, layers, every_path_last=False):
+    """The FP32 kernel that takes most of a stage (layers > 1)."""
+    if stage == "radial_fwd":
+        return "k_radial_rows"
+    scalar = layer == layers and not every_path_last
+    if stage == "tp_fwd":
+        return "k_tps_fwd" if scalar else "k_tp_full_fwd"
+    if stage == "tp_bwd_edge":
+        return "k_tps_sender" if scalar else "k_tp_full_bwd"
+    return "k_tp_msg_node" if stage == "tp_bwd_node" else "k_" + stage
+
+
+def matrix_peak(stage):
+    """Peak of the matrix cores a stage's dense products run on, or None."""
+    if stage == "radial_fwd":
+        return PEAK_FP32_SPLIT
+    return PEAK_FP32_MFMA if stage.startswith(("first", "last")) else None
+
+
 KAPPA = 0.009648533
 
 
@@ -61,10 +81,10 @@ def layer_paths(cfg, t):
 
 
 def work_model(cfg, t, E, N, pairs=False):
-    """Algorithmic (flops, HBM bytes) of one launch of each stage of layer t.
-    pairs: the layer's radial MLP runs once per edge pair and R is stored once
-    per pair (an unchunked layer in an energy+forces evaluation); every pruned
-    edge has its reverse in the list, so there are E / 2 pairs."""
+    """Algorithmic (flops, HBM bytes) of one launch of each stage of layer t of
+    an FP32 energy+forces evaluation. pairs: the layer's radial MLP runs once
+    per edge pair and R and R' are stored once per pair (an unchunked layer);
+    every pruned edge has its reverse in the list, so there are E / 2 pairs."""
     C = cfg.channels
     P = (E + 1) // 2 if pairs else E   # radial MLP evaluations = R rows
     ps = layer_paths(cfg, t)
@@ -75,16 +95,14 @@ def work_model(cfg, t, E, N, pairs=False):
     mlp_hidden = 2 * (cfg.n_basis * H + H * H)
     tp_flops = 2 * C * sum(nz + 2 * l3 + 1 for (_, _, l3, nz) in ps)
     out = {}
-    # species-factorised first layer: the hidden MLP's pre-activation P2 once
-    # per edge pair (the first layer is never chunked; stored, 4 H bytes),
-    # the outer product per edge, G per atom; the adjoint reads P2 per edge
-    # (no hidden-layer recompute)
+    # species-factorised first layer: [H2 | H2'] once per edge pair (8 H bytes),
+    # the outer product per edge, G per atom; the adjoint contracts both with dG
     nc3 = (cfg.lmax + 1) ** 2 if cfg.layers > 1 else 1
     s64 = cfg.n_species * H
     Ph = (E + 1) // 2
-    out["first_fwd"] = (Ph * mlp_hidden + E * 2 * H * nc3, Ph * (16 + 4 * H) + E * (24 + 4 * H) + N * 4 * nc3 * s64)
-    out["first_bwd"] = (E * (2 * H * H + 2 * H * cfg.n_basis + 4 * H * nc3),
-                        E * (24 + 16 + 4 * H) + N * 4 * nc3 * s64)
+    out["first_fwd"] = (2 * Ph * mlp_hidden + E * 2 * H * nc3,
+                        Ph * (16 + 8 * H) + E * 24 + Ph * 4 * H + N * 4 * nc3 * s64)
+    out["first_bwd"] = (E * 4 * H * nc3, E * (24 + 16 + 64) + Ph * 8 * H + N * 4 * nc3 * s64)
     # fused last layer (scalar outputs): hidden MLP, T = sum_e H2 s^T and its
     # W3 contraction forward; R recomputed, dH2 = W3 dR, MLP adjoint, and the
     # contracted-feature terms backward. Bytes: edge vectors, h once per atom,
@@ -95,13 +113,9 @@ def work_model(cfg, t, E, N, pairs=False):
                        E * 20 + N * 4 * (NY * C + NL * C))
     out["last_bwd"] = (E * (mlp_hidden + 4 * H * NL * C + 2 * H * H + 2 * H * cfg.n_basis + 6 * C * NY),
                        E * (20 + 32) + N * 4 * (3 * NY * C + NL * C))
-    # radial MLP: flops on the matrix cores; bytes = edge vectors in, R out
-    # (per pair: the owner's edge vector and its owner and reverse indices)
-    out["radial_fwd"] = (P * (mlp_hidden + 2 * H * PC), P * (16 + 4 * PC + (8 if pairs else 0)))
-    # adjoint: recompute hidden layers, dR W3^T, dH2 W2^T, dH1 W1^T; dR and dY
-    # of every edge in (summed per pair), g read+write
-    out["radial_bwd"] = (P * (mlp_hidden + 2 * H * PC + 2 * H * H + 2 * H * cfg.n_basis),
-                         E * (16 + 4 * PC + 64 + 32) + (P * 8 if pairs else 0))
+    # radial MLP: R and its derivative R'; flops on the matrix cores; bytes =
+    # edge vectors in, both rows out (per pair: the owner's vector and index)
+    out["radial_fwd"] = (2 * P * (mlp_hidden + 2 * H * PC), P * (16 + 8 * PC + (4 if pairs else 0)))
     # tensor product + neighbour sum: R streamed once (each pair's row, found
     # through the edge's pair index), h read and A written once per atom
     r_in = P * 4 * PC + (E * 4 if pairs else 0)
@@ -109,47 +123,32 @@ def work_model(cfg, t, E, N, pairs=False):
     edge_adj = E * (tp_flops + 2 * C * sum(nz for *_, nz in ps) + 2 * C * nout)
     node_adj = E * 2 * C * sum(nz + 2 * l3 + 1 for (_, _, l3, nz) in ps)
     if t == cfg.layers and C in (64, 128, 256) and getattr(cfg, "correlation", 1) != 2:
-        # scalar-output layer: the sender-side adjoint (tps.hip) gives dR, dY
-        # and dh in one pass: R read once, dR and dY written, edge vector, sender
-        # and reverse index per edge; h, dA and dh (read and written) once per atom
+        # scalar-output layer: the sender-side adjoint (tps.hip) gives dE/dr, dY
+        # and dh in one pass: R and R' read once, a row of 16 written, edge vector,
+        # sender and reverse index per edge; h, dA and dh (read and written) once
+        # per atom
         out["tp_bwd_edge"] = (edge_adj + (node_adj if t > 1 else 0),
-                              r_in + E * (4 * PC + 64 + 16 + 4 + 4)
+                              r_in + P * 4 * PC + E * (64 + 16 + 4 + 4)
                               + N * 4 * C * (nc_in + nout + (2 * nc_in if t > 1 else 0)))
     elif t > 1:
         # every path: the edge adjoint also writes each edge's sender-gradient
         # message (nc_in x C values); the node pass reads the messages of each
         # sender's edges (and the reverse index) and reads/writes dh once
         out["tp_bwd_edge"] = (edge_adj + 2 * E * C * sum(nz for *_, nz in ps),
-                              r_in + E * (4 * PC + 16 + 4 + 64 + 4 * nc_in * C) + N * 4 * C * (nc_in + nout))
+                              r_in + P * 4 * PC + E * (16 + 4 + 64 + 4 * nc_in * C) + N * 4 * C * (nc_in + nout))
         out["tp_bwd_node"] = (E * nc_in * C, E * (4 * nc_in * C + 8) + N * 4 * C * 2 * nc_in)
     else:
-        out["tp_bwd_edge"] = (edge_adj, r_in + E * (4 * PC + 16 + 4 + 64) + N * 4 * C * (nc_in + nout))
+        out["tp_bwd_edge"] = (edge_adj, r_in + P * 4 * PC + E * (16 + 4 + 64) + N * 4 * C * (nc_in + nout))
         out["tp_bwd_node"] = (node_adj, r_in + E * (16 + 4) + N * 4 * C * (nc_in + nout))
     return out
 
 
-def fp32_row_pattern(cfg, kern, t):
-    """The FP32-mode instantiation of a per-edge kernel of layer t, as the
-    100,000-atom traffic summary lists it: the radial kernels serve several
-    layers (rows split by layer), the tensor-product kernels are per layer
-    kind by their template arguments (1: every path, 2: scalar outputs)."""
-    kind = 2 if t == cfg.layers else 1
-    # chunked layers run the per-edge instantiations (radial mode 0 / no
-    # pairs, R rows without the pair index)
-    if kern.startswith("k_radial"):
-        return re.escape(kern) + r"<8, (\d+, )?false, float, (0|false)> \[layer %d\]" % t
-    if kern in ("k_tp_fwd", "k_tp_bwd_edge", "k_tps_bwd_sender"):
-        return re.escape(kern) + r"<%d, %d, \d+(, (true|false))?, float(, false)?>" % (cfg.lmax, kind)
-    return re.escape(kern) + r"(<.*>)?"
-
-
-def measured_traffic(kernel, summary="md_step_3000_hbm_traffic.md", pattern=None):
+def measured_traffic(kernel, summary="md_step_3000_hbm_traffic.md"):
     """HBM bytes per launch of a kernel (FETCH_SIZE + WRITE_SIZE,
     copy-calibrated) from a committed counter summary, or None when the
     kernel's source file has changed since the counters were taken. kernel:
     the name as listed, with its template arguments or without (the first
-    listed); pattern (a regular expression), when given, must match the
-    listed name whole instead."""
+    listed)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", summary)
     if not os.path.exists(path):
@@ -159,8 +158,7 @@ def measured_traffic(kernel, summary="md_step_3000_hbm_traffic.md", pattern=None
         if not m:
             continue
         name = m.group(1)
-        hit = re.fullmatch(pattern, name) if pattern else kernel in (name, name.split("<")[0])
-        if not hit:
+        if kernel not in (name, name.split("<")[0]):
             continue
         src = os.path.join(ROOT, "paper_2605_22698_amd", "csrc", m.group(4))
         if not os.path.exists(src) or hashlib.sha256(open(src, "rb").read()).hexdigest()[:16] != m.group(5):
@@ -547,9 +545,10 @@ def scale_run(e3, synth, torch, dev, steps, warmup, log, cpu_baseline=True):
     or earlier, so a rebuild falls inside the timed region once steps >= 20);
     the dominant stage of an FP32 step against its roofline; the errors of
     both precisions against the FP64 oracle on the independent 2,000-atom box;
-    the oracle timed on a bounded sample. Its middle layer keeps per-edge R,
-    about 106 GB in FP32 for the 9 million edges, so it runs in receiver
-    chunks of at most 8 GiB."""
+    the oracle timed on a bounded sample. In FP32 R and R' of both per-edge
+    layers are kept per edge pair, 120 GB for the 9 million edges; the middle
+    layer's adjoint runs in receiver chunks (its messages), and the BF16 mode in
+    chunks of at most 8 GiB of R."""
     cfg, b = synth.scale_config()
     w = synth.flatten_weights(cfg, synth.model_weights(cfg, 5))
     vel = synth.maxwell_boltzmann(b, 300.0, synth.seed_for(5, 9))
@@ -588,24 +587,19 @@ def scale_run(e3, synth, torch, dev, steps, warmup, log, cpu_baseline=True):
             g.close()
             best, stage = None, {}
             for t in range(1, cfg.layers + 1):
-                for st_name, (flops, nbytes) in work_model(cfg, t, n_edges, b.n_atoms).items():
+                for st_name, (flops, nbytes) in work_model(cfg, t, n_edges, b.n_atoms, pairs=True).items():
                     tot, n = m.stage_time(f"{st_name}@{t}")
                     if n == 0:
                         continue
                     stage[f"{st_name}@{t}"] = tot / 2
-                    # a layer in receiver chunks recomputes R chunk by chunk in
-                    # the adjoint: its radial forward covers every edge twice per step
-                    chunks = m.stage_time(f"tp_fwd@{t}")[1] / 2
-                    passes = 2 if st_name == "radial_fwd" and chunks > 1 else 1
                     if best is None or tot > best[0]:
-                        best = (tot, n, st_name, t, flops * passes, nbytes * passes)
+                        best = (tot, n, st_name, t, flops, nbytes)
             tot, n, st_name, t, flops, nbytes = best
             step_s = tot / 2 / 1e3
             t_hbm, t_alu = nbytes / PEAK_HBM, flops / PEAK_FP32_VALU
-            mfma = st_name.startswith("radial") or st_name.startswith("first")
-            if mfma and flops / PEAK_FP32_MFMA > t_hbm:
-                roof = {"bound": "mfma", "achieved": flops / step_s / 1e12, "peak": PEAK_FP32_MFMA / 1e12,
-                        "unit": "TFLOP/s"}
+            mfma = matrix_peak(st_name)
+            if mfma and flops / mfma > t_hbm:
+                roof = {"bound": "mfma", "achieved": flops / step_s / 1e12, "peak": mfma / 1e12, "unit": "TFLOP/s"}
             elif not mfma and t_alu > t_hbm:
                 roof = {"bound": "alu", "achieved": flops / step_s / 1e12, "peak": PEAK_FP32_VALU / 1e12,
                         "unit": "TFLOP/s"}
@@ -615,8 +609,8 @@ def scale_run(e3, synth, torch, dev, steps, warmup, log, cpu_baseline=True):
             if not mfma:
                 # the VALU peak above counts packed FP32, which this build does not emit
                 roof["frac_of_nonpacked_alu"] = flops / step_s / PEAK_FP32_VALU_NONPACKED
-            kern = KERNEL_OF_STAGE.get((st_name, t == cfg.layers), "k_" + st_name)
-            traffic = measured_traffic(kern, "scale_100k_hbm_traffic.md", fp32_row_pattern(cfg, kern, t))
+            kern = kernel_of_stage(st_name, t, cfg.layers)
+            traffic = measured_traffic(kern, "scale_100k_hbm_traffic.md")
             roof["traffic"] = None if traffic is None else traffic * n / 2
             roof["kernel"] = f"{st_name} (layer {t}), {kern}"
             roof["launches_per_step"] = n / 2
@@ -875,8 +869,8 @@ def main():
     s, t = dom_s, dom_t
     tot, n = m.stage_time(f"{s}@{t}")
     avg_s = tot / n / 1e3
-    mfma = s.startswith("radial") or s.startswith("first") or s.startswith("last")
-    peak_flop = PEAK_FP32_MFMA if mfma else PEAK_FP32_VALU
+    mfma = matrix_peak(s)
+    peak_flop = mfma or PEAK_FP32_VALU
     t_hbm, t_flop = nbytes / PEAK_HBM, flops / peak_flop
     if t_flop >= t_hbm:
         bound = "mfma" if mfma else "alu"
@@ -884,8 +878,7 @@ def main():
     else:
         roof = {"bound": "hbm", "achieved": nbytes / avg_s / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    # the last layer's edge adjoint stage is the sender-side kernel (tps.hip)
-    roof["traffic"] = measured_traffic("k_tps_bwd_sender" if (s, t) == ("tp_bwd_edge", cfg.layers) else "k_" + s)
+    roof["traffic"] = measured_traffic(kernel_of_stage(s, t, cfg.layers))
     roof["kernel"] = f"{s} (layer {t})"
     roof["avg_launch_ms"] = tot / n
     roof["algorithmic_per_launch"] = {"flops": flops, "bytes": nbytes, "edges": n_edges,
