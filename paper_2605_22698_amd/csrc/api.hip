@@ -588,7 +588,8 @@ e3mi_graph* new_graph(e3mi_model* M, int S, const int64_t* off, const double* po
 
 // ---- energy + forces ---------------------------------------------------------------
 
-void prune(e3mi_graph* G, const double* pos, hipStream_t st) {
+// and h0, the embedding
+void prune(e3mi_graph* G, const double* pos, float* h0, hipStream_t st) {
   const int N = G->N;
   const double rc2 = G->model->cfg.cutoff * G->model->cfg.cutoff;
   auto p = [](const std::unique_ptr<DevBuf>& b) { return b->as<int>(); };
@@ -613,6 +614,10 @@ void prune(e3mi_graph* G, const double* pos, hipStream_t st) {
   a.rev_x = p(G->rev_x);
   a.own = p(G->own);
   a.pair_of = p(G->pair_of);
+  a.species = p(G->species);
+  a.emb = G->model->emb->as<float>();
+  a.h0 = h0;
+  a.C = G->model->cfg.channels;
   launch_prune(a, st);
 }
 
@@ -1040,7 +1045,8 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
   (void)S;
   {
     ProfScope ps(&M->prof, stage_id(kPrune), st);
-    prune(G, pos, st);
+    w.h.resize(T + 1);
+    prune(G, pos, ensure(w.h[0], a, sizeof(float) * (size_t)N * C).as<float>(), st);
   }
   w.rp_valid = false;
   const int* row_ptr = G->row_ptr_x->as<int>();
@@ -1050,10 +1056,8 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
 
   // ---- workspace (grows, never shrinks) ----
   w.r_bf16 = bf16 && !keep_A;
-  w.h.resize(T + 1);
   w.ht.resize(T + 1);
   w.R.resize(T + 1);
-  ensure(w.h[0], a, sizeof(float) * (size_t)N * C);
   long a_max = 0;
   size_t dr_bytes = 0, kept = 0;
   // rows of radial weights: one of every two edges of the list owns a pair
@@ -1115,10 +1119,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
     ensure(w.e_atom, a, sizeof(double) * (size_t)N);
   }
   // ---- forward ----
-  {
-    ProfScope ps(&M->prof, stage_id(kEmbed), st);
-    launch_embed(species, M->emb->as<float>(), w.h[0]->as<float>(), N, C, st);
-  }
+  { ProfScope ps(&M->prof, stage_id(kEmbed), st); }  // formed with the edges
   const bool fact = factorised_first(M) && !keep_A;
   const int S64 = c.n_species * c.radial_hidden;
   if (fact) {
@@ -1334,14 +1335,12 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
     launch_readout_gated(w.last_parts > 0 ? w.mixp->as<float>() : w.ht[T]->as<float>(), w.last_parts, species,
                          M->read1->as<float>(), M->read2->as<float>(), M->e0->as<float>(), N, C,
                          w.e_atom->as<double>(), w.dht->as<float>(), st);
-    launch_energy(w.e_atom->as<double>(), G->off_d->as<int64_t>(), S, energy, st);
   } else {
     ProfScope ps(&M->prof, stage_id(kReadout), st);
     launch_readout(w.h[T]->as<float>(), M->plans[T - 1].nc_out, species, M->read1->as<float>(),
                    M->read2->as<float>(), M->e0->as<float>(), N, C, w.e_atom->as<double>(), dcur, st,
                    coulomb ? M->qhead->as<float>() : nullptr, coulomb ? M->qbias->as<float>() : nullptr,
                    coulomb ? w.q_raw->as<float>() : nullptr);
-    if (!coulomb) launch_energy(w.e_atom->as<double>(), G->off_d->as<int64_t>(), S, energy, st);
   }
   if (coulomb) {
     const int64_t* offd = G->off_d->as<int64_t>();
@@ -1353,7 +1352,6 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
     }
     launch_coulomb_dq(offd, G->owner->as<int>(), S, N, w.pot->as<float>(), w.pot_mean->as<float>(),
                       M->qhead->as<float>(), C, dcur, st);
-    launch_energy(w.e_atom->as<double>(), offd, S, energy, st);
   }
   if (atom_energy)
     E3MI_HIP(hipMemcpyAsync(atom_energy, w.e_atom->p, sizeof(double) * N, hipMemcpyDeviceToDevice, st));
@@ -1571,7 +1569,8 @@ void energy_forces(e3mi_model* M, e3mi_graph* G, const double* pos, double* ener
   {
     ProfScope ps(&M->prof, stage_id(kForces), st);
     if (rows_live) launch_edge_geo(c.lmax, row_ptr, N, Ecap, dvec, w.dY->as<float>(), g_live ? 1 : 0, g, st);
-    launch_forces(row_ptr, G->rev_x->as<int>(), g, N, forces, st, coulomb ? w.fc->as<float>() : nullptr);
+    launch_forces(row_ptr, G->rev_x->as<int>(), g, N, forces, st, coulomb ? w.fc->as<float>() : nullptr, 1, 0,
+                  EnergySum{w.e_atom->as<double>(), G->off_d->as<int64_t>(), S, energy});
   }
 }
 

@@ -308,13 +308,21 @@ __device__ __forceinline__ void edge_vec(const double* __restrict__ pos, const d
 // equal lengths (edge_vec), so both are selected or neither; the one that comes
 // first in the list owns the pair, and a function of the length is computed
 // once per owner. Selection keeps the order, so the order in the skin list
-// decides. Bound: the launches (three; with the owners counted after the
+// decides. The embedding rides in the first launch. Bound: the launches (three; with the owners counted after the
 // reverse index and two scans there were six: 3,000 atoms 29 us, now 18).
 __global__ void __launch_bounds__(256) k_prune_count(const double* __restrict__ pos, const int* __restrict__ owner,
                                                      const double* __restrict__ box, const int* __restrict__ row_ptr,
                                                      const int* __restrict__ src, const int* __restrict__ shift,
                                                      const int* __restrict__ rev, int N, double rc2,
-                                                     int* __restrict__ cnt, int* __restrict__ own_cnt) {
+                                                     int* __restrict__ cnt, int* __restrict__ own_cnt,
+                                                     const int* __restrict__ species, const float* __restrict__ emb,
+                                                     float* __restrict__ h0, int C) {
+  const int row_blocks = (N + 3) / 4;
+  if ((int)blockIdx.x >= row_blocks) {  // the embedding
+    const long k = (long)(blockIdx.x - row_blocks) * 256 + threadIdx.x;
+    if (k < (long)N * C) h0[k] = emb[(long)species[k / C] * C + k % C];
+    return;
+  }
   const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (i >= N) return;
@@ -508,8 +516,9 @@ void launch_unpack_shift(const int* shift_packed, int E, int* shift3, hipStream_
 void launch_prune(const PruneArgs& a, hipStream_t st) {
   const int N = a.N, grid = blocks((long)N * 64, 256);
   if (N > 0)
-    k_prune_count<<<grid, 256, 0, st>>>(a.pos, a.owner, a.box, a.row_ptr, a.src, a.shift, a.rev, N, a.rc2, a.cnt,
-                                        a.own_cnt);
+    k_prune_count<<<grid + blocks((long)N * a.C, 256), 256, 0, st>>>(a.pos, a.owner, a.box, a.row_ptr, a.src, a.shift,
+                                                                     a.rev, N, a.rc2, a.cnt, a.own_cnt, a.species,
+                                                                     a.emb, a.h0, a.C);
   if (N == 0 || N > kSumRows) {
     launch_exclusive_scan(a.cnt, a.row_ptr_x, N, st);
     launch_exclusive_scan(a.own_cnt, a.own_ptr, N, st);

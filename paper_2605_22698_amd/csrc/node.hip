@@ -1,7 +1,7 @@
 // Per-atom stages of the interaction besides its dense contractions (gemm.hip):
 //   gate (MACE table of Appendix F: gate_nodes):
 //     h[0] = silu(h~[0]),  h[l>0] = h~[l] sigmoid(h~[0])
-//   embedding h0 = W_emb[z];  readout E_i = w2 . silu(W_r^T h[0]) + E0[z_i]
+//   readout E_i = w2 . silu(W_r^T h[0]) + E0[z_i]
 //   (Section 5.3 readout with one head), fused with its adjoint dE/dh[0]
 //   energy reduction per structure in FP64, fixed summation order
 //   force assembly F_i = sum_{e in in(i)} (g_e - g_rev(e))
@@ -62,15 +62,6 @@ __global__ void __launch_bounds__(256) k_gate_bwd(const float* __restrict__ ht, 
   }
   // (the contraction is fixed: the BF16 mode rounds what follows)
   dht[at] = __builtin_fmaf(acc * s, 1.0f - s, g[0] * silu_grad(x[0]));
-}
-
-__global__ void k_embed(const int* __restrict__ species, const float* __restrict__ emb, float* __restrict__ h0, int N,
-                        int C) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long)N * C) return;
-  const long i = idx / C;
-  const int k = (int)(idx % C);
-  h0[idx] = emb[(long)species[i] * C + k];
 }
 
 // One wave per atom; readout_hidden = 16.
@@ -162,27 +153,30 @@ __global__ void __launch_bounds__(256) k_readout_gated(const float* __restrict__
   }
 }
 
-__global__ void __launch_bounds__(256) k_energy(const double* __restrict__ e_atom, const int64_t* __restrict__ off,
-                                                double* __restrict__ energy) {
+// Energy of structure s, by one workgroup
+__device__ __forceinline__ void sum_energy(const EnergySum& es, int s) {
   __shared__ double red[256];
-  const int s = blockIdx.x;
-  const int64_t a = off[s], b = off[s + 1];
+  const int64_t a = es.off[s], b = es.off[s + 1];
   double acc = 0.0;
-  for (int64_t i = a + threadIdx.x; i < b; i += 256) acc += e_atom[i];
+  for (int64_t i = a + threadIdx.x; i < b; i += 256) acc += es.e_atom[i];
   red[threadIdx.x] = acc;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) energy[s] = red[0];
+  if (threadIdx.x == 0) es.energy[s] = red[0];
 }
 
 // One wave per atom: the lanes take the row's edges in turn, then a fixed
-// reduction tree over the wave (bitwise repeatable).
+// reduction tree over the wave (bitwise repeatable). The workgroups past the
+// atoms' add up the structures' energies, which need a launch of their own
+// otherwise (2 us of a 24-atom call, 5 of a 3,000-atom step).
 __global__ void __launch_bounds__(256) k_forces(const int* __restrict__ row_ptr, const int* __restrict__ rev,
                                                 const float4* __restrict__ g, int N, const float* __restrict__ extra,
-                                                float* __restrict__ F, long e_stride) {
+                                                float* __restrict__ F, long e_stride, EnergySum es) {
+  const int atom_blocks = (N + 3) / 4;
+  if ((int)blockIdx.x >= atom_blocks) return sum_energy(es, blockIdx.x - atom_blocks);
   g += blockIdx.y * e_stride;
   F += 3L * blockIdx.y * N;
   const int i = (int)(((long)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
@@ -233,10 +227,6 @@ void launch_gate_bwd(const float* ht, const float* dh, float* dht, int N, int nc
     k_gate_bwd<decltype(n)::value><<<blocks((long)N * C, 256), 256, 0, st>>>(ht, dh, dht, N, C);
   });
 }
-void launch_embed(const int* species, const float* emb, float* h0, int N, int C, hipStream_t st) {
-  if (N == 0) return;
-  k_embed<<<blocks((long)N * C, 256), 256, 0, st>>>(species, emb, h0, N, C);
-}
 void launch_readout(const float* h, int nc, const int* species, const float* Wr, const float* w2, const float* e0,
                     int N, int C, double* e_atom, float* dh, hipStream_t st, const float* wq, const float* bq,
                     float* q_raw) {
@@ -248,13 +238,10 @@ void launch_readout_gated(const float* xt, int n_parts, const int* species, cons
   if (N == 0) return;
   k_readout_gated<<<blocks((long)N * 64, 256), 256, 0, st>>>(xt, n_parts, species, Wr, w2, e0, N, C, e_atom, dht);
 }
-void launch_energy(const double* e_atom, const int64_t* off, int S, double* energy, hipStream_t st) {
-  k_energy<<<S, 256, 0, st>>>(e_atom, off, energy);
-}
 void launch_forces(const int* row_ptr, const int* rev, const float4* g, int N, float* F, hipStream_t st,
-                   const float* extra, int B, long e_stride) {
+                   const float* extra, int B, long e_stride, const EnergySum& es) {
   if (N == 0) return;
-  k_forces<<<dim3(blocks((long)N * 64, 256), B), 256, 0, st>>>(row_ptr, rev, g, N, extra, F, e_stride);
+  k_forces<<<dim3(blocks(N, 4) + es.S, B), 256, 0, st>>>(row_ptr, rev, g, N, extra, F, e_stride, es);
 }
 
 }  // namespace e3mi

@@ -216,6 +216,11 @@ struct PruneArgs {
   int *cnt, *own_cnt, *row_ptr_x, *own_ptr, *src_x;
   float4* dvec_x;
   int *old_idx, *new_idx, *rev_x, *own, *pair_of;
+  // the embedding h0 = W_emb[species] [N, C], in the first launch
+  const int* species;
+  const float* emb;
+  float* h0;
+  int C;
 };
 void launch_prune(const PruneArgs& a, hipStream_t st);
 
@@ -310,7 +315,6 @@ void launch_gate_fwd(const float* ht, float* h, int N, int nc, int C, hipStream_
 void launch_gate_bwd(const float* ht, const float* dh, float* dht, int N, int nc, int C, hipStream_t st);
 // h~ [N, C] = sum of n_parts partial products [n_parts, N, C] in order; h = silu(h~)
 void launch_gate_fwd_sum(const float* part, int n_parts, float* ht, float* h, int N, int C, hipStream_t st);
-void launch_embed(const int* species, const float* emb, float* h0, int N, int C, hipStream_t st);
 void launch_readout(const float* h, int nc, const int* species, const float* Wr, const float* w2, const float* e0,
                     int N, int C, double* e_atom, float* dh, hipStream_t st, const float* wq = nullptr,
                     const float* bq = nullptr, float* q_raw = nullptr);
@@ -319,10 +323,16 @@ void launch_readout(const float* h, int nc, const int* species, const float* Wr,
 // the gate and its adjoint folded in: writes E_i and dE/dh~ [N, C]
 void launch_readout_gated(const float* xt, int n_parts, const int* species, const float* Wr, const float* w2,
                           const float* e0, int N, int C, double* e_atom, float* dht, hipStream_t st);
-void launch_energy(const double* e_atom, const int64_t* off, int S, double* energy, hipStream_t st);
+// energy[s] = the sum of e_atom over structure s (S 0: none)
+struct EnergySum {
+  const double* e_atom = nullptr;
+  const int64_t* off = nullptr;
+  int S = 0;
+  double* energy = nullptr;
+};
 // (B > 1: g [B, e_stride] -> F [B, N, 3])
 void launch_forces(const int* row_ptr, const int* rev, const float4* g, int N, float* F, hipStream_t st,
-                   const float* extra = nullptr, int B = 1, long e_stride = 0);
+                   const float* extra = nullptr, int B = 1, long e_stride = 0, const EnergySum& es = EnergySum{});
 
 // ---- Hessian-vector products (hvp.hip) ------------------------------------------------
 // One layer's tangent or adjoint for a batch of B directions: atom rows are
