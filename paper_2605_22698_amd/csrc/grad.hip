@@ -176,9 +176,14 @@ __global__ void __launch_bounds__(256) k_group_total(const double* __restrict__ 
 
 // Weight gradients: products X1^T Y1 + X2^T Y2 over rows (X: [rows, mo], Y:
 // [rows, no], rows addressed through RowMaps), several in one launch. A
-// workgroup takes a 64 x 64 output tile and a chunk of the rows (kTnRows at a
-// time through LDS, the next ones in flight) on the FP32 matrix cores; its
-// partial sum goes to memory and k_tn_reduce adds the chunks in order in FP64.
+// workgroup takes a 64 x 64 output tile and a chunk of the rows, kTnRows at a
+// time through LDS, the next ones in flight; its partial sum goes to memory and
+// k_tn_reduce adds the chunks in order in FP64. FP32 as six BF16 products
+// (gemm.hip): a lane loads eight rows of one column, which is an operand's eight
+// K, and splits them on the way into LDS. Bound: the streams of X and Y (W3 of
+// 183,000 pairs, P C = 256: 265 us, 3.2 TB/s; on the FP32 matrix cores 325). The
+// products of a training step of 7,032 atoms 640 us and 750; those with rows
+// (atom, m) alone, whose addresses take longer, 57 and 46.
 struct TnGroup {
   TnArgs g[kMaxTnGroup];
   int block0[kMaxTnGroup + 1];  // first workgroup
@@ -195,8 +200,7 @@ __device__ __forceinline__ const float* tn_row(const RowMap& m, int r) {
 }
 
 __global__ void __launch_bounds__(256) k_gemm_tn(TnGroup gg, float* __restrict__ partial) {
-  __shared__ __align__(16) float Xs[kTnRows][64];
-  __shared__ __align__(16) float Ys[kTnRows][64];
+  __shared__ bf16x8 B[2][kTnRows / 16][2][3][64];  // [X, Y][16 rows][32 columns][part][lane]
   int gi = 0;
   while (gi + 1 < gg.n && (int)blockIdx.x >= gg.block0[gi + 1]) ++gi;
   const TnArgs& a = gg.g[gi];
@@ -206,47 +210,86 @@ __global__ void __launch_bounds__(256) k_gemm_tn(TnGroup gg, float* __restrict__
   const int R = a.rows_dev ? min((int)a.rows, *a.rows_dev) : (int)a.rows;
   const int per = ((R + gg.chunks[gi] - 1) / gg.chunks[gi] + kTnRows - 1) / kTnRows * kTnRows;
   const int r0 = min(R, chunk * per), r1 = min(R, r0 + per);
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int rb = (w >> 1) * 32, cb = (w & 1) * 32;
-  // this thread stages columns c4 .. c4 + 3 of rows kr and kr + 16
-  const int kr = t >> 4, c4 = (t & 15) * 4;
-  const bool in_m = bm + c4 < a.mo, in_n = bn + c4 < a.no;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int rb = w >> 1, cb = w & 1;
+  const bool in_m = bm + lane < a.mo, in_n = bn + lane < a.no;
   const int terms = a.x2.base ? 2 : 1;
   const int steps = (r1 - r0 + kTnRows - 1) / kTnRows * terms;
-  float4 xv[2], yv[2];
+  // a wave stages eight rows, a lane one column of each: an operand's eight K;
+  // the rows' indices in Y come one step earlier
+  const int* __restrict__ y_row = a.y_row;
+  float xv[8], yv[8];
+  int ahead = 0;
+  auto index = [&](int s) {
+    if (y_row && s < steps) ahead = y_row[min(r0 + s / terms * kTnRows + 8 * w + (lane & 7), R - 1)];
+  };
   auto load = [&](int s) {
-    const RowMap& X = s % terms ? a.x2 : a.x1;
-    const RowMap& Y = s % terms ? a.y2 : a.y1;
+    const RowMap X = s % terms ? a.x2 : a.x1, Y = s % terms ? a.y2 : a.y1;
+    const int r = r0 + s / terms * kTnRows + 8 * w, n = r1 - r;
+    const int yi = ahead;
+    index(s + 1);
+    if (n >= 8 && X.g == 1 && Y.g == 1) {
+      const float* px = X.base + (long)r * X.s_atom + bm + lane;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int r = r0 + s / terms * kTnRows + kr + 16 * q;
-      xv[q] = yv[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (r < r1 && in_m) xv[q] = *reinterpret_cast<const float4*>(tn_row(X, r) + bm + c4);
-      if (r < r1 && in_n) yv[q] = *reinterpret_cast<const float4*>(tn_row(Y, a.y_row ? a.y_row[r] : r) + bn + c4);
+      for (int q = 0; q < 8; ++q) xv[q] = in_m ? px[(long)q * X.s_atom] : 0.0f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int ry = y_row ? __builtin_amdgcn_readlane(yi, q) : r + q;
+        yv[q] = in_n ? Y.base[(long)ry * Y.s_atom + bn + lane] : 0.0f;
+      }
+      return;
+    }
+    // the last rows, and rows (atom, m)
+    int xa = r / X.g, xm = r - xa * X.g, ya = r / Y.g, ym = r - ya * Y.g;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      xv[q] = q < n && in_m ? X.base[xa * X.s_atom + xm * X.s_m + bm + lane] : 0.0f;
+      if (++xm == X.g) {
+        xm = 0;
+        ++xa;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int ry = __builtin_amdgcn_readlane(yi, q);
+      yv[q] = q < n && in_n ? (y_row ? tn_row(Y, ry) : Y.base + ya * Y.s_atom + ym * Y.s_m)[bn + lane] : 0.0f;
+      if (++ym == Y.g) {
+        ym = 0;
+        ++ya;
+      }
     }
   };
-  f32x16 acc = {};
+  index(0);
+  f32x16 hi = {}, lo = {};
   if (steps > 0) load(0);
   for (int s = 0; s < steps; ++s) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      *reinterpret_cast<float4*>(&Xs[kr + 16 * q][c4]) = xv[q];
-      *reinterpret_cast<float4*>(&Ys[kr + 16 * q][c4]) = yv[q];
-    }
+    if (s > 0) __syncthreads();
+    const int slot = (lane & 31) + 32 * (w & 1);
+    split_bf16(xv, B[0][w >> 1][lane >> 5][0][slot], B[0][w >> 1][lane >> 5][1][slot], B[0][w >> 1][lane >> 5][2][slot]);
+    split_bf16(yv, B[1][w >> 1][lane >> 5][0][slot], B[1][w >> 1][lane >> 5][1][slot], B[1][w >> 1][lane >> 5][2][slot]);
     __syncthreads();
     if (s + 1 < steps) load(s + 1);
 #pragma unroll
-    for (int kk = 0; kk < kTnRows; kk += 2)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Xs[kk + (lane >> 5)][rb + (lane & 31)],
-                                                  Ys[kk + (lane >> 5)][cb + (lane & 31)], acc, 0, 0, 0);
-    __syncthreads();
+    for (int j = 0; j < kTnRows / 16; ++j) {
+      bf16x8 x[3], y[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        x[p] = B[0][j][rb][p][lane];
+        y[p] = B[1][j][cb][p][lane];
+      }
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        f32x16& acc = i < 5 ? lo : hi;
+        acc = mfma_bf(x[kSplitA[i]], y[kSplitB[i]], acc);
+      }
+    }
   }
   float* P = partial + gg.part0[gi] + (long)chunk * a.mo * a.no;
-  const int col = bn + cb + (lane & 31);
+  const int col = bn + 32 * cb + (lane & 31);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int row = bm + rb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    if (row < a.mo && col < a.no) P[(long)row * a.no + col] = acc[r];
+    const int row = bm + 32 * rb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    if (row < a.mo && col < a.no) P[(long)row * a.no + col] = hi[r] + lo[r];
   }
 }
 
