@@ -119,18 +119,27 @@ __global__ void __launch_bounds__(256) k_readout_gated(const float* __restrict__
   const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (i >= N) return;
+  // every partial product of the lane's channels in flight at once (a loop over
+  // them, once forward and once back: 138 atoms 7.4 us for 5.0, 3,000 9.2 for 7.3)
   const long NC = (long)N * C;
-  auto x_of = [&](int k) {
-    float x = xt[(long)i * C + k];
-    for (int p = 1; p < n_parts; ++p) x += xt[p * NC + (long)i * C + k];
-    return x;
-  };
+  float part[2][kMaxGemmGroup], x[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int p = 0; p < kMaxGemmGroup; ++p)
+      part[u][p] = lane + 64 * u < C && (p == 0 || p < n_parts) ? xt[p * NC + (long)i * C + lane + 64 * u] : 0.0f;
   float pre[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) pre[q] = 0.0f;
-  for (int k = lane; k < C; k += 64) {
-    const float x = x_of(k);
-    const float hv = x * sigmoidf(x);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int k = lane + 64 * u;
+    if (k >= C) break;
+    x[u] = part[u][0];
+#pragma unroll
+    for (int p = 1; p < kMaxGemmGroup; ++p)
+      if (p < n_parts) x[u] += part[u][p];
+    const float hv = x[u] * sigmoidf(x[u]);
 #pragma unroll
     for (int q = 0; q < 16; ++q) pre[q] += hv * Wr[k * 16 + q];
   }
@@ -145,11 +154,14 @@ __global__ void __launch_bounds__(256) k_readout_gated(const float* __restrict__
   float gq[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) gq[q] = __shfl(gl, 4 * q);
-  for (int k = lane; k < C; k += 64) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int k = lane + 64 * u;
+    if (k >= C) break;
     float s = 0.0f;
 #pragma unroll
     for (int q = 0; q < 16; ++q) s += Wr[k * 16 + q] * gq[q];
-    dht[(long)i * C + k] = s * silu_grad(x_of(k));
+    dht[(long)i * C + k] = s * silu_grad(x[u]);
   }
 }
 
