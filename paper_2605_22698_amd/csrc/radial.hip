@@ -331,7 +331,8 @@ __global__ void __launch_bounds__(256) k_radial_bwd(const float4* __restrict__ d
 // which the tensor product's adjoint takes while it forms dR_e. So dR never
 // goes to memory and no adjoint of the MLP is evaluated. R' is streamed past
 // the caches: the forward pass reads only R, which then stays in the
-// last-level cache. ND 1 (the same R): the forward pass of receiver chunks.
+// last-level cache (a call of 3,000 atoms 5 % faster, of 1,205, where both fit,
+// 1 % slower). ND 1 (the same R): the forward pass of receiver chunks.
 // ND 3, for Hessian-vector products and weight gradients: the tangent of R
 // along any direction is R' r_dot, and the adjoint of the MLP a dot product
 // with R' and R'', so that one evaluation serves every direction of a call.
