@@ -266,6 +266,7 @@ struct e3mi_graph {
   int S = 0, N = 0;
   long E = 0;       // skin-list edges
   long E_room = 0;  // edges the edge buffers (and the models' edge workspaces) hold, >= E
+  bool built = false;  // false from the start of a rebuild until it succeeds: the lists are not to be read
   double cutoff = 0, skin = 0;
   std::vector<int64_t> off_h;
   std::vector<double> box_h;
@@ -354,7 +355,9 @@ struct Pieces {
     all.push_back({&b, total, bytes});
     total += (std::max<size_t>(bytes, 1) + 255) & ~(size_t)255;
   }
+  // (when the allocation fails, no piece is left pointing into the block it had)
   void place(std::unique_ptr<DevBuf>& block, Allocator* a) {
+    for (const Piece& q : all) q.buf->reset();
     char* base = ensure(block, a, total).as<char>();
     for (const Piece& q : all) {
       *q.buf = std::make_unique<DevBuf>();  // no allocator: the block owns the memory
@@ -411,6 +414,7 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st, bool check = 
   e3mi_model* M = G->model;
   Allocator* a = &M->alloc;
   const int S = G->S, N = G->N;
+  G->built = false;
   const double rc_eff = G->cutoff + G->skin;
   // bounding boxes of open axes
   std::vector<double> bbox((size_t)6 * S, 0.0);
@@ -495,6 +499,7 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st, bool check = 
   E3MI_REQUIRE(!(errh & 2), E3MI_EDEVICE, "neighbour list is not symmetric");
   // the reference positions for the skin check
   if (N) E3MI_HIP(hipMemcpyAsync(G->x_ref->p, pos, sizeof(double) * 3 * N, hipMemcpyDeviceToDevice, st));
+  G->built = true;
 }
 
 e3mi_graph* new_graph(e3mi_model* M, int S, const int64_t* off, const double* pos, const int32_t* species,
@@ -1043,6 +1048,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
   const int p_env = c.envelope_p;
   Workspace& w = M->ws;
   (void)S;
+  E3MI_REQUIRE(G->built, E3MI_EINVAL, "the last rebuild of the neighbour lists failed");
   {
     ProfScope ps(&M->prof, stage_id(kPrune), st);
     w.h.resize(T + 1);
@@ -2372,8 +2378,8 @@ void md_step(e3mi_md* D, int n_steps, double dt, double* energy_out, hipStream_t
     // so the redone step equals one whose lists were exact throughout. So that
     // redoing stays rare, the drift's forecast of the next step's largest
     // displacement brings the rebuild forward to the next step when it
-    // reaches skin/2.
-    const bool scheduled = ++D->since_build >= D->rebuild_every || D->rebuild_next;
+    // reaches skin/2. After a rebuild that failed (memory) the next step rebuilds.
+    const bool scheduled = ++D->since_build >= D->rebuild_every || D->rebuild_next || !G->built;
     if (scheduled) {
       md_rebuild(D, st);
     } else {
@@ -2882,6 +2888,7 @@ int e3mi_md_set_total_charge(e3mi_md* md, const double* total_charge, void* stre
   const int rc = e3mi_graph_set_total_charge(md->graph, total_charge);
   if (rc != E3MI_OK) return rc;
   hipStream_t st = e3mi::as_stream(stream);
+  if (!md->graph->built) e3mi::md_rebuild(md, st);
   e3mi::energy_forces(md->model, md->graph, md->x->as<double>(), md->energy->as<double>(), md->F->as<float>(),
                       nullptr, st);
   E3MI_HIP(hipStreamSynchronize(st));

@@ -1,0 +1,54 @@
+"""Device memory that runs out, and what is asked of the allocator."""
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import device, gpu_energy_forces, model, say
+
+pytestmark = pytest.mark.gpu
+
+
+class _Torch:
+    """Stands in for torch in a model's allocator: refuses what `refuse(bytes)` says."""
+
+    def __init__(self):
+        import torch
+        self.uint8, self.empty_of, self.refuse = torch.uint8, torch.empty, None
+
+    def empty(self, n, **kw):
+        if self.refuse and self.refuse(n):
+            raise MemoryError
+        return self.empty_of(n, **kw)
+
+
+def _limited(cfg, seed, precision=0):
+    m = model(cfg, seed, precision=precision)
+    m._alloc._torch = _Torch()
+    return m, m._alloc._torch
+
+
+@pytest.mark.parametrize("rebuild_every", [1, 1000])
+def test_md_goes_on_after_a_rebuild_that_found_no_memory(rebuild_every):
+    # the cluster contracts by a twentieth in the first step, past half the skin:
+    # the rebuild (scheduled, or of the step that overran the skin) needs room
+    # for more edges and gets none. The next step rebuilds before it evaluates
+    import torch
+    import paper_2605_22698_amd as e3
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=2, n_species=3, cutoff=4.0, avg_neighbors=15.0)
+    b = synth.open_box(120, 3, np.random.default_rng(210))
+    m, memory = _limited(cfg, 211)
+    d = device()
+    x0 = torch.tensor(b.pos, dtype=torch.float64, device=d)
+    sp = torch.tensor(b.species, dtype=torch.int32, device=d)
+    vel = -0.1 * (x0 - x0.mean(0))
+    md = e3.MD(m, b.offsets, x0, vel, sp, synth.SPECIES_MASS[:3], b.cell, b.pbc, cfg.cutoff, 0.3, rebuild_every)
+    memory.refuse = lambda n: True
+    with pytest.raises(e3.E3miError, match="ENOMEM"):
+        md.step(1, 0.5)
+    memory.refuse = None
+    E = torch.empty(1, dtype=torch.float64, device=d)
+    md.step(1, 1e-4, E)
+    x, _, F = md.state()
+    say(f"after the failed rebuild: max displacement {float((x - x0).abs().max()):.3f}")
+    E1, F1, _ = m.energy_forces(m.build_graph(b.offsets, x, sp, b.cell, b.pbc, cfg.cutoff), x)
+    assert torch.isfinite(x).all() and torch.equal(E, E1) and torch.equal(F, F1)
