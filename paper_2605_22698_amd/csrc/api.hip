@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <array>
 #include <cmath>
+#include <exception>
 #include <limits>
 #include <cstdio>
 #include <cstring>
@@ -409,6 +410,17 @@ void fill_plan(const Config& c, int S, const std::vector<int64_t>& off, const do
   }
 }
 
+// Waits for the stream when an exception leaves the scope: the copies from host
+// memory and the kernels that are under way use what the unwinding gives back.
+struct WaitOnThrow {
+  hipStream_t st;
+  int thrown = std::uncaught_exceptions();
+  explicit WaitOnThrow(hipStream_t s) : st(s) {}
+  ~WaitOnThrow() {
+    if (std::uncaught_exceptions() > thrown) (void)hipStreamSynchronize(st);
+  }
+};
+
 // check: read the flag of new_graph's checks of the inputs too
 void build_lists(e3mi_graph* G, const double* pos, hipStream_t st, bool check = false) {
   e3mi_model* M = G->model;
@@ -416,6 +428,8 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st, bool check = 
   const int S = G->S, N = G->N;
   G->built = false;
   const double rc_eff = G->cutoff + G->skin;
+  std::vector<double> back((size_t)6 * S + 1);
+  WaitOnThrow wait(st);
   // bounding boxes of open axes
   std::vector<double> bbox((size_t)6 * S, 0.0);
   bool any_open = false;
@@ -424,7 +438,6 @@ void build_lists(e3mi_graph* G, const double* pos, hipStream_t st, bool check = 
   if (any_open && N) launch_bbox(pos, G->off_d->as<int64_t>(), S, G->bb->as<double>(), st);
   if ((any_open || check) && N) {
     // the check's flag lies behind the boxes: one copy, one wait
-    std::vector<double> back((size_t)6 * S + 1);
     E3MI_HIP(hipMemcpyAsync(back.data(), G->bb->p, sizeof(double) * back.size(), hipMemcpyDeviceToHost, st));
     E3MI_HIP(hipStreamSynchronize(st));
     if (check) {
@@ -572,6 +585,7 @@ e3mi_graph* new_graph(e3mi_model* M, int S, const int64_t* off, const double* po
     b.add(*q, sizeof(int) * N1);
   b.place(G->batch_block, a);
   std::vector<char> host(sent, 0);  // outlives the copy: build_lists waits for the stream
+  WaitOnThrow wait(st);
   auto put = [&](const std::unique_ptr<DevBuf>& d, const void* from) {
     if (d && d->bytes) std::memcpy(&host[d->as<char>() - G->batch_block->as<char>()], from, d->bytes);
   };

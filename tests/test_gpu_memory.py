@@ -52,3 +52,37 @@ def test_md_goes_on_after_a_rebuild_that_found_no_memory(rebuild_every):
     say(f"after the failed rebuild: max displacement {float((x - x0).abs().max()):.3f}")
     E1, F1, _ = m.energy_forces(m.build_graph(b.offsets, x, sp, b.cell, b.pbc, cfg.cutoff), x)
     assert torch.isfinite(x).all() and torch.equal(E, E1) and torch.equal(F, F1)
+
+
+@pytest.mark.parametrize("n_atoms,allocations", [(0, 1), (90, 1), (90, 2)])
+def test_a_build_without_memory_gives_nothing_back_while_it_is_used(n_atoms, allocations):
+    # the device is busy when the build starts; an allocation after the first
+    # fails, and what was allocated may go back only once the copies and kernels
+    # under way are done with it
+    import torch
+    import paper_2605_22698_amd as e3
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=2, n_species=3, cutoff=4.0, avg_neighbors=15.0)
+    b = synth.open_box(max(n_atoms, 8), 3, np.random.default_rng(212))
+    m, memory = _limited(cfg, 213)
+    idle = []
+
+    class Live(dict):
+        def pop(self, *a):
+            idle.append(torch.cuda.current_stream().query())
+            return super().pop(*a)
+    m._alloc.live = Live(m._alloc.live)
+    left = [allocations]
+
+    def refuse(n):
+        left[0] -= 1
+        return left[0] < 0
+    memory.refuse = refuse
+    pos = torch.tensor(b.pos[:n_atoms], dtype=torch.float64, device=device())
+    sp = torch.tensor(b.species[:n_atoms], dtype=torch.int32, device=device())
+    torch.cuda._sleep(50_000_000)
+    with pytest.raises(e3.E3miError, match="ENOMEM"):
+        m.build_graph(np.array([0, n_atoms]), pos, sp, b.cell, b.pbc, cfg.cutoff, 0.5)
+    assert len(idle) == allocations and all(idle)
+    memory.refuse = None
+    g = m.build_graph(np.array([0, n_atoms]), pos, sp, b.cell, b.pbc, cfg.cutoff, 0.5)
+    assert g.n_atoms == n_atoms
