@@ -254,6 +254,7 @@ struct e3mi_model {
   // receiver chunks: such a layer's adjoint then reads R instead of recomputing it
   size_t r_keep_bytes = size_t(160) << 30;
   std::unique_ptr<e3mi::DevBuf> U[4], UT[4];
+  int device = 0;  // where the weights are
   // how the flat FP64 vector becomes the tensors above
   e3mi::FirstWeights first_w{};
   int n_copies = 0;
@@ -1793,9 +1794,20 @@ std::vector<WeightCopy> plan_weights(e3mi_model* M) {
   return out;
 }
 
-// Lay the weights out on the device. wts: host or device FP64; values of a
-// device vector are checked there. Synchronous.
-void upload_weights(e3mi_model* M, const double* wts, bool on_device) {
+// Makes a device current for a scope.
+struct OnDevice {
+  int before = 0;
+  explicit OnDevice(int d) {
+    E3MI_HIP(hipGetDevice(&before));
+    E3MI_HIP(hipSetDevice(d));
+  }
+  ~OnDevice() { (void)hipSetDevice(before); }
+};
+
+// Lay the weights out on the model's device, which is current. wts: FP64 on the
+// host, or with `at` in device memory; values of a device vector are checked
+// there. Synchronous.
+void upload_weights(e3mi_model* M, const double* wts, const hipPointerAttribute_t* at) {
   Allocator* a = &M->alloc;
   const size_t n = weight_count(M->cfg);
   if (!M->w_copies) {
@@ -1804,13 +1816,13 @@ void upload_weights(e3mi_model* M, const double* wts, bool on_device) {
     M->w_copies = upload(a, copies.data(), sizeof(WeightCopy) * copies.size());
   }
   const double* src = wts;
-  if (!on_device) {
+  if (!at || at->device != M->device) {  // kernels reach the memory of their own device only
     ensure(M->w_flat, a, sizeof(double) * n);
-    E3MI_HIP(hipMemcpy(M->w_flat->p, wts, sizeof(double) * n, hipMemcpyHostToDevice));
+    E3MI_HIP(hipMemcpy(M->w_flat->p, wts, sizeof(double) * n, at ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice));
     src = M->w_flat->as<double>();
   }
   int* bad = ensure(M->w_bad, a, sizeof(int)).as<int>();
-  launch_weights(src, (long)n, M->w_copies->as<WeightCopy>(), M->n_copies, M->first_w, on_device, bad, nullptr);
+  launch_weights(src, (long)n, M->w_copies->as<WeightCopy>(), M->n_copies, M->first_w, at != nullptr, bad, nullptr);
   int bad_h = 0;
   E3MI_HIP(hipMemcpy(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost));
   E3MI_REQUIRE(!bad_h, E3MI_ENAN, "weights are not finite");
@@ -1831,7 +1843,8 @@ e3mi_model* new_model(const char* json, const double* wts, size_t n, int precisi
   M->alloc.alloc = al;
   M->alloc.free_fn = fr;
   M->alloc.ctx = ctx;
-  upload_weights(M.get(), wts, false);
+  E3MI_HIP(hipGetDevice(&M->device));
+  upload_weights(M.get(), wts, nullptr);
   return M.release();
 }
 
@@ -2255,8 +2268,13 @@ void set_weights(e3mi_model* M, const double* wts, size_t n) {
   (void)hipGetLastError();  // an ordinary host pointer is not an error
   if (!on_device)
     for (size_t i = 0; i < n; ++i) E3MI_REQUIRE(std::isfinite(wts[i]), E3MI_ENAN, "weights are not finite");
+  const OnDevice here(M->device);  // the caller's current device may be another one
+  if (on_device && at.device != M->device) {  // the vector may still be under way there
+    const OnDevice there(at.device);
+    E3MI_HIP(hipDeviceSynchronize());
+  }
   E3MI_HIP(hipDeviceSynchronize());  // no kernel may still read the old weights
-  upload_weights(M, wts, on_device);
+  upload_weights(M, wts, on_device ? &at : nullptr);
 }
 
 // ---- MD -----------------------------------------------------------------------------------

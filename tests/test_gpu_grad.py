@@ -257,3 +257,27 @@ def test_weights_rounded_to_fp32_first(precision):
         out.append(gpu_energy_forces(m, b)[:3])
     for x, y in zip(*out):
         assert np.array_equal(x, y)
+
+
+def test_weights_replaced_while_another_device_is_current():
+    # from a host vector and from either device's memory
+    import torch
+    import paper_2605_22698_amd as e3
+    if torch.cuda.device_count() < 2:
+        pytest.skip("needs two GPUs")
+    cfg, b, _, _ = synth.differentiation_config(2, 20, 30)
+    w0, w1 = (synth.flatten_weights(cfg, synth.model_weights(cfg, k)) for k in (200, 201))
+    d = torch.device("cuda:1")
+    pos = torch.tensor(b.pos, dtype=torch.float64, device=d)
+    sp = torch.tensor(b.species, dtype=torch.int32, device=d)
+
+    def evaluate(x):
+        with torch.cuda.device(d):
+            E, F, _ = x.energy_forces(x.build_graph(b.offsets, pos, sp, b.cell, b.pbc, cfg.cutoff), pos)
+            return E.cpu().numpy(), F.cpu().numpy()
+    ref = evaluate(e3.Model(cfg.to_json(), w1, device=d))
+    for w in (w1, torch.tensor(w1, device=d), torch.tensor(w1, device="cuda:0")):
+        m = e3.Model(cfg.to_json(), w0, device=d)
+        with torch.cuda.device(0):
+            m.set_weights(w)
+        assert all(np.array_equal(a, r) for a, r in zip(evaluate(m), ref))
