@@ -47,6 +47,8 @@ class Model:
         a = self._alloc.alloc_cb if self._alloc else _lib.ALLOC_FN()
         f = self._alloc.free_cb if self._alloc else _lib.FREE_FN()
         with torch.cuda.device(self.device):
+            # self.device with its index, as tensors' devices have it ("cuda" alone compares unequal)
+            self._weights_device = torch.device("cuda", torch.cuda.current_device())
             check(lib().e3mi_model_create(config_json.encode(), w.ctypes.data, w.size, precision, a, f, None,
                                           ctypes.byref(h)))
         self.handle = h
@@ -94,7 +96,7 @@ class Model:
     def set_weights(self, weights) -> None:
         """Replace the weights (FP64 vector in the documented layout; any device)."""
         import torch
-        if isinstance(weights, torch.Tensor) and weights.device == self.device:
+        if isinstance(weights, torch.Tensor) and weights.device == self._weights_device:
             w = weights.detach().to(torch.float64).contiguous()
             check(lib().e3mi_model_set_weights(self.handle, w.data_ptr(), w.numel()))
         else:

@@ -281,3 +281,32 @@ def test_weights_replaced_while_another_device_is_current():
         with torch.cuda.device(0):
             m.set_weights(w)
         assert all(np.array_equal(a, r) for a, r in zip(evaluate(m), ref))
+
+
+def test_weights_of_a_model_on_the_default_device_stay_on_the_device(monkeypatch):
+    # the default device has no index, tensors' devices have one: the library is
+    # handed the tensor's own memory, in set_weights and under autograd
+    import torch
+    import paper_2605_22698_amd as e3
+    cfg, b, _, _ = synth.differentiation_config(2, 20, 30)
+    w0, w1 = (synth.flatten_weights(cfg, synth.model_weights(cfg, k)) for k in (200, 201))
+    m = e3.Model(cfg.to_json(), w0)
+    pos = torch.tensor(b.pos, dtype=torch.float64, device="cuda")
+    sp = torch.tensor(b.species, dtype=torch.int32, device="cuda")
+    g = m.build_graph(b.offsets, pos, sp, b.cell, b.pbc, cfg.cutoff)
+    given = []
+    real = e3.lib()
+
+    class Spy:
+        def __getattr__(self, name):
+            if name == "e3mi_model_set_weights":
+                given.append(name)
+                return lambda handle, p, n: (given.__setitem__(-1, p), real.e3mi_model_set_weights(handle, p, n))[1]
+            return getattr(real, name)
+    monkeypatch.setattr(e3, "lib", Spy)
+    w = torch.tensor(w1, device="cuda", requires_grad=True)
+    m.set_weights(w)
+    E, _ = e3.energy_forces(w, pos, m, g)
+    E.sum().backward()
+    assert set(given) == {w.data_ptr()}
+    assert m.device == torch.device("cuda")
