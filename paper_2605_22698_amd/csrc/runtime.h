@@ -491,7 +491,7 @@ struct TnArgs {
   long ld_out;
 };
 constexpr int kMaxTnGroup = 8;
-constexpr long kTnPartial = 16L << 20;  // floats of partial sums per group
+constexpr long kTnPartial = 16L << 20;  // floats of partial sums per launch
 // floats of `partial` for products of up to mo_no_max outputs
 size_t tn_partial_floats(long mo_no_max);
 void launch_gemm_tn(const TnArgs* args, int n, float* partial, hipStream_t st);

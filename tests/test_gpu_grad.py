@@ -310,3 +310,43 @@ def test_weights_of_a_model_on_the_default_device_stay_on_the_device(monkeypatch
     E.sum().backward()
     assert set(given) == {w.data_ptr()}
     assert m.device == torch.device("cuda")
+
+
+@pytest.mark.parametrize("channels,copies", [(128, (6, 6, 7))])
+def test_gradient_of_many_copies_of_a_cell(channels, copies):
+    # n copies of a periodic cell have n times its gradient, sums of the same
+    # rows over and over: what differs is the rounding of long FP32 sums. The
+    # middle layer's widest tensors are sums over 180,000 pairs. A sum in FP32
+    # over at most 1,024 rows takes 128 additions on the matrix cores (two
+    # terms, 16 rows at a time), each off by half of 2^-24 of it or so either way,
+    # so about sqrt(128) of them add up (the widest tensor's sums are twice as
+    # long, as many as there is room for)
+    import torch
+    import paper_2605_22698_amd as e3
+    cfg = synth.ModelConfig(lmax=3, channels=channels, layers=3, n_species=3, cutoff=5.0,
+                            avg_neighbors=synth.nominal_neighbors(0.1, 5.0))
+    rng = np.random.default_rng(220)
+    cell = synth.jittered_lattice(27, 0.1, 0.3, 3, rng)
+    v = 0.1 * rng.standard_normal(cell.pos.shape)
+    d = device()
+    m = e3.Model(cfg.to_json(), synth.flatten_weights(cfg, synth.model_weights(cfg, 221)), device=d)
+
+    def gradient(k):
+        n = int(np.prod(k))
+        at = np.stack(np.meshgrid(*[np.arange(x) for x in k], indexing="ij"), -1).reshape(-1, 1, 3)
+        pos = torch.tensor((cell.pos[None] + at * np.diagonal(cell.cell[0])).reshape(-1, 3), device=d)
+        sp = torch.tensor(np.tile(cell.species, n), dtype=torch.int32, device=d)
+        g = m.build_graph(np.array([0, 27 * n]), pos, sp, cell.cell * np.array(k)[None, :, None], cell.pbc, cfg.cutoff, 0.1)
+        gE = torch.ones(1, dtype=torch.float64, device=d)
+        return m.param_grad(g, pos, gE, torch.tensor(np.tile(v, (n, 1)), device=d)).cpu().numpy() / n
+    one, many = gradient((1, 1, 1)), gradient(copies)
+    off, worst = 0, {}
+    for name, shape, _ in synth.weight_shapes(cfg):
+        n = int(np.prod(shape))
+        a, r = many[off:off + n], one[off:off + n]
+        off += n
+        if np.linalg.norm(r) > 1e-9 * np.linalg.norm(one):
+            worst[name] = float(np.linalg.norm(a - r) / np.linalg.norm(r))
+    bound = np.sqrt(128) * 2.0 ** -25
+    record("gradient_of_copies", rel_l2={k: f"{x:.1e}" for k, x in worst.items()}, bound=bound)
+    assert max(worst.values()) <= bound, worst
