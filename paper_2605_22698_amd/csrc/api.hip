@@ -1601,6 +1601,7 @@ size_t footprint(const e3mi_model* M, int64_t n_atoms, int64_t n_edges) {
   const size_t n_e = (size_t)std::max<int64_t>(n_edges, 0);
   const size_t N = (size_t)std::max<int64_t>(n_atoms, 0), E = n_e + n_e / 8 + 65;
   const size_t C = c.channels, NC = (size_t)(c.lmax + 1) * (c.lmax + 1);
+  const size_t rows = M->edge_pairs ? E / 2 + 1 : E;  // of the radial MLPs, as forward_pass has them
   size_t b = 0;
   b += E * (8 + 4 * 3) + E * (4 + 16 + 4 + 4 + 4);   // skin list + pruned list
   b += N * (4 * 4 + 24 + 8) + 64 * 1024;             // per-atom graph data
@@ -1614,26 +1615,22 @@ size_t footprint(const e3mi_model* M, int64_t n_atoms, int64_t n_edges) {
     a_max = std::max(a_max, (size_t)L.a_per_atom);
     if (t == 1 && factorised_first(M)) {
       b += 2 * N * L.nc_out * (size_t)c.n_species * c.radial_hidden * 4;  // G and dG
-      b += 2 * E * (size_t)c.radial_hidden * 4;                            // hidden layer and its derivative
+      b += 2 * rows * (size_t)c.radial_hidden * 4;                         // hidden layer and its derivative
       continue;
     }
     if (fused_last(M, L, false, bf16)) continue;  // no per-edge R
-    // FP32: R and R' of every edge where one chunk holds them, else of every
-    // pair (n_edges stands for the edges inside the cutoff) where that can be
-    // kept, else of one receiver chunk's edges. BF16 mode (its FP32 bound): R of
-    // every edge, or of one receiver chunk unless kept whole; dR per chunk.
-    // The sender-gradient messages of a full layer per chunk
+    // FP32: R and R' of every pair where one chunk holds every edge or where they
+    // can be kept (n_edges stands for the edges inside the cutoff), else of one
+    // receiver chunk's edges. BF16 mode (its FP32 bound): R of every edge, or of
+    // one receiver chunk unless kept whole; dR per chunk. The sender-gradient
+    // messages of a full layer per chunk
     const size_t PCu = (size_t)L.p_used * C;
     const size_t chunk = std::min(E, M->r_chunk_bytes / (PCu * 4));
     if (L.kind == 1 && t > 1) msg_max = std::max(msg_max, chunk * L.nc_in * C * 4);
     if (!bf16) {
-      const size_t rows = M->edge_pairs ? E / 2 + 1 : E;
-      if (chunk < E && kept + 8 * rows * PCu <= M->r_keep_bytes) {
-        b += 8 * rows * PCu;
-        kept += 8 * rows * PCu;
-      } else {
-        b += 8 * chunk * PCu;
-      }
+      const bool keep = chunk < E && kept + 8 * rows * PCu <= M->r_keep_bytes;
+      b += 8 * (chunk >= E || keep ? rows : chunk) * PCu;
+      if (keep) kept += 8 * rows * PCu;
       continue;
     }
     bool whole = chunk >= E;

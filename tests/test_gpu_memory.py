@@ -86,3 +86,28 @@ def test_a_build_without_memory_gives_nothing_back_while_it_is_used(n_atoms, all
     memory.refuse = None
     g = m.build_graph(np.array([0, n_atoms]), pos, sp, b.cell, b.pbc, cfg.cutoff, 0.5)
     assert g.n_atoms == n_atoms
+
+
+@pytest.mark.parametrize("layers,channels,correlation,precision,per_edge,chunk", [
+    (2, 128, 1, 0, False, None), (2, 128, 1, 0, True, None), (4, 64, 1, 0, False, None), (3, 64, 2, 0, False, None),
+    (3, 64, 1, 0, False, 1 << 22), (2, 128, 1, 1, False, None), (4, 64, 1, 1, False, None)])
+def test_footprint_holds_what_a_call_allocates(layers, channels, correlation, precision, per_edge, chunk):
+    # the estimate that admission goes by covers a call's allocations, and in FP32
+    # no more than the eighth of room it leaves for edges that a rebuild adds and
+    # as much again for rounding (the mixed mode is estimated with R in FP32,
+    # twice what layers with scalar outputs hold; rows kept whole past the chunk
+    # are those of the edges inside the cutoff, here 1.1^3 times fewer than listed)
+    import torch
+    cfg = synth.ModelConfig(lmax=3, channels=channels, layers=layers, n_species=4, cutoff=5.0,
+                            avg_neighbors=synth.nominal_neighbors(0.1, 5.0), correlation=correlation)
+    b = synth.jittered_lattice(1000, 0.1, 0.3, 4, np.random.default_rng(214))
+    m = model(cfg, 215, precision=precision)
+    m.set_flags(radial_per_edge=per_edge)
+    if chunk:
+        m.set_r_chunk_bytes(chunk)
+    weights = m._alloc.bytes_live
+    g = gpu_energy_forces(m, b, skin=0.5)[3]
+    torch.cuda.synchronize()
+    live, estimate = m._alloc.bytes_live - weights, m.footprint_bytes(b.n_atoms, g.n_skin_edges)
+    say(f"footprint: {live / 2**20:.1f} MiB allocated, {estimate / 2**20:.1f} MiB estimated, {estimate / live:.3f}")
+    assert live <= estimate <= (2.0 if precision else 1.25 * 1.1 ** 3 if chunk else 1.25) * live
