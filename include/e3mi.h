@@ -256,7 +256,8 @@ int e3mi_hessian_vectors(e3mi_model* model, e3mi_graph* graph, const double* pos
  *     likewise.
  *   E3MI_FLAG_RADIAL_PER_EDGE (8) runs all of them per edge instead, as
  *     layers in receiver chunks always do; results are then bitwise those of
- *     any chunking. */
+ *     any chunking. (e3mi_energy_forces_static keeps the first layer's hidden
+ *     rows and FP32's R and R' per pair all the same, for room: the same bits.) */
 #define E3MI_FLAG_RADIAL_PER_EDGE 8
 int e3mi_model_set_flags(e3mi_model* model, int flags);
 

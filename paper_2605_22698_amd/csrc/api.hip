@@ -922,9 +922,14 @@ EdgePairs graph_pairs(const e3mi_graph* G) {
 const EdgePairs* pairs_for(const e3mi_model* M, const RChunk& ch, const EdgePairs& p) {
   return M->edge_pairs && ch.e1 < 0 ? &p : nullptr;
 }
-// rows of the first layer's hidden layers and of R: pair_of[e] per edge pair, or e
+// Whether the rows of the first layer's hidden layers and, in FP32, of R and its
+// derivatives are held once per edge pair. In the static scratch they always
+// are: the flag's rows per edge hold the same bits (a row is a function of the
+// length alone) and take twice the room.
+bool rows_per_pair(const e3mi_model* M) { return M->edge_pairs || M->alloc.arena; }
+// such a row of edge e: pair_of[e], or e
 const int* first_pair_index(const e3mi_model* M, const e3mi_graph* G) {
-  return M->edge_pairs ? G->pair_of->as<int>() : nullptr;
+  return rows_per_pair(M) ? G->pair_of->as<int>() : nullptr;
 }
 // BF16 mode: R of a layer once per edge pair, in the pair mode on a single chunk
 bool r_compact_for(const e3mi_model* M, const std::vector<RChunk>& chunks) {
@@ -937,7 +942,7 @@ void launch_rows(e3mi_model* M, e3mi_graph* G, const RadialJob* jobs, int n_jobs
                  hipStream_t st) {
   const Config& c = M->cfg;
   const EdgePairs prs = graph_pairs(G);
-  const bool pairs = M->edge_pairs && !ch;
+  const bool pairs = rows_per_pair(M) && !ch;
   launch_radial_rows(c.n_basis, G->dvec_x->as<float4>(), G->row_ptr_x->as<int>(), G->N, G->E_room, jobs, n_jobs, n_out,
                      (float)c.cutoff, c.envelope_p, ch ? ch->e0 : 0, ch ? ch->e1 : -1, pairs ? prs.own : nullptr,
                      pairs ? prs.n_own : nullptr, st);
@@ -971,7 +976,7 @@ size_t r_rows_plan(e3mi_model* M, e3mi_graph* G, int t, int PCu, size_t& kept, h
   w.r_whole[t] = 1;
   if (chunk >= cap) return cap;
   const size_t e_in = (size_t)pruned_rows(M, G, st)[G->N];
-  const size_t n = (M->edge_pairs ? (size_t)w.n_own_host : e_in) + 1;
+  const size_t n = (rows_per_pair(M) ? (size_t)w.n_own_host : e_in) + 1;
   // room for 1/8 more rows than this call has, so that the count's drift
   // between rebuilds does not reallocate
   const size_t room = std::min(cap, n + n / 8), bytes = 2 * sizeof(float) * room * PCu;
@@ -1082,7 +1087,7 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
   long a_max = 0;
   size_t dr_bytes = 0, kept = 0;
   // rows of radial weights: one of every two edges of the list owns a pair
-  const size_t rows_cap = (M->edge_pairs ? (size_t)Ecap / 2 : (size_t)Ecap) + 1;
+  const size_t rows_cap = (rows_per_pair(M) ? (size_t)Ecap / 2 : (size_t)Ecap) + 1;
   w.r_whole.assign(T + 1, 0);
   w.r_compact.assign(T + 1, 0);
   for (int t = 1; t <= T; ++t) {
@@ -1180,8 +1185,8 @@ void forward_pass(e3mi_model* M, e3mi_graph* G, const double* pos, bool keep_A, 
         ProfScope ps(&M->prof, stage_id(kFirstFwd, 1), st);
         const EdgePairs prs = graph_pairs(G);
         if (bf16)
-          launch_first_hidden(dvec, row_ptr, N, Ecap, M->edge_pairs ? prs.own : nullptr,
-                              M->edge_pairs ? prs.n_own : nullptr, W.rad1.as<float>(), W.rad2.as<float>(), rc, p_env,
+          launch_first_hidden(dvec, row_ptr, N, Ecap, rows_per_pair(M) ? prs.own : nullptr,
+                              rows_per_pair(M) ? prs.n_own : nullptr, W.rad1.as<float>(), W.rad2.as<float>(), rc, p_env,
                               w.H2f->as<float>(), st);
         launch_first(true, c.lmax, L.l3max_used, row_ptr, src, dvec, species, N, S64, first_pair_index(M, G),
                      w.H2f->as<float>(), G1, nullptr, nullptr, nullptr, 0, st);

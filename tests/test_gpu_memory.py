@@ -111,3 +111,28 @@ def test_footprint_holds_what_a_call_allocates(layers, channels, correlation, pr
     live, estimate = m._alloc.bytes_live - weights, m.footprint_bytes(b.n_atoms, g.n_skin_edges)
     say(f"footprint: {live / 2**20:.1f} MiB allocated, {estimate / 2**20:.1f} MiB estimated, {estimate / live:.3f}")
     assert live <= estimate <= (2.0 if precision else 1.25 * 1.1 ** 3 if chunk else 1.25) * live
+
+
+@pytest.mark.parametrize("precision,n_atoms,flags", [
+    (0, 100, {}), (0, 1600, {}), (1, 2100, {}), (0, 1780, {"unfactorised_first_layer": True})])
+def test_static_scratch_with_the_radial_mlp_per_edge(precision, n_atoms, flags):
+    # systems that the scratch of 128 MiB holds with rows per pair, and held with
+    # them per edge before the rows carried derivatives; the bits of the call that
+    # allocates
+    import ctypes
+
+    import torch
+    from paper_2605_22698_amd import _lib
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=2, n_species=3, cutoff=5.0, avg_neighbors=30.0)
+    b = synth.open_box(n_atoms, 3, np.random.default_rng(n_atoms))
+    m = model(cfg, 216, precision=precision)
+    m.set_flags(radial_per_edge=True, **flags)
+    E1, F1, Ei1, g = gpu_energy_forces(m, b, skin=0.5)
+    pos = torch.tensor(b.pos, dtype=torch.float64, device=device())
+    E = torch.empty(1, dtype=torch.float64, device=device())
+    F = torch.empty((n_atoms, 3), dtype=torch.float32, device=device())
+    code = _lib.lib().e3mi_energy_forces_static(m.handle, g.handle, _lib.ptr(pos), _lib.ptr(E), _lib.ptr(F), None,
+                                                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert code == 0, _lib.lib().e3mi_last_error().decode()
+    assert np.array_equal(E.cpu().numpy(), E1) and np.array_equal(F.cpu().numpy().astype(np.float64), F1)
