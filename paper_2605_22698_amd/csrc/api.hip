@@ -2243,6 +2243,12 @@ void hvp_directions(e3mi_model* M, e3mi_graph* G, int B, const float* v, float* 
   launch_forces(row_ptr, G->rev_x->as<int>(), g, N, hv, st, nullptr, B, ha.e_stride);
 }
 
+// The buffers that hvp_directions sizes by the directions of a batch
+void release_directions(Workspace& w) {
+  for (auto* q : {&w.vhd, &w.vhtd, &w.vatd, &w.vBpd}) q->clear();
+  for (auto* q : {&w.vdd, &w.vg, &w.vAd, &w.vA, &w.vx, &w.vh_a, &w.vh_b, &w.vgeo, &w.vmsg, &w.vBp, &w.vat}) q->reset();
+}
+
 // H v_k for k < n_vec (v, hv: [n_vec, N, 3]); the primal pass runs once for
 // all directions.
 void hessian_vectors(e3mi_model* M, e3mi_graph* G, const double* pos, int n_vec, const float* v, float* hv,
@@ -2254,10 +2260,23 @@ void hessian_vectors(e3mi_model* M, e3mi_graph* G, const double* pos, int n_vec,
                "second-order passes (parameter gradients, Hessian-vector products) of the Coulomb term are not implemented");
   forward_pass(M, G, pos, false, st, false, false, true);
   if (factorised_first(M)) radial_derivs(M, G, 1, st);
-  const int batch = hvp_batch(M, G, n_vec);
+  int batch = hvp_batch(M, G, n_vec);
   const size_t stride = 3 * (size_t)G->N;
-  for (int k = 0; k < n_vec; k += batch)
-    hvp_directions(M, G, std::min(batch, n_vec - k), v + k * stride, hv + k * stride, st);
+  for (int k = 0; k < n_vec;) {
+    const int B = std::min(batch, n_vec - k);
+    try {
+      hvp_directions(M, G, B, v + k * stride, hv + k * stride, st);
+    } catch (const Error& e) {
+      // no memory for the batch: fewer directions together, down to one, which
+      // takes a small part of it
+      if (e.code != E3MI_ENOMEM || B == 1) throw;
+      E3MI_HIP(hipStreamSynchronize(st));  // kernels of the batch may be under way
+      release_directions(M->ws);
+      batch = B / 2;
+      continue;
+    }
+    k += B;
+  }
 }
 
 // Replace the weights of a model (same configuration), e.g. after an optimiser step.

@@ -136,3 +136,33 @@ def test_static_scratch_with_the_radial_mlp_per_edge(precision, n_atoms, flags):
     torch.cuda.synchronize()
     assert code == 0, _lib.lib().e3mi_last_error().decode()
     assert np.array_equal(E.cpu().numpy(), E1) and np.array_equal(F.cpu().numpy().astype(np.float64), F1)
+
+
+@pytest.mark.parametrize("layers,correlation", [(2, 1), (3, 1), (2, 2)])
+def test_directions_taken_one_by_one_where_memory_is_short(layers, correlation):
+    # a batch of directions does not fit, one does: the products all the same,
+    # within what an allocator that holds one direction's call gives
+    import torch
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=layers, n_species=3, cutoff=5.0, avg_neighbors=30.0,
+                            correlation=correlation)
+    b = synth.open_box(90, 3, np.random.default_rng(217))
+    V = torch.tensor(np.random.default_rng(218).normal(size=(13,) + b.pos.shape), dtype=torch.float32, device=device())
+    pos = torch.tensor(b.pos, dtype=torch.float64, device=device())
+    sp = torch.tensor(b.species, dtype=torch.int32, device=device())
+
+    held = []  # the graphs stay
+
+    def products(m, n):
+        held.append(m.build_graph(b.offsets, pos, sp, b.cell, b.pbc, cfg.cutoff))
+        return m.hessian_vectors(held[-1], pos, V[:n])
+    one = model(cfg, 219)
+    products(one, 1)
+    room = one._alloc.bytes_live
+    ample = model(cfg, 219)
+    ref = products(ample, 13)
+    assert ample._alloc.bytes_live > 2 * room
+    m, memory = _limited(cfg, 219)
+    memory.refuse = lambda n: m._alloc.bytes_live + n > room
+    hv = products(m, 13)
+    assert m._alloc.bytes_live <= room
+    assert float((hv - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
