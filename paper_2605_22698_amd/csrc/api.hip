@@ -1041,6 +1041,7 @@ bool first_rows(e3mi_model* M, e3mi_graph* G, bool fact, bool whole_rows, hipStr
     jobs.resize(fact ? 1 : 0);
     stage = stage_id(kFirstFwd, 1);
   }
+  if (jobs.empty()) return together;
   ProfScope ps(&M->prof, stage, st);
   for (size_t k = 0; k < jobs.size(); k += kMaxRadialJobs)
     launch_rows(M, G, &jobs[k], (int)std::min<size_t>(kMaxRadialJobs, jobs.size() - k), 2, nullptr, st);

@@ -263,3 +263,16 @@ def test_contractions_of_few_and_many_rows(channels, copies, correlation, bf16):
         Er, Fr, Eir = _oracle(cfg, 191, one)
         check_energy(E1, Er, Eir)
         check_forces(F1, Fr)
+
+
+@pytest.mark.parametrize("flags,launches", [({"unfactorised_first_layer": True}, 0), ({}, 1)])
+def test_stages_that_do_not_run_are_not_counted(flags, launches):
+    cfg, b = synth.tiny_config()
+    m = model(cfg, 1)
+    m.set_flags(**flags)
+    gpu_energy_forces(m, b)
+    m.profile(True)
+    gpu_energy_forces(m, b)
+    n = m.stage_time("first_fwd")[1]
+    m.profile(False)
+    assert min(n, 1) == launches
