@@ -143,28 +143,30 @@ def work_model(cfg, t, E, N, pairs=False):
     return out
 
 
-def measured_traffic(kernel, summary="md_step_3000_hbm_traffic.md"):
+def measured_traffic(kernel, summary="md_step_3000_hbm_traffic.md", layer=None):
     """HBM bytes per launch of a kernel (FETCH_SIZE + WRITE_SIZE,
     copy-calibrated) from a committed counter summary, or None when the
     kernel's source file has changed since the counters were taken. kernel:
-    the name as listed, with its template arguments or without (the first
-    listed)."""
+    the name as listed, with its template arguments or without (then one row
+    only may have it). A kernel that serves several layers is listed once per
+    layer, "`name` [layer t]"; layer picks the row, and None is returned where
+    the summary has none for it."""
     import hashlib
     path = os.path.join(ROOT, "profiles", summary)
     if not os.path.exists(path):
         return None
+    found = []
     for line in open(path):
-        m = re.match(r"\|\s*`([^`]+)`\s*\|\s*\d+\s*\|\s*([\d.]+)\s*\|\s*([\d.]+)\s*\|\s*(\S+)\s*\|\s*(\S+)", line)
-        if not m:
-            continue
-        name = m.group(1)
-        if kernel not in (name, name.split("<")[0]):
-            continue
-        src = os.path.join(ROOT, "paper_2605_22698_amd", "csrc", m.group(4))
-        if not os.path.exists(src) or hashlib.sha256(open(src, "rb").read()).hexdigest()[:16] != m.group(5):
-            return None
-        return (float(m.group(2)) + float(m.group(3))) * 1024 * 1024
-    return None
+        m = re.match(r"\|\s*`([^`]+)`(?: \[([^\]]+)\])?\s*\|\s*\d+\s*\|\s*([\d.]+)\s*\|\s*([\d.]+)\s*\|\s*(\S+)\s*\|\s*(\S+)", line)
+        if m and kernel in (m.group(1), m.group(1).split("<")[0]) and m.group(2) in (None, f"layer {layer}"):
+            found.append(m)
+    if len(found) != 1:
+        return None
+    m = found[0]
+    src = os.path.join(ROOT, "paper_2605_22698_amd", "csrc", m.group(5))
+    if not os.path.exists(src) or hashlib.sha256(open(src, "rb").read()).hexdigest()[:16] != m.group(6):
+        return None
+    return (float(m.group(3)) + float(m.group(4))) * 1024 * 1024
 
 
 def serving_run(e3, synth, torch, dev, n_requests, n_steps, log):
@@ -287,7 +289,8 @@ def product_run(e3, synth, torch, dev, n_atoms, steps, warmup, log):
     out["stage_ms_per_step"] = stage
     out["roofline"] = {"bound": "hbm", "achieved": nbytes / (ms / 1e3) / 1e9, "peak": PEAK_HBM / 1e9,
                        "unit": "GB/s", "frac": nbytes / (ms / 1e3) / PEAK_HBM,
-                       "traffic": measured_traffic(f"k_{s}", "product_hbm_traffic.md"),
+                       "traffic": measured_traffic(f"k_{s}<{cfg.lmax}, {0 if t == cfg.layers else cfg.lmax}>",
+                                               "product_hbm_traffic.md"),
                        "kernel": f"{s} (layer {t})", "avg_launch_ms": ms,
                        "algorithmic_per_launch": {"flops": flops, "bytes": nbytes}}
     # the block's second-order pass on the same box: one Hessian-vector
@@ -610,7 +613,7 @@ def scale_run(e3, synth, torch, dev, steps, warmup, log, cpu_baseline=True):
                 # the VALU peak above counts packed FP32, which this build does not emit
                 roof["frac_of_nonpacked_alu"] = flops / step_s / PEAK_FP32_VALU_NONPACKED
             kern = kernel_of_stage(st_name, t, cfg.layers)
-            traffic = measured_traffic(kern, "scale_100k_hbm_traffic.md")
+            traffic = measured_traffic(kern, "scale_100k_hbm_traffic.md", t)
             roof["traffic"] = None if traffic is None else traffic * n / 2
             roof["kernel"] = f"{st_name} (layer {t}), {kern}"
             roof["launches_per_step"] = n / 2
@@ -843,7 +846,8 @@ def main():
                 continue
             if best is None or tot > best[0]:
                 best = (tot, n, s, t, flops, nbytes)
-    _, _, dom_s, dom_t, flops, nbytes = best
+    _, dom_n, dom_s, dom_t, flops, nbytes = best
+    dom_launches = max(1, round(dom_n / k_prof))  # of an evaluation, which the work is counted for
 
     # ---- timed region ----
     m.profile(True, only=f"{dom_s}@{dom_t}")
@@ -868,7 +872,7 @@ def main():
     # ---- roofline of the dominant kernel, timed over the timed region ----
     s, t = dom_s, dom_t
     tot, n = m.stage_time(f"{s}@{t}")
-    avg_s = tot / n / 1e3
+    avg_s = tot / n / 1e3 * dom_launches
     mfma = matrix_peak(s)
     peak_flop = mfma or PEAK_FP32_VALU
     t_hbm, t_flop = nbytes / PEAK_HBM, flops / peak_flop
@@ -878,7 +882,7 @@ def main():
     else:
         roof = {"bound": "hbm", "achieved": nbytes / avg_s / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    roof["traffic"] = measured_traffic(kernel_of_stage(s, t, cfg.layers))
+    roof["traffic"] = measured_traffic(kernel_of_stage(s, t, cfg.layers), layer=t)
     roof["kernel"] = f"{s} (layer {t})"
     roof["avg_launch_ms"] = tot / n
     roof["algorithmic_per_launch"] = {"flops": flops, "bytes": nbytes, "edges": n_edges,
