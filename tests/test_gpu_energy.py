@@ -276,3 +276,18 @@ def test_stages_that_do_not_run_are_not_counted(flags, launches):
     n = m.stage_time("first_fwd")[1]
     m.profile(False)
     assert min(n, 1) == launches
+
+
+@pytest.mark.parametrize("layers,correlation,flags", [(5, 1, {}), (6, 1, {}), (8, 1, {"unfactorised_first_layer": True}),
+                                                      (5, 2, {})])
+def test_more_layers_than_a_radial_launch_takes(layers, correlation, flags):
+    # the radial rows of all layers go out together, four jobs a launch
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=layers, n_species=3, cutoff=5.0, avg_neighbors=15.0,
+                            correlation=correlation)
+    b = synth.open_box(24, 3, np.random.default_rng(230))
+    m = model(cfg, 231)
+    m.set_flags(**flags)
+    E, F, Ei, _ = gpu_energy_forces(m, b, skin=0.5)
+    Er, Fr, Eir = _oracle(cfg, 231, b)
+    check_energy(E, Er, Eir)
+    check_forces(F, Fr)

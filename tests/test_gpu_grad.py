@@ -350,3 +350,11 @@ def test_gradient_of_many_copies_of_a_cell(channels, copies):
     bound = np.sqrt(128) * 2.0 ** -25
     record("gradient_of_copies", rel_l2={k: f"{x:.1e}" for k, x in worst.items()}, bound=bound)
     assert max(worst.values()) <= bound, worst
+
+
+@pytest.mark.parametrize("layers", [5, 6])
+def test_gradient_of_many_layers(layers):
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=layers, n_species=3, cutoff=5.0, avg_neighbors=15.0)
+    rng = np.random.default_rng(232)
+    b = synth.open_box(24, 3, rng)
+    _compare(cfg, 233, b, rng.standard_normal(1), rng.standard_normal((24, 3)) * 0.01)

@@ -211,3 +211,20 @@ def test_more_directions_than_one_batch_holds():
         v = np.zeros(270)
         v[k] = 1.0
         _check(H[:, k].reshape(-1, 3), om.hessian_vector(ref, b, v.reshape(-1, 3)), f"column {k}")
+
+
+def test_directions_in_batches_that_memory_bounds():
+    # a direction of this box takes 1.8 GB of tangents, adjoints and messages (16 KB
+    # an edge of the middle layer), so two go together; each as if alone
+    import torch
+    cfg = synth.ModelConfig(lmax=3, channels=128, layers=3, n_species=3, cutoff=5.0,
+                            avg_neighbors=synth.nominal_neighbors(0.1, 5.0))
+    b = synth.jittered_lattice(2000, 0.1, 0.3, 3, np.random.default_rng(164))
+    m = model(cfg, 165)
+    g, pos = _graph(m, b)
+    V = torch.tensor(np.random.default_rng(166).normal(size=(3,) + b.pos.shape), dtype=torch.float32, device=device())
+    H = m.hessian_vectors(g, pos, V)
+    assert m._alloc.bytes_live < 12e9
+    for k in range(3):
+        one = m.hessian_vector(g, pos, V[k])
+        _check(H[k].cpu().numpy().astype(np.float64), one.cpu().numpy().astype(np.float64), f"direction {k}")

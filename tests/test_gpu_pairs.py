@@ -102,3 +102,17 @@ def test_selected_edges_and_pairs_at_block_edges(n, species_seed):
     assert abs(E[0] - E1[0]) <= 1e-6 * np.abs(Ei).sum()
     # (a lone atom among its images: forces of rounding alone)
     assert np.abs(F - F1).max() <= 1e-5 * max(np.abs(F1).max(), 1e-2)
+
+
+@pytest.mark.parametrize("n,species_seed", [(1, 5), (4, 6), (5, 7), (9, 10)])
+def test_selected_edges_of_a_few_atoms_and_their_images(n, species_seed):
+    # boxes smaller than the cutoff's sphere, counted over the images
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=2, n_species=2, cutoff=2.5, avg_neighbors=6.5)
+    b = synth.jittered_lattice(n, 0.1, 0.3, 2, np.random.default_rng(species_seed))
+    g = gpu_energy_forces(model(cfg, 196), b, skin=0.3)[3]
+    L = np.diagonal(np.asarray(b.cell).reshape(-1, 3, 3)[0])
+    shifts = np.stack(np.meshgrid(*[np.arange(-k, k + 1) for k in np.ceil(2.5 / L).astype(int) + 1], indexing="ij"),
+                      -1).reshape(-1, 3) * L
+    assert np.asarray(b.pbc).all()
+    r = np.linalg.norm(b.pos[None, :, None] - b.pos[:, None, None] + shifts, axis=-1)
+    assert g.last_edge_count() == int(((r < 2.5) & (r > 0)).sum())
