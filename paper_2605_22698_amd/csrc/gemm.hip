@@ -11,6 +11,9 @@
 // Gaussian operands, this and the FP32 instruction: K = 64 5.0e-8 and 1.4e-7,
 // K = 256 9.0e-8 and 2.8e-7, K = 640 1.4e-7 and 4.5e-7 (three products, without
 // the last bracket, 4.4e-6: not FP32).
+// A value that BF16 cannot hold, infinite or past 3.39e38, has parts that are
+// not numbers: what it reaches is NaN, where the FP32 instruction's sums were
+// infinite or NaN. Energies and forces of an overflow are NaN either way.
 //
 // The weights are split once, when they are laid out (kFragments), in the order
 // the operands are loaded in: for every 16 K and 32 columns, per part, lane l

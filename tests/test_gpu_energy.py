@@ -291,3 +291,23 @@ def test_more_layers_than_a_radial_launch_takes(layers, correlation, flags):
     Er, Fr, Eir = _oracle(cfg, 231, b)
     check_energy(E, Er, Eir)
     check_forces(F, Fr)
+
+
+@pytest.mark.parametrize("correlation,scale", [(1, 1e37), (1, 3.4e38), (2, 1e30)])
+def test_an_overflow_shows_and_stays_in_its_structure(correlation, scale):
+    # one species' embedding near or past what FP32 and BF16 hold: the structure
+    # that has it is finite or NaN throughout, the other has the bits it has alone
+    cfg = synth.ModelConfig(lmax=2, channels=32, layers=3, n_species=3, cutoff=5.0, avg_neighbors=15.0,
+                            correlation=correlation)
+    rng = np.random.default_rng(234)
+    a, b = synth.open_box(20, 2, rng), synth.open_box(20, 3, rng)
+    w = synth.model_weights(cfg, 235)
+    flat = synth.flatten_weights(cfg, w)
+    flat[2 * cfg.channels:3 * cfg.channels] *= scale
+    m = model(cfg, 235)
+    m.set_weights(flat)
+    E0, F0, _, _ = gpu_energy_forces(m, a)
+    E, F, _, _ = gpu_energy_forces(m, synth.concat([a, b]))
+    assert np.isfinite(E0).all() and E[0] == E0[0] and np.array_equal(F[:20], F0)
+    for x in (E[1:], F[20:]):
+        assert np.isfinite(x).all() if scale == 1e37 else np.isnan(x).all()
