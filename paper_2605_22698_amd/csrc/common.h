@@ -102,9 +102,6 @@ __device__ __forceinline__ void str_n(__bf16* p, const float* v) {
 
 // Element at a byte offset from a uniform address: the address stays in scalar
 // registers and only the 32-bit offset is per lane.
-__device__ __forceinline__ float ld_off(const float* base, unsigned bytes) {
-  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + bytes);
-}
 __device__ __forceinline__ float* at_off(float* base, unsigned bytes) {
   return reinterpret_cast<float*>(reinterpret_cast<char*>(base) + bytes);
 }

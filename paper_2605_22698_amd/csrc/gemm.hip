@@ -178,19 +178,19 @@ __global__ void __launch_bounds__(256, 2) k_gemm(GemmGroup gg) {
       load();
     }
     // one column block's operands at a time, the next ones on their way from LDS
-    constexpr int NG = 1, kG = NB * (kStep / 16);
-    bf16x8 y[2][NG * PARTS];
+    constexpr int kG = NB * (kStep / 16);
+    bf16x8 y[2][PARTS];
     auto fetch = [&](int g) {
 #pragma unroll
-      for (int i = 0; i < NG * PARTS; ++i) y[g & 1][i] = Bt[(g * NG * PARTS + i) * 64 + lane];
+      for (int i = 0; i < PARTS; ++i) y[g & 1][i] = Bt[(g * PARTS + i) * 64 + lane];
     };
     fetch(0);
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
       if (g + 1 < kG) fetch(g + 1);
       __builtin_amdgcn_sched_barrier(0);
-      const int j = g / (NB / NG), n = g % (NB / NG) * NG;
-      mul_split<PARTS, NG>(x[j], y[g & 1], hi + n, lo + n);
+      const int j = g / NB, n = g % NB;
+      mul_split<PARTS, 1>(x[j], y[g & 1], hi + n, lo + n);
     }
   }
   store_rows<BF, NB>(a, row, bm + 32 * w, cb, lane, hi, lo);

@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(64 * W) k_tps_sender(const int* __restrict__ r
   constexpr int NP = PS::NP, NIN = PS::NIN, NY = PS::NY;
   constexpr int NA = DH ? NIN : 1;
   static_assert(PS::NOUT == NP, "scalar outputs only");
-  __shared__ float part[DH && W > 1 ? W : 1][DH && W > 1 ? NIN : 1][64 * CH];
+  __shared__ float part[DH ? W : 1][DH ? NIN : 1][64 * CH];
   const int j = i0 + xcd_contiguous(blockIdx.x, gridDim.x);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool on = lane * CH < C;
@@ -233,17 +233,15 @@ __global__ void __launch_bounds__(64 * W) k_tps_sender(const int* __restrict__ r
     if ((lane & 3) == 0 && q < NY) dY[(long)e2 * 16 + q] = odd ? -tot : tot;
   }
   if constexpr (DH) {
-    if constexpr (W > 1) {
 #pragma unroll
-      for (int q = 0; q < NIN; ++q) str_n<CH>(&part[w][q][lane * CH], acc[q]);
-      __syncthreads();
-    }
+    for (int q = 0; q < NIN; ++q) str_n<CH>(&part[w][q][lane * CH], acc[q]);
+    __syncthreads();
     if (!on) return;
     // components below dh_acc (all when dh_acc <= 0) are added to, the others
     // written (zero past the paths' inputs); wave w takes components w, w + W, ...
 #pragma unroll
     for (int q = 0; q < NIN; ++q) {
-      if (W > 1 && q % W != w) continue;
+      if (q % W != w) continue;
       float* o = dh + ((long)j * dh_nc + q) * C + k0;
       float v[CH];
       const bool add = dh_acc <= 0 || q < dh_acc;
@@ -251,12 +249,8 @@ __global__ void __launch_bounds__(64 * W) k_tps_sender(const int* __restrict__ r
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         float sum = add ? v[c] : 0.0f;
-        if constexpr (W > 1) {
 #pragma unroll
-          for (int x = 0; x < W; ++x) sum += part[x][q][lane * CH + c];
-        } else {
-          sum += acc[q][c];
-        }
+        for (int x = 0; x < W; ++x) sum += part[x][q][lane * CH + c];
         v[c] = sum;
       }
       str_n<CH>(o, v);
@@ -298,12 +292,9 @@ __global__ void __launch_bounds__(64) k_tps_bwd_sender(const int* __restrict__ r
   for (int q = 0; q < NA; ++q)
 #pragma unroll
     for (int c = 0; c < CH; ++c) acc[q][c] = 0.0f;
-  // Software pipeline over j's row (up to 128 channels): the indices of edge
-  // e2 + 2 and the R and dA rows of edge e2 + 1 are in flight while edge e2
-  // is processed (the rows of consecutive edges lie far apart, and a wave
-  // owns one sender). With 256 channels the prefetched rows would halve the
-  // waves per SIMD: each edge's rows are loaded when it is processed.
-  constexpr bool kPipe = CH <= 2;
+  // Software pipeline over j's row: the indices of edge e2 + 2 and the R and dA
+  // rows of edge e2 + 1 are in flight while edge e2 is processed (the rows of
+  // consecutive edges lie far apart, and a wave owns one sender).
   const int eb = row_ptr[j], e1 = row_ptr[j + 1];
   struct Idx {
     int rev, i, row;
@@ -326,35 +317,27 @@ __global__ void __launch_bounds__(64) k_tps_bwd_sender(const int* __restrict__ r
       ldr_n<CH>(dAi + PS::T.rank[pi] * C, oA[pi]);
     });
   };
-  float nR[kPipe ? NP : 1][CH], nA[kPipe ? NP : 1][CH];
+  float nR[NP][CH], nA[NP][CH];
   Idx nx{-1, 0, 0, make_float4(0.f, 0.f, 1.f, 1.f)}, nnx = nx;
-  if constexpr (kPipe) {
-    if (eb < e1) {
-      nx = load_idx(eb);
-      load_rows(nx, nR, nA);
-    }
-    if (eb + 1 < e1) nnx = load_idx(eb + 1);
+  if (eb < e1) {
+    nx = load_idx(eb);
+    load_rows(nx, nR, nA);
   }
+  if (eb + 1 < e1) nnx = load_idx(eb + 1);
   for (int e2 = eb; e2 < e1; ++e2) {
-    Idx cx;
+    const Idx cx = nx;
     float cR[NP][CH], cA[NP][CH];
-    if constexpr (kPipe) {
-      cx = nx;
 #pragma unroll
-      for (int p = 0; p < NP; ++p)
+    for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          cR[p][c] = nR[p][c];
-          cA[p][c] = nA[p][c];
-        }
-      if (e2 + 1 < e1) {
-        nx = nnx;
-        load_rows(nx, nR, nA);
-        if (e2 + 2 < e1) nnx = load_idx(e2 + 2);
+      for (int c = 0; c < CH; ++c) {
+        cR[p][c] = nR[p][c];
+        cA[p][c] = nA[p][c];
       }
-    } else {
-      cx = load_idx(e2);
-      load_rows(cx, cR, cA);
+    if (e2 + 1 < e1) {
+      nx = nnx;
+      load_rows(nx, nR, nA);
+      if (e2 + 2 < e1) nnx = load_idx(e2 + 2);
     }
     __bf16* dRe = dR + (long)(e2 - e_first) * r_stride + k0;
     if (cx.rev < 0) {  // the edge i <- j is not in i's list
