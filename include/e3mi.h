@@ -140,7 +140,8 @@ int e3mi_model_destroy(e3mi_model* model);
  *                  diagonal (orthorhombic) on periodic axes, else EUNSUPPORTED
  *   pbc            host uint8 [S, 3], periodic flags
  *   cutoff         >= the model's cutoff; skin >= 0
- * Synchronises `stream` twice (to size the cell grid and the edge arrays).
+ * Synchronises `stream` (to check the inputs and size the cell grid, to size the
+ * edge arrays, and for the lists' own checks).
  * The graph stays valid while every atom stays within skin/2 of its position
  * at build time; energy_forces re-selects the edges inside the model cutoff on
  * every call. */
@@ -219,8 +220,9 @@ int e3mi_hessian_vector(e3mi_model* model, e3mi_graph* graph, const double* pos,
 
 /* n_vec Hessian-vector products at the same positions: v and hv are device
  * FP32 [n_vec, N, 3]; hv[k] = H v[k]. The primal forward pass runs once and
- * each direction costs one tangent and one reverse pass. Same errors as
- * e3mi_hessian_vector. */
+ * each direction costs one tangent and one reverse pass; directions are taken
+ * together within 4 GiB of tangents and adjoints, and within what the allocator
+ * gives. Same errors as e3mi_hessian_vector. */
 int e3mi_hessian_vectors(e3mi_model* model, e3mi_graph* graph, const double* pos, int n_vec, const float* v,
                          float* hv, void* stream);
 
@@ -316,7 +318,8 @@ int e3mi_graph_set_total_charge(e3mi_graph* graph, const double* total_charge);
  * displacement after the next drift (|x - x_build| + dt |v|); when that
  * reaches skin/2 the next step rebuilds before its force evaluation.
  * pos/vel are copied; the caller's buffers are not referenced afterwards.
- * Synchronises `stream`. */
+ * Synchronises `stream`. A step whose rebuild fails (ENOMEM) is left unfinished;
+ * the next one rebuilds before it evaluates. */
 int e3mi_md_create(e3mi_model* model, int n_structures, const int64_t* atom_offsets,
                    const double* pos, const double* vel, const int32_t* species,
                    const double* masses, const double* cell, const uint8_t* pbc, double cutoff,

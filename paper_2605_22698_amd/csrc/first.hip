@@ -35,9 +35,10 @@
 // species' edges out of the receiver's row (the order of the row is kept) and
 // reads the hidden rows and dG straight into matrix-core operands, so no wave
 // waits for another. Per launch on the 3,000-atom box (160k edges, 4 species):
-// hidden layers 32 us (18 without the derivative), forward 18 us (23 with a
-// workgroup per receiver and the tile's hidden rows in LDS), adjoint 33 us (94
-// with dH2 and the hidden layers' adjoint per edge).
+// hidden layers 28 us by k_radial_rows, 32 by k_first_hidden (18 without the
+// derivative), forward 18 us (23 with a workgroup per receiver and the tile's
+// hidden rows in LDS), adjoint 37 us (94 with dH2 and the hidden layers' adjoint
+// per edge).
 #include "common.h"
 #include "paths.h"
 #include "runtime.h"

@@ -6,8 +6,9 @@
 //   -> per-receiver stencil scan, two passes (count, fill) -> per-row sort of
 //   (j, n) keys -> reverse-edge index by binary search.
 // Per energy evaluation:
-//   prune the skin list to r < r_c (count per row, scan, compact, remap the
-//   reverse index), writing the FP32 edge vectors the interaction consumes.
+//   prune the skin list to r < r_c in three launches (count edges and pair owners
+//   per row; write both lists, with the FP32 edge vectors the interaction consumes;
+//   the reverse and pair indices), five past kSumRows rows (two scans).
 //
 // Edge key: (uint64)j << 24 | (nx+128) << 16 | (ny+128) << 8 | (nz+128),
 // so sorting keys sorts by (j, nx, ny, nz); the low 24 bits are the packed
@@ -308,8 +309,9 @@ __device__ __forceinline__ void edge_vec(const double* __restrict__ pos, const d
 // equal lengths (edge_vec), so both are selected or neither; the one that comes
 // first in the list owns the pair, and a function of the length is computed
 // once per owner. Selection keeps the order, so the order in the skin list
-// decides. The embedding rides in the first launch. Bound: the launches (three; with the owners counted after the
-// reverse index and two scans there were six: 3,000 atoms 29 us, now 18).
+// decides. The embedding rides in the first launch. Bound: the launches (three;
+// with the owners counted after the reverse index and two scans there were six:
+// 3,000 atoms 29 us, now 18).
 __global__ void __launch_bounds__(256) k_prune_count(const double* __restrict__ pos, const int* __restrict__ owner,
                                                      const double* __restrict__ box, const int* __restrict__ row_ptr,
                                                      const int* __restrict__ src, const int* __restrict__ shift,
