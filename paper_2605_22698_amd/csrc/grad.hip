@@ -180,10 +180,11 @@ __global__ void __launch_bounds__(256) k_group_total(const double* __restrict__ 
 // time through LDS, the next ones in flight; its partial sum goes to memory and
 // k_tn_reduce adds the chunks in order in FP64. FP32 as six BF16 products
 // (gemm.hip): a lane loads eight rows of one column, which is an operand's eight
-// K, and splits them on the way into LDS. Bound: the streams of X and Y (W3 of
-// 183,000 pairs, P C = 256: 265 us, 3.2 TB/s; on the FP32 matrix cores 325). The
-// products of a training step of 7,032 atoms 640 us and 750; those with rows
-// (atom, m) alone, whose addresses take longer, 57 and 46.
+// K, and splits them on the way into LDS. Bound: the streams of X and Y (W3, W2
+// and W1 of 183,000 pairs, P C = 256, 760 MB: 204 us, 3.7 TB/s). The products of a
+// training step of 7,032 atoms 510 us and 45 for the sums of the chunks (640 and
+// fewer with half the chunks, on the FP32 matrix cores 750); those with rows
+// (atom, m), whose addresses take longer, 49.
 struct TnGroup {
   TnArgs g[kMaxTnGroup];
   int block0[kMaxTnGroup + 1];  // first workgroup
